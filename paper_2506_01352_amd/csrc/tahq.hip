@@ -163,12 +163,9 @@ struct LaunchDecode {
     static void go(const uint8_t *packed, void *d_out, Layout lay, uint32_t T, uint32_t total_wide, Enqueue *qp)
     {
         Enqueue &q = *qp;
-        using B = Batch<G, BF16 ? 2 : 4>;
-        const uint32_t nb = (T + B::TILES - 1) / B::TILES;
-        static ResidentCache cache;
-        const uint32_t res = resident_blocks(reinterpret_cast<const void *>(k_decode<G, BF16, LOW>), B::TILES, cache);
-        q(k_decode<G, BF16, LOW>, dim3(nb < res ? nb : res), dim3(B::TILES), packed, d_out, lay,
-                           T, total_wide);
+        using W = Wave<G, BF16 ? 2 : 4>;
+        const uint32_t groups = (T + W::TILES - 1) / W::TILES;
+        q(k_decode<G, BF16, LOW>, dim3((groups + 3) / 4), dim3(256), packed, d_out, lay, T, total_wide);
     }
     static void run(uint32_t low, const uint8_t *packed, void *d_out, Layout lay, uint32_t T, uint32_t total_wide,
                     Enqueue *qp)

@@ -868,39 +868,152 @@ __device__ __forceinline__ void dequantize_codes(const uint32_t *dw, float sf, f
     }
 }
 
-// Alg. 1 step 5 for my tile: my LOW or LOW + 1 payload units at `src` (LDS) -> codes -> q*s + z -> for
-// transformed tiles the butterfly, 1/sqrt(G) and P_d -> my LDS row in the output type.
-template <int G, bool OUT_BF16, int LOW>
-__device__ __forceinline__ void decode_row(const typename Unit<G>::type *src, uint32_t b, uint32_t s16, uint32_t z16,
-                                           uint32_t pv, uint8_t *row)
-{
-    using U = typename Unit<G>::type;
-    constexpr int WIDE = LOW + 1;
-    const float sf = f16_widen(s16), mnf = f16_widen(z16);
-    // my LOW or WIDE units (the last one is read in any case: it stays inside the array)
-    constexpr int DW = BitString<G, WIDE>::DWORDS > G / 8 ? BitString<G, WIDE>::DWORDS : (G / 8 ? G / 8 : 1);
-    uint32_t dw[DW + 1];                         // one more: the one-by-one reader may look past the string
-#pragma unroll
-    for (int i = 0; i < DW + 1; ++i) dw[i] = 0;
-#pragma unroll
-    for (int u = 0; u < WIDE; ++u) {
-        const U t = src[u];
-        if constexpr (G == 8) dw[u >> 2] |= (uint32_t)t << (8 * (u & 3));
-        else if constexpr (G == 16) dw[u >> 1] |= (uint32_t)t << (16 * (u & 1));
-        else if constexpr (G == 32) dw[u] = t;
-        else if constexpr (G == 64) { dw[2 * u] = t.x; dw[2 * u + 1] = t.y; }
-        else { dw[4 * u] = t.x; dw[4 * u + 1] = t.y; dw[4 * u + 2] = t.z; dw[4 * u + 3] = t.w; }
+// Geometry of the wavefront-per-group kernels: a wavefront takes a group of TILES consecutive tiles, LPT lanes per tile,
+// EPL consecutive elements per lane: a lane holds at most 128 bytes of the tensor.
+template <int G, int ESIZE>
+struct Wave {
+    static constexpr int MAX_EPL = 128 / ESIZE;
+    static constexpr int EPL = G < MAX_EPL ? G : MAX_EPL;                     // elements per lane
+    static constexpr int LPT = G / EPL;                                       // lanes per tile
+    static constexpr int TILES = 64 / LPT;                                    // tiles per wavefront
+    static constexpr int LANE_BYTES = EPL * ESIZE;
+    static constexpr int CHUNKS = LANE_BYTES / 16;                            // 16-byte chunks per lane
+    static constexpr int LDS_BYTES = 64 * LANE_BYTES;
+    static_assert(TILES * LPT == 64 && CHUNKS >= 1 && CHUNKS <= 8, "whole tiles, whole chunks");
+    // Lane r's chunks lie in LDS at slots r * CHUNKS + (c ^ swizzle(r)): eight lanes that read the same chunk of their
+    // rows, like eight that read consecutive chunks of one row, meet eight different 16-byte columns of the banks.
+    static __device__ __forceinline__ uint32_t swizzle(uint32_t r)
+    {
+        return CHUNKS == 8 ? (r & 7u) : CHUNKS == 4 ? ((r >> 1) & 3u) : CHUNKS == 2 ? ((r >> 2) & 1u) : 0u;
     }
-    float x[G];
+    // byte offset of element e of the tile that starts at lane `row0`
+    static __device__ __forceinline__ uint32_t element_at(uint32_t row0, uint32_t e)
+    {
+        const uint32_t r = row0 + e / EPL, byte = (e % EPL) * ESIZE;
+        return r * LANE_BYTES + (((byte >> 4) ^ swizzle(r)) << 4) + (byte & 15u);
+    }
+};
+
+// Orders the LDS accesses of one wavefront for the compiler; the hardware performs them in program order.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The value of lane (mine ^ X), X = 1 or 2.
+template <int X>
+__device__ __forceinline__ float lane_xor(float v)
+{
+    static_assert(X == 1 || X == 2, "inside a quad");
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), X == 1 ? 0xB1 : 0x4E, 0xF, 0xF, true));
+}
+
+// The butterfly stages that cross lanes: element i of lane part p meets element i of part p ^ (h / EPL).
+template <int EPL, int LPT>
+__device__ __forceinline__ void butterfly_across(float *x, uint32_t part)
+{
+    if constexpr (LPT >= 2) {
+        const float s1 = (part & 1u) ? -1.0f : 1.0f;
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) x[i] = __builtin_fmaf(x[i], s1, lane_xor<1>(x[i]));     // p + q, or p - q: one rounding
+    }
+    if constexpr (LPT >= 4) {
+        const float s2 = (part & 2u) ? -1.0f : 1.0f;
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) x[i] = __builtin_fmaf(x[i], s2, lane_xor<2>(x[i]));
+    }
+    static_assert(LPT <= 4, "two stages across lanes");
+}
+
+// My share of a tile's bit string: LOW or LOW + 1 units of UB = EPL / 8 bytes at `p`, as dwords.  `end` is the end of the
+// stream.
+template <int UB, int LOW>
+__device__ __forceinline__ void load_codes(const uint8_t *__restrict__ p, bool wide, const uint8_t *end, uint32_t *dw)
+{
+    constexpr int WIDE = LOW + 1;
+    if constexpr (UB >= 4) {
+        const uint8_t *q = static_cast<const uint8_t *>(__builtin_assume_aligned(p, 4));
+        __builtin_memcpy(dw, q, LOW * UB);
+        // a narrow tile's last unit is its first one again: an address that is in the stream, and ignored
+        const uint8_t *last = static_cast<const uint8_t *>(__builtin_assume_aligned(p + (wide ? LOW * UB : 0), 4));
+        __builtin_memcpy(dw + LOW * UB / 4, last, UB);
+    } else {
+        constexpr int BYTES = (WIDE * UB + 3) & ~3;      // one unaligned load of whole dwords, except at the stream's end
+        if (p + BYTES <= end) {
+            __builtin_memcpy(dw, p, BYTES);
+        } else {
+#pragma unroll
+            for (int i = 0; i < WIDE * UB; ++i)
+                if (i < LOW * UB || wide) dw[i >> 2] |= (uint32_t)p[i] << (8 * (i & 3));
+        }
+    }
+}
+
+// Alg. 1 step 5: codes -> q*s + z -> for transformed tiles the butterfly, 1/sqrt(G) and P_d -> output type.
+//
+// One wavefront per group of tiles, no workgroup barriers: every wavefront finds its payload from the group's bit map word
+// and rank-table entry, decodes its tiles in registers and brings them into storage order through its own piece of LDS.
+// Bound by HBM, four fifths of the bytes being stores.  Lanes hold at most 128 bytes, so 4 workgroups of 32 KB of LDS and at
+// most 128 registers share a compute unit whatever the tile: vector instructions issue at their full rate only from four
+// wavefronts per SIMD.  The butterfly then runs in nearly every wavefront that meets transformed tiles (~250 of ~600 issue
+// slots per tile at G = 64) and still hides behind the stores.  Before, four wavefronts shared a batch, regrouped by class
+// through LDS (three workgroups per compute unit, three barriers per batch), and a tile of 128 channels took one lane.
+// Measured (back to back on one box; before -> now): bf16 [8,4096,8192] G = 64 3.25 bits 107.4 -> 92.4 us (667 MB, 7.2 TB/s),
+// [8,2048,8192] G = 128 79.8 -> 51.3, fp32 [4,2048,8192] G = 64 53.1 -> 45.7, G = 128 61.6 -> 45.9, bf16 [4,2048,4096] G = 8
+// 24.4 -> 18.2; half as many elements per lane: 98.8 us where 64 take 92.4.
+template <int G, bool OUT_BF16, int LOW>
+__global__ __launch_bounds__(256, 4)
+void k_decode(const uint8_t *__restrict__ packed, void *__restrict__ out, Layout lay, uint32_t T, uint32_t total_wide)
+{
+    constexpr int ES = OUT_BF16 ? 2 : 4;
+    using W = Wave<G, ES>;
+    constexpr int EPL = W::EPL, LPT = W::LPT;
+    constexpr uint32_t WIDE = LOW + 1;           // the two code widths are LOW and WIDE bits
+    __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * W::LDS_BYTES];
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63u;
+    const uint32_t group = blockIdx.x * 4 + wave;
+    const uint32_t j0 = group * W::TILES;
+    if (j0 >= T) return;
+    uint8_t *lds = lds_all + wave * W::LDS_BYTES;
+    const bool full = T - j0 >= (uint32_t)W::TILES;
+    const uint32_t t = lane / LPT, part = lane % LPT;
+    const uint32_t j = (full || j0 + t < T) ? j0 + t : T - 1;            // lanes past the end repeat the last tile
+
+    const uint64_t word = reinterpret_cast<const uint64_t *>(packed + lay.bitmap)[j0 >> 6];
+    const uint32_t rank0 = reinterpret_cast<const uint32_t *>(packed + lay.ranks)[j0 >> 6];
+    const uint32_t s16 = reinterpret_cast<const uint16_t *>(packed + lay.scale)[j];
+    const uint32_t z16 = reinterpret_cast<const uint16_t *>(packed + lay.zero)[j];
+    const uint32_t pv = packed[lay.pivot + j];
+
+    // width and place of my tile: wide tiles before it
+    const uint32_t at = j & 63u;
+    const uint32_t half = at < 32u ? (uint32_t)word : (uint32_t)(word >> 32);
+    // The stream may have been damaged on its way here: the number of wide tiles before mine is clamped to what the
+    // configuration implies, so that every payload address stays inside the payload section whatever the stream holds.
+    const uint32_t bit = ((half >> (at & 31u)) & 1u) & (total_wide != 0u ? 1u : 0u);
+    uint32_t rank = rank0 + (uint32_t)__popc(half & ((1u << (at & 31u)) - 1u)) + (at < 32u ? 0u : (uint32_t)__popc((uint32_t)word));
+    rank = rank < total_wide - bit ? rank : total_wide - bit;
+    const bool wide = bit != 0;
+    const uint8_t *src = packed + lay.payload + ((uint64_t)LOW * j + rank) * (G / 8) + part * ((LOW + bit) * (EPL / 8));
+
+    constexpr int DW = (EPL * (int)WIDE + 31) / 32;
+    uint32_t dw[DW + 2];                         // the readers below may look past the string
+#pragma unroll
+    for (int i = 0; i < DW + 2; ++i) dw[i] = 0;
+    load_codes<EPL / 8, LOW>(src, wide, packed + lay.total, dw);
+
+    const float sf = f16_widen(s16), mnf = f16_widen(z16);
+    float x[EPL];
     if constexpr (WIDE <= 4) {
-        uint32_t nib[G / 8];
-        if (b == (uint32_t)WIDE) codes_to_nibbles<G, WIDE>(dw, nib);
-        else codes_to_nibbles<G, LOW>(dw, nib);
+        uint32_t nib[EPL / 8];
+        if (wide) codes_to_nibbles<EPL, WIDE>(dw, nib);
+        else codes_to_nibbles<EPL, LOW>(dw, nib);
         // de-quantize: even codes sit in the low nibbles of the bytes, odd codes in the high nibbles
         // (scaled by 16, undone exactly by a scale of sf/16)
         const float sf16 = sf * 0.0625f;
 #pragma unroll
-        for (int i = 0; i < G / 8; ++i) {
+        for (int i = 0; i < EPL / 8; ++i) {
             const uint32_t lo = nib[i] & 0x0f0f0f0fu, hi = nib[i] & 0xf0f0f0f0u;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -909,180 +1022,63 @@ __device__ __forceinline__ void decode_row(const typename Unit<G>::type *src, ui
             }
         }
     } else {
-        if (b == (uint32_t)WIDE) dequantize_codes<G, WIDE>(dw, sf, mnf, x);
-        else dequantize_codes<G, LOW>(dw, sf, mnf, x);
+        if (wide) dequantize_codes<EPL, WIDE>(dw, sf, mnf, x);
+        else dequantize_codes<EPL, LOW>(dw, sf, mnf, x);
     }
-    if (pv & 0x80u) {
-        butterfly<G>(x);
+    const bool flag = (pv & 0x80u) != 0;
+    if (flag) {                                  // the lanes of a tile agree
+        butterfly<EPL>(x);
+        butterfly_across<EPL, LPT>(x, part);
 #pragma unroll
-        for (int k = 0; k < G; ++k) x[k] = x[k] * TileConst<G>::c;
+        for (int k = 0; k < EPL; ++k) x[k] = x[k] * TileConst<G>::c;
     }
-    // my tile into its LDS row, narrowed to the output type
-    if constexpr (OUT_BF16) {
-        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-        typedef float floatx2 __attribute__((ext_vector_type(2)));
+    // my elements into my row of LDS, narrowed to the output type
+    const uint32_t row = lane * W::LANE_BYTES + (W::swizzle(lane) << 4);
 #pragma unroll
-        for (int c = 0; c < G / 8; ++c) {
+    for (int c = 0; c < W::CHUNKS; ++c) {
+        uint4 v;
+        if constexpr (OUT_BF16) {
+            typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+            typedef float floatx2 __attribute__((ext_vector_type(2)));
             uint32_t ws[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const floatx2 pr = {x[8 * c + 2 * i], x[8 * c + 2 * i + 1]};
                 ws[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));
             }
-            *reinterpret_cast<uint4 *>(row + c * 16) = make_uint4(ws[0], ws[1], ws[2], ws[3]);
-        }
-    } else {
-#pragma unroll
-        for (int c = 0; c < G / 4; ++c)
-            *reinterpret_cast<float4 *>(row + c * 16) = make_float4(x[4 * c], x[4 * c + 1], x[4 * c + 2], x[4 * c + 3]);
-    }
-    const uint32_t d = pv & 0x7fu & (uint32_t)(G - 1);      // masked: a corrupted pivot byte stays inside the row
-    if ((pv & 0x80u) && d != 0) {
-        // undo P_d inside my row
-        if constexpr (OUT_BF16) {
-            uint16_t *r16 = reinterpret_cast<uint16_t *>(row);
-            const uint16_t v0 = r16[0], vd = r16[d];
-            r16[0] = vd; r16[d] = v0;
+            v = make_uint4(ws[0], ws[1], ws[2], ws[3]);
         } else {
-            float *r32 = reinterpret_cast<float *>(row);
-            const float v0 = r32[0], vd = r32[d];
-            r32[0] = vd; r32[d] = v0;
+            v = make_uint4(__float_as_uint(x[4 * c]), __float_as_uint(x[4 * c + 1]), __float_as_uint(x[4 * c + 2]),
+                           __float_as_uint(x[4 * c + 3]));
+        }
+        *reinterpret_cast<uint4 *>(lds + (row ^ (uint32_t)(c << 4))) = v;
+    }
+    wave_lds_fence();
+    const uint32_t d = pv & 0x7fu & (uint32_t)(G - 1);      // masked: a corrupted pivot byte stays inside the tile
+    if (flag && d != 0 && part == 0) {
+        // undo P_d
+        uint8_t *e0 = lds + W::element_at(lane, 0), *ed = lds + W::element_at(lane, d);
+        if constexpr (OUT_BF16) {
+            const uint16_t v0 = *reinterpret_cast<uint16_t *>(e0), vd = *reinterpret_cast<uint16_t *>(ed);
+            *reinterpret_cast<uint16_t *>(e0) = vd; *reinterpret_cast<uint16_t *>(ed) = v0;
+        } else {
+            const float v0 = *reinterpret_cast<float *>(e0), vd = *reinterpret_cast<float *>(ed);
+            *reinterpret_cast<float *>(e0) = vd; *reinterpret_cast<float *>(ed) = v0;
         }
     }
-}
-
-// Persistent workgroups over contiguous runs of full batches, software-pipelined: while batch i is decoded,
-// the payload span, bit map words and per-tile metadata of batch i+1 are in flight; the rows of batch i are
-// written out one iteration late, just before the next loads are issued, so that no wait for loads has a
-// younger store in front of it.  The fast loop has no per-thread conditions on global memory operations.
-// The only two-step dependency -- the rank-table entries that locate a batch's payload and give its length
-// -- is taken out of the loop: the entries of the workgroup's batches are read into LDS up front.
-// The ragged last batch is handled after the loop by one workgroup.
-template <int G, bool OUT_BF16, int LOW>
-__global__ __launch_bounds__((Batch<G, OUT_BF16 ? 2 : 4>::TILES))
-void k_decode(const uint8_t *__restrict__ packed, void *__restrict__ out, Layout lay, uint32_t T, uint32_t total_wide)
-{
-    constexpr int ES = OUT_BF16 ? 2 : 4;
-    using B = Batch<G, ES>;
-    using U = typename Unit<G>::type;
-    using Meta = BatchMeta<B::TILES>;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[B::LDS_BYTES];
-    constexpr uint32_t WIDE = LOW + 1;           // the two code widths are LOW and WIDE bits
-    __shared__ __attribute__((aligned(16))) U pay[B::TILES * WIDE];
-    __shared__ uint32_t rank_lds[B::TILES + 1];
-    constexpr int WAVES = (B::TILES + 63) / 64;
-    __shared__ uint2 tile_meta[B::TILES];        // per tile: scale | zero << 16, pivot byte | (b == WIDE) << 8 | rel << 9
-    __shared__ uint16_t order[B::TILES];         // tiles in class order
-    __shared__ uint32_t class_count[4 * WAVES];  // tiles per class and wavefront, class-major
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t nfull = T / B::TILES, tail = T % B::TILES;
-    const uint32_t per = (nfull + gridDim.x - 1) / gridDim.x;
-    const uint32_t first = blockIdx.x * per;
-    const uint32_t last = first + per < nfull ? first + per : nfull;      // my batches: [first, last)
-    const uint16_t *scale = reinterpret_cast<const uint16_t *>(packed + lay.scale);
-    const uint16_t *zero = reinterpret_cast<const uint16_t *>(packed + lay.zero);
-    const uint8_t *pivot = packed + lay.pivot;
-    const uint32_t *ranks = reinterpret_cast<const uint32_t *>(packed + lay.ranks);
-    const U *payload = reinterpret_cast<const U *>(packed + lay.payload);
-    uint8_t *row = lds + tid * B::STRIDE;
-    uint32_t lane_zero = 0;
-    asm volatile("" : "+v"(lane_zero));
-    const uint64_t *bitmap = reinterpret_cast<const uint64_t *>(packed + lay.bitmap) + lane_zero;
-
-    // wide tiles before batch b (for the batch past the end of the tensor: all of them)
-    // The stream may have been damaged on its way here: the table's entries are clamped to the number of wide
-    // tiles the configuration implies, and a batch's count of wide tiles is taken as 0 if the table decreases, so
-    // that every payload address below stays inside the payload section whatever the stream holds.
-    auto rank_of_batch = [&](uint64_t b) {
-        const uint32_t r = b * B::TILES < T ? ranks[b * (B::TILES / 64)] : total_wide;
-        return r < total_wide ? r : total_wide;
-    };
-    // slots 0..TILES of the window hold the entries of batches wfirst .. wfirst + TILES
-    auto load_rank_window = [&](uint32_t wfirst) {
-        rank_lds[tid] = rank_of_batch((uint64_t)wfirst + tid);
-        if (tid == 0) rank_lds[B::TILES] = rank_of_batch((uint64_t)wfirst + B::TILES);
-        __syncthreads();
-    };
-    uint32_t wfirst = first;
-    if (first < last) load_rank_window(wfirst);
-
-    Meta m;            // bit map words of the batch whose loads are in flight / have just arrived
-    U pre[WIDE];
-    uint32_t s16 = 0, z16 = 0, pv = 0;
-    // issue the loads of full batch `batch` (inside the current window)
-    auto fetch = [&](uint32_t batch) {
-        const uint64_t j0 = (uint64_t)batch * B::TILES;
-        m.rank0 = rank_lds[batch - wfirst];
-        const uint32_t next_rank = rank_lds[batch - wfirst + 1];
-        const uint32_t total4 = next_rank > m.rank0 ? next_rank - m.rank0 : 0u;
-        const uint64_t base = (uint64_t)LOW * j0 + m.rank0;
+    wave_lds_fence();
+    // rows to the tensor in storage order: chunk lane, lane + 64, ... of the group (streaming stores: the decoded tensor is
+    // not read again by this library)
+    uint8_t *dst = static_cast<uint8_t *>(out) + (uint64_t)j0 * (G * ES) + lane * 16;
+    const uint32_t r = lane / W::CHUNKS;         // (64 / CHUNKS rows per step: a multiple of the swizzle's period)
+    const uint8_t *from = lds + r * W::LANE_BYTES + (((lane % W::CHUNKS) ^ W::swizzle(r)) << 4);
+    const uint32_t rows = full ? 64u : (T - j0) * LPT;
 #pragma unroll
-        for (int i = 0; i < LOW; ++i) pre[i] = payload[base + (uint32_t)i * B::TILES + tid];
-        // a thread's last unit exists only if the batch has more than `tid` wide tiles; otherwise the
-        // load is pointed at the batch's first unit (a line that is being read anyway) and ignored
-        pre[LOW] = payload[base + ((uint32_t)tid < total4 ? (uint32_t)LOW * (uint32_t)B::TILES + (uint32_t)tid : 0u)];
-#pragma unroll
-        for (int w = 0; w < Meta::WORDS; ++w) m.word[w] = bitmap[(j0 >> 6) + w];
-        s16 = scale[j0 + tid];
-        z16 = zero[j0 + tid];
-        pv = pivot[j0 + tid];
-    };
-
-    if (first < last) fetch(first);
-    bool have_prev = false;
-    uint32_t prev_batch = 0;
-    for (uint32_t batch = first; batch < last; ++batch) {
-        uint32_t b, rel, total4;
-        tile_pos<B::TILES, LOW>(m, tid, &b, &rel, &total4);
-#pragma unroll
-        for (int i = 0; i < (int)WIDE; ++i) pay[(uint32_t)i * B::TILES + tid] = pre[i];
-        // Tiles are regrouped by class -- (plain | transformed) x (narrow | wide) -- as in the encoder: lane p decodes
-        // the p-th tile in class order, so the butterfly runs only in the wavefronts that hold transformed tiles.
-        tile_meta[tid] = make_uint2(s16 | (z16 << 16), pv | ((b == WIDE) ? 0x100u : 0u) | (rel << 9));
-        const uint32_t cls = ((pv >> 7) << 1) | (b == WIDE ? 1u : 0u);
-        const uint32_t rank_in_wave = class_rank_in_wave<WAVES>(cls, (uint32_t)wave, (uint32_t)lane, class_count);
-        __syncthreads();
-        if (have_prev) stage_out<G, ES, true>(out, (uint64_t)prev_batch * B::TILES, B::TILES, lds);
-        order[rank_in_wave + class_group_base<WAVES>(cls, (uint32_t)wave, (uint32_t)lane, class_count)] = (uint16_t)tid;
-        __syncthreads();
-
-        if (batch + 1 < last) {
-            if (batch + 1 - wfirst == (uint32_t)B::TILES) {      // once every TILES iterations
-                __syncthreads();
-                wfirst = batch + 1;
-                load_rank_window(wfirst);
-            }
-            fetch(batch + 1);
+    for (int i = 0; i < W::CHUNKS; ++i) {
+        if (full || r + i * (64 / W::CHUNKS) < rows) {
+            const u32x4 v = *reinterpret_cast<const u32x4 *>(from + i * 1024);
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(dst + i * 1024));
         }
-        {
-            const uint32_t t = order[tid];
-            const uint2 tm = tile_meta[t];
-            decode_row<G, OUT_BF16, LOW>(pay + (tm.y >> 9), (tm.y & 0x100u) ? WIDE : (uint32_t)LOW, tm.x & 0xffffu,
-                                         tm.x >> 16, tm.y & 0xffu, lds + t * B::STRIDE);
-        }
-        prev_batch = batch;
-        have_prev = true;
-        __syncthreads();
-    }
-    if (have_prev) stage_out<G, ES, true>(out, (uint64_t)prev_batch * B::TILES, B::TILES, lds);
-
-    if (tail != 0 && blockIdx.x == gridDim.x - 1) {
-        __syncthreads();
-        const uint64_t j0 = (uint64_t)nfull * B::TILES;
-        load_meta<B::TILES>(packed, lay, j0, T, 0u, m);
-        uint32_t b, rel, total4;
-        tile_pos<B::TILES, LOW>(m, tid, &b, &rel, &total4);
-        // clamped like the table entries above: the span never reaches past the payload section
-        const uint32_t rank0 = m.rank0 < total_wide ? m.rank0 : total_wide;
-        const uint32_t room = total_wide - rank0;
-        const uint32_t span = (uint32_t)LOW * tail + (total4 < room ? total4 : room);
-        const U *gsrc = payload + ((uint64_t)LOW * j0 + rank0);
-        for (uint32_t q = tid; q < span; q += B::TILES) pay[q] = gsrc[q];
-        __syncthreads();
-        if ((uint32_t)tid < tail)
-            decode_row<G, OUT_BF16, LOW>(pay + rel, b, scale[j0 + tid], zero[j0 + tid], pivot[j0 + tid], row);
-        __syncthreads();
-        stage_out<G, ES, false>(out, j0, tail, lds);
     }
 }
 

@@ -506,6 +506,24 @@ def test_all_tile_widths_and_dtypes_over_several_batches(tahq, G, dtype_name):
                    out_dtype=(tahq.BF16 if dtype == tahq.F32 else tahq.F32))
 
 
+@pytest.mark.parametrize("G", (8, 16, 32, 64, 128))
+@pytest.mark.parametrize("dtype_name", ("f32", "bf16"))
+def test_edges_of_a_wavefronts_group_of_tiles(tahq, G, dtype_name):
+    # a wavefront takes 64, 32 or 16 tiles, a workgroup four times as many: one tile, one less, one more, several groups
+    # and a rest; both output types, so that every number of lanes per tile occurs
+    dtype = tahq.F32 if dtype_name == "f32" else tahq.BF16
+    rng = np.random.default_rng(400 + G)
+    for T in (1, 15, 16, 17, 31, 33, 63, 64, 65, 127, 129, 255, 257):
+        x = rng.standard_normal((1, T, G)).astype(np.float32)
+        x[0, ::3, (5 * G) // 8] *= 25.0                   # transformed tiles with a pivot in every lane's part
+        x[0, 1::5, G - 1] *= 40.0
+        xin = x if dtype == tahq.F32 else workloads.f32_to_bf16_bits(x)
+        _say(f"[case] group edges: T={T} G={G} {dtype_name}")
+        check_case(tahq, xin, 1, T, G, G, dtype, 3.5)
+        check_case(tahq, xin, 1, T, G, G, dtype, 3.0, out_dtype=tahq.F32 if dtype == tahq.BF16 else tahq.BF16)
+        check_case(tahq, xin, 1, T, G, G, dtype, 5.5, low_bits=5)
+
+
 @pytest.mark.parametrize("G", (8, 16, 32, 64))
 def test_hidden_size_1600_and_small_tiles_on_a_workload(tahq, G):
     # 1600 channels: 200 / 100 / 50 / 25 tiles per token, sample boundaries inside batches and 64-tile groups
