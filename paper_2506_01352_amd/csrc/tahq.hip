@@ -218,6 +218,18 @@ void launch_entropy(const Shape &s, const tahq_config *cfg, const void *d_in, fl
                             bin_scale, s.n, qp);
 }
 
+template <uint32_t PLACES, uint32_t BINS, int SHIFT>
+void launch_select_small(dim3 grid, const float *H, uint32_t n, uint32_t k, const Shape &s, uint64_t *bitmap, uint32_t *ranks,
+                         Enqueue *qp)
+{
+    // the topmost bin but one holds ln A, the largest an entropy can be
+    const float ln_a = (float)__builtin_log((double)s.A);
+    int bits;
+    memcpy(&bits, &ln_a, 4);
+    (*qp)(k_select_small<PLACES, BINS, SHIFT>, grid, dim3(kSmallUnitThreads), H, n, k, s.m, (bits >> SHIFT) - (int)(BINS - 2),
+          bitmap, ranks);
+}
+
 // ---- backward-pass fixed-point compressor
 
 struct NaiveShape {
@@ -368,9 +380,6 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
     if (packed_capacity < lay.total) return TAHQ_ERR_BUFFER_TOO_SMALL;
     if (workspace_capacity < ws.total) return TAHQ_ERR_WORKSPACE_TOO_SMALL;
     if (misaligned(d_in) || misaligned(d_packed) || misaligned(d_workspace)) return TAHQ_ERR_MISALIGNED;
-    // the selection kernels of large ranking units put the unit into the grid's second dimension
-    if (s.kA != 0 && s.kA != s.nA && s.U > 65535u && (s.nA > kSmallUnitMaxKeys || multi_launch))
-        return TAHQ_ERR_UNSUPPORTED;
 
     Enqueue q{(hipStream_t)stream};
     uint8_t *packed = static_cast<uint8_t *>(d_packed);
@@ -380,7 +389,11 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
     const bool select = s.kA != 0 && s.kA != s.nA;
     const bool wide = s.m > 1;     // allocation tiles of several quantization tiles
     // ranking units that one workgroup can hold are ranked in a single launch
-    const bool small_units = select && s.nA <= kSmallUnitMaxKeys && !multi_launch;
+    const uint64_t places = s.nA + (!wide && s.n % 64 != 0 ? 63u : 0u);       // counted from a 64-tile boundary
+    const bool small_units = select && places <= kSmallUnitMaxKeys && !multi_launch;
+
+    // the selection kernels of large ranking units put the unit into the grid's second dimension
+    if (select && !small_units && s.U > 65535u) return TAHQ_ERR_UNSUPPORTED;
 
     // header, section padding, selection scratch
     HeaderWords hdr;
@@ -409,9 +422,11 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
     const bool const_in_prologue = !select && (phases & TAHQ_PHASE_PROLOGUE) && (phases & TAHQ_PHASE_SELECT);
     if (phases & TAHQ_PHASE_PROLOGUE) {
         const uint32_t const_words = const_in_prologue ? (uint32_t)words64 : 0u;
-        const uint32_t blocks = histograms ? 32u : (const_words ? (blocks_for(words64) < 256u ? blocks_for(words64) : 256u) : 1u);
+        const uint32_t edge_units = small_units && s.n % 64 != 0 ? s.U : 0u;
+        const uint64_t items = const_words > edge_units ? const_words : edge_units;
+        const uint32_t blocks = histograms ? 32u : blocks_for(items < 1 ? 1 : (items > 65536 ? 65536 : items));
         q(k_prologue, dim3(blocks), dim3(256), packed, hdr, pads, reinterpret_cast<uint32_t *>(wsb + ws.hist0), zero_words,
-          const_words, (uint32_t)s.T, s.kA == s.nA ? 1 : 0, bitmap, ranks);
+          edge_units, (uint32_t)s.n, const_words, (uint32_t)s.T, s.kA == s.nA ? 1 : 0, bitmap, ranks);
     }
 
     if (select) {
@@ -456,20 +471,14 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
         } else
         if ((phases & TAHQ_PHASE_SELECT) && small_units) {
             const uint32_t n32 = (uint32_t)s.nA, k32 = (uint32_t)s.kA;
-            const int aligned = (!wide && s.n % 64 == 0) ? 1 : 0;
-            uint32_t *ranks_a = reinterpret_cast<uint32_t *>(wsb + ws.ranks_a);
-            uint32_t *rank_out = wide ? ranks_a : ranks;
-            const dim3 grid(s.U), block(kSmallUnitThreads);
-            if (n32 <= 16 * kSmallUnitThreads)
-                q(k_select_small<16>, grid, block, (const float *)H, n32, k32, bitmap, rank_out, sel, aligned);
-            else
-                q(k_select_small<32>, grid, block, (const float *)H, n32, k32, bitmap, rank_out, sel, aligned);
-            if (wide)
-                q(k_expand_alloc, dim3(blocks_for(words64 * 64)), dim3(256),
-                                   (const uint8_t *)sel, (const uint32_t *)ranks_a, (uint32_t)s.T, s.m, bitmap, ranks);
-            else if (!aligned)
-                q(k_bitmap_pack, dim3(blocks_for(words64 * 64)), dim3(256),
-                                   (const uint8_t *)sel, (uint32_t)s.T, bitmap);
+            // with A > G every workgroup expands a part of the unit's bit map (a unit may start inside a word)
+            const uint64_t unit_words = s.n / 64 + 2;
+            const dim3 grid(s.U, wide ? (uint32_t)((unit_words + kExpandWords - 1) / kExpandWords) : 1u);
+            // as little LDS as will do; the largest units leave room for half as many bins
+            if (places <= 4096) launch_select_small<4096, 8192, 12>(grid, H, n32, k32, s, bitmap, ranks, &q);
+            else if (places <= 16384) launch_select_small<16384, 8192, 12>(grid, H, n32, k32, s, bitmap, ranks, &q);
+            else if (places <= 28672) launch_select_small<28672, 8192, 12>(grid, H, n32, k32, s, bitmap, ranks, &q);
+            else launch_select_small<kSmallUnitMaxKeys, 4096, 13>(grid, H, n32, k32, s, bitmap, ranks, &q);
         } else if (phases & TAHQ_PHASE_SELECT) {
             // the selection ranks allocation tiles; with A = G they are the stream's tiles
             const uint32_t n32 = (uint32_t)s.nA, k32 = (uint32_t)s.kA;

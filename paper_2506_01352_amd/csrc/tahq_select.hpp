@@ -3,8 +3,8 @@
 // Entropies map to order-preserving 32-bit keys; three ways to find the k-th largest key K*, how many tiles equal to
 // K* are still wanted (`take`), and from them the bit map and the rank table:
 //
-//   * ranking units of at most 32768 tiles: k_select_small, one workgroup per unit in one launch (keys in registers,
-//     radix passes on an LDS histogram), because at that size several launches cost more than the work;
+//   * ranking units of at most 32768 tiles: k_select_small, one workgroup per unit in one launch (entropies in
+//     registers, one histogram in LDS, the threshold's bin ranked directly), because at that size several launches cost more than the work;
 //   * larger units that start on 64-tile boundaries and are whole batches of the entropy kernel: that kernel also
 //     counts the entropies over 2048 linear bins per unit; k_select_classify settles every tile outside the bin that
 //     holds K* and lists the tiles inside it, k_select_resolve ranks that list (further down in this file);
@@ -527,123 +527,278 @@ constexpr uint32_t kSmallUnitThreads = kBlockSelectThreads;
 #ifndef TAHQ_SMALL_UNIT_MAX
 #define TAHQ_SMALL_UNIT_MAX 32768
 #endif
-constexpr uint32_t kSmallUnitMaxKeys = TAHQ_SMALL_UNIT_MAX;    // 32 keys per thread; beyond that the keys no longer fit the
-                                                 // register file of a 1024-thread workgroup and the multi-launch path is as fast
+// Places (tiles, counted from the 64-tile boundary at or before the unit's first tile) that the LDS of one workgroup holds.
+constexpr uint32_t kSmallUnitMaxKeys = TAHQ_SMALL_UNIT_MAX;
+constexpr uint32_t kSmallListCap = 256;          // tiles of the threshold bin that are placed directly
+constexpr uint32_t kExpandWords = 2048;          // bit map words a workgroup expands when A > G
 
-// A ranking unit of at most 1024 * KPT keys, ranked by ONE workgroup that keeps the keys in registers: the
-// radix passes (12 bits at a time of key - smallest key, two passes as a rule) run on an LDS histogram, the per-group counts and their prefix sums stay in LDS, and
-// the bit map and rank table (or, for units that do not start on 64-tile boundaries, one byte per tile and
-// the rank entries of the 64-tile groups) are written at the end.  Same result as k_radix_pass x 3,
-// k_seg_count and k_assign, in one launch instead of five: small tensors are bound by launch latency.
-// Wavefront w owns the KPT consecutive 64-tile groups KPT*w ..: thread (w, lane l) holds, for r = 0 .. KPT-1, the
-// key of tile 64 * (KPT w + r) + l of the unit.  KPT is 16 or 32.
-template <int KPT>
-__global__ __launch_bounds__(kSmallUnitThreads) void k_select_small(const float *__restrict__ H, uint32_t n, uint32_t k,
-                                                                    uint64_t *__restrict__ bitmap,
-                                                                    uint32_t *__restrict__ ranks,
-                                                                    uint8_t *__restrict__ sel_bytes, int aligned)
+// The 16 wavefronts' entries of `totals` that come before mine, added up.
+__device__ __forceinline__ uint32_t sum_of_waves_before(const uint32_t *totals, uint32_t wave, int lane)
 {
-    constexpr int NG = 16 * KPT;                 // 64-tile groups the workgroup can hold
-    constexpr int PER = NG / 64;                 // lane l of wavefront 0 scans the PER consecutive groups PER*l ..
-    __shared__ BlockSelectLds L;
-    __shared__ uint32_t grp_eq[NG], grp_sel[NG];
+    const uint32_t own = totals[lane & 15];
+    uint32_t v = own;
+    v += dpp_or_zero<0x111, 0xF>(v);             // a scan over each row of 16 lanes
+    v += dpp_or_zero<0x112, 0xF>(v);
+    v += dpp_or_zero<0x114, 0xF>(v);
+    v += dpp_or_zero<0x118, 0xF>(v);
+    return (uint32_t)__builtin_amdgcn_readlane((int)(v - own), (int)wave);
+}
+
+// LDS of k_select_small, for units of at most PLACES places and BINS bins of the first cut
+template <uint32_t PLACES, uint32_t BINS>
+struct SmallSelectLds {
+    union {
+        int key[PLACES];                         // the entropies' bit patterns, by place
+        BlockSelectLds sel;                      // the crowded-bin path, which reads the entropies from memory again
+    };
+    uint32_t hist[BINS];
+    uint64_t list[kSmallListCap];                // tiles of the threshold bin: key << 32 | ~place
+    uint64_t words[PLACES / 64];                 // bit map words over places
+    uint64_t equal[PLACES / 64];                 // the crowded-bin path: keys equal to the threshold
+    uint32_t prefix[PLACES / 64];                // selected places before each word
+    uint32_t wave_total[kSmallUnitThreads / 64], wave_equal[kSmallUnitThreads / 64];
+    uint32_t chosen[3];                          // threshold bin, wanted inside it, its tiles
+    uint32_t listed;
+};
+
+// A ranking unit that one workgroup can hold, ranked in one launch, everything in LDS.
+//
+// A place is a tile's index counted from the 64-tile boundary at or before the unit's first tile, so that 64 places are
+// one word of the stream's bit map whatever the unit's length (with A > G: the index of the allocation tile, from 0).
+// Wavefront w takes the blocks w, w + 16, .. of 256 places, four consecutive places per lane.
+//
+// The entropies' bit patterns fall into BINS bins of 2^SHIFT neighbouring floats each, four octaves below ln A (`bin0` is
+// the number of the lowest bin); the bins at the ends take what lies beyond.  The bin that holds the k-th largest settles
+// every other tile with one comparison each; its own tiles (about a hundred) are placed directly among each other by (key
+// descending, tile ascending).  A crowded bin (ties) goes through a radix select instead.
+//
+// Bound by the instruction issue of its one compute unit, scalar instructions included (a ballot per 64 entropies and what
+// follows it cost three times as much as the carries that collect a lane's four bits here), and by a dozen dependent
+// steps.  25600 tiles: 7.3 us; 14.4 us as a two-pass radix select with the entropies in registers, 8192 tiles 11.0 -> 6.6,
+// the 2048 allocation tiles (A = 4096) of four samples with their expansion 11.3 + 4.9 -> 6.4.
+//
+// With A > G (m > 1) the words of the allocation tiles are expanded to quantization tiles from LDS, kExpandWords words by
+// each of the unit's gridDim.y workgroups, all of which select for themselves.
+template <uint32_t PLACES, uint32_t BINS, int SHIFT>
+__global__ __launch_bounds__(kSmallUnitThreads) void k_select_small(const float *__restrict__ H, uint32_t n, uint32_t k, uint32_t m,
+                                                                    int bin0, uint64_t *__restrict__ bitmap,
+                                                                    uint32_t *__restrict__ ranks)
+{
+    __shared__ __attribute__((aligned(16))) SmallSelectLds<PLACES, BINS> L;
+    static_assert(sizeof(L) <= 163840, "the LDS of a compute unit");
+    constexpr uint32_t WAVES = kSmallUnitThreads / 64;
+    constexpr uint32_t PER = BINS / kSmallUnitThreads;       // bins per thread
+    constexpr uint32_t BLOCKS = PLACES / 256 / WAVES;        // blocks per wavefront
+    static_assert(PER % 4 == 0 && PLACES / 64 <= kSmallUnitThreads && BLOCKS >= 1 && BLOCKS <= 8, "four bits per block in a dword");
     const uint32_t u = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const float *uH = H + (uint64_t)u * n;
-    const uint64_t below = (1ull << lane) - 1ull;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t phase = m == 1 ? (uint32_t)(((uint64_t)u * n) & 63u) : 0u;      // place of the unit's first tile
+    const uint32_t end = phase + n, nwords = (end + 63) / 64, nblocks = (end + 255) / 256;
+    const float *uH = H + ((uint64_t)u * n - phase);         // by place
 
-    // all loads first (from a clamped index, so that none of them sits behind a branch), then the keys
-    float h[KPT];
-#pragma unroll
-    for (int r = 0; r < KPT; ++r) {
-        const uint32_t i = (uint32_t)(KPT * wave + r) * 64u + lane;
-        h[r] = uH[i < n ? i : n - 1];
+    // All loads at once, straight to LDS.  (Whole words of 64 places are read, which may reach into the neighbouring units or up
+    // to 63 floats past the entropies, where the workspace goes on; beyond them from a clamped index.)
+    for (uint32_t b = wave; b < nblocks; b += WAVES) {
+        const uint32_t place = b * 256u + 4u * lane, top = nwords * 64u - 4u;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(uH + (place < top ? place : top)),
+                                         (__attribute__((address_space(3))) void *)&L.key[b * 256u], 16, 0, 0);
     }
-    uint32_t key[KPT];
 #pragma unroll
-    for (int r = 0; r < KPT; ++r) key[r] = order_key(h[r]);
-    auto in_unit = [&](int r) { return (uint32_t)(KPT * wave + r) * 64u + lane < n; };
-
-    // the k-th largest key, how many tiles equal to it are taken, and how many there are
-    uint32_t thr, take, equal;
-    block_radix_select(k, [&](auto &&visit) {
-#pragma unroll
-        for (int r = 0; r < KPT; ++r) {
-            if (in_unit(r)) visit(key[r]);
+    for (uint32_t i = 0; i < PER / 4; ++i)
+        reinterpret_cast<uint4 *>(L.hist)[i * kSmallUnitThreads + tid] = make_uint4(0, 0, 0, 0);
+    if (tid == 0) L.listed = 0;
+    __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0): my wavefront's entropies are in LDS
+    __syncthreads();
+    for (uint32_t b = wave; b < nblocks; b += WAVES) {
+        int4 *at = reinterpret_cast<int4 *>(&L.key[b * 256u + 4u * lane]);
+        int4 q = *at;
+        if ((b == 0 && phase != 0) || (b == nblocks - 1 && (end & 255u) != 0)) {
+            // places outside the unit take the bit pattern of -0.0f, the lowest of all as a signed integer and no entropy's
+            const uint32_t i = b * 256u + 4u * lane - phase;
+            q.x = i < n ? q.x : INT32_MIN; q.y = i + 1u < n ? q.y : INT32_MIN;
+            q.z = i + 2u < n ? q.z : INT32_MIN; q.w = i + 3u < n ? q.w : INT32_MIN;
+            *at = q;
         }
-    }, L, &thr, &take, &equal);
-
-    // The width bit of every tile; lane r keeps the bit map word of the wavefront's r-th group.
-    uint64_t my_word = 0;
-    if (take == equal) {
-        // every tile whose key equals the threshold is taken (one such tile, as a rule)
+        const int v[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-        for (int r = 0; r < KPT; ++r) {
-            const bool sel = in_unit(r) && key[r] >= thr;
-            const uint64_t selm = __ballot(sel);
-            if (lane == r) my_word = selm;
-            if (!aligned && in_unit(r)) sel_bytes[(uint64_t)u * n + (uint64_t)(KPT * wave + r) * 64u + lane] = sel ? 1 : 0;
+        for (int c = 0; c < 4; ++c) {
+            const int bin = (v[c] >> SHIFT) - bin0;          // as signed integers: negative values and NaN with the sign bit set lowest
+            atomicAdd(&L.hist[bin < 0 ? 0 : bin > (int)BINS - 1 ? (int)BINS - 1 : bin], 1u);
         }
-    } else {
-        // Keys equal to thr are taken in index order until `take` are used up, so every group needs the number of
-        // equal keys before it: lane r keeps the count of the wavefront's r-th group, wavefront 0 scans the groups.
-        uint32_t my_eq = 0;
+    }
+    __syncthreads();
+    // The bin of the k-th largest: thread t adds up the PER bins from BINS - PER (t + 1) on, a scan over the workgroup tells
+    // it how many entropies lie above them.  1 <= k <= n, so exactly one thread finds it.
+    {
+        uint32_t c[PER], mine = 0;
+        const uint32_t low = BINS - PER * ((uint32_t)tid + 1);
 #pragma unroll
-        for (int r = 0; r < KPT; ++r) {
-            const uint32_t ne = (uint32_t)__popcll(__ballot(in_unit(r) && key[r] == thr));
-            if (lane == r) my_eq = ne;
+        for (uint32_t i = 0; i < PER / 4; ++i) {
+            const uint4 q = reinterpret_cast<const uint4 *>(L.hist + low)[i];
+            c[4 * i] = q.x; c[4 * i + 1] = q.y; c[4 * i + 2] = q.z; c[4 * i + 3] = q.w;
+            mine += q.x + q.y + q.z + q.w;
         }
-        if (lane < KPT) grp_eq[KPT * wave + lane] = my_eq;
+        const uint32_t incl = wave_incl_scan(mine);
+        if (lane == 63) L.wave_total[wave] = incl;
         __syncthreads();
-        if (tid < 64) {
-            uint32_t e[PER], esum = 0;
+        uint32_t above = sum_of_waves_before(L.wave_total, wave, lane) + incl - mine;
+        if (above < k && k <= above + mine) {
 #pragma unroll
-            for (int i = 0; i < PER; ++i) { e[i] = grp_eq[lane * PER + i]; esum += e[i]; }
-            uint32_t eq_before = wave_incl_scan(esum) - esum;
-#pragma unroll
-            for (int i = 0; i < PER; ++i) { grp_eq[lane * PER + i] = eq_before; eq_before += e[i]; }
-        }
-        __syncthreads();
-        const uint32_t my_eq_before = lane < KPT ? grp_eq[KPT * wave + lane] : 0u;
-#pragma unroll
-        for (int r = 0; r < KPT; ++r) {
-            const bool ok = in_unit(r);
-            const bool eq = ok && key[r] == thr;
-            const uint64_t eqm = __ballot(eq);
-            bool sel = ok && key[r] > thr;
-            if (eqm) {                           // at most a few groups hold keys equal to the threshold, as a rule
-                const uint32_t eq_before = (uint32_t)__builtin_amdgcn_readlane((int)my_eq_before, r);
-                sel = sel || (eq && eq_before + (uint32_t)__popcll(eqm & below) < take);
+            for (uint32_t i = PER; i-- > 0;) {
+                if (above < k && k <= above + c[i]) {
+                    const uint32_t outside = low + i == 0 ? nblocks * 256u - n : 0u;     // bin 0 has counted those as well
+                    L.chosen[0] = low + i; L.chosen[1] = k - above; L.chosen[2] = c[i] - outside;
+                }
+                above += c[i];
             }
-            const uint64_t selm = __ballot(sel);
-            if (lane == r) my_word = selm;
-            if (!aligned && ok) sel_bytes[(uint64_t)u * n + (uint64_t)(KPT * wave + r) * 64u + lane] = sel ? 1 : 0;
         }
+        __syncthreads();
     }
-    if (lane < KPT) grp_sel[KPT * wave + lane] = (uint32_t)__popcll(my_word);
-    __syncthreads();
-    if (tid < 64) {
-        uint32_t c[PER], csum = 0;
+    const uint32_t bstar = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[0]);
+    const uint32_t rem = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[1]);
+    const uint32_t crowd = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[2]);
+    // the bit patterns of that bin, first and last
+    const int first = bstar == 0 ? INT32_MIN + 1 : (int)((bstar + (uint32_t)bin0) << SHIFT);
+    const int last = bstar == BINS - 1 ? INT32_MAX : (int)(((bstar + (uint32_t)bin0 + 1u) << SHIFT) - 1u);
+    // places of word g that belong to the unit
+    auto in_unit = [&](uint32_t g) -> uint64_t {
+        uint64_t mask = ~0ull;
+        if (g == 0) mask <<= phase;
+        if (end - g * 64u < 64u) mask &= (1ull << (end - g * 64u)) - 1ull;
+        return mask;
+    };
+    // block b's four bits per lane -> its eight dwords of `out`: eight neighbouring lanes fill one
+    auto put_bits = [&](uint64_t *out, uint32_t b, uint32_t four) {
+        uint32_t d = four << (4 * (lane & 7));
+        d |= dpp_or_zero<0xB1, 0xF>(d);          // lane ^ 1
+        d |= dpp_or_zero<0x4E, 0xF>(d);          // lane ^ 2
+        d |= dpp_or_zero<0x141, 0xF>(d);         // lane ^ 7: the other four
+        if ((lane & 7) == 0) reinterpret_cast<uint32_t *>(out)[b * 8u + (lane >> 3)] = d;
+    };
+    if (crowd <= kSmallListCap) {
+        uint32_t inside = 0;                     // my tiles of the bin, four bits per block, the last block lowest
+        int4 next = *reinterpret_cast<const int4 *>(&L.key[wave * 256u + 4u * lane]);
+        for (uint32_t b = wave; b < nblocks; b += WAVES) {
+            const int4 q = next;
+            if (b + WAVES < nblocks) next = *reinterpret_cast<const int4 *>(&L.key[(b + WAVES) * 256u + 4u * lane]);
+            const uint32_t above = (q.x > last ? 1u : 0u) | (q.y > last ? 2u : 0u) | (q.z > last ? 4u : 0u) | (q.w > last ? 8u : 0u);
+            const uint32_t reach = (q.x >= first ? 1u : 0u) | (q.y >= first ? 2u : 0u) | (q.z >= first ? 4u : 0u) | (q.w >= first ? 8u : 0u);
+            put_bits(L.words, b, above);
+            inside = (inside << 4) | (reach & ~above);
+        }
+        if (__ballot(inside != 0) != 0) {
+            // one place in the list for all of the wavefront's
+            const uint32_t count = (uint32_t)__popc(inside), incl = wave_incl_scan(count);
+            uint32_t at = 0;
+            if (lane == 63) at = atomicAdd(&L.listed, incl);
+            at = (uint32_t)__builtin_amdgcn_readlane((int)at, 63) + incl - count;
+            const uint32_t mine_blocks = (nblocks - wave + WAVES - 1) / WAVES;
+            while (inside != 0) {
+                const uint32_t bit = (uint32_t)__ffs((int)inside) - 1u;
+                inside &= inside - 1u;
+                const uint32_t place = (wave + WAVES * (mine_blocks - 1u - bit / 4)) * 256u + 4u * lane + bit % 4;
+                L.list[at++] = ((uint64_t)order_key(__uint_as_float((uint32_t)L.key[place])) << 32) | (uint32_t)~place;
+            }
+        }
+        __syncthreads();
+        // four threads per listed tile count the tiles ahead of it
+        if ((uint32_t)tid < 4 * crowd) {
+            const uint64_t mine = L.list[tid >> 2];
+            uint32_t ahead = 0;
+#pragma unroll 4
+            for (uint32_t i = (uint32_t)tid & 3u; i < crowd; i += 4) ahead += L.list[i] > mine ? 1u : 0u;
+            ahead += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ahead, 0xB1, 0xF, 0xF, true);      // lane ^ 1
+            ahead += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ahead, 0x4E, 0xF, 0xF, true);      // lane ^ 2
+            const uint32_t place = ~(uint32_t)mine;
+            if (((uint32_t)tid & 3u) == 0 && ahead < rem)
+                atomicOr(reinterpret_cast<uint32_t *>(L.words) + (place >> 5), 1u << (place & 31u));
+        }
+        __syncthreads();
+    } else {
+        // the entropies' LDS serves the radix select, the entropies come from memory again (-0.0f outside the unit)
+        auto each = [&](auto &&visit) {
+            for (uint32_t p0 = wave * 64u; p0 < nwords * 64u; p0 += 8 * kSmallUnitThreads) {
+                float h[8];
 #pragma unroll
-        for (int i = 0; i < PER; ++i) { c[i] = grp_sel[lane * PER + i]; csum += c[i]; }
-        uint32_t rank_before = wave_incl_scan(csum) - csum;
+                for (uint32_t r = 0; r < 8; ++r) {           // from a clamped index: none of the loads sits behind a branch
+                    const uint32_t p = p0 + r * kSmallUnitThreads + lane;
+                    h[r] = uH[p - phase < n ? p : phase];
+                    if (p - phase >= n) h[r] = -0.0f;
+                }
 #pragma unroll
-        for (int i = 0; i < PER; ++i) { grp_sel[lane * PER + i] = rank_before; rank_before += c[i]; }
+                for (uint32_t r = 0; r < 8; ++r)
+                    if (p0 + r * kSmallUnitThreads < nwords * 64u) visit(p0 + r * kSmallUnitThreads + lane, h[r]);
+            }
+        };
+        uint32_t thr, take, equal;
+        block_radix_select(rem, [&](auto &&visit) {
+            each([&](uint32_t, float h) {
+                const int v = (int)__float_as_uint(h);
+                if (v >= first && v <= last) visit(order_key(h));
+            });
+        }, L.sel, &thr, &take, &equal);
+        each([&](uint32_t p, float h) {
+            const uint32_t key = order_key(h);
+            const uint64_t eq = __ballot(key == thr), above = __ballot(key > thr);
+            if (lane == 0) { L.equal[p >> 6] = eq; L.words[p >> 6] = above; }
+        });
+        __syncthreads();
+        // Keys equal to thr are taken in index order until `take` are used up.  (A place outside the unit may lie above a
+        // threshold that is a NaN with the sign bit set.)
+        const uint64_t eq = (uint32_t)tid < nwords ? L.equal[tid] : 0ull;
+        const uint32_t count = (uint32_t)__popcll(eq), incl = wave_incl_scan(count);
+        if (lane == 63) L.wave_equal[wave] = incl;
+        __syncthreads();
+        const uint32_t eq_before = sum_of_waves_before(L.wave_equal, wave, lane) + incl - count;
+        if ((uint32_t)tid < nwords) {
+            uint64_t taken = eq;
+            if (eq_before >= take) taken = 0;
+            else
+                for (uint32_t over = eq_before + count; over > take; --over) taken &= ~(1ull << (63 - __builtin_clzll(taken)));
+            L.words[tid] = (L.words[tid] & in_unit((uint32_t)tid)) | taken;
+        }
+        __syncthreads();
     }
+    // selected places before every word
+    const uint64_t word = (uint32_t)tid < nwords ? L.words[tid] : 0ull;
+    const uint32_t cnt = (uint32_t)__popcll(word), incl = wave_incl_scan(cnt);
+    if (lane == 63) L.wave_total[wave] = incl;
     __syncthreads();
-    // lane r writes what belongs to the wavefront's r-th group
-    const uint32_t g = (uint32_t)(KPT * wave + lane);
-    if (lane < KPT && g * 64u < n) {
-        const uint32_t rank = u * k + grp_sel[g];            // wide tiles before the group, in the whole tensor
-        const uint64_t j0 = (uint64_t)u * n + (uint64_t)g * 64u;     // the group's first tile in the tensor
-        if (aligned) {
-            bitmap[j0 >> 6] = my_word;
-            ranks[j0 >> 6] = rank;
-        } else {
-            // units do not start on 64-tile boundaries: the rank-table entry of the boundary inside this group
-            // (if the group still reaches it)
-            const uint32_t p = (uint32_t)((64u - (uint32_t)(j0 & 63u)) & 63u);        // distance to the boundary
-            if (g * 64u + p < n) ranks[(j0 + p) >> 6] = rank + (uint32_t)__popcll(my_word & ((1ull << p) - 1ull));
+    const uint32_t before = sum_of_waves_before(L.wave_total, wave, lane) + incl - cnt;
+    if (m == 1) {
+        if ((uint32_t)tid < nwords) {
+            const uint64_t at = (((uint64_t)u * n) >> 6) + (uint32_t)tid;
+            // a word that the unit shares with a neighbour has been cleared by an earlier kernel
+            if (in_unit((uint32_t)tid) == ~0ull) bitmap[at] = word;
+            else atomicOr(reinterpret_cast<unsigned long long *>(bitmap) + at, (unsigned long long)word);
+            if (tid != 0 || phase == 0) ranks[at] = u * k + before;        // every earlier unit holds exactly k
+        }
+        return;
+    }
+    // A > G: the words and rank-table entries of the quantization tiles, m of which share the width of their allocation tile
+    if ((uint32_t)tid < nwords) L.prefix[tid] = before;
+    __syncthreads();
+    const uint32_t *bits = reinterpret_cast<const uint32_t *>(L.words);
+    const uint64_t nq = (uint64_t)n * m, q0 = (uint64_t)u * nq;            // the unit's quantization tiles
+    const uint64_t w_end = (q0 + nq + 63) >> 6;
+    uint64_t w_stop = (q0 >> 6) + (uint64_t)(blockIdx.y + 1) * kExpandWords;
+    if (w_stop > w_end) w_stop = w_end;
+    for (uint64_t w = (q0 >> 6) + (uint64_t)blockIdx.y * kExpandWords + (uint32_t)tid; w < w_stop; w += kSmallUnitThreads) {
+        // quantization tiles [lo, hi) of the word belong to the unit
+        const uint64_t lo = 64 * w > q0 ? 64 * w : q0, hi = 64 * w + 64 < q0 + nq ? 64 * w + 64 : q0 + nq;
+        const uint32_t a0 = (uint32_t)((lo - q0) / m), r0 = (uint32_t)((lo - q0) % m);
+        uint64_t out = 0;
+        uint32_t a = a0, run = m - r0;           // quantization tiles left of allocation tile a
+        for (uint64_t j = lo; j < hi; j += run, run = m, ++a) {
+            const uint64_t len = hi - j < run ? hi - j : run;
+            if ((bits[a >> 5] >> (a & 31u)) & 1u) out |= (~0ull >> (64 - len)) << (j & 63u);
+        }
+        if (hi - lo == 64) bitmap[w] = out;
+        else atomicOr(reinterpret_cast<unsigned long long *>(bitmap) + w, (unsigned long long)out);
+        if (lo == 64 * w) {
+            const uint32_t rank_a = u * k + L.prefix[a0 >> 6] + (uint32_t)__popcll(L.words[a0 >> 6] & ((1ull << (a0 & 63u)) - 1ull));
+            ranks[w] = rank_a * m + (((bits[a0 >> 5] >> (a0 & 31u)) & 1u) ? r0 : 0u);
         }
     }
 }
@@ -1013,12 +1168,15 @@ __global__ __launch_bounds__(256) void k_bitmap_const(uint32_t T, int all_wide, 
 struct HeaderWords { uint32_t w[16]; };
 struct PadList { uint64_t begin[5]; uint32_t len[5]; };
 
+// With `edge_units` != 0 it clears the bit map words that ranking units of `unit_tiles` tiles share with a neighbour or
+// with the end of the map: the selection adds to them.
 // With `const_words` != 0 it also writes the bit map and the rank table of a tensor whose tiles all have the same width
 // (what k_bitmap_const does in a launch of its own).
 __global__ __launch_bounds__(256) void k_prologue(uint8_t *__restrict__ packed, HeaderWords hdr, PadList pads,
                                                   uint32_t *__restrict__ zero_base, uint32_t zero_words,
-                                                  uint32_t const_words, uint32_t T, int all_wide,
-                                                  uint64_t *__restrict__ bitmap, uint32_t *__restrict__ ranks)
+                                                  uint32_t edge_units, uint32_t unit_tiles, uint32_t const_words,
+                                                  uint32_t T, int all_wide, uint64_t *__restrict__ bitmap,
+                                                  uint32_t *__restrict__ ranks)
 {
     const uint32_t gid = blockIdx.x * 256 + threadIdx.x;
     if (blockIdx.x == 0) {
@@ -1027,6 +1185,10 @@ __global__ __launch_bounds__(256) void k_prologue(uint8_t *__restrict__ packed, 
             if (threadIdx.x < pads.len[s]) packed[pads.begin[s] + threadIdx.x] = 0;
     }
     for (uint32_t i = gid; i < zero_words; i += gridDim.x * 256) zero_base[i] = 0u;
+    for (uint32_t i = gid; i < edge_units; i += gridDim.x * 256) {
+        const uint64_t j = (uint64_t)(i + 1) * unit_tiles;     // the first tile after unit i
+        if ((j & 63u) != 0) bitmap[j >> 6] = 0;
+    }
     for (uint32_t w = gid; w < const_words; w += gridDim.x * 256) constant_width_word(w, T, all_wide, bitmap, ranks);
 }
 

@@ -557,6 +557,35 @@ def test_ranking_units_of_every_single_launch_size(tahq, B, S, Cc, G):
     check_case(tahq, x, B, S, Cc, G, tahq.F32, 3.3, scope=1 if B * S * (Cc // G) <= 65536 else 0)
 
 
+@pytest.mark.parametrize("B,S,Cc,G,A", [
+    (2, 63, 520, 8, 0), (2, 64, 512, 8, 0), (3, 4097, 8, 8, 0),          # 4095 / 4096 / 4097 tiles: 4 or 16 per thread
+    (2, 16384, 8, 8, 0), (2, 16383, 8, 8, 0), (1, 16385, 8, 8, 0),       # 16 or 32 per thread
+    (2, 32705, 8, 8, 0), (2, 32706, 8, 8, 0), (1, 32768, 8, 8, 0),       # the single launch's last sizes
+    (2, 17, 8 * 33, 8, 24), (3, 5, 8 * 70, 8, 8 * 70), (1, 40, 8192, 8, 8192),   # expansion to quantization tiles
+    (2, 70, 8 * 1024, 8, 8 * 512), (2, 131, 8 * 1025, 8, 8 * 1025)])     # ... of more words than one workgroup takes
+def test_single_launch_selection_at_the_edges_of_its_sizes(tahq, B, S, Cc, G, A):
+    rng = np.random.default_rng(S + Cc)
+    x = rng.standard_normal((B, S, Cc)).astype(np.float32)
+    x[:, ::5, :] *= 1e-3
+    _say(f"[case] single-launch selection: {B} units of {S * (Cc // (A or G))} tiles, A={A or G}")
+    for budget in (3.02, 3.8):
+        check_case(tahq, workloads.f32_to_bf16_bits(x), B, S, Cc, G, tahq.BF16, budget, alloc_tile=A)
+
+
+@pytest.mark.parametrize("crowd", (1, 255, 256, 257, 1500))
+def test_single_launch_selection_with_a_crowded_threshold_bin(tahq, crowd):
+    # `crowd` tiles of equal entropy, in a bin of their own, hold the threshold: up to 256 are placed directly
+    rng = np.random.default_rng(crowd)
+    n, G = 2000, 16
+    x = rng.standard_normal((2, n, G)).astype(np.float32)
+    x[:, :, 0] *= 30.0                                   # the others: entropies spread out below
+    where = rng.permutation(n)[:crowd]
+    x[:, where, :] = np.sign(rng.standard_normal((2, crowd, G))).astype(np.float32)       # entropy ln G
+    for take in sorted({1, (crowd + 1) // 2, crowd}):
+        _say(f"[case] threshold bin of {crowd} equal tiles, {take} of them wide")
+        check_case(tahq, x, 2, n, G, G, tahq.F32, 3.0 + take / n)
+
+
 def test_many_ranking_units_with_few_tiles_each(tahq):
     # 300 samples of 6 tiles: units smaller than a wavefront, a batch spans many units
     rng = np.random.default_rng(5)
