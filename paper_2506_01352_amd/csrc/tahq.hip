@@ -111,7 +111,7 @@ struct LaunchEntropy {
     // hist != nullptr: also build the selection's first histogram, `bins` bins per ranking unit (units must be whole
     // batches): the keys' first radix digit if bin_scale == 0, the entropies' linear bins otherwise
     static void run(const void *d_in, float *d_H, uint32_t T, float eps_l1, float eps_log, uint32_t *hist,
-                    uint32_t bins, float bin_scale, uint64_t n_per_unit, Enqueue *qp)
+                    uint32_t bins, float bin_scale, uint64_t n_per_unit, Prologue pro, Enqueue *qp)
     {
         Enqueue &q = *qp;
         using B = Batch<G, BF16 ? 2 : 4>;
@@ -120,7 +120,7 @@ struct LaunchEntropy {
         const uint32_t res = resident_blocks(reinterpret_cast<const void *>(k_entropy<G, BF16>), B::TILES, cache);
         const uint32_t unit_batches = hist ? (uint32_t)(n_per_unit / B::TILES) : 1u;
         q(k_entropy<G, BF16>, dim3(nb < res ? nb : res), dim3(B::TILES), d_in, d_H, T,
-                           eps_l1, eps_log, hist, unit_batches, bins, bin_scale);
+                           eps_l1, eps_log, hist, unit_batches, bins, bin_scale, pro);
     }
     static bool can_fuse_histogram(uint64_t n_per_unit) { return n_per_unit % Batch<G, BF16 ? 2 : 4>::TILES == 0; }
 };
@@ -134,25 +134,26 @@ struct CanFuse {
 template <int G, bool BF16>
 struct LaunchQuantPack {
     template <int LOW>
-    static void go(const void *d_in, uint8_t *packed, Layout lay, uint32_t T, float tau, float eps_ratio, Enqueue *qp)
+    static void go(const void *d_in, uint8_t *packed, Layout lay, uint32_t T, float tau, float eps_ratio, bool ranked,
+                   bool all_wide, const Prologue &pro, Enqueue *qp)
     {
         Enqueue &q = *qp;
         using B = Batch<G, BF16 ? 2 : 4>;
         const uint32_t nb = (T + B::TILES - 1) / B::TILES;
-        q(k_quant_pack<G, BF16, LOW>, dim3(nb), dim3(B::TILES), d_in, packed, lay, T, tau,
-                           eps_ratio);
+        if (ranked) q(k_quant_pack<G, BF16, LOW, true>, dim3(nb), dim3(B::TILES), d_in, packed, lay, T, tau, eps_ratio, false, pro);
+        else q(k_quant_pack<G, BF16, LOW, false>, dim3(nb), dim3(B::TILES), d_in, packed, lay, T, tau, eps_ratio, all_wide, pro);
     }
     static void run(uint32_t low, const void *d_in, uint8_t *packed, Layout lay, uint32_t T, float tau, float eps_ratio,
-                    Enqueue *qp)
+                    bool ranked, bool all_wide, Prologue pro, Enqueue *qp)
     {
         switch (low) {
-        case 1: go<1>(d_in, packed, lay, T, tau, eps_ratio, qp); break;
-        case 2: go<2>(d_in, packed, lay, T, tau, eps_ratio, qp); break;
-        case 3: go<3>(d_in, packed, lay, T, tau, eps_ratio, qp); break;
-        case 4: go<4>(d_in, packed, lay, T, tau, eps_ratio, qp); break;
-        case 5: go<5>(d_in, packed, lay, T, tau, eps_ratio, qp); break;
-        case 6: go<6>(d_in, packed, lay, T, tau, eps_ratio, qp); break;
-        default: go<7>(d_in, packed, lay, T, tau, eps_ratio, qp); break;
+        case 1: go<1>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
+        case 2: go<2>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
+        case 3: go<3>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
+        case 4: go<4>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
+        case 5: go<5>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
+        case 6: go<6>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
+        default: go<7>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
         }
     }
 };
@@ -187,7 +188,7 @@ struct LaunchAllocEntropy {
     // Entropies of allocation tiles of m > 1 quantization tiles: one pass if a workgroup's batch holds whole
     // allocation tiles, otherwise two streaming passes over the tensor.
     static void run(const void *d_in, float *d_H, float *part, float *inv_norm, uint32_t T, uint32_t m, float eps_l1,
-                    float eps_log, Enqueue *qp)
+                    float eps_log, Prologue pro, Enqueue *qp)
     {
         Enqueue &q = *qp;
         using B = Batch<G, BF16 ? 2 : 4>;
@@ -195,15 +196,15 @@ struct LaunchAllocEntropy {
         const uint32_t n_alloc = T / m;
         if (B::TILES % m == 0) {
             q(k_alloc_entropy<G, BF16>, dim3(nb), dim3(B::TILES), d_in, d_H, T, m, eps_l1,
-                               eps_log);
+                               eps_log, pro);
             return;
         }
         q(k_tile_partial<G, BF16, false>, dim3(nb), dim3(B::TILES), d_in,
-                           (const float *)nullptr, part, T, m, eps_log);
+                           (const float *)nullptr, part, T, m, eps_log, pro);
         q(k_alloc_reduce<false>, dim3(blocks_for(n_alloc)), dim3(256), (const float *)part, (const float *)nullptr,
                            inv_norm, n_alloc, m, eps_l1);
         q(k_tile_partial<G, BF16, true>, dim3(nb), dim3(B::TILES), d_in,
-                           (const float *)inv_norm, part, T, m, eps_log);
+                           (const float *)inv_norm, part, T, m, eps_log, Prologue{});
         q(k_alloc_reduce<true>, dim3(blocks_for(n_alloc)), dim3(256), (const float *)part, (const float *)inv_norm,
                            d_H, n_alloc, m, eps_l1);
     }
@@ -212,10 +213,10 @@ struct LaunchAllocEntropy {
 // Entropy of every quantization tile; with `hist`, also the selection's first histogram (the caller has checked
 // that the ranking units are whole batches).
 void launch_entropy(const Shape &s, const tahq_config *cfg, const void *d_in, float *d_H, uint32_t *hist, uint32_t bins,
-                    float bin_scale, Enqueue *qp)
+                    float bin_scale, const Prologue &pro, Enqueue *qp)
 {
     dispatch<LaunchEntropy>(s.G, s.dtype == TAHQ_BF16, d_in, d_H, (uint32_t)s.T, cfg->eps_l1, cfg->eps_log, hist, bins,
-                            bin_scale, s.n, qp);
+                            bin_scale, s.n, pro, qp);
 }
 
 template <uint32_t PLACES, uint32_t BINS, int SHIFT>
@@ -333,7 +334,7 @@ tahq_status tahq_tile_entropy(const tahq_config *cfg, const void *d_in, float *d
     if (!d_in || !d_entropy) return TAHQ_ERR_NULL;
     if (misaligned(d_in) || misaligned(d_entropy)) return TAHQ_ERR_MISALIGNED;
     Enqueue q{(hipStream_t)stream};
-    launch_entropy(s, cfg, d_in, d_entropy, nullptr, 0u, 0.0f, &q);
+    launch_entropy(s, cfg, d_in, d_entropy, nullptr, 0u, 0.0f, Prologue{}, &q);
     return q.result();
 }
 
@@ -347,7 +348,7 @@ tahq_status tahq_alloc_tile_entropy(const tahq_config *cfg, const void *d_in, fl
     if (misaligned(d_in) || misaligned(d_entropy)) return TAHQ_ERR_MISALIGNED;
     Enqueue q{(hipStream_t)stream};
     if (s.m == 1) {
-        launch_entropy(s, cfg, d_in, d_entropy, nullptr, 0u, 0.0f, &q);
+        launch_entropy(s, cfg, d_in, d_entropy, nullptr, 0u, 0.0f, Prologue{}, &q);
     } else {
         if (!d_workspace) return TAHQ_ERR_NULL;
         Workspace ws;
@@ -358,7 +359,7 @@ tahq_status tahq_alloc_tile_entropy(const tahq_config *cfg, const void *d_in, fl
         dispatch<LaunchAllocEntropy>(s.G, s.dtype == TAHQ_BF16, d_in, d_entropy,
                                      reinterpret_cast<float *>(wsb + ws.part),
                                      reinterpret_cast<float *>(wsb + ws.inv_norm), (uint32_t)s.T, s.m, cfg->eps_l1,
-                                     cfg->eps_log, &q);
+                                     cfg->eps_log, Prologue{}, &q);
     }
     return q.result();
 }
@@ -395,39 +396,42 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
     // the selection kernels of large ranking units put the unit into the grid's second dimension
     if (select && !small_units && s.U > 65535u) return TAHQ_ERR_UNSUPPORTED;
 
-    // header, section padding, selection scratch
-    HeaderWords hdr;
-    memset(&hdr, 0, sizeof hdr);
-    hdr.w[0] = 0x51484154u;   // "TAHQ"
-    hdr.w[1] = 1;
-    hdr.w[2] = s.dtype; hdr.w[3] = s.B; hdr.w[4] = s.S; hdr.w[5] = s.C; hdr.w[6] = s.G; hdr.w[7] = s.scope;
-    hdr.w[8] = (uint32_t)s.kA;
-    hdr.w[14] = s.A;
-    hdr.w[15] = s.low;
-    memcpy(&hdr.w[9], &cfg->budget_bits, 4);
-    memcpy(&hdr.w[10], &cfg->tau, 4);
-    memcpy(&hdr.w[11], &cfg->eps_l1, 4);
-    memcpy(&hdr.w[12], &cfg->eps_log, 4);
-    memcpy(&hdr.w[13], &cfg->eps_ratio, 4);
-    PadList pads;
+    // header and section padding
+    Prologue pro;
+    memset(&pro, 0, sizeof pro);
+    uint32_t *hdr = pro.hdr.w;
+    hdr[0] = 0x51484154u;   // "TAHQ"
+    hdr[1] = 1;
+    hdr[2] = s.dtype; hdr[3] = s.B; hdr[4] = s.S; hdr[5] = s.C; hdr[6] = s.G; hdr[7] = s.scope;
+    hdr[8] = (uint32_t)s.kA;
+    hdr[14] = s.A;
+    hdr[15] = s.low;
+    memcpy(&hdr[9], &cfg->budget_bits, 4);
+    memcpy(&hdr[10], &cfg->tau, 4);
+    memcpy(&hdr[11], &cfg->eps_l1, 4);
+    memcpy(&hdr[12], &cfg->eps_log, 4);
+    memcpy(&hdr[13], &cfg->eps_ratio, 4);
     const uint64_t words64 = (s.T + 63) / 64;
     const uint64_t sec_begin[5] = {lay.bitmap + words64 * 8, lay.ranks + words64 * 4, lay.pivot + s.T,
                                    lay.scale + 2 * s.T, lay.zero + 2 * s.T};
     const uint64_t sec_end[5] = {lay.ranks, lay.pivot, lay.scale, lay.zero, lay.payload};
-    for (int i = 0; i < 5; ++i) { pads.begin[i] = sec_begin[i]; pads.len[i] = (uint32_t)(sec_end[i] - sec_begin[i]); }
+    for (int i = 0; i < 5; ++i) { pro.pads.begin[i] = sec_begin[i]; pro.pads.len[i] = (uint32_t)(sec_end[i] - sec_begin[i]); }
+    pro.bitmap = bitmap;
+    pro.unit_tiles = (uint32_t)s.n;
+    // The prologue is part of the call's first kernel: of the quantizer where there is nothing to rank, of the entropies where the
+    // selection has no scratch to clear.  Where it has, that must have happened before the entropies are counted.
     const bool histograms = select && !small_units;
-    const uint32_t zero_words = histograms ? (uint32_t)(ws.zero_bytes / 4) : 0u;
-    // a tensor whose tiles all have the same width needs no selection: its bit map and rank table are constants, which
-    // the prologue writes as well when the caller asks for both phases at once
-    const bool const_in_prologue = !select && (phases & TAHQ_PHASE_PROLOGUE) && (phases & TAHQ_PHASE_SELECT);
-    if (phases & TAHQ_PHASE_PROLOGUE) {
-        const uint32_t const_words = const_in_prologue ? (uint32_t)words64 : 0u;
-        const uint32_t edge_units = small_units && s.n % 64 != 0 ? s.U : 0u;
-        const uint64_t items = const_words > edge_units ? const_words : edge_units;
-        const uint32_t blocks = histograms ? 32u : blocks_for(items < 1 ? 1 : (items > 65536 ? 65536 : items));
-        q(k_prologue, dim3(blocks), dim3(256), packed, hdr, pads, reinterpret_cast<uint32_t *>(wsb + ws.hist0), zero_words,
-          edge_units, (uint32_t)s.n, const_words, (uint32_t)s.T, s.kA == s.nA ? 1 : 0, bitmap, ranks);
+    const bool all_in_quant = !select && (phases & (uint32_t)TAHQ_PHASE_QUANT) && (phases & (uint32_t)TAHQ_PHASE_PROLOGUE) &&
+                              (phases & (uint32_t)TAHQ_PHASE_SELECT);
+    const bool with_entropy = select && !histograms && (phases & (uint32_t)TAHQ_PHASE_PROLOGUE) && (phases & (uint32_t)TAHQ_PHASE_ENTROPY);
+    if (phases & TAHQ_PHASE_PROLOGUE) pro.packed = packed;
+    if ((phases & TAHQ_PHASE_PROLOGUE) && !all_in_quant && !with_entropy) {
+        q(k_prologue, dim3(histograms ? 32u : 1u), dim3(256), pro, reinterpret_cast<uint32_t *>(wsb + ws.hist0),
+          histograms ? (uint32_t)(ws.zero_bytes / 4) : 0u);
+        pro.packed = nullptr;
     }
+    // words of the bit map that units share are cleared with the entropies, for the selection that follows them
+    if (small_units && s.n % 64 != 0) pro.edge_units = s.U;
 
     if (select) {
         float *H = reinterpret_cast<float *>(wsb + ws.keys);
@@ -451,11 +455,11 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
             if (wide)
                 dispatch<LaunchAllocEntropy>(s.G, s.dtype == TAHQ_BF16, d_in, H, reinterpret_cast<float *>(wsb + ws.part),
                                              reinterpret_cast<float *>(wsb + ws.inv_norm), (uint32_t)s.T, s.m,
-                                             cfg->eps_l1, cfg->eps_log, &q);
+                                             cfg->eps_l1, cfg->eps_log, pro, &q);
             else if (fused_select)
-                launch_entropy(s, cfg, d_in, H, lin_hist, kLinBins, bin_scale, &q);
+                launch_entropy(s, cfg, d_in, H, lin_hist, kLinBins, bin_scale, pro, &q);
             else
-                launch_entropy(s, cfg, d_in, H, fused ? hist0 : (uint32_t *)nullptr, kDigit0Bins, 0.0f, &q);
+                launch_entropy(s, cfg, d_in, H, fused ? hist0 : (uint32_t *)nullptr, kDigit0Bins, 0.0f, pro, &q);
         }
         if ((phases & TAHQ_PHASE_SELECT) && fused_select) {
             const dim3 grid((uint32_t)((s.n + kFusedKeysPerBlock - 1) / kFusedKeysPerBlock), s.U);
@@ -502,14 +506,14 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
                 q(k_bitmap_pack, dim3(blocks_for(words64 * 64)), dim3(256),
                                    (const uint8_t *)sel, (uint32_t)s.T, bitmap);
         }
-    } else if ((phases & TAHQ_PHASE_SELECT) && !const_in_prologue) {
+    } else if ((phases & TAHQ_PHASE_SELECT) && !all_in_quant) {
         q(k_bitmap_const, dim3(blocks_for(words64)), dim3(256), (uint32_t)s.T,
                            s.kA == s.nA ? 1 : 0, bitmap, ranks);
     }
 
     if (phases & TAHQ_PHASE_QUANT) {
         dispatch<LaunchQuantPack>(s.G, s.dtype == TAHQ_BF16, s.low, d_in, packed, lay, (uint32_t)s.T, cfg->tau,
-                                  cfg->eps_ratio, &q);
+                                  cfg->eps_ratio, !all_in_quant, s.kA == s.nA, pro, &q);
     }
     return q.result();
 }

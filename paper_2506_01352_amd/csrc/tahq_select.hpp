@@ -1144,19 +1144,6 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
     }
 }
 
-// A budget of exactly `lo` or `lo + 1` bits: every tile has the same width.  Bit map word and rank-table entry `w`.
-__device__ __forceinline__ void constant_width_word(uint64_t w, uint32_t T, int all_wide, uint64_t *__restrict__ bitmap,
-                                                    uint32_t *__restrict__ ranks)
-{
-    uint64_t bits = 0;
-    if (all_wide) {
-        const uint64_t left = (uint64_t)T - w * 64;
-        bits = left >= 64 ? ~0ull : ((1ull << left) - 1ull);
-    }
-    bitmap[w] = bits;
-    ranks[w] = all_wide ? (uint32_t)(w * 64) : 0u;
-}
-
 __global__ __launch_bounds__(256) void k_bitmap_const(uint32_t T, int all_wide, uint64_t *__restrict__ bitmap,
                                                       uint32_t *__restrict__ ranks)
 {
@@ -1164,32 +1151,12 @@ __global__ __launch_bounds__(256) void k_bitmap_const(uint32_t T, int all_wide, 
     if (w < ((uint64_t)T + 63) / 64) constant_width_word(w, T, all_wide, bitmap, ranks);
 }
 
-// Header, zeroed section padding, zeroed histograms.
-struct HeaderWords { uint32_t w[16]; };
-struct PadList { uint64_t begin[5]; uint32_t len[5]; };
-
-// With `edge_units` != 0 it clears the bit map words that ranking units of `unit_tiles` tiles share with a neighbour or
-// with the end of the map: the selection adds to them.
-// With `const_words` != 0 it also writes the bit map and the rank table of a tensor whose tiles all have the same width
-// (what k_bitmap_const does in a launch of its own).
-__global__ __launch_bounds__(256) void k_prologue(uint8_t *__restrict__ packed, HeaderWords hdr, PadList pads,
-                                                  uint32_t *__restrict__ zero_base, uint32_t zero_words,
-                                                  uint32_t edge_units, uint32_t unit_tiles, uint32_t const_words,
-                                                  uint32_t T, int all_wide, uint64_t *__restrict__ bitmap,
-                                                  uint32_t *__restrict__ ranks)
+// The prologue in a launch of its own, with the scratch of the large units' selections cleared.
+__global__ __launch_bounds__(256) void k_prologue(Prologue pro, uint32_t *__restrict__ zero_base, uint32_t zero_words)
 {
     const uint32_t gid = blockIdx.x * 256 + threadIdx.x;
-    if (blockIdx.x == 0) {
-        if (threadIdx.x < 16) reinterpret_cast<uint32_t *>(packed)[threadIdx.x] = hdr.w[threadIdx.x];
-        for (int s = 0; s < 5; ++s)
-            if (threadIdx.x < pads.len[s]) packed[pads.begin[s] + threadIdx.x] = 0;
-    }
+    write_prologue(pro, gid, gridDim.x * 256);
     for (uint32_t i = gid; i < zero_words; i += gridDim.x * 256) zero_base[i] = 0u;
-    for (uint32_t i = gid; i < edge_units; i += gridDim.x * 256) {
-        const uint64_t j = (uint64_t)(i + 1) * unit_tiles;     // the first tile after unit i
-        if ((j & 63u) != 0) bitmap[j >> 6] = 0;
-    }
-    for (uint32_t w = gid; w < const_words; w += gridDim.x * 256) constant_width_word(w, T, all_wide, bitmap, ranks);
 }
 
 }  // namespace tahq

@@ -140,6 +140,52 @@ __device__ __forceinline__ void butterfly(float *x)
     }
 }
 
+// ------------------------------------------------------------- prologue
+
+// What a stream holds besides the kernels' results: header and zeroed section padding.  And the bit map words that ranking
+// units share with a neighbour or with the end of the map, cleared because the selection adds to them.
+struct HeaderWords { uint32_t w[16]; };
+struct PadList { uint64_t begin[5]; uint32_t len[5]; };
+struct Prologue {
+    uint8_t *packed;                             // header and padding go here; null: none of them
+    uint64_t *bitmap;
+    uint32_t edge_units, unit_tiles;             // edge_units != 0: clear the shared words of that many units
+    HeaderWords hdr;
+    PadList pads;
+};
+
+// Thread `gid` of `threads` (at least 64).  The small launches of a call cost more than what they do, so the prologue rides
+// along with the call's first kernel: in front of the entropies (encode of 1024 x 1600 channels: 18.8 -> 17.5 us), or of the
+// quantizer where all tiles have one width (fp32 [1,128,512], encode and decode: 19.7 -> 16.8).
+__device__ __forceinline__ void write_prologue(const Prologue &p, uint32_t gid, uint32_t threads)
+{
+    if (p.packed != nullptr && gid < 64) {
+        if (gid < 16) reinterpret_cast<uint32_t *>(p.packed)[gid] = p.hdr.w[gid];
+#pragma unroll
+        for (int s = 0; s < 5; ++s)
+            if (gid < p.pads.len[s]) p.packed[p.pads.begin[s] + gid] = 0;            // paddings are shorter than 64 bytes
+    }
+    for (uint32_t i = gid; i < p.edge_units; i += threads) {
+        const uint64_t j = (uint64_t)(i + 1) * p.unit_tiles;   // the first tile after unit i
+        if ((j & 63u) != 0) p.bitmap[j >> 6] = 0;
+    }
+}
+
+// A budget of exactly `lo` or `lo + 1` bits: every tile has the same width.  Bit map word `w`.
+__device__ __forceinline__ uint64_t constant_word(uint64_t w, uint32_t T, bool all_wide)
+{
+    const uint64_t left = (uint64_t)T - w * 64;
+    return !all_wide ? 0ull : left >= 64 ? ~0ull : ((1ull << left) - 1ull);
+}
+
+// ... and its rank-table entry, both written.
+__device__ __forceinline__ void constant_width_word(uint64_t w, uint32_t T, int all_wide, uint64_t *__restrict__ bitmap,
+                                                    uint32_t *__restrict__ ranks)
+{
+    bitmap[w] = constant_word(w, T, all_wide != 0);
+    ranks[w] = all_wide ? (uint32_t)(w * 64) : 0u;
+}
+
 // -------------------------------------------------------------- K0: entropy
 
 // Eq. 1-2 for my tile, read from its LDS row.
@@ -173,8 +219,9 @@ static_assert((1u << kDigit0Bits) == kDigit0Bins, "digit 0 width");
 template <int G, bool BF16>
 __global__ __launch_bounds__((Batch<G, BF16 ? 2 : 4>::TILES))
 void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, float eps_l1, float eps_log,
-               uint32_t *__restrict__ hist0, uint32_t unit_batches, uint32_t hist_stride, float bin_scale)
+               uint32_t *__restrict__ hist0, uint32_t unit_batches, uint32_t hist_stride, float bin_scale, Prologue pro)
 {
+    write_prologue(pro, blockIdx.x * Batch<G, BF16 ? 2 : 4>::TILES + threadIdx.x, gridDim.x * Batch<G, BF16 ? 2 : 4>::TILES);
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<G, ES>;
     __shared__ __attribute__((aligned(16))) uint8_t lds[B::LDS_BYTES];
@@ -252,8 +299,9 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, f
 template <int G, bool BF16, bool WEIGHTED>
 __global__ __launch_bounds__((Batch<G, BF16 ? 2 : 4>::TILES))
 void k_tile_partial(const void *__restrict__ in, const float *__restrict__ inv_norm, float *__restrict__ part,
-                    uint32_t T, uint32_t m, float eps_log)
+                    uint32_t T, uint32_t m, float eps_log, Prologue pro)
 {
+    write_prologue(pro, blockIdx.x * Batch<G, BF16 ? 2 : 4>::TILES + threadIdx.x, gridDim.x * Batch<G, BF16 ? 2 : 4>::TILES);
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<G, ES>;
     __shared__ __attribute__((aligned(16))) uint8_t lds[B::LDS_BYTES];
@@ -290,8 +338,9 @@ void k_tile_partial(const void *__restrict__ in, const float *__restrict__ inv_n
 template <int G, bool BF16>
 __global__ __launch_bounds__((Batch<G, BF16 ? 2 : 4>::TILES), (G * (BF16 ? 2 : 4) <= 128 ? 4 : 1))
 void k_alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, uint32_t m, float eps_l1,
-                     float eps_log)
+                     float eps_log, Prologue pro)
 {
+    write_prologue(pro, blockIdx.x * Batch<G, BF16 ? 2 : 4>::TILES + threadIdx.x, gridDim.x * Batch<G, BF16 ? 2 : 4>::TILES);
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<G, ES>;
     __shared__ __attribute__((aligned(16))) uint8_t lds[B::LDS_BYTES];
@@ -437,15 +486,12 @@ struct BatchMeta {
     uint32_t rank0;
 };
 
-// `lane_zero` is a per-lane zero the compiler cannot see through: it turns these uniform loads into
-// vector loads, which are counted in order with the other global loads (scalar loads are not, and a
-// wait for LDS data would also wait for them).
 template <int TILES>
 __device__ __forceinline__ void load_meta(const uint8_t *__restrict__ packed, const Layout &lay, uint64_t j0, uint32_t T,
-                                          uint32_t lane_zero, BatchMeta<TILES> &m)
+                                          BatchMeta<TILES> &m)
 {
-    const uint64_t *bitmap = reinterpret_cast<const uint64_t *>(packed + lay.bitmap) + lane_zero;
-    const uint32_t *ranks = reinterpret_cast<const uint32_t *>(packed + lay.ranks) + lane_zero;
+    const uint64_t *bitmap = reinterpret_cast<const uint64_t *>(packed + lay.bitmap);
+    const uint32_t *ranks = reinterpret_cast<const uint32_t *>(packed + lay.ranks);
     const uint64_t last_word = ((uint64_t)T - 1) >> 6;
 #pragma unroll
     for (int w = 0; w < BatchMeta<TILES>::WORDS; ++w) {
@@ -716,10 +762,10 @@ struct QuantPackOccupancy { static constexpr int WAVES_PER_SIMD = (G * ESIZE <= 
 // paths rarely both run.  The payload buffer reuses the rows' LDS once every lane holds its tile in
 // registers, which keeps the workgroup small enough for four to share a compute unit: this kernel
 // lives on the loads of its neighbours being in flight while it computes.
-template <int G, bool BF16, int LOW, bool FULL>
+template <int G, bool BF16, int LOW, bool RANKED, bool FULL>
 __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, uint8_t *__restrict__ packed, const Layout &lay,
                                                  uint32_t T, float tau, float eps_ratio, uint32_t batch, uint32_t nvalid,
-                                                 uint8_t *lds, uint32_t *info, uint16_t *order, uint32_t *class_count)
+                                                 bool all_wide, uint8_t *lds, uint32_t *info, uint16_t *order, uint32_t *class_count)
 {
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<G, ES>;
@@ -738,7 +784,18 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
     uint4 v[B::CHUNKS];
     load_batch<G, ES, FULL, true>(in, j0, nvalid, v, tid);           // second and last read of the tensor
     BatchMeta<B::TILES> meta;
-    load_meta<B::TILES>(packed, lay, j0, T, 0u, meta);
+    if constexpr (RANKED) {
+        load_meta<B::TILES>(packed, lay, j0, T, meta);
+    } else {
+        // one width for all tiles: the batch's bit map words and rank-table entries are constants, and written here
+        const uint64_t w0 = j0 >> 6, words = ((uint64_t)T + 63) >> 6;
+#pragma unroll
+        for (int w = 0; w < BatchMeta<B::TILES>::WORDS; ++w) meta.word[w] = w0 + w < words ? constant_word(w0 + w, T, all_wide) : 0ull;
+        meta.rank0 = all_wide ? (uint32_t)j0 : 0u;
+        if (tid < BatchMeta<B::TILES>::WORDS && w0 + tid < words)
+            constant_width_word(w0 + tid, T, all_wide, reinterpret_cast<uint64_t *>(packed + lay.bitmap),
+                                reinterpret_cast<uint32_t *>(packed + lay.ranks));
+    }
     store_batch<G, ES, FULL>(v, nvalid, lds, tid);
     uint32_t b, rel, total4;
     tile_pos<B::TILES, LOW>(meta, tid, &b, &rel, &total4);
@@ -788,10 +845,13 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
     }
 }
 
-template <int G, bool BF16, int LOW>
+// RANKED: the widths are in the stream's bit map.  Otherwise all tiles have one, and the kernel is the call's only one and
+// writes bit map, rank table and prologue as well.  (A variant of its own: the same as a run-time choice delayed the loads of
+// the ranked case, 126 -> 136 us on bf16 [8,4096,8192].)
+template <int G, bool BF16, int LOW, bool RANKED>
 __global__ __launch_bounds__((Batch<G, BF16 ? 2 : 4>::TILES), (QuantPackOccupancy<G, BF16 ? 2 : 4>::WAVES_PER_SIMD))
 void k_quant_pack(const void *__restrict__ in, uint8_t *__restrict__ packed, Layout lay, uint32_t T, float tau,
-                  float eps_ratio)
+                  float eps_ratio, bool all_wide, Prologue pro)
 {
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<G, ES>;
@@ -800,13 +860,14 @@ void k_quant_pack(const void *__restrict__ in, uint8_t *__restrict__ packed, Lay
     __shared__ uint32_t info[B::TILES];          // per tile: pivot byte | (b == WIDE) << 8 | rel << 9
     __shared__ uint16_t order[B::TILES];         // tiles in class order
     __shared__ uint32_t class_count[4 * WAVES];  // tiles per class and wavefront, class-major
+    if constexpr (!RANKED) write_prologue(pro, blockIdx.x * B::TILES + threadIdx.x, gridDim.x * B::TILES);
     const uint32_t nfull = T / B::TILES;        // a workgroup per batch; the last one may be ragged
     if (blockIdx.x < nfull)
-        quant_pack_batch<G, BF16, LOW, true>(in, packed, lay, T, tau, eps_ratio, blockIdx.x, B::TILES, lds, info, order,
-                                             class_count);
+        quant_pack_batch<G, BF16, LOW, RANKED, true>(in, packed, lay, T, tau, eps_ratio, blockIdx.x, B::TILES, all_wide, lds, info,
+                                             order, class_count);
     else
-        quant_pack_batch<G, BF16, LOW, false>(in, packed, lay, T, tau, eps_ratio, nfull, T % B::TILES, lds, info, order,
-                                              class_count);
+        quant_pack_batch<G, BF16, LOW, RANKED, false>(in, packed, lay, T, tau, eps_ratio, nfull, T % B::TILES, all_wide, lds, info,
+                                              order, class_count);
 }
 
 // ------------------------------------------------------------- K4: decode
