@@ -108,8 +108,7 @@ inline uint32_t resident_blocks(const void *kernel, int threads, ResidentCache &
 
 template <int G, bool BF16>
 struct LaunchEntropy {
-    // hist != nullptr: also build the selection's first histogram, `bins` bins per ranking unit (units must be whole
-    // batches): the keys' first radix digit if bin_scale == 0, the entropies' linear bins otherwise
+    // hist != nullptr: also build the selection's first histogram, `bins` bins per ranking unit (of at least one batch): the keys' first radix digit if bin_scale == 0, the entropies' linear bins otherwise
     static void run(const void *d_in, float *d_H, uint32_t T, float eps_l1, float eps_log, uint32_t *hist,
                     uint32_t bins, float bin_scale, uint64_t n_per_unit, Prologue pro, Enqueue *qp)
     {
@@ -118,9 +117,8 @@ struct LaunchEntropy {
         const uint32_t nb = (T + B::TILES - 1) / B::TILES;
         static ResidentCache cache;
         const uint32_t res = resident_blocks(reinterpret_cast<const void *>(k_entropy<G, BF16>), B::TILES, cache);
-        const uint32_t unit_batches = hist ? (uint32_t)(n_per_unit / B::TILES) : 1u;
         q(k_entropy<G, BF16>, dim3(nb < res ? nb : res), dim3(B::TILES), d_in, d_H, T,
-                           eps_l1, eps_log, hist, unit_batches, bins, bin_scale, pro);
+                           eps_l1, eps_log, hist, (uint32_t)n_per_unit, bins, bin_scale, pro);
     }
     static bool can_fuse_histogram(uint64_t n_per_unit) { return n_per_unit % Batch<G, BF16 ? 2 : 4>::TILES == 0; }
 };
@@ -431,7 +429,7 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
         pro.packed = nullptr;
     }
     // words of the bit map that units share are cleared with the entropies, for the selection that follows them
-    if (small_units && s.n % 64 != 0) pro.edge_units = s.U;
+    if (select && !multi_launch && (small_units || !wide) && s.n % 64 != 0) pro.edge_units = s.U;
 
     if (select) {
         float *H = reinterpret_cast<float *>(wsb + ws.keys);
@@ -441,13 +439,12 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
         uint32_t *state = reinterpret_cast<uint32_t *>(wsb + ws.state);
         uint32_t *seg = reinterpret_cast<uint32_t *>(wsb + ws.seg);
         uint8_t *sel = wsb + ws.sel;
-        // the entropy kernel builds the selection's first histogram itself when units are whole batches
-        bool whole_batches = false;
-        if (!wide && !small_units) dispatch<CanFuse>(s.G, s.dtype == TAHQ_BF16, s.n, &whole_batches);
-        // Large units that start on 64-tile boundaries are ranked in one launch from a histogram of linear bins;
-        // everything else (and every unit when the caller forces it) by the multi-launch radix select.
-        const bool fused_select = whole_batches && !multi_launch && s.n % 64 == 0;
-        const bool fused = whole_batches && !fused_select;       // first radix digit folded into the entropy kernel
+        // Large units are ranked in two launches from a histogram of linear bins that the entropy kernel builds; allocation
+        // tiles, and every unit when the caller forces it, by the multi-launch radix select, whose first digit the entropy
+        // kernel counts where units are whole batches.
+        const bool fused_select = !wide && !small_units && !multi_launch;
+        bool fused = false;
+        if (!wide && multi_launch) dispatch<CanFuse>(s.G, s.dtype == TAHQ_BF16, s.n, &fused);
         uint32_t *lin_hist = reinterpret_cast<uint32_t *>(wsb + ws.lin_hist);
         // bins of width ln(A) / kLinBins: the entropy of A channels lies in [0, ln A]
         const float bin_scale = (float)((double)kLinBins / __builtin_log((double)s.A));
@@ -462,10 +459,10 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
                 launch_entropy(s, cfg, d_in, H, fused ? hist0 : (uint32_t *)nullptr, kDigit0Bins, 0.0f, pro, &q);
         }
         if ((phases & TAHQ_PHASE_SELECT) && fused_select) {
-            const dim3 grid((uint32_t)((s.n + kFusedKeysPerBlock - 1) / kFusedKeysPerBlock), s.U);
+            const dim3 grid((uint32_t)((places + kFusedKeysPerBlock - 1) / kFusedKeysPerBlock), s.U);
             uint32_t *fused_state = reinterpret_cast<uint32_t *>(wsb + ws.fused);
             uint2 *cand = reinterpret_cast<uint2 *>(wsb + ws.cand);
-            uint32_t *block_above = reinterpret_cast<uint32_t *>(wsb + ws.block_above);
+            uint32_t *block_above = seg;             // fewer entries than the segments it was made for
             q(k_select_classify, grid, dim3(kFusedThreads), (const float *)H, (uint32_t)s.n,
                                (uint32_t)s.k, bin_scale, (const uint32_t *)lin_hist, fused_state, cand, block_above,
                                bitmap);

@@ -47,8 +47,8 @@ struct Workspace {
     uint64_t partial;    // uint32[U][2][hb][kHistBins]: per-workgroup histograms of digits 1, 2
     uint64_t keys;       // float[T] entropies
     uint64_t cand;       // uint2[U][kCandCap]: (key, tile) of the tiles in the threshold bin
-    uint64_t block_above; // uint32[U][ceil(n / 16384)]: tiles above the threshold bin, per block of 16384 tiles
-    uint64_t seg;        // uint32[U][nseg][2]: keys equal to / above the threshold, per segment
+    uint64_t seg;        // uint32[U][nseg][2]: keys equal to / above the threshold, per segment; the two-launch
+                         // selection: tiles above the threshold bin, per block of 16384 places
     uint64_t sel;        // uint8[T] (only when n % 64 != 0, or A > G)
     uint64_t part;       // float[T]: per-quantization-tile partial sums            (only when A > G)
     uint64_t inv_norm;   // float[T/m]: 1 / (L1 norm + eps) of every allocation tile (only when A > G)
@@ -123,7 +123,6 @@ void make_workspace(const Shape &s, Workspace *w)
     off = pad256(off);
     w->partial = off; off = pad256(off + (uint64_t)s.U * 2 * w->hb * kHistBins * 4);
     w->cand = off;  off = pad256(off + (uint64_t)s.U * kCandCap * 8);
-    w->block_above = off; off = pad256(off + (uint64_t)s.U * ((s.nA + 16383) / 16384) * 4);
     w->keys = off;  off = pad256(off + s.T * 4);
     w->seg = off;   off = pad256(off + (uint64_t)s.U * w->nseg * 8);
     w->sel = off;   off = pad256(off + s.T);

@@ -5,10 +5,10 @@
 //
 //   * ranking units of at most 32768 tiles: k_select_small, one workgroup per unit in one launch (entropies in
 //     registers, one histogram in LDS, the threshold's bin ranked directly), because at that size several launches cost more than the work;
-//   * larger units that start on 64-tile boundaries and are whole batches of the entropy kernel: that kernel also
-//     counts the entropies over 2048 linear bins per unit; k_select_classify settles every tile outside the bin that
-//     holds K* and lists the tiles inside it, k_select_resolve ranks that list (further down in this file);
-//   * everything else, and every unit when the caller forces it: three histogram passes (10 + 11 + 11 bits, from the
+//   * larger units: the entropy kernel also counts the entropies over 2048 linear bins per unit; k_select_classify
+//     settles every tile outside the bin that holds K* and lists the tiles inside it, k_select_resolve ranks that list
+//     (further down in this file);
+//   * larger units of allocation tiles (A > G), and every unit when the caller forces it: three histogram passes (10 + 11 + 11 bits, from the
 //     top; the first one folded into the entropy kernel where units are whole batches) find K* and `take`; then, per
 //     segment of tiles, counts of keys == K* and > K*, whose prefix sums give every tile its place among the equal keys
 //     (index order) and every 64-tile group its rank-table entry: k_radix_pass x 2, k_seg_count, k_assign.
@@ -44,6 +44,46 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
     v += dpp_or_zero<0x142, 0xA>(v);     // row_bcast:15 into rows 1 and 3
     v += dpp_or_zero<0x143, 0xC>(v);     // row_bcast:31 into rows 2 and 3
     return v;
+}
+
+// The 16 wavefronts' entries of `totals` that come before mine, added up.
+__device__ __forceinline__ uint32_t sum_of_waves_before(const uint32_t *totals, uint32_t wave, int lane)
+{
+    const uint32_t own = totals[lane & 15];
+    uint32_t v = own;
+    v += dpp_or_zero<0x111, 0xF>(v);             // a scan over each row of 16 lanes
+    v += dpp_or_zero<0x112, 0xF>(v);
+    v += dpp_or_zero<0x114, 0xF>(v);
+    v += dpp_or_zero<0x118, 0xF>(v);
+    return (uint32_t)__builtin_amdgcn_readlane((int)(v - own), (int)wave);
+}
+
+// Which of BINS bins holds the `want`-th largest value (bins counted from the top) and how many values are wanted inside it, found
+// by the whole workgroup of 1024 threads: BINS / 1024 bins per thread and a scan.  chosen[0..1] is written before the last of
+// its two barriers; `totals`: 16 words of LDS.  (One wavefront with a sixteenth of the bins per lane, its loads as far apart,
+// took 1.5 us longer.)
+template <int BINS>
+__device__ __forceinline__ void block_pick_bin(const uint32_t *hist, uint32_t want, uint32_t *totals, uint32_t *chosen)
+{
+    constexpr int PER = BINS / 1024;
+    static_assert(PER == 1 || PER == 2, "one load per thread");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    uint32_t hi = 0, lo = 0;                     // my bins: top and, if there are two, the one below it
+    if constexpr (PER == 2) {
+        const uint2 q = reinterpret_cast<const uint2 *>(hist)[BINS / 2 - 1 - tid];
+        lo = q.x; hi = q.y;
+    } else {
+        hi = hist[BINS - 1 - tid];
+    }
+    const uint32_t incl = wave_incl_scan(hi + lo);
+    if (lane == 63) totals[wave] = incl;
+    __syncthreads();
+    const uint32_t above = sum_of_waves_before(totals, wave, lane) + incl - (hi + lo);
+    const uint32_t top = (uint32_t)(BINS - 1 - PER * tid);
+    if (above < want && want <= above + hi) { chosen[0] = top; chosen[1] = want - above; }
+    else if (PER == 2 && above + hi < want && want <= above + hi + lo) { chosen[0] = top - 1; chosen[1] = want - above - hi; }
+    __syncthreads();
 }
 
 // selection state of one ranking unit (uint32[8] in the workspace)
@@ -532,18 +572,6 @@ constexpr uint32_t kSmallUnitMaxKeys = TAHQ_SMALL_UNIT_MAX;
 constexpr uint32_t kSmallListCap = 256;          // tiles of the threshold bin that are placed directly
 constexpr uint32_t kExpandWords = 2048;          // bit map words a workgroup expands when A > G
 
-// The 16 wavefronts' entries of `totals` that come before mine, added up.
-__device__ __forceinline__ uint32_t sum_of_waves_before(const uint32_t *totals, uint32_t wave, int lane)
-{
-    const uint32_t own = totals[lane & 15];
-    uint32_t v = own;
-    v += dpp_or_zero<0x111, 0xF>(v);             // a scan over each row of 16 lanes
-    v += dpp_or_zero<0x112, 0xF>(v);
-    v += dpp_or_zero<0x114, 0xF>(v);
-    v += dpp_or_zero<0x118, 0xF>(v);
-    return (uint32_t)__builtin_amdgcn_readlane((int)(v - own), (int)wave);
-}
-
 // LDS of k_select_small, for units of at most PLACES places and BINS bins of the first cut
 template <uint32_t PLACES, uint32_t BINS>
 struct SmallSelectLds {
@@ -820,13 +848,42 @@ __global__ __launch_bounds__(kSmallUnitThreads) void k_select_small(const float 
 //     counts; selected candidates before it, counted while ranking).  Ranking a few thousand candidates sixteen to
 //     thirty-two times over costs less than one workgroup walking the unit's whole bit map.
 // If a unit's bin b* holds more tiles than the list does (massive ties), the unit's first workgroup of the second
-// kernel does all of it alone, straight from the entropies: slower but as exact.  Needs ranking units that start on
-// 64-tile boundaries.
+// kernel does all of it alone, straight from the entropies: slower but as exact.
 // (One launch, with the last workgroup of every unit doing the second part, measured ten times slower: what a
 // workgroup wrote becomes visible to a workgroup on another XCD only through fences that write back the L2.)
 
 constexpr uint32_t kFusedThreads = kBlockSelectThreads;
 constexpr uint32_t kFusedKeysPerBlock = 16 * kFusedThreads;
+
+// A ranking unit in places: a place is a tile's index counted from the 64-tile boundary at or before the unit's first tile, so
+// that 64 places are one word of the bit map, which the unit may share with a neighbour at either end.
+struct UnitPlaces {
+    uint32_t phase, end, nwords;                 // places of the unit: [phase, end)
+    uint64_t word0;                              // its first word in the bit map
+    __device__ __forceinline__ UnitPlaces(uint32_t u, uint32_t n)
+    {
+        const uint64_t j0 = (uint64_t)u * n;
+        phase = (uint32_t)(j0 & 63u);
+        end = phase + n;
+        nwords = (end + 63) / 64;
+        word0 = j0 >> 6;
+    }
+    // places of word g that belong to the unit
+    __device__ __forceinline__ uint64_t mask(uint32_t g) const
+    {
+        uint64_t m = ~0ull;
+        if (g == 0) m <<= phase;
+        if (end - g * 64u < 64u) m &= (1ull << (end - g * 64u)) - 1ull;
+        return m;
+    }
+};
+
+// Word g of a unit whose selected places are `bits`; a shared word has been cleared by an earlier kernel.
+__device__ __forceinline__ void put_word(uint64_t *word, uint64_t mask, uint64_t bits)
+{
+    if (mask == ~0ull) *word = bits;
+    else atomicOr(reinterpret_cast<unsigned long long *>(word), (unsigned long long)bits);
+}
 
 __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *__restrict__ H, uint32_t n, uint32_t k,
                                                                    float bin_scale,
@@ -844,38 +901,34 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *
     const float *uH = H + (uint64_t)u * n;
     uint32_t *listed = fused + (uint64_t)u * 4;              // candidates listed so far
     uint2 *ucand = cand + (uint64_t)u * kCandCap;
-    uint64_t *ubitmap = bitmap + (((uint64_t)u * n) >> 6);   // units start on 64-tile boundaries
-    const uint32_t ngroups = n >> 6;
+    const UnitPlaces at(u, n);
+    uint64_t *ubitmap = bitmap + at.word0;
 
     // all loads first (from a clamped index: none of them sits behind a branch)
     const uint32_t group0 = blockIdx.x * (kFusedKeysPerBlock / 64) + (uint32_t)(KPT * wave);
     float h[KPT];
 #pragma unroll
     for (int r = 0; r < KPT; ++r) {
-        const uint32_t i = (group0 + r) * 64u + lane;
+        const uint32_t i = (group0 + r) * 64u + lane - at.phase;
         h[r] = uH[i < n ? i : n - 1];
     }
-    if (tid < 64) {
-        uint32_t bin, rem;
-        pick_bin<kLinBins>(lin_hist + (uint64_t)u * kLinBins, k, &bin, &rem);
-        if (lane == 0) { chosen[0] = bin; chosen[1] = rem; }
-    }
-    __syncthreads();
+    block_pick_bin<kLinBins>(lin_hist + (uint64_t)u * kLinBins, k, wave_above, chosen);
     const uint32_t bstar = chosen[0];
+    __syncthreads();                             // `chosen` and `wave_above` are used again below
 
     uint32_t bins[KPT];
     uint64_t my_word = 0;
     uint32_t n_cand = 0, n_above = 0;            // of my wavefront (the same in every lane)
 #pragma unroll
     for (int r = 0; r < KPT; ++r) {
-        const bool ok = (group0 + r) * 64u + lane < n;
+        const bool ok = (group0 + r) * 64u + lane - at.phase < n;
         bins[r] = ok ? linear_bin(h[r], bin_scale) : 0xffffffffu;
         const uint64_t above = __ballot(ok && bins[r] > bstar);
         if (lane == r) my_word = above;
         n_above += (uint32_t)__popcll(above);
         n_cand += (uint32_t)__popcll(__ballot(bins[r] == bstar));
     }
-    if (lane < KPT && group0 + lane < ngroups) ubitmap[group0 + lane] = my_word;
+    if (lane < KPT && group0 + lane < at.nwords) put_word(&ubitmap[group0 + lane], at.mask(group0 + lane), my_word);
     // one place in the list for the whole workgroup (a unit's workgroups all add to one counter: few, large additions)
     if (lane == 0) { wave_cand[wave] = n_cand; wave_above[wave] = n_above; }
     __syncthreads();
@@ -955,19 +1008,18 @@ __device__ __forceinline__ void rank_candidates(uint32_t rem, EachCandidate each
 }
 
 // The overflow path: one workgroup resolves a whole unit from the entropies (bin b* holds more tiles than the list).
-__device__ __noinline__ void resolve_unit_alone(const float *__restrict__ uH, uint32_t n, uint32_t rank_base,
+__device__ __noinline__ void resolve_unit_alone(const float *__restrict__ uH, uint32_t n, const UnitPlaces &at, uint32_t rank_base,
                                                 float bin_scale, uint32_t bstar, uint32_t rem,
                                                 uint64_t *__restrict__ ubitmap, uint32_t *__restrict__ uranks,
                                                 ResolveLds &L)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t ngroups = n >> 6;
     uint32_t *ubits32 = reinterpret_cast<uint32_t *>(ubitmap);
     if (rem != 0) {
         rank_candidates(rem, [&](auto f) {
             for (uint32_t i = tid; i < n; i += kFusedThreads) {
                 const float hv = uH[i];
-                if (linear_bin(hv, bin_scale) == bstar) f(order_key(hv), i);
+                if (linear_bin(hv, bin_scale) == bstar) f(order_key(hv), i + at.phase);
             }
         }, [&](uint32_t tile) { atomicOr(&ubits32[tile >> 5], 1u << (tile & 31u)); }, L);
     }
@@ -979,15 +1031,15 @@ __device__ __noinline__ void resolve_unit_alone(const float *__restrict__ uH, ui
     // workgroup's L1 may hold older copies of some words); a thread takes eight consecutive groups per sweep
     constexpr int GPT = 8;
     uint32_t running = rank_base;
-    for (uint32_t g0 = 0; g0 < ngroups; g0 += GPT * kFusedThreads) {
+    for (uint32_t g0 = 0; g0 < at.nwords; g0 += GPT * kFusedThreads) {
         const uint32_t first = g0 + (uint32_t)tid * GPT;
         uint32_t c[GPT], mine = 0;
 #pragma unroll
         for (int i = 0; i < GPT; ++i) {
-            const uint32_t g = first + i < ngroups ? first + i : ngroups - 1;      // clamped, masked below
+            const uint32_t g = first + i < at.nwords ? first + i : at.nwords - 1;      // clamped, masked below
             const uint32_t lo = __hip_atomic_load(&ubits32[2 * g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const uint32_t hi = __hip_atomic_load(&ubits32[2 * g + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            c[i] = first + i < ngroups ? (uint32_t)__popc(lo) + (uint32_t)__popc(hi) : 0u;
+            c[i] = first + i < at.nwords ? (uint32_t)__popcll((((uint64_t)hi << 32) | lo) & at.mask(g)) : 0u;
             mine += c[i];
         }
         const uint32_t incl = wave_incl_scan(mine);
@@ -1003,7 +1055,7 @@ __device__ __noinline__ void resolve_unit_alone(const float *__restrict__ uH, ui
         uint32_t rank = running + before + incl - mine;
 #pragma unroll
         for (int i = 0; i < GPT; ++i) {
-            if (first + i < ngroups) uranks[first + i] = rank;
+            if (first + i < at.nwords && (first + i != 0 || at.phase == 0)) uranks[first + i] = rank;
             rank += c[i];
         }
         running += total;
@@ -1026,40 +1078,34 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float *uH = H + (uint64_t)u * n;
     const uint2 *ucand = cand + (uint64_t)u * kCandCap;
-    uint64_t *ubitmap = bitmap + (((uint64_t)u * n) >> 6);
-    uint32_t *uranks = ranks + (((uint64_t)u * n) >> 6);
-    const uint32_t ngroups = n >> 6;
+    const UnitPlaces at(u, n);
+    uint64_t *ubitmap = bitmap + at.word0;
+    uint32_t *uranks = ranks + at.word0;
     const uint32_t group0 = blk * GROUPS;
-    const uint32_t mygroups = ngroups - group0 < GROUPS ? ngroups - group0 : GROUPS;
+    const uint32_t left = group0 < at.nwords ? at.nwords - group0 : 0u, mygroups = left < GROUPS ? left : GROUPS;
 
-    // everything this workgroup reads from global memory, requested at once: the candidates (sixteen per thread; the
-    // list always has room for them, what lies beyond its end is ignored), the block's words, the counts of the
-    // blocks before it, the histogram
-    constexpr int CPT = (int)(kCandCap / kFusedThreads);
+    // everything this workgroup reads from global memory, requested at once: the first candidates (the list always has
+    // room for them, what lies beyond its end is ignored; the others, where there are more, once their number is known),
+    // the block's words, the counts of the blocks before it, the histogram
+    constexpr int CPT = (int)(kCandCap / kFusedThreads), AHEAD = 4;
     uint2 c[CPT];
 #pragma unroll
-    for (int r = 0; r < CPT; ++r) c[r] = ucand[(uint32_t)r * kFusedThreads + tid];
+    for (int r = 0; r < AHEAD; ++r) c[r] = ucand[(uint32_t)r * kFusedThreads + tid];
     const uint32_t listed = fused[(uint64_t)u * 4];
     uint64_t my_word = 0;
-    if ((uint32_t)tid < mygroups) my_word = ubitmap[group0 + tid];
+    if ((uint32_t)tid < mygroups) my_word = ubitmap[group0 + tid] & at.mask(group0 + tid);
     uint32_t above_before = 0;
     for (uint32_t b = tid; b < blk; b += kFusedThreads) above_before += block_above[(uint64_t)u * gridDim.x + b];
-    if (tid < 64) {
-        uint32_t bin, rem;
-        pick_bin<kLinBins>(lin_hist + (uint64_t)u * kLinBins, k, &bin, &rem);
-        if (lane == 0) { L.chosen[0] = bin; L.chosen[1] = rem; }
-    }
     if (tid == 0) { L.n_before = 0; L.n_equal = 0; }
     static_assert(kSubBins == kFusedThreads, "one sub-bin per thread");
     uint32_t *sub_hist = L.sel.copies;           // the threshold bin's candidates by sub-bin
     sub_hist[tid] = 0;
     if ((uint32_t)tid < GROUPS) { L.words[2 * tid] = (uint32_t)my_word; L.words[2 * tid + 1] = (uint32_t)(my_word >> 32); }
-    __syncthreads();
+    block_pick_bin<kLinBins>(lin_hist + (uint64_t)u * kLinBins, k, L.wave_total, L.chosen);
     const uint32_t bstar = L.chosen[0], rem = L.chosen[1];
-    __syncthreads();                             // `chosen` is used again below
 
     if (listed > kCandCap) {
-        if (blk == 0) resolve_unit_alone(uH, n, u * k, bin_scale, bstar, rem, ubitmap, uranks, L);
+        if (blk == 0) resolve_unit_alone(uH, n, at, u * k, bin_scale, bstar, rem, ubitmap, uranks, L);
         return;
     }
     // the selected candidates: those of my block go into its words, those before it are counted
@@ -1073,6 +1119,10 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
         // A histogram of the candidates over 1024 sub-bins of their bin narrows the threshold down once more:
         // candidates in a higher sub-bin are selected, those in the threshold's own sub-bin (a handful, as a rule) are
         // ranked directly, thread t placing the t-th of them among all of them by (key descending, tile ascending).
+        if (listed > (uint32_t)AHEAD * kFusedThreads) {
+#pragma unroll
+            for (int r = AHEAD; r < CPT; ++r) c[r] = ucand[(uint32_t)r * kFusedThreads + tid];
+        }
         uint32_t sub[CPT];
 #pragma unroll
         for (int r = 0; r < CPT; ++r) {
@@ -1083,12 +1133,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
             }
         }
         __syncthreads();
-        if (tid < 64) {
-            uint32_t s, r2;
-            pick_bin<kSubBins>(sub_hist, rem, &s, &r2);
-            if (lane == 0) { L.chosen[2] = s; L.chosen[3] = r2; }
-        }
-        __syncthreads();
+        block_pick_bin<kSubBins>(sub_hist, rem, L.wave_total, L.chosen + 2);
         const uint32_t sstar = L.chosen[2], rem2 = L.chosen[3];
         uint32_t *list_key = L.sel.copies + kSubBins, *list_tile = L.equal_tile;
         uint32_t in_sub = 0;                     // bit r: my r-th candidate lies in the threshold's sub-bin
@@ -1136,11 +1181,10 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
     const uint32_t incl = wave_incl_scan(cnt);
     if (lane == 63) L.wave_total[wave] = incl;
     __syncthreads();
-    if ((uint32_t)tid < mygroups) {
-        uint32_t rank = u * k + L.n_before + incl - cnt;     // every earlier unit holds exactly k wide tiles
-        for (int w = 0; w < wave; ++w) rank += L.wave_total[w];
-        ubitmap[group0 + tid] = ((uint64_t)hi << 32) | lo;
-        uranks[group0 + tid] = rank;
+    const uint32_t rank = u * k + L.n_before + sum_of_waves_before(L.wave_total, (uint32_t)wave, lane) + incl - cnt;
+    if ((uint32_t)tid < mygroups) {              // (every earlier unit holds exactly k wide tiles)
+        put_word(&ubitmap[group0 + tid], at.mask(group0 + tid), ((uint64_t)hi << 32) | lo);
+        if (group0 + tid != 0 || at.phase == 0) uranks[group0 + tid] = rank;
     }
 }
 

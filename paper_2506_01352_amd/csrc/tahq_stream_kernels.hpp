@@ -212,14 +212,14 @@ static_assert((1u << kDigit0Bits) == kDigit0Bins, "digit 0 width");
 // The ragged last batch (T not a multiple of TILES) is handled after the loop by one workgroup.
 //
 // If `hist0` is given, the kernel also builds the first histogram of the selection (Sec. 3.2, top-p%): per
-// ranking unit of `unit_batches` batches, counts of the keys' top 10 bits (bin_scale == 0) or of the entropies'
+// ranking unit of `unit_tiles` tiles, counts of the keys' top 10 bits (bin_scale == 0) or of the entropies'
 // linear bins (bin_scale > 0), `hist_stride` bins per unit, accumulated in LDS and flushed with global atomics
-// when the workgroup moves to another unit and at its end.  This needs units that are whole numbers of batches
-// (the caller checks; otherwise it passes no histogram).
+// when the workgroup moves to another unit, in the middle of a batch if need be, and at its end.  A batch may touch two
+// units, not more: `unit_tiles` is at least TILES (the caller checks; otherwise it passes no histogram).
 template <int G, bool BF16>
 __global__ __launch_bounds__((Batch<G, BF16 ? 2 : 4>::TILES))
 void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, float eps_l1, float eps_log,
-               uint32_t *__restrict__ hist0, uint32_t unit_batches, uint32_t hist_stride, float bin_scale, Prologue pro)
+               uint32_t *__restrict__ hist0, uint32_t unit_tiles, uint32_t hist_stride, float bin_scale, Prologue pro)
 {
     write_prologue(pro, blockIdx.x * Batch<G, BF16 ? 2 : 4>::TILES + threadIdx.x, gridDim.x * Batch<G, BF16 ? 2 : 4>::TILES);
     constexpr int ES = BF16 ? 2 : 4;
@@ -256,19 +256,31 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, f
     float h_prev = 0.0f;
     uint64_t j_prev = 0;
     bool have_prev = false;
-    uint32_t cur_unit = hist0 && first < last ? first / unit_batches : 0u;
+    uint32_t cur_unit = hist0 && first < last ? first * B::TILES / unit_tiles : 0u;
+    uint32_t unit_end = (cur_unit + 1) * unit_tiles;         // the first tile after it
+    auto bin_of = [&](float h) {
+        return bin_scale > 0.0f ? linear_bin(h, bin_scale) : order_key(h) >> (32 - kDigit0Bits);
+    };
     for (uint32_t batch = first; batch < last; ++batch) {
-        if (hist0) {
-            const uint32_t unit = batch / unit_batches;
-            if (unit != cur_unit) { flush(cur_unit); cur_unit = unit; }
-        }
+        if (hist0 && batch * B::TILES >= unit_end) { flush(cur_unit); ++cur_unit; unit_end += unit_tiles; }
         store_batch<G, ES, true>(v, B::TILES, lds);
         __syncthreads();
         if (have_prev) H[j_prev] = h_prev;
         if (batch + 1 < last) load_full(batch + 1);
         h_prev = entropy_of_row<G, BF16>(row, eps_l1, eps_log);
-        if (hist0)
-            atomicAdd(&lh[bin_scale > 0.0f ? linear_bin(h_prev, bin_scale) : order_key(h_prev) >> (32 - kDigit0Bits)], 1u);
+        if (hist0) {
+            uint32_t *at = &lh[bin_of(h_prev)];
+            const uint32_t mine = unit_end - batch * B::TILES;           // tiles of the batch that belong to cur_unit
+            if (mine >= (uint32_t)B::TILES) {
+                atomicAdd(at, 1u);
+            } else {
+                if ((uint32_t)tid < mine) atomicAdd(at, 1u);
+                flush(cur_unit);
+                ++cur_unit;
+                unit_end += unit_tiles;
+                if ((uint32_t)tid >= mine) atomicAdd(at, 1u);
+            }
+        }
         j_prev = (uint64_t)batch * B::TILES + tid;
         have_prev = true;
         __syncthreads();
@@ -277,12 +289,15 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, f
     if (hist0 && first < last) flush(cur_unit);
 
     if (tail != 0 && blockIdx.x == gridDim.x - 1) {
-        // never combined with a histogram: a ragged batch means units are not whole batches
         const uint64_t j0 = (uint64_t)nfull * B::TILES;
         load_batch<G, ES, false>(in, j0, tail, v);
         store_batch<G, ES, false>(v, tail, lds);
         __syncthreads();
-        if ((uint32_t)tid < tail) H[j0 + tid] = entropy_of_row<G, BF16>(row, eps_l1, eps_log);
+        if ((uint32_t)tid < tail) {
+            const float h = entropy_of_row<G, BF16>(row, eps_l1, eps_log);
+            H[j0 + tid] = h;
+            if (hist0) atomicAdd(&hist0[(j0 + tid) / unit_tiles * hist_stride + bin_of(h)], 1u);
+        }
     }
 }
 

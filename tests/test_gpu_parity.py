@@ -586,6 +586,25 @@ def test_single_launch_selection_with_a_crowded_threshold_bin(tahq, crowd):
         check_case(tahq, x, 2, n, G, G, tahq.F32, 3.0 + take / n)
 
 
+@pytest.mark.parametrize("B,n", [(3, 32706), (2, 32769), (2, 49151), (3, 49153), (2, 65535), (5, 40001)])
+@pytest.mark.parametrize("ties", (False, True))
+def test_large_units_off_the_64_tile_boundaries(tahq, B, n, ties):
+    # two-launch selection of units that share bit map words: blocks of 16384 places that a unit fills, overhangs by a few
+    # places or does not reach; batches of the entropy kernel that hold two units; `ties`: more tiles in the threshold's bin
+    # than the candidate list takes
+    G = 16
+    rng = np.random.default_rng(B * n + ties)
+    x = rng.standard_normal((B, n, G)).astype(np.float32)
+    x[:, ::7, :] *= 1e-3
+    if ties:
+        x[:, rng.permutation(n)[: n * 2 // 3], :] = 1.5              # entropy ln G
+    _say(f"[case] {B} units x {n} tiles, ties={ties}")
+    for budget in (3.01, 3.4) if ties else (3.01, 3.5, 3.99):
+        check_case(tahq, x, B, n, G, G, tahq.F32, budget)
+    x16 = np.ascontiguousarray(workloads.f32_to_bf16_bits(x).reshape(B, n, G))
+    check_case(tahq, x16, B, n, G, 8, tahq.BF16, 2.6, low_bits=2)
+
+
 def test_many_ranking_units_with_few_tiles_each(tahq):
     # 300 samples of 6 tiles: units smaller than a wavefront, a batch spans many units
     rng = np.random.default_rng(5)
