@@ -138,8 +138,9 @@ struct LaunchQuantPack {
         Enqueue &q = *qp;
         using B = Batch<G, BF16 ? 2 : 4>;
         const uint32_t nb = (T + B::TILES - 1) / B::TILES;
-        if (ranked) q(k_quant_pack<G, BF16, LOW, true>, dim3(nb), dim3(B::TILES), d_in, packed, lay, T, tau, eps_ratio, false, pro);
-        else q(k_quant_pack<G, BF16, LOW, false>, dim3(nb), dim3(B::TILES), d_in, packed, lay, T, tau, eps_ratio, all_wide, pro);
+        const dim3 block(B::TILES * Wave<G, BF16 ? 2 : 4>::LPT);
+        if (ranked) q(k_quant_pack<G, BF16, LOW, true>, dim3(nb), block, d_in, packed, lay, T, tau, eps_ratio, false, pro);
+        else q(k_quant_pack<G, BF16, LOW, false>, dim3(nb), block, d_in, packed, lay, T, tau, eps_ratio, all_wide, pro);
     }
     static void run(uint32_t low, const void *d_in, uint8_t *packed, Layout lay, uint32_t T, float tau, float eps_ratio,
                     bool ranked, bool all_wide, Prologue pro, Enqueue *qp)

@@ -23,7 +23,7 @@ struct Batch {
 
 // A batch's tiles travel global -> registers -> padded LDS rows, in two steps, so that the loads of the
 // next batch can be in flight while the current one is being processed.  Thread t moves the 16-byte
-// chunks t, t + TILES, t + 2 TILES, ... of the batch (coalesced).  FULL: all TILES tiles exist, no
+// chunks t, t + THREADS, t + 2 THREADS, ... of the batch (coalesced); TILES threads, or more.  FULL: all TILES tiles exist, no
 // per-thread conditions (so that the compiler can count outstanding memory operations exactly).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -39,15 +39,16 @@ __device__ __forceinline__ uint4 load16(const uint8_t *p)
     }
 }
 
-template <int G, int ESIZE, bool FULL, bool STREAM = false>
-__device__ __forceinline__ void load_batch(const void *__restrict__ in, uint64_t j0, uint32_t nvalid,
-                                           uint4 (&v)[Batch<G, ESIZE>::CHUNKS], int tid = (int)threadIdx.x)
+template <int G, int ESIZE, bool FULL, bool STREAM = false, int N>
+__device__ __forceinline__ void load_batch(const void *__restrict__ in, uint64_t j0, uint32_t nvalid, uint4 (&v)[N],
+                                           int tid = (int)threadIdx.x)
 {
     using B = Batch<G, ESIZE>;
+    constexpr int THREADS = B::TILES * B::CHUNKS / N;        // N chunks per thread
     const uint8_t *src = static_cast<const uint8_t *>(in) + j0 * B::BYTES;
 #pragma unroll
-    for (int i = 0; i < B::CHUNKS; ++i) {
-        const uint32_t q = (uint32_t)i * B::TILES + tid;
+    for (int i = 0; i < N; ++i) {
+        const uint32_t q = (uint32_t)i * THREADS + tid;
         if constexpr (FULL) {
             v[i] = load16<STREAM>(src + (uint64_t)q * 16);
         } else {
@@ -57,14 +58,14 @@ __device__ __forceinline__ void load_batch(const void *__restrict__ in, uint64_t
     }
 }
 
-template <int G, int ESIZE, bool FULL>
-__device__ __forceinline__ void store_batch(const uint4 (&v)[Batch<G, ESIZE>::CHUNKS], uint32_t nvalid, uint8_t *lds,
-                                            int tid = (int)threadIdx.x)
+template <int G, int ESIZE, bool FULL, int N>
+__device__ __forceinline__ void store_batch(const uint4 (&v)[N], uint32_t nvalid, uint8_t *lds, int tid = (int)threadIdx.x)
 {
     using B = Batch<G, ESIZE>;
+    constexpr int THREADS = B::TILES * B::CHUNKS / N;
 #pragma unroll
-    for (int i = 0; i < B::CHUNKS; ++i) {
-        const uint32_t q = (uint32_t)i * B::TILES + tid;
+    for (int i = 0; i < N; ++i) {
+        const uint32_t q = (uint32_t)i * THREADS + tid;
         const uint32_t tile = q / B::CHUNKS, sub = q % B::CHUNKS;
         if (FULL || tile < nvalid) *reinterpret_cast<uint4 *>(lds + tile * B::STRIDE + sub * 16) = v[i];
     }
@@ -419,6 +420,62 @@ __global__ __launch_bounds__(256) void k_alloc_reduce(const float *__restrict__ 
     else out[ja] = 1.0f / (acc + eps_l1);
 }
 
+// How tiles spread over lanes in the quantizer and in the decoder: LPT lanes per tile, EPL consecutive elements per lane, so
+// that a lane holds at most 128 bytes of the tensor; TILES tiles per wavefront.
+template <int G, int ESIZE>
+struct Wave {
+    static constexpr int MAX_EPL = 128 / ESIZE;
+    static constexpr int EPL = G < MAX_EPL ? G : MAX_EPL;                     // elements per lane
+    static constexpr int LPT = G / EPL;                                       // lanes per tile
+    static constexpr int TILES = 64 / LPT;                                    // tiles per wavefront
+    static constexpr int LANE_BYTES = EPL * ESIZE;
+    static constexpr int CHUNKS = LANE_BYTES / 16;                            // 16-byte chunks per lane
+    static constexpr int LDS_BYTES = 64 * LANE_BYTES;
+    static_assert(TILES * LPT == 64 && CHUNKS >= 1 && CHUNKS <= 8, "whole tiles, whole chunks");
+    // Lane r's chunks lie in LDS at slots r * CHUNKS + (c ^ swizzle(r)): eight lanes that read the same chunk of their
+    // rows, like eight that read consecutive chunks of one row, meet eight different 16-byte columns of the banks.
+    static __device__ __forceinline__ uint32_t swizzle(uint32_t r)
+    {
+        return CHUNKS == 8 ? (r & 7u) : CHUNKS == 4 ? ((r >> 1) & 3u) : CHUNKS == 2 ? ((r >> 2) & 1u) : 0u;
+    }
+    // byte offset of element e of the tile that starts at lane `row0`
+    static __device__ __forceinline__ uint32_t element_at(uint32_t row0, uint32_t e)
+    {
+        const uint32_t r = row0 + e / EPL, byte = (e % EPL) * ESIZE;
+        return r * LANE_BYTES + (((byte >> 4) ^ swizzle(r)) << 4) + (byte & 15u);
+    }
+};
+
+// The value of lane (mine ^ X), X = 1 or 2.
+template <int X>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v)
+{
+    static_assert(X == 1 || X == 2, "inside a quad");
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, X == 1 ? 0xB1 : 0x4E, 0xF, 0xF, true);
+}
+template <int X>
+__device__ __forceinline__ float lane_xor(float v)
+{
+    return __uint_as_float(lane_xor<X>(__float_as_uint(v)));
+}
+
+// The butterfly stages that cross lanes: element i of lane part p meets element i of part p ^ (h / EPL).
+template <int EPL, int LPT>
+__device__ __forceinline__ void butterfly_across(float *x, uint32_t part)
+{
+    if constexpr (LPT >= 2) {
+        const float s1 = (part & 1u) ? -1.0f : 1.0f;
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) x[i] = __builtin_fmaf(x[i], s1, lane_xor<1>(x[i]));     // p + q, or p - q: one rounding
+    }
+    if constexpr (LPT >= 4) {
+        const float s2 = (part & 2u) ? -1.0f : 1.0f;
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) x[i] = __builtin_fmaf(x[i], s2, lane_xor<2>(x[i]));
+    }
+    static_assert(LPT <= 4, "two stages across lanes");
+}
+
 // ------------------------------------ K3: transform + quantize + pack
 
 // Payload unit: a tile's payload is b units of G/8 bytes (b = 3 or 4).
@@ -437,10 +494,10 @@ __device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c)
     return r;
 }
 
-// Eq. 3 on my tile, read from its LDS row: magnitude of the largest and second-largest element
-// (with multiplicity) and the lowest index of the largest.
-template <int G, bool BF16>
-__device__ __forceinline__ void top2(const uint8_t *row, float *a1_out, float *a2_out, uint32_t *d_out)
+// Eq. 3 on my tile, of which `row` (LDS) is my part of G elements: magnitude of the largest and second-largest element
+// (with multiplicity) and the lowest index of the largest, in the whole tile of LPT parts.
+template <int G, bool BF16, int LPT>
+__device__ __forceinline__ void top2(const uint8_t *row, uint32_t part, float *a1_out, float *a2_out, uint32_t *d_out)
 {
     if constexpr (BF16) {
         // A bf16 magnitude has 16 free low bits: key = |bits| << 16 | (G-1-k) orders by magnitude, then by
@@ -463,13 +520,24 @@ __device__ __forceinline__ void top2(const uint8_t *row, float *a1_out, float *a
             }
         }
         e1 >>= 1; e2 >>= 1;
-        const uint32_t k1 = e1 > o1 ? e1 : o1;
+        uint32_t k1 = e1 > o1 ? e1 : o1;
         const uint32_t lo = e1 > o1 ? o1 : e1;
         const uint32_t hi2 = e2 > o2 ? e2 : o2;
-        const uint32_t k2 = lo > hi2 ? lo : hi2;
+        uint32_t k2 = lo > hi2 ? lo : hi2;
+        // the other parts of the tile: two pairs become one
+        auto merge = [&](uint32_t p1, uint32_t p2) {
+            const uint32_t less = k1 < p1 ? k1 : p1, more2 = k2 > p2 ? k2 : p2;
+            k1 = k1 > p1 ? k1 : p1;
+            k2 = less > more2 ? less : more2;
+        };
+        if constexpr (LPT >= 2) {
+            k1 += (LPT - 1 - part) * G;          // the low bits count indices of the whole tile from its end
+            merge(lane_xor<1>(k1), lane_xor<1>(k2));
+        }
+        if constexpr (LPT >= 4) merge(lane_xor<2>(k1), lane_xor<2>(k2));
         *a1_out = __uint_as_float(k1 & 0x7fff0000u);
         *a2_out = __uint_as_float(k2 & 0x7fff0000u);
-        *d_out = (G - 1) - (k1 & 0x7fu);
+        *d_out = (LPT * G - 1) - (k1 & 0x7fu);
     } else {
         float a1 = -1.0f, a2 = 0.0f;     // magnitudes are >= 0: the first element always replaces a1
         uint32_t d = 0;
@@ -486,6 +554,17 @@ __device__ __forceinline__ void top2(const uint8_t *row, float *a1_out, float *a
                 a1 = gt ? a : a1;
             }
         }
+        auto merge = [&](float p1, float p2, uint32_t pd) {
+            const bool other = p1 > a1 || (p1 == a1 && pd < d);
+            a2 = __builtin_fmaxf(__builtin_fminf(a1, p1), __builtin_fmaxf(a2, p2));
+            a1 = other ? p1 : a1;
+            d = other ? pd : d;
+        };
+        if constexpr (LPT >= 2) {
+            d += part * G;
+            merge(lane_xor<1>(a1), lane_xor<1>(a2), lane_xor<1>(d));
+        }
+        if constexpr (LPT >= 4) merge(lane_xor<2>(a1), lane_xor<2>(a2), lane_xor<2>(d));
         *a1_out = a1;
         *a2_out = __builtin_fmaxf(a2, 0.0f);
         *d_out = d;
@@ -524,22 +603,25 @@ __device__ __forceinline__ uint32_t bits_below_me(uint64_t mask)
 }
 
 // Width of my tile (LOW or LOW + 1 bits), its payload position inside the batch (in units of G/8 bytes), and
-// the number of wide tiles in the batch.  A wavefront's 64 tiles are one bit map word.
-template <int TILES, int LOW>
+// the number of wide tiles in the batch.  My tile is tid / LPT: a wavefront's tiles lie in one bit map word.
+template <int TILES, int LOW, int LPT>
 __device__ __forceinline__ void tile_pos(const BatchMeta<TILES> &m, int tid, uint32_t *b, uint32_t *rel, uint32_t *total4)
 {
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);      // the same in every lane
-    const uint32_t lane = (uint32_t)tid & 63u;
+    const uint32_t mine_word = (uint32_t)__builtin_amdgcn_readfirstlane(tid / (64 * LPT));      // the same in every lane
+    const uint32_t tile = (uint32_t)tid / LPT, at = tile & 63u;
     uint64_t mine = 0;
     uint32_t before = 0, tot = 0;
 #pragma unroll
     for (int w = 0; w < BatchMeta<TILES>::WORDS; ++w) {
-        if ((uint32_t)w == wave) { mine = m.word[w]; before = tot; }
+        if ((uint32_t)w == mine_word) { mine = m.word[w]; before = tot; }
         tot += (uint32_t)__popcll(m.word[w]);
     }
-    const uint32_t half = lane < 32u ? (uint32_t)mine : (uint32_t)(mine >> 32);
-    *b = (uint32_t)LOW + ((half >> (lane & 31u)) & 1u);
-    *rel = (uint32_t)LOW * (uint32_t)tid + before + bits_below_me(mine);
+    const uint32_t half = at < 32u ? (uint32_t)mine : (uint32_t)(mine >> 32);
+    *b = (uint32_t)LOW + ((half >> (at & 31u)) & 1u);
+    uint32_t below;
+    if constexpr (LPT == 1) below = bits_below_me(mine);
+    else below = (uint32_t)__popc(half & ((1u << (at & 31u)) - 1u)) + (at < 32u ? 0u : (uint32_t)__popc((uint32_t)mine));
+    *rel = (uint32_t)LOW * tile + before + below;
     *total4 = tot;
 }
 
@@ -591,16 +673,17 @@ __device__ __forceinline__ float fmax3(float a, float b, float c)
     return r;
 }
 
-// Eq. 3 for the tile in `row`: outlier flag and pivot index; for an outlier tile with d != 0 the pivot
-// swap P_d is applied to the LDS row on the spot.  Returns the pivot byte (bit 7 = flag, bits 0..6 = d).
-template <int G, bool BF16>
-__device__ __forceinline__ uint32_t analyse_row(uint8_t *row, float tau, float eps_ratio)
+// Eq. 3 for the tile in `row`, my part of which is the part-th of LPT: outlier flag and pivot index; for an outlier tile
+// with d != 0 the pivot swap P_d is applied to the LDS row on the spot.  Returns the pivot byte (bit 7 = flag, bits 0..6 = d).
+template <int G, bool BF16, int LPT>
+__device__ __forceinline__ uint32_t analyse_row(uint8_t *row, uint32_t part, float tau, float eps_ratio)
 {
     float a1, a2;
     uint32_t d;
-    top2<G, BF16>(row, &a1, &a2, &d);
+    constexpr int EPL = G / LPT;
+    top2<EPL, BF16, LPT>(row + part * (EPL * (BF16 ? 2 : 4)), part, &a1, &a2, &d);
     const bool flag = a1 > tau * (a2 + eps_ratio);
-    if (flag && d != 0) {
+    if (flag && d != 0 && part == 0) {           // (the tile's other lanes have read the row: they are in this wavefront)
         if constexpr (BF16) {
             uint16_t *r16 = reinterpret_cast<uint16_t *>(row);
             const uint16_t v0 = r16[0], vd = r16[d];
@@ -616,15 +699,17 @@ __device__ __forceinline__ uint32_t analyse_row(uint8_t *row, float tau, float e
 
 // The rest of the encoder for one tile, in two steps with a workgroup barrier between them (the payload
 // buffer that step 2 writes shares LDS with the rows that step 1 reads).
-// Step 1: the row (which already carries P_d) into registers; Eq. 4 on outlier tiles.
-template <int G, bool BF16>
-__device__ __forceinline__ void transform_row(const uint8_t *row, bool flag, float *x)
+// Step 1: my part of the row (which already carries P_d) into registers; Eq. 4 on outlier tiles.
+template <int G, bool BF16, int LPT>
+__device__ __forceinline__ void transform_row(const uint8_t *row, uint32_t part, bool flag, float *x)
 {
-    read_tile<G, BF16>(row, x);
-    if (flag) {
-        butterfly<G>(x);
+    constexpr int EPL = G / LPT;
+    read_tile<EPL, BF16>(row + part * (EPL * (BF16 ? 2 : 4)), x);
+    if (flag) {                                  // the lanes of a tile agree
+        butterfly<EPL>(x);
+        butterfly_across<EPL, LPT>(x, part);
 #pragma unroll
-        for (int k = 0; k < G; ++k) x[k] = x[k] * TileConst<G>::c;
+        for (int k = 0; k < EPL; ++k) x[k] = x[k] * TileConst<G>::c;
     }
 }
 
@@ -685,17 +770,21 @@ __device__ __forceinline__ void place_codes(const uint32_t *q, uint32_t *dw)
     }
 }
 
-// Step 2: range, quantizer parameters, codes, and the tile's LSB-first bit string written as b units at
-// `dst` (LDS); b is LOW or LOW + 1.  Returns scale | zero << 16.
-template <int G, int LOW>
+// Step 2: range and quantizer parameters of the tile, codes of my G elements of it, and their LSB-first bit string written
+// as b units at `dst` (LDS); b is LOW or LOW + 1.  Returns scale | zero << 16.
+template <int G, int LOW, int LPT>
 __device__ __forceinline__ uint32_t quantize_values(const float *x, uint32_t b, typename Unit<G>::type *dst)
 {
     constexpr uint32_t WIDE = LOW + 1;
     float mn = fmin3(x[0], x[1], x[2]), mx = fmax3(x[0], x[1], x[2]);
 #pragma unroll
     for (int k = 3; k + 1 < G; k += 2) { mn = fmin3(mn, x[k], x[k + 1]); mx = fmax3(mx, x[k], x[k + 1]); }
-    mn = __builtin_fminf(mn, x[G - 1]) + 0.0f;
-    mx = __builtin_fmaxf(mx, x[G - 1]) + 0.0f;
+    mn = __builtin_fminf(mn, x[G - 1]);
+    mx = __builtin_fmaxf(mx, x[G - 1]);
+    if constexpr (LPT >= 2) { mn = __builtin_fminf(mn, lane_xor<1>(mn)); mx = __builtin_fmaxf(mx, lane_xor<1>(mx)); }
+    if constexpr (LPT >= 4) { mn = __builtin_fminf(mn, lane_xor<2>(mn)); mx = __builtin_fmaxf(mx, lane_xor<2>(mx)); }
+    mn = mn + 0.0f;
+    mx = mx + 0.0f;
 
     // asymmetric quantizer, binary16 metadata rounded outwards
     const float Lv = (b == WIDE) ? (float)((1u << WIDE) - 1u) : (float)((1u << LOW) - 1u);
@@ -765,11 +854,6 @@ __device__ __forceinline__ uint32_t quantize_values(const float *x, uint32_t b, 
     return s16 | (z16 << 16);
 }
 
-// Occupancy hint: with small tiles the kernel fits four workgroups per compute unit if it stays within
-// 128 vector registers.
-template <int G, int ESIZE>
-struct QuantPackOccupancy { static constexpr int WAVES_PER_SIMD = (G * ESIZE <= 128) ? 4 : 1; };
-
 // One workgroup per batch of TILES tiles, in two stages.  Stage one: lane i examines tile i (Eq. 3, pivot
 // swap in LDS).  The tiles are then regrouped by class -- (plain | transformed) x (narrow | wide) -- so that in
 // stage two, where lane p takes the p-th tile in class order, most wavefronts hold a single class: the
@@ -777,6 +861,10 @@ struct QuantPackOccupancy { static constexpr int WAVES_PER_SIMD = (G * ESIZE <= 
 // paths rarely both run.  The payload buffer reuses the rows' LDS once every lane holds its tile in
 // registers, which keeps the workgroup small enough for four to share a compute unit: this kernel
 // lives on the loads of its neighbours being in flight while it computes.
+// Tiles of more than 128 bytes take LPT lanes each, so that a workgroup has 256 threads and a lane at most 64 elements for
+// every tile: with a lane per tile such workgroups had 64 or 128 threads of 200 registers, one or two wavefronts per
+// vector unit, where it takes four to issue at the full rate.  bf16 [8,1024,4096] G = 128 at 3 bits: 28.5 -> 24.2 us, fp32
+// [4,512,2048] G = 64: 8.3 -> 6.7.
 template <int G, bool BF16, int LOW, bool RANKED, bool FULL>
 __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, uint8_t *__restrict__ packed, const Layout &lay,
                                                  uint32_t T, float tau, float eps_ratio, uint32_t batch, uint32_t nvalid,
@@ -785,7 +873,8 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<G, ES>;
     using U = typename Unit<G>::type;
-    constexpr int WAVES = (B::TILES + 63) / 64;
+    constexpr int EPL = Wave<G, ES>::EPL, LPT = Wave<G, ES>::LPT, THREADS = B::TILES * LPT;
+    constexpr int WAVES = THREADS / 64;
     constexpr uint32_t WIDE = LOW + 1;           // the two code widths are LOW and WIDE bits
     static_assert(sizeof(U) * WIDE * B::TILES <= (size_t)B::LDS_BYTES, "payload buffer must fit in the rows");
     U *pay = reinterpret_cast<U *>(lds);         // valid only after every lane has left the rows
@@ -794,9 +883,10 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t slot = (uint32_t)tid / LPT, part = (uint32_t)tid % LPT;
     const uint64_t j0 = (uint64_t)batch * B::TILES;
 
-    uint4 v[B::CHUNKS];
+    uint4 v[B::CHUNKS / LPT];
     load_batch<G, ES, FULL, true>(in, j0, nvalid, v, tid);           // second and last read of the tensor
     BatchMeta<B::TILES> meta;
     if constexpr (RANKED) {
@@ -813,40 +903,47 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
     }
     store_batch<G, ES, FULL>(v, nvalid, lds, tid);
     uint32_t b, rel, total4;
-    tile_pos<B::TILES, LOW>(meta, tid, &b, &rel, &total4);
+    tile_pos<B::TILES, LOW, LPT>(meta, tid, &b, &rel, &total4);
     __syncthreads();
 
-    // stage one: my own tile
-    const bool valid = FULL || (uint32_t)tid < nvalid;
-    uint32_t cls = 4;                            // tiles past the end sort last
+    // stage one: the tile of my slot in storage order
+    const bool valid = FULL || slot < nvalid;
+    uint32_t cls = 4;                            // tiles past the end, and all lanes of a tile but its first, sort nowhere
     if (valid) {
-        const uint32_t pv = analyse_row<G, BF16>(lds + tid * B::STRIDE, tau, eps_ratio);
-        info[tid] = pv | ((b == WIDE) ? 0x100u : 0u) | (rel << 9);
-        cls = ((pv >> 7) << 1) | (b == WIDE ? 1u : 0u);
+        const uint32_t pv = analyse_row<G, BF16, LPT>(lds + slot * B::STRIDE, part, tau, eps_ratio);
+        if (part == 0) {
+            info[slot] = pv | ((b == WIDE) ? 0x100u : 0u) | (rel << 9);
+            cls = ((pv >> 7) << 1) | (b == WIDE ? 1u : 0u);
+        }
     }
     const uint32_t rank_in_wave = class_rank_in_wave<WAVES>(cls, (uint32_t)wave, (uint32_t)lane, class_count);
     __syncthreads();
     {
         const uint32_t pos = rank_in_wave + class_group_base<WAVES>(cls, (uint32_t)wave, (uint32_t)lane, class_count);
-        if (valid) order[pos] = (uint16_t)tid;
+        if (cls < 4) order[pos] = (uint16_t)slot;
     }
     __syncthreads();
 
-    // stage two: the tid-th tile in class order
-    float x[G];
+    // stage two: the tile of my slot in class order
+    float x[EPL];
     uint32_t t = 0, inf = 0;
     if (valid) {
-        t = order[tid];
+        t = order[slot];
         inf = info[t];
-        transform_row<G, BF16>(lds + t * B::STRIDE, (inf & 0x80u) != 0, x);
+        transform_row<G, BF16, LPT>(lds + t * B::STRIDE, part, (inf & 0x80u) != 0, x);
     }
     __syncthreads();                             // the rows are dead: their LDS becomes the payload buffer
     if (valid) {
-        const uint32_t meta16 = quantize_values<G, LOW>(x, (inf & 0x100u) ? WIDE : (uint32_t)LOW, pay + (inf >> 9));
+        // (a part's share of the payload is b units of EPL/8 bytes)
+        const uint32_t width = (inf & 0x100u) ? WIDE : (uint32_t)LOW;
+        const uint32_t meta16 = quantize_values<EPL, LOW, LPT>(
+            x, width, reinterpret_cast<typename Unit<EPL>::type *>(pay + (inf >> 9)) + part * width);
         const uint64_t j = j0 + t;
-        reinterpret_cast<uint16_t *>(packed + lay.scale)[j] = (uint16_t)meta16;
-        reinterpret_cast<uint16_t *>(packed + lay.zero)[j] = (uint16_t)(meta16 >> 16);
-        packed[lay.pivot + j] = (uint8_t)inf;
+        if (part == 0) {
+            reinterpret_cast<uint16_t *>(packed + lay.scale)[j] = (uint16_t)meta16;
+            reinterpret_cast<uint16_t *>(packed + lay.zero)[j] = (uint16_t)(meta16 >> 16);
+            packed[lay.pivot + j] = (uint8_t)inf;
+        }
     }
     __syncthreads();
 
@@ -854,8 +951,8 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
     const uint32_t span = (uint32_t)LOW * nvalid + total4;
     U *gdst = reinterpret_cast<U *>(packed + lay.payload) + ((uint64_t)LOW * j0 + meta.rank0);
 #pragma unroll
-    for (int i = 0; i < (int)WIDE; ++i) {
-        const uint32_t q = (uint32_t)i * B::TILES + tid;
+    for (int i = 0; i < ((int)WIDE + LPT - 1) / LPT; ++i) {
+        const uint32_t q = (uint32_t)i * THREADS + tid;
         if (q < span) gdst[q] = pay[q];
     }
 }
@@ -864,18 +961,18 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
 // writes bit map, rank table and prologue as well.  (A variant of its own: the same as a run-time choice delayed the loads of
 // the ranked case, 126 -> 136 us on bf16 [8,4096,8192].)
 template <int G, bool BF16, int LOW, bool RANKED>
-__global__ __launch_bounds__((Batch<G, BF16 ? 2 : 4>::TILES), (QuantPackOccupancy<G, BF16 ? 2 : 4>::WAVES_PER_SIMD))
+__global__ __launch_bounds__((Batch<G, BF16 ? 2 : 4>::TILES * Wave<G, BF16 ? 2 : 4>::LPT), 4)
 void k_quant_pack(const void *__restrict__ in, uint8_t *__restrict__ packed, Layout lay, uint32_t T, float tau,
                   float eps_ratio, bool all_wide, Prologue pro)
 {
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<G, ES>;
-    constexpr int WAVES = (B::TILES + 63) / 64;
+    constexpr int THREADS = B::TILES * Wave<G, ES>::LPT, WAVES = THREADS / 64;
     __shared__ __attribute__((aligned(16))) uint8_t lds[B::LDS_BYTES];
     __shared__ uint32_t info[B::TILES];          // per tile: pivot byte | (b == WIDE) << 8 | rel << 9
     __shared__ uint16_t order[B::TILES];         // tiles in class order
     __shared__ uint32_t class_count[4 * WAVES];  // tiles per class and wavefront, class-major
-    if constexpr (!RANKED) write_prologue(pro, blockIdx.x * B::TILES + threadIdx.x, gridDim.x * B::TILES);
+    if constexpr (!RANKED) write_prologue(pro, blockIdx.x * THREADS + threadIdx.x, gridDim.x * THREADS);
     const uint32_t nfull = T / B::TILES;        // a workgroup per batch; the last one may be ragged
     if (blockIdx.x < nfull)
         quant_pack_batch<G, BF16, LOW, RANKED, true>(in, packed, lay, T, tau, eps_ratio, blockIdx.x, B::TILES, all_wide, lds, info,
@@ -944,62 +1041,11 @@ __device__ __forceinline__ void dequantize_codes(const uint32_t *dw, float sf, f
     }
 }
 
-// Geometry of the wavefront-per-group kernels: a wavefront takes a group of TILES consecutive tiles, LPT lanes per tile,
-// EPL consecutive elements per lane: a lane holds at most 128 bytes of the tensor.
-template <int G, int ESIZE>
-struct Wave {
-    static constexpr int MAX_EPL = 128 / ESIZE;
-    static constexpr int EPL = G < MAX_EPL ? G : MAX_EPL;                     // elements per lane
-    static constexpr int LPT = G / EPL;                                       // lanes per tile
-    static constexpr int TILES = 64 / LPT;                                    // tiles per wavefront
-    static constexpr int LANE_BYTES = EPL * ESIZE;
-    static constexpr int CHUNKS = LANE_BYTES / 16;                            // 16-byte chunks per lane
-    static constexpr int LDS_BYTES = 64 * LANE_BYTES;
-    static_assert(TILES * LPT == 64 && CHUNKS >= 1 && CHUNKS <= 8, "whole tiles, whole chunks");
-    // Lane r's chunks lie in LDS at slots r * CHUNKS + (c ^ swizzle(r)): eight lanes that read the same chunk of their
-    // rows, like eight that read consecutive chunks of one row, meet eight different 16-byte columns of the banks.
-    static __device__ __forceinline__ uint32_t swizzle(uint32_t r)
-    {
-        return CHUNKS == 8 ? (r & 7u) : CHUNKS == 4 ? ((r >> 1) & 3u) : CHUNKS == 2 ? ((r >> 2) & 1u) : 0u;
-    }
-    // byte offset of element e of the tile that starts at lane `row0`
-    static __device__ __forceinline__ uint32_t element_at(uint32_t row0, uint32_t e)
-    {
-        const uint32_t r = row0 + e / EPL, byte = (e % EPL) * ESIZE;
-        return r * LANE_BYTES + (((byte >> 4) ^ swizzle(r)) << 4) + (byte & 15u);
-    }
-};
-
 // Orders the LDS accesses of one wavefront for the compiler; the hardware performs them in program order.
 __device__ __forceinline__ void wave_lds_fence()
 {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-}
-
-// The value of lane (mine ^ X), X = 1 or 2.
-template <int X>
-__device__ __forceinline__ float lane_xor(float v)
-{
-    static_assert(X == 1 || X == 2, "inside a quad");
-    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), X == 1 ? 0xB1 : 0x4E, 0xF, 0xF, true));
-}
-
-// The butterfly stages that cross lanes: element i of lane part p meets element i of part p ^ (h / EPL).
-template <int EPL, int LPT>
-__device__ __forceinline__ void butterfly_across(float *x, uint32_t part)
-{
-    if constexpr (LPT >= 2) {
-        const float s1 = (part & 1u) ? -1.0f : 1.0f;
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) x[i] = __builtin_fmaf(x[i], s1, lane_xor<1>(x[i]));     // p + q, or p - q: one rounding
-    }
-    if constexpr (LPT >= 4) {
-        const float s2 = (part & 2u) ? -1.0f : 1.0f;
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) x[i] = __builtin_fmaf(x[i], s2, lane_xor<2>(x[i]));
-    }
-    static_assert(LPT <= 4, "two stages across lanes");
 }
 
 // My share of a tile's bit string: LOW or LOW + 1 units of UB = EPL / 8 bytes at `p`, as dwords.  `end` is the end of the
