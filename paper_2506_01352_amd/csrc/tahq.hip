@@ -115,9 +115,10 @@ struct LaunchEntropy {
         Enqueue &q = *qp;
         using B = Batch<G, BF16 ? 2 : 4>;
         const uint32_t nb = (T + B::TILES - 1) / B::TILES;
+        constexpr int THREADS = B::TILES * Wave<G, BF16 ? 2 : 4>::LPT;
         static ResidentCache cache;
-        const uint32_t res = resident_blocks(reinterpret_cast<const void *>(k_entropy<G, BF16>), B::TILES, cache);
-        q(k_entropy<G, BF16>, dim3(nb < res ? nb : res), dim3(B::TILES), d_in, d_H, T,
+        const uint32_t res = resident_blocks(reinterpret_cast<const void *>(k_entropy<G, BF16>), THREADS, cache);
+        q(k_entropy<G, BF16>, dim3(nb < res ? nb : res), dim3(THREADS), d_in, d_H, T,
                            eps_l1, eps_log, hist, (uint32_t)n_per_unit, bins, bin_scale, pro);
     }
     static bool can_fuse_histogram(uint64_t n_per_unit) { return n_per_unit % Batch<G, BF16 ? 2 : 4>::TILES == 0; }

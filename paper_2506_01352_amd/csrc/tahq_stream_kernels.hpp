@@ -141,6 +141,62 @@ __device__ __forceinline__ void butterfly(float *x)
     }
 }
 
+// How tiles spread over lanes in the entropy kernel, the quantizer and the decoder: LPT lanes per tile, EPL consecutive elements per lane, so
+// that a lane holds at most 128 bytes of the tensor; TILES tiles per wavefront.
+template <int G, int ESIZE>
+struct Wave {
+    static constexpr int MAX_EPL = 128 / ESIZE;
+    static constexpr int EPL = G < MAX_EPL ? G : MAX_EPL;                     // elements per lane
+    static constexpr int LPT = G / EPL;                                       // lanes per tile
+    static constexpr int TILES = 64 / LPT;                                    // tiles per wavefront
+    static constexpr int LANE_BYTES = EPL * ESIZE;
+    static constexpr int CHUNKS = LANE_BYTES / 16;                            // 16-byte chunks per lane
+    static constexpr int LDS_BYTES = 64 * LANE_BYTES;
+    static_assert(TILES * LPT == 64 && CHUNKS >= 1 && CHUNKS <= 8, "whole tiles, whole chunks");
+    // Lane r's chunks lie in LDS at slots r * CHUNKS + (c ^ swizzle(r)): eight lanes that read the same chunk of their
+    // rows, like eight that read consecutive chunks of one row, meet eight different 16-byte columns of the banks.
+    static __device__ __forceinline__ uint32_t swizzle(uint32_t r)
+    {
+        return CHUNKS == 8 ? (r & 7u) : CHUNKS == 4 ? ((r >> 1) & 3u) : CHUNKS == 2 ? ((r >> 2) & 1u) : 0u;
+    }
+    // byte offset of element e of the tile that starts at lane `row0`
+    static __device__ __forceinline__ uint32_t element_at(uint32_t row0, uint32_t e)
+    {
+        const uint32_t r = row0 + e / EPL, byte = (e % EPL) * ESIZE;
+        return r * LANE_BYTES + (((byte >> 4) ^ swizzle(r)) << 4) + (byte & 15u);
+    }
+};
+
+// The value of lane (mine ^ X), X = 1 or 2.
+template <int X>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v)
+{
+    static_assert(X == 1 || X == 2, "inside a quad");
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, X == 1 ? 0xB1 : 0x4E, 0xF, 0xF, true);
+}
+template <int X>
+__device__ __forceinline__ float lane_xor(float v)
+{
+    return __uint_as_float(lane_xor<X>(__float_as_uint(v)));
+}
+
+// The butterfly stages that cross lanes: element i of lane part p meets element i of part p ^ (h / EPL).
+template <int EPL, int LPT>
+__device__ __forceinline__ void butterfly_across(float *x, uint32_t part)
+{
+    if constexpr (LPT >= 2) {
+        const float s1 = (part & 1u) ? -1.0f : 1.0f;
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) x[i] = __builtin_fmaf(x[i], s1, lane_xor<1>(x[i]));     // p + q, or p - q: one rounding
+    }
+    if constexpr (LPT >= 4) {
+        const float s2 = (part & 2u) ? -1.0f : 1.0f;
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) x[i] = __builtin_fmaf(x[i], s2, lane_xor<2>(x[i]));
+    }
+    static_assert(LPT <= 4, "two stages across lanes");
+}
+
 // ------------------------------------------------------------- prologue
 
 // What a stream holds besides the kernels' results: header and zeroed section padding.  And the bit map words that ranking
@@ -189,19 +245,26 @@ __device__ __forceinline__ void constant_width_word(uint64_t w, uint32_t T, int 
 
 // -------------------------------------------------------------- K0: entropy
 
-// Eq. 1-2 for my tile, read from its LDS row.
-template <int G, bool BF16>
+// Eq. 1-2 for a tile, of whose LDS row `row` is my part: the sums of the LPT parts meet in pairs, which are the top of the
+// tile's binary tree.
+template <int G, bool BF16, int LPT>
 __device__ __forceinline__ float entropy_of_row(const uint8_t *row, float eps_l1, float eps_log)
 {
-    float a[G];
-    read_tile<G, BF16>(row, a);
+    constexpr int EPL = G / LPT;
+    auto whole = [](float part) {
+        if constexpr (LPT >= 2) part = part + lane_xor<1>(part);
+        if constexpr (LPT >= 4) part = part + lane_xor<2>(part);
+        return part;
+    };
+    float a[EPL];
+    read_tile<EPL, BF16>(row, a);
 #pragma unroll
-    for (int k = 0; k < G; ++k) a[k] = __builtin_fabsf(a[k]);
-    const float L1 = tree_sum<G>(a);
+    for (int k = 0; k < EPL; ++k) a[k] = __builtin_fabsf(a[k]);
+    const float L1 = whole(tree_sum<EPL>(a));
     const float invL = 1.0f / (L1 + eps_l1);
 #pragma unroll
-    for (int k = 0; k < G; ++k) a[k] = a[k] * log_contract(__builtin_fmaf(a[k], invL, eps_log));
-    return 0.0f - invL * tree_sum<G>(a);
+    for (int k = 0; k < EPL; ++k) a[k] = a[k] * log_contract(__builtin_fmaf(a[k], invL, eps_log));
+    return 0.0f - invL * whole(tree_sum<EPL>(a));
 }
 
 constexpr int kDigit0Bits = 10;                  // first radix digit of the selection: key bits 31..22
@@ -211,6 +274,9 @@ static_assert((1u << kDigit0Bits) == kDigit0Bins, "digit 0 width");
 // are issued before the current batch is processed, and a batch's result is stored one iteration later,
 // just before those loads, so that no wait for loads ever has a younger store in front of it.
 // The ragged last batch (T not a multiple of TILES) is handled after the loop by one workgroup.
+// Tiles of more than 128 bytes take LPT lanes each, as in the quantizer.  fp32 [4,2048,8192] G = 64: 44.7 -> 42.7 us, G = 128:
+// 56.2 -> 41.1, bf16
+// [8,2048,8192] G = 128: 65.2 -> 53.9.
 //
 // If `hist0` is given, the kernel also builds the first histogram of the selection (Sec. 3.2, top-p%): per
 // ranking unit of `unit_tiles` tiles, counts of the keys' top 10 bits (bin_scale == 0) or of the entropies'
@@ -218,36 +284,38 @@ static_assert((1u << kDigit0Bits) == kDigit0Bins, "digit 0 width");
 // when the workgroup moves to another unit, in the middle of a batch if need be, and at its end.  A batch may touch two
 // units, not more: `unit_tiles` is at least TILES (the caller checks; otherwise it passes no histogram).
 template <int G, bool BF16>
-__global__ __launch_bounds__((Batch<G, BF16 ? 2 : 4>::TILES))
+__global__ __launch_bounds__((Batch<G, BF16 ? 2 : 4>::TILES * Wave<G, BF16 ? 2 : 4>::LPT))
 void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, float eps_l1, float eps_log,
                uint32_t *__restrict__ hist0, uint32_t unit_tiles, uint32_t hist_stride, float bin_scale, Prologue pro)
 {
-    write_prologue(pro, blockIdx.x * Batch<G, BF16 ? 2 : 4>::TILES + threadIdx.x, gridDim.x * Batch<G, BF16 ? 2 : 4>::TILES);
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<G, ES>;
+    constexpr int LPT = Wave<G, ES>::LPT, THREADS = B::TILES * LPT;
+    write_prologue(pro, blockIdx.x * THREADS + threadIdx.x, gridDim.x * THREADS);
     __shared__ __attribute__((aligned(16))) uint8_t lds[B::LDS_BYTES];
     static_assert(kLinBins >= kDigit0Bins, "one LDS histogram serves both kinds of bins");
     __shared__ uint32_t lh[kLinBins];
     const int tid = threadIdx.x;
     const uint32_t nfull = T / B::TILES, tail = T % B::TILES;
-    const uint8_t *row = lds + tid * B::STRIDE;
+    const uint32_t tile = (uint32_t)tid / LPT, part = (uint32_t)tid % LPT;
+    const uint8_t *row = lds + tile * B::STRIDE + part * Wave<G, ES>::LANE_BYTES;
     const uint32_t per = (nfull + gridDim.x - 1) / gridDim.x;
     const uint32_t first = blockIdx.x * per;
     const uint32_t last = first + per < nfull ? first + per : nfull;      // my batches: [first, last)
 
     if (hist0) {
-        for (int i = tid; i < (int)hist_stride; i += B::TILES) lh[i] = 0;
+        for (int i = tid; i < (int)hist_stride; i += THREADS) lh[i] = 0;
     }
     auto flush = [&](uint32_t unit) {
         __syncthreads();
-        for (int i = tid; i < (int)hist_stride; i += B::TILES) {
+        for (int i = tid; i < (int)hist_stride; i += THREADS) {
             const uint32_t c = lh[i];
             if (c) { atomicAdd(&hist0[(uint64_t)unit * hist_stride + i], c); lh[i] = 0; }
         }
         __syncthreads();
     };
 
-    uint4 v[B::CHUNKS];
+    uint4 v[B::CHUNKS / LPT];
     // non-temporal loads: the tensor is much larger than any cache, and keeping part of it for the second
     // pass measured slower than streaming all of it
     auto load_full = [&](uint32_t batch) {
@@ -266,27 +334,27 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, f
         if (hist0 && batch * B::TILES >= unit_end) { flush(cur_unit); ++cur_unit; unit_end += unit_tiles; }
         store_batch<G, ES, true>(v, B::TILES, lds);
         __syncthreads();
-        if (have_prev) H[j_prev] = h_prev;
+        if (have_prev && part == 0) H[j_prev] = h_prev;
         if (batch + 1 < last) load_full(batch + 1);
-        h_prev = entropy_of_row<G, BF16>(row, eps_l1, eps_log);
-        if (hist0) {
+        h_prev = entropy_of_row<G, BF16, LPT>(row, eps_l1, eps_log);
+        if (hist0) {                             // (a tile counts in its first lane)
             uint32_t *at = &lh[bin_of(h_prev)];
             const uint32_t mine = unit_end - batch * B::TILES;           // tiles of the batch that belong to cur_unit
             if (mine >= (uint32_t)B::TILES) {
-                atomicAdd(at, 1u);
+                if (part == 0) atomicAdd(at, 1u);
             } else {
-                if ((uint32_t)tid < mine) atomicAdd(at, 1u);
+                if (part == 0 && tile < mine) atomicAdd(at, 1u);
                 flush(cur_unit);
                 ++cur_unit;
                 unit_end += unit_tiles;
-                if ((uint32_t)tid >= mine) atomicAdd(at, 1u);
+                if (part == 0 && tile >= mine) atomicAdd(at, 1u);
             }
         }
-        j_prev = (uint64_t)batch * B::TILES + tid;
+        j_prev = (uint64_t)batch * B::TILES + tile;
         have_prev = true;
         __syncthreads();
     }
-    if (have_prev) H[j_prev] = h_prev;
+    if (have_prev && part == 0) H[j_prev] = h_prev;
     if (hist0 && first < last) flush(cur_unit);
 
     if (tail != 0 && blockIdx.x == gridDim.x - 1) {
@@ -294,10 +362,12 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, f
         load_batch<G, ES, false>(in, j0, tail, v);
         store_batch<G, ES, false>(v, tail, lds);
         __syncthreads();
-        if ((uint32_t)tid < tail) {
-            const float h = entropy_of_row<G, BF16>(row, eps_l1, eps_log);
-            H[j0 + tid] = h;
-            if (hist0) atomicAdd(&hist0[(j0 + tid) / unit_tiles * hist_stride + bin_of(h)], 1u);
+        if (tile < tail) {
+            const float h = entropy_of_row<G, BF16, LPT>(row, eps_l1, eps_log);
+            if (part == 0) {
+                H[j0 + tile] = h;
+                if (hist0) atomicAdd(&hist0[(j0 + tile) / unit_tiles * hist_stride + bin_of(h)], 1u);
+            }
         }
     }
 }
@@ -418,62 +488,6 @@ __global__ __launch_bounds__(256) void k_alloc_reduce(const float *__restrict__ 
     for (uint32_t q = 0; q < m; ++q) acc = acc + p[q];
     if constexpr (FINAL) out[ja] = 0.0f - inv_norm[ja] * acc;
     else out[ja] = 1.0f / (acc + eps_l1);
-}
-
-// How tiles spread over lanes in the quantizer and in the decoder: LPT lanes per tile, EPL consecutive elements per lane, so
-// that a lane holds at most 128 bytes of the tensor; TILES tiles per wavefront.
-template <int G, int ESIZE>
-struct Wave {
-    static constexpr int MAX_EPL = 128 / ESIZE;
-    static constexpr int EPL = G < MAX_EPL ? G : MAX_EPL;                     // elements per lane
-    static constexpr int LPT = G / EPL;                                       // lanes per tile
-    static constexpr int TILES = 64 / LPT;                                    // tiles per wavefront
-    static constexpr int LANE_BYTES = EPL * ESIZE;
-    static constexpr int CHUNKS = LANE_BYTES / 16;                            // 16-byte chunks per lane
-    static constexpr int LDS_BYTES = 64 * LANE_BYTES;
-    static_assert(TILES * LPT == 64 && CHUNKS >= 1 && CHUNKS <= 8, "whole tiles, whole chunks");
-    // Lane r's chunks lie in LDS at slots r * CHUNKS + (c ^ swizzle(r)): eight lanes that read the same chunk of their
-    // rows, like eight that read consecutive chunks of one row, meet eight different 16-byte columns of the banks.
-    static __device__ __forceinline__ uint32_t swizzle(uint32_t r)
-    {
-        return CHUNKS == 8 ? (r & 7u) : CHUNKS == 4 ? ((r >> 1) & 3u) : CHUNKS == 2 ? ((r >> 2) & 1u) : 0u;
-    }
-    // byte offset of element e of the tile that starts at lane `row0`
-    static __device__ __forceinline__ uint32_t element_at(uint32_t row0, uint32_t e)
-    {
-        const uint32_t r = row0 + e / EPL, byte = (e % EPL) * ESIZE;
-        return r * LANE_BYTES + (((byte >> 4) ^ swizzle(r)) << 4) + (byte & 15u);
-    }
-};
-
-// The value of lane (mine ^ X), X = 1 or 2.
-template <int X>
-__device__ __forceinline__ uint32_t lane_xor(uint32_t v)
-{
-    static_assert(X == 1 || X == 2, "inside a quad");
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, X == 1 ? 0xB1 : 0x4E, 0xF, 0xF, true);
-}
-template <int X>
-__device__ __forceinline__ float lane_xor(float v)
-{
-    return __uint_as_float(lane_xor<X>(__float_as_uint(v)));
-}
-
-// The butterfly stages that cross lanes: element i of lane part p meets element i of part p ^ (h / EPL).
-template <int EPL, int LPT>
-__device__ __forceinline__ void butterfly_across(float *x, uint32_t part)
-{
-    if constexpr (LPT >= 2) {
-        const float s1 = (part & 1u) ? -1.0f : 1.0f;
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) x[i] = __builtin_fmaf(x[i], s1, lane_xor<1>(x[i]));     // p + q, or p - q: one rounding
-    }
-    if constexpr (LPT >= 4) {
-        const float s2 = (part & 2u) ? -1.0f : 1.0f;
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) x[i] = __builtin_fmaf(x[i], s2, lane_xor<2>(x[i]));
-    }
-    static_assert(LPT <= 4, "two stages across lanes");
 }
 
 // ------------------------------------ K3: transform + quantize + pack
