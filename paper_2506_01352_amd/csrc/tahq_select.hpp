@@ -46,6 +46,16 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
     return v;
 }
 
+// The four bits of eight neighbouring lanes as one dword, lowest lane first; in each of the eight.
+__device__ __forceinline__ uint32_t nibbles_to_dword(uint32_t four, int lane)
+{
+    uint32_t d = four << (4 * (lane & 7));
+    d |= dpp_or_zero<0xB1, 0xF>(d);              // lane ^ 1
+    d |= dpp_or_zero<0x4E, 0xF>(d);              // lane ^ 2
+    d |= dpp_or_zero<0x141, 0xF>(d);             // lane ^ 7: the other four
+    return d;
+}
+
 // The 16 wavefronts' entries of `totals` that come before mine, added up.
 __device__ __forceinline__ uint32_t sum_of_waves_before(const uint32_t *totals, uint32_t wave, int lane)
 {
@@ -698,10 +708,7 @@ __global__ __launch_bounds__(kSmallUnitThreads) void k_select_small(const float 
     };
     // block b's four bits per lane -> its eight dwords of `out`: eight neighbouring lanes fill one
     auto put_bits = [&](uint64_t *out, uint32_t b, uint32_t four) {
-        uint32_t d = four << (4 * (lane & 7));
-        d |= dpp_or_zero<0xB1, 0xF>(d);          // lane ^ 1
-        d |= dpp_or_zero<0x4E, 0xF>(d);          // lane ^ 2
-        d |= dpp_or_zero<0x141, 0xF>(d);         // lane ^ 7: the other four
+        const uint32_t d = nibbles_to_dword(four, lane);
         if ((lane & 7) == 0) reinterpret_cast<uint32_t *>(out)[b * 8u + (lane >> 3)] = d;
     };
     if (crowd <= kSmallListCap) {
@@ -885,6 +892,17 @@ __device__ __forceinline__ void put_word(uint64_t *word, uint64_t mask, uint64_t
     else atomicOr(reinterpret_cast<unsigned long long *>(word), (unsigned long long)bits);
 }
 
+// The bit pattern of the smallest entropy in linear bin `b` >= 1: at most a few floats from b / scale.
+__device__ __forceinline__ int linear_bin_edge(uint32_t b, float scale)
+{
+    int e = (int)__float_as_uint((float)b / scale) - 4;
+    while (linear_bin(__uint_as_float((uint32_t)e), scale) < b) ++e;
+    return e;
+}
+
+// A workgroup takes 16384 places, its wavefront w the blocks w, w + 16, .. of 256, four consecutive places per lane.  The
+// threshold bin's edges turn into bit patterns once, so that an entropy costs two comparisons and its two bits; lanes collect
+// them in nibbles (a ballot per 64 entropies, and the bin of every entropy, took 2.5 us longer).
 __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *__restrict__ H, uint32_t n, uint32_t k,
                                                                    float bin_scale,
                                                                    const uint32_t *__restrict__ lin_hist,
@@ -893,65 +911,73 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *
                                                                    uint32_t *__restrict__ block_above,
                                                                    uint64_t *__restrict__ bitmap)
 {
-    constexpr int KPT = 16;                      // keys per thread: wavefront w owns 16 groups of 64 tiles
-    __shared__ uint32_t chosen[2];
-    __shared__ uint32_t wave_cand[kFusedThreads / 64], wave_above[kFusedThreads / 64];
+    constexpr uint32_t WAVES = kFusedThreads / 64, BLOCKS = kFusedKeysPerBlock / 256 / WAVES;
+    __shared__ uint32_t chosen[3];               // threshold bin, wanted inside it; the workgroup's place in the list
+    __shared__ uint32_t wave_cand[WAVES], wave_above[WAVES];
     const uint32_t u = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const float *uH = H + (uint64_t)u * n;
-    uint32_t *listed = fused + (uint64_t)u * 4;              // candidates listed so far
-    uint2 *ucand = cand + (uint64_t)u * kCandCap;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
     const UnitPlaces at(u, n);
-    uint64_t *ubitmap = bitmap + at.word0;
+    const float *uH = H + ((uint64_t)u * n - at.phase);      // by place
+    uint2 *ucand = cand + (uint64_t)u * kCandCap;
+    uint32_t *ubits = reinterpret_cast<uint32_t *>(bitmap + at.word0);
 
-    // all loads first (from a clamped index: none of them sits behind a branch)
-    const uint32_t group0 = blockIdx.x * (kFusedKeysPerBlock / 64) + (uint32_t)(KPT * wave);
-    float h[KPT];
+    // all loads first.  (Whole words of 64 places, which may reach into the neighbouring units or past the entropies to the end of
+    // their padded array; beyond them from a clamped index.)
+    const uint32_t place0 = blockIdx.x * kFusedKeysPerBlock + wave * 256u + 4u * lane, top = at.nwords * 64u - 4u;
+    int4 q[BLOCKS];
 #pragma unroll
-    for (int r = 0; r < KPT; ++r) {
-        const uint32_t i = (group0 + r) * 64u + lane - at.phase;
-        h[r] = uH[i < n ? i : n - 1];
+    for (uint32_t r = 0; r < BLOCKS; ++r) {
+        const uint32_t p = place0 + r * (WAVES * 256u);
+        q[r] = *reinterpret_cast<const int4 *>(uH + (p < top ? p : top));
     }
     block_pick_bin<kLinBins>(lin_hist + (uint64_t)u * kLinBins, k, wave_above, chosen);
-    const uint32_t bstar = chosen[0];
-    __syncthreads();                             // `chosen` and `wave_above` are used again below
+    const uint32_t bstar = (uint32_t)__builtin_amdgcn_readfirstlane((int)chosen[0]);
+    // the bit patterns of that bin, first and last, as signed integers (negative values and NaN with the sign bit set lowest)
+    const int first = bstar == 0 ? INT32_MIN + 1 : linear_bin_edge(bstar, bin_scale);
+    const int last = bstar == kLinBins - 1 ? INT32_MAX : linear_bin_edge(bstar + 1, bin_scale) - 1;
 
-    uint32_t bins[KPT];
-    uint64_t my_word = 0;
-    uint32_t n_cand = 0, n_above = 0;            // of my wavefront (the same in every lane)
+    uint32_t inside = 0, n_above = 0;            // my tiles of the bin, four bits per block, the last block lowest
 #pragma unroll
-    for (int r = 0; r < KPT; ++r) {
-        const bool ok = (group0 + r) * 64u + lane - at.phase < n;
-        bins[r] = ok ? linear_bin(h[r], bin_scale) : 0xffffffffu;
-        const uint64_t above = __ballot(ok && bins[r] > bstar);
-        if (lane == r) my_word = above;
-        n_above += (uint32_t)__popcll(above);
-        n_cand += (uint32_t)__popcll(__ballot(bins[r] == bstar));
-    }
-    if (lane < KPT && group0 + lane < at.nwords) put_word(&ubitmap[group0 + lane], at.mask(group0 + lane), my_word);
-    // one place in the list for the whole workgroup (a unit's workgroups all add to one counter: few, large additions)
-    if (lane == 0) { wave_cand[wave] = n_cand; wave_above[wave] = n_above; }
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t total = 0, above = 0;
-        for (int w = 0; w < (int)(kFusedThreads / 64); ++w) { total += wave_cand[w]; above += wave_above[w]; }
-        chosen[1] = total ? atomicAdd(listed, total) : 0u;
-        block_above[(uint64_t)u * gridDim.x + blockIdx.x] = above;
-    }
-    __syncthreads();
-    if (n_cand != 0) {
-        uint32_t base = chosen[1];
-        for (int w = 0; w < wave; ++w) base += wave_cand[w];
-        base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
-#pragma unroll
-        for (int r = 0; r < KPT; ++r) {
-            const uint64_t m = __ballot(bins[r] == bstar);
-            if (bins[r] == bstar) {
-                const uint32_t pos = base + bits_below_me(m);
-                if (pos < kCandCap) ucand[pos] = make_uint2(order_key(h[r]), (group0 + r) * 64u + lane);
-            }
-            base += (uint32_t)__popcll(m);
+    for (uint32_t r = 0; r < BLOCKS; ++r) {
+        const uint32_t base = blockIdx.x * kFusedKeysPerBlock + (r * WAVES + wave) * 256u, p = base + 4u * lane;
+        if (base < at.phase || base + 256u > at.end) {
+            // places outside the unit: the bit pattern of -0.0f, the lowest of all and no entropy's
+            q[r].x = p - at.phase < n ? q[r].x : INT32_MIN; q[r].y = p + 1u - at.phase < n ? q[r].y : INT32_MIN;
+            q[r].z = p + 2u - at.phase < n ? q[r].z : INT32_MIN; q[r].w = p + 3u - at.phase < n ? q[r].w : INT32_MIN;
         }
+        const uint32_t above = (q[r].x > last ? 1u : 0u) | (q[r].y > last ? 2u : 0u) | (q[r].z > last ? 4u : 0u) | (q[r].w > last ? 8u : 0u);
+        const uint32_t reach = (q[r].x >= first ? 1u : 0u) | (q[r].y >= first ? 2u : 0u) | (q[r].z >= first ? 4u : 0u) | (q[r].w >= first ? 8u : 0u);
+        inside = (inside << 4) | (reach & ~above);
+        n_above += (uint32_t)__popc(above);
+        // eight neighbouring lanes fill a dword of the bit map
+        const uint32_t d = nibbles_to_dword(above, lane);
+        if ((lane & 7) == 0 && p < at.nwords * 64u) {
+            if (p >= at.phase && p + 32u <= at.end) ubits[p >> 5] = d;
+            else atomicOr(&ubits[p >> 5], d);    // (a word that units share: cleared by an earlier kernel)
+        }
+    }
+    // one place in the list for the whole workgroup (a unit's workgroups all add to one counter: few, large additions)
+    const uint32_t count = (uint32_t)__popc(inside), incl = wave_incl_scan(count), incl_above = wave_incl_scan(n_above);
+    __syncthreads();                             // everybody has the threshold bin: `wave_above` is used again
+    if (lane == 63) { wave_cand[wave] = incl; wave_above[wave] = incl_above; }
+    __syncthreads();
+    const uint32_t before = sum_of_waves_before(wave_cand, wave, lane);
+    if (wave == WAVES - 1) {
+        const uint32_t above_before = sum_of_waves_before(wave_above, wave, lane);
+        if (lane == 63) {
+            chosen[2] = before + incl ? atomicAdd(&fused[(uint64_t)u * 4], before + incl) : 0u;
+            block_above[(uint64_t)u * gridDim.x + blockIdx.x] = above_before + incl_above;
+        }
+    }
+    __syncthreads();
+    uint32_t pos = chosen[2] + before + incl - count;
+    while (inside != 0) {
+        const uint32_t bit = (uint32_t)__ffs((int)inside) - 1u;
+        inside &= inside - 1u;
+        const uint32_t p = place0 + (BLOCKS - 1u - bit / 4) * (WAVES * 256u) + bit % 4;
+        if (pos < kCandCap) ucand[pos] = make_uint2(order_key(uH[p]), p);
+        ++pos;
     }
 }
 
@@ -1127,6 +1153,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
 #pragma unroll
         for (int r = 0; r < CPT; ++r) {
             sub[r] = 0xffffffffu;
+            if ((uint32_t)r * kFusedThreads >= listed) continue;         // (the same for all threads)
             if ((uint32_t)r * kFusedThreads + tid < listed) {
                 sub[r] = linear_sub_bin(key_to_float(c[r].x), bin_scale, bstar);
                 atomicAdd(&sub_hist[sub[r]], 1u);
@@ -1139,6 +1166,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
         uint32_t in_sub = 0;                     // bit r: my r-th candidate lies in the threshold's sub-bin
 #pragma unroll
         for (int r = 0; r < CPT; ++r) {
+            if ((uint32_t)r * kFusedThreads >= listed) continue;
             if (sub[r] != 0xffffffffu) {
                 if (sub[r] > sstar) take_it(c[r].y);
                 else if (sub[r] == sstar) {
