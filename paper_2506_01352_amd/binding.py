@@ -138,13 +138,11 @@ def tahq_version():
 
 
 def _dev_ptr(t):
-    """Device address of a torch tensor (None -> NULL)."""
-    if t is None:
-        return None
-    if isinstance(t, int):
-        return C.c_void_p(t)
+    """Device address of a torch tensor (None -> NULL); ctypes converts it."""
+    if t is None or isinstance(t, int):
+        return t
     assert t.is_cuda and t.is_contiguous(), "device tensor, contiguous"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _nbytes(t):
@@ -162,9 +160,10 @@ def _check_tensor(where, name, t, elements, dtype):
     esize = _ESIZE.get(dtype)
     if esize is None:
         return                                   # the library rejects the dtype itself
-    if t.element_size() not in (1, esize):
-        raise ValueError(f"{where}: {name} has {t.element_size()}-byte elements, the configuration says {esize}")
-    if _nbytes(t) < elements * esize:
+    size = t.element_size()
+    if size != esize and size != 1:
+        raise ValueError(f"{where}: {name} has {size}-byte elements, the configuration says {esize}")
+    if t.numel() * size < elements * esize:
         raise ValueError(f"{where}: {name} holds {_nbytes(t)} bytes, the configuration needs {elements * esize}")
 
 
@@ -172,13 +171,25 @@ def _elements(cfg):
     return cfg.batch * cfg.seq * cfg.hidden
 
 
+_current_raw_stream = None
+
+
 def _stream_handle(stream):
+    """Address of a stream; of torch's current stream on the current device if there is none.  The calls on small tensors are
+    bound by what they cost the host, and the stream object torch.cuda.current_stream() builds was a fifth of that."""
+    global _current_raw_stream
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
+        if _current_raw_stream is None:
+            import torch
+            handle = torch.cuda.current_stream().cuda_stream         # initialises torch.cuda if nothing has yet
+            raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+            if raw is None or device is None:
+                return handle
+            _current_raw_stream = lambda: raw(device())
+        return _current_raw_stream()
     if isinstance(stream, int):
-        return C.c_void_p(stream)
-    return C.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
 def tahq_encode(cfg, d_in, d_packed, d_workspace, stream=None, packed_capacity=None, workspace_capacity=None):
@@ -186,7 +197,7 @@ def tahq_encode(cfg, d_in, d_packed, d_workspace, stream=None, packed_capacity=N
     cap = _nbytes(d_packed) if packed_capacity is None else packed_capacity
     wcap = _nbytes(d_workspace) if workspace_capacity is None else workspace_capacity
     _check_tensor("tahq_encode", "d_in", d_in, _elements(cfg), cfg.dtype)
-    rc = _load().tahq_encode(C.byref(cfg), _dev_ptr(d_in), _dev_ptr(d_packed), cap, _dev_ptr(d_workspace), wcap,
+    rc = (_lib or _load()).tahq_encode(C.byref(cfg), _dev_ptr(d_in), _dev_ptr(d_packed), cap, _dev_ptr(d_workspace), wcap,
                              _stream_handle(stream))
     if rc != 0:
         raise TahqError(rc, "tahq_encode")
@@ -199,7 +210,7 @@ def tahq_encode_noalloc(cfg, d_in, d_packed, stream=None, packed_capacity=None):
     """tahq_encode on the library's built-in scratch: no workspace argument, nothing allocated."""
     cap = _nbytes(d_packed) if packed_capacity is None else packed_capacity
     _check_tensor("tahq_encode_noalloc", "d_in", d_in, _elements(cfg), cfg.dtype)
-    rc = _load().tahq_encode_noalloc(C.byref(cfg), _dev_ptr(d_in), _dev_ptr(d_packed), cap, _stream_handle(stream))
+    rc = (_lib or _load()).tahq_encode_noalloc(C.byref(cfg), _dev_ptr(d_in), _dev_ptr(d_packed), cap, _stream_handle(stream))
     if rc != 0:
         raise TahqError(rc, "tahq_encode_noalloc")
 
@@ -210,7 +221,7 @@ SELECT_MULTI_LAUNCH = 16      # option bit for tahq_encode_phases: see include/t
 
 def tahq_encode_phases(cfg, d_in, d_packed, d_workspace, phases, stream=None):
     _check_tensor("tahq_encode_phases", "d_in", d_in, _elements(cfg), cfg.dtype)
-    rc = _load().tahq_encode_phases(C.byref(cfg), _dev_ptr(d_in), _dev_ptr(d_packed), _nbytes(d_packed),
+    rc = (_lib or _load()).tahq_encode_phases(C.byref(cfg), _dev_ptr(d_in), _dev_ptr(d_packed), _nbytes(d_packed),
                                     _dev_ptr(d_workspace), _nbytes(d_workspace), phases, _stream_handle(stream))
     if rc != 0:
         raise TahqError(rc, "tahq_encode_phases")
@@ -219,7 +230,7 @@ def tahq_encode_phases(cfg, d_in, d_packed, d_workspace, phases, stream=None):
 def tahq_decode(cfg, d_packed, d_out, out_dtype, stream=None, packed_bytes=None):
     nbytes = _nbytes(d_packed) if packed_bytes is None else packed_bytes
     _check_tensor("tahq_decode", "d_out", d_out, _elements(cfg), out_dtype)
-    rc = _load().tahq_decode(C.byref(cfg), _dev_ptr(d_packed), nbytes, _dev_ptr(d_out), out_dtype, None, 0,
+    rc = (_lib or _load()).tahq_decode(C.byref(cfg), _dev_ptr(d_packed), nbytes, _dev_ptr(d_out), out_dtype, None, 0,
                              _stream_handle(stream))
     if rc != 0:
         raise TahqError(rc, "tahq_decode")
@@ -236,7 +247,7 @@ def tahq_samples_workspace_size(cfg, count):
 def tahq_encode_samples(cfg, first, count, d_in, d_packed, d_workspace, stream=None):
     """Samples [first, first + count) of the whole tensor d_in -> a self-contained stream in d_packed."""
     _check_tensor("tahq_encode_samples", "d_in", d_in, _elements(cfg), cfg.dtype)
-    rc = _load().tahq_encode_samples(C.byref(cfg), first, count, _dev_ptr(d_in), _dev_ptr(d_packed), _nbytes(d_packed),
+    rc = (_lib or _load()).tahq_encode_samples(C.byref(cfg), first, count, _dev_ptr(d_in), _dev_ptr(d_packed), _nbytes(d_packed),
                                      _dev_ptr(d_workspace), _nbytes(d_workspace), _stream_handle(stream))
     if rc != 0:
         raise TahqError(rc, "tahq_encode_samples")
@@ -245,7 +256,7 @@ def tahq_encode_samples(cfg, first, count, d_in, d_packed, d_workspace, stream=N
 def tahq_decode_samples(cfg, first, count, d_packed, d_out, out_dtype, stream=None):
     """A stream of tahq_encode_samples -> samples [first, first + count) of the whole tensor d_out."""
     _check_tensor("tahq_decode_samples", "d_out", d_out, _elements(cfg), out_dtype)
-    rc = _load().tahq_decode_samples(C.byref(cfg), first, count, _dev_ptr(d_packed), _nbytes(d_packed), _dev_ptr(d_out),
+    rc = (_lib or _load()).tahq_decode_samples(C.byref(cfg), first, count, _dev_ptr(d_packed), _nbytes(d_packed), _dev_ptr(d_out),
                                      out_dtype, _stream_handle(stream))
     if rc != 0:
         raise TahqError(rc, "tahq_decode_samples")
@@ -254,7 +265,7 @@ def tahq_decode_samples(cfg, first, count, d_packed, d_out, out_dtype, stream=No
 def tahq_tile_entropy(cfg, d_in, d_entropy, stream=None):
     _check_tensor("tahq_tile_entropy", "d_in", d_in, _elements(cfg), cfg.dtype)
     _check_tensor("tahq_tile_entropy", "d_entropy", d_entropy, _elements(cfg) // max(cfg.tile, 1), F32)
-    rc = _load().tahq_tile_entropy(C.byref(cfg), _dev_ptr(d_in), _dev_ptr(d_entropy), _stream_handle(stream))
+    rc = (_lib or _load()).tahq_tile_entropy(C.byref(cfg), _dev_ptr(d_in), _dev_ptr(d_entropy), _stream_handle(stream))
     if rc != 0:
         raise TahqError(rc, "tahq_tile_entropy")
 
@@ -263,7 +274,7 @@ def tahq_alloc_tile_entropy(cfg, d_in, d_entropy, d_workspace, stream=None):
     _check_tensor("tahq_alloc_tile_entropy", "d_in", d_in, _elements(cfg), cfg.dtype)
     _check_tensor("tahq_alloc_tile_entropy", "d_entropy", d_entropy,
                   _elements(cfg) // max(cfg.alloc_tile or cfg.tile, 1), F32)
-    rc = _load().tahq_alloc_tile_entropy(C.byref(cfg), _dev_ptr(d_in), _dev_ptr(d_entropy), _dev_ptr(d_workspace),
+    rc = (_lib or _load()).tahq_alloc_tile_entropy(C.byref(cfg), _dev_ptr(d_in), _dev_ptr(d_entropy), _dev_ptr(d_workspace),
                                          _nbytes(d_workspace), _stream_handle(stream))
     if rc != 0:
         raise TahqError(rc, "tahq_alloc_tile_entropy")
@@ -299,7 +310,7 @@ def tahq_naive_packed_size(cfg):
 def tahq_naive_encode(cfg, d_in, d_packed, stream=None, packed_capacity=None):
     cap = _nbytes(d_packed) if packed_capacity is None else packed_capacity
     _check_tensor("tahq_naive_encode", "d_in", d_in, _elements(cfg), cfg.dtype)
-    rc = _load().tahq_naive_encode(C.byref(cfg), _dev_ptr(d_in), _dev_ptr(d_packed), cap, _stream_handle(stream))
+    rc = (_lib or _load()).tahq_naive_encode(C.byref(cfg), _dev_ptr(d_in), _dev_ptr(d_packed), cap, _stream_handle(stream))
     if rc != 0:
         raise TahqError(rc, "tahq_naive_encode")
 
@@ -307,7 +318,7 @@ def tahq_naive_encode(cfg, d_in, d_packed, stream=None, packed_capacity=None):
 def tahq_naive_decode(cfg, d_packed, d_out, out_dtype, stream=None, packed_bytes=None):
     nbytes = _nbytes(d_packed) if packed_bytes is None else packed_bytes
     _check_tensor("tahq_naive_decode", "d_out", d_out, _elements(cfg), out_dtype)
-    rc = _load().tahq_naive_decode(C.byref(cfg), _dev_ptr(d_packed), nbytes, _dev_ptr(d_out), out_dtype,
+    rc = (_lib or _load()).tahq_naive_decode(C.byref(cfg), _dev_ptr(d_packed), nbytes, _dev_ptr(d_out), out_dtype,
                                    _stream_handle(stream))
     if rc != 0:
         raise TahqError(rc, "tahq_naive_decode")
