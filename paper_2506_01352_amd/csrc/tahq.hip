@@ -106,25 +106,41 @@ inline uint32_t resident_blocks(const void *kernel, int threads, ResidentCache &
     return res;
 }
 
+// Fewer wavefronts than the chip has vector units (256 compute units of four), at the usual number of lanes per tile: the launch
+// takes as long as one lane does, and tiles are spread over more lanes, as long as those make no more wavefronts per vector
+// unit than `deep`: 4, all that run at once, or 2 in the quantizer, which has more to do once per lane.  Above that the usual
+// lanes have less to issue.  bf16, G = 64, usual -> few: 25600 tiles: entropies 4.2 -> 3.1 us, quantizer 5.6 -> 4.4, decoder
+// 4.5 -> 3.6; 51200: 4.3 -> 3.9, 5.7 -> 5.8, 4.7 -> 4.2; 64512: 4.4 -> 4.0, 5.8 -> 6.0, 4.8 -> 4.4.
+template <class N>
+inline bool few_tiles(uint64_t T, uint32_t deep) { return T * N::usual < 65536u && T * N::few < deep * 65536u; }
+
 template <int G, bool BF16>
 struct LaunchEntropy {
-    // hist != nullptr: also build the selection's first histogram, `bins` bins per ranking unit (of at least one batch): the keys' first radix digit if bin_scale == 0, the entropies' linear bins otherwise
-    static void run(const void *d_in, float *d_H, uint32_t T, float eps_l1, float eps_log, uint32_t *hist,
-                    uint32_t bins, float bin_scale, uint64_t n_per_unit, Prologue pro, Enqueue *qp)
+    template <int LPT>
+    static void go(const void *d_in, float *d_H, uint32_t T, float eps_l1, float eps_log, uint32_t *hist,
+                   uint32_t bins, float bin_scale, uint64_t n_per_unit, const Prologue &pro, Enqueue *qp)
     {
         Enqueue &q = *qp;
-        using B = Batch<G, BF16 ? 2 : 4>;
+        using B = Batch<G, BF16 ? 2 : 4, LPT>;
         const uint32_t nb = (T + B::TILES - 1) / B::TILES;
-        constexpr int THREADS = B::TILES * Wave<G, BF16 ? 2 : 4>::LPT;
+        constexpr int THREADS = B::TILES * LPT;
         static ResidentCache cache;
-        const uint32_t res = resident_blocks(reinterpret_cast<const void *>(k_entropy<G, BF16>), THREADS, cache);
+        const uint32_t res = resident_blocks(reinterpret_cast<const void *>(k_entropy<G, BF16, LPT>), THREADS, cache);
         // Every workgroup adds its histogram to the unit's, and what that costs are the additions that meet on one bin: four
         // batches per workgroup where that still leaves a workgroup per compute unit (three units of 77700 tiles of 16
         // channels: 14.1 -> 8.4 us)
         const uint32_t few = nb / 4 > 256u ? nb / 4 : 256u;
         const uint32_t most = hist && few < res ? few : res;
-        q(k_entropy<G, BF16>, dim3(nb < most ? nb : most), dim3(THREADS), d_in, d_H, T,
-                           eps_l1, eps_log, hist, (uint32_t)n_per_unit, bins, bin_scale, pro);
+        q(k_entropy<G, BF16, LPT>, dim3(nb < most ? nb : most), dim3(THREADS), d_in, d_H, T, eps_l1, eps_log, hist,
+          (uint32_t)n_per_unit, bins, bin_scale, pro);
+    }
+    // hist != nullptr: also build the selection's first histogram, `bins` bins per ranking unit (of at least one batch): the keys' first radix digit if bin_scale == 0, the entropies' linear bins otherwise
+    static void run(const void *d_in, float *d_H, uint32_t T, float eps_l1, float eps_log, uint32_t *hist,
+                    uint32_t bins, float bin_scale, uint64_t n_per_unit, Prologue pro, Enqueue *qp)
+    {
+        using N = Lanes<G, BF16 ? 2 : 4>;
+        if (few_tiles<N>(T, 4)) go<N::few>(d_in, d_H, T, eps_l1, eps_log, hist, bins, bin_scale, n_per_unit, pro, qp);
+        else go<N::usual>(d_in, d_H, T, eps_l1, eps_log, hist, bins, bin_scale, n_per_unit, pro, qp);
     }
     static bool can_fuse_histogram(uint64_t n_per_unit) { return n_per_unit % Batch<G, BF16 ? 2 : 4>::TILES == 0; }
 };
@@ -137,16 +153,23 @@ struct CanFuse {
 // `low`: the narrower of the two code widths, 1..7 (3: INT3/INT4).
 template <int G, bool BF16>
 struct LaunchQuantPack {
+    template <int LOW, int LPT>
+    static void with(const void *d_in, uint8_t *packed, Layout lay, uint32_t T, float tau, float eps_ratio, bool ranked,
+                   bool all_wide, const Prologue &pro, Enqueue *qp)
+    {
+        Enqueue &q = *qp;
+        using B = Batch<G, BF16 ? 2 : 4, LPT>;
+        const dim3 grid((T + B::TILES - 1) / B::TILES), block(B::TILES * LPT);
+        if (ranked) q(k_quant_pack<G, BF16, LOW, true, LPT>, grid, block, d_in, packed, lay, T, tau, eps_ratio, false, pro);
+        else q(k_quant_pack<G, BF16, LOW, false, LPT>, grid, block, d_in, packed, lay, T, tau, eps_ratio, all_wide, pro);
+    }
     template <int LOW>
     static void go(const void *d_in, uint8_t *packed, Layout lay, uint32_t T, float tau, float eps_ratio, bool ranked,
                    bool all_wide, const Prologue &pro, Enqueue *qp)
     {
-        Enqueue &q = *qp;
-        using B = Batch<G, BF16 ? 2 : 4>;
-        const uint32_t nb = (T + B::TILES - 1) / B::TILES;
-        const dim3 block(B::TILES * Wave<G, BF16 ? 2 : 4>::LPT);
-        if (ranked) q(k_quant_pack<G, BF16, LOW, true>, dim3(nb), block, d_in, packed, lay, T, tau, eps_ratio, false, pro);
-        else q(k_quant_pack<G, BF16, LOW, false>, dim3(nb), block, d_in, packed, lay, T, tau, eps_ratio, all_wide, pro);
+        using N = Lanes<G, BF16 ? 2 : 4>;
+        if (few_tiles<N>(T, 2)) with<LOW, N::few>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp);
+        else with<LOW, N::usual>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp);
     }
     static void run(uint32_t low, const void *d_in, uint8_t *packed, Layout lay, uint32_t T, float tau, float eps_ratio,
                     bool ranked, bool all_wide, Prologue pro, Enqueue *qp)
@@ -168,10 +191,17 @@ struct LaunchDecode {
     template <int LOW>
     static void go(const uint8_t *packed, void *d_out, Layout lay, uint32_t T, uint32_t total_wide, Enqueue *qp)
     {
+        using N = Lanes<G, BF16 ? 2 : 4>;
+        if (few_tiles<N>(T, 4)) with<LOW, N::few>(packed, d_out, lay, T, total_wide, qp);
+        else with<LOW, N::usual>(packed, d_out, lay, T, total_wide, qp);
+    }
+    template <int LOW, int LPT>
+    static void with(const uint8_t *packed, void *d_out, Layout lay, uint32_t T, uint32_t total_wide, Enqueue *qp)
+    {
         Enqueue &q = *qp;
-        using W = Wave<G, BF16 ? 2 : 4>;
+        using W = Wave<G, BF16 ? 2 : 4, LPT>;
         const uint32_t groups = (T + W::TILES - 1) / W::TILES;
-        q(k_decode<G, BF16, LOW>, dim3((groups + 3) / 4), dim3(256), packed, d_out, lay, T, total_wide);
+        q(k_decode<G, BF16, LOW, LPT>, dim3((groups + 3) / 4), dim3(256), packed, d_out, lay, T, total_wide);
     }
     static void run(uint32_t low, const uint8_t *packed, void *d_out, Layout lay, uint32_t T, uint32_t total_wide,
                     Enqueue *qp)

@@ -37,11 +37,11 @@ void k_naive_encode(const void *__restrict__ in, uint8_t *__restrict__ packed, N
 
     uint4 v[B::CHUNKS];
     if (nvalid == (uint32_t)kNaiveChunks) {
-        load_batch<kNaiveChunk, ES, true, true>(in, j0, nvalid, v);
-        store_batch<kNaiveChunk, ES, true>(v, nvalid, rows);
+        load_batch<B, true, true>(in, j0, nvalid, v);
+        store_batch<B, true>(v, nvalid, rows);
     } else {
-        load_batch<kNaiveChunk, ES, false>(in, j0, nvalid, v);
-        store_batch<kNaiveChunk, ES, false>(v, nvalid, rows);
+        load_batch<B, false>(in, j0, nvalid, v);
+        store_batch<B, false>(v, nvalid, rows);
     }
     __syncthreads();
     if ((uint32_t)tid < nvalid) {

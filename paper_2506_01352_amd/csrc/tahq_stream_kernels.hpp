@@ -11,11 +11,21 @@
 
 namespace tahq {
 
-// Geometry of one workgroup's batch of tiles for an element type of ESIZE bytes.
+// Lanes per tile.  `usual`: as many as keep a lane at 128 bytes of the tensor or less.  `few`: for tensors of so few tiles that the
+// usual lanes do not make a wavefront for every vector unit of the chip; what counts then is how long one lane takes, so a
+// tile gets up to four lanes of at least 8 elements.
 template <int G, int ESIZE>
+struct Lanes {
+    static constexpr int usual = G * ESIZE > 128 ? G * ESIZE / 128 : 1;
+    static constexpr int few = G >= 32 ? 4 : G / 8;
+    static_assert(usual <= few && few <= 4, "quads");
+};
+
+// Geometry of one workgroup's batch of tiles for an element type of ESIZE bytes: 256 threads, LPT lanes per tile.
+template <int G, int ESIZE, int LPT = Lanes<G, ESIZE>::usual>
 struct Batch {
     static constexpr int BYTES = G * ESIZE;                                   // one tile
-    static constexpr int TILES = (32768 / BYTES) < 256 ? (32768 / BYTES) : 256;   // tiles = threads per workgroup
+    static constexpr int TILES = 256 / LPT;                                   // tiles per workgroup
     static constexpr int STRIDE = BYTES + 16;                                 // padded LDS row
     static constexpr int CHUNKS = BYTES / 16;                                 // 16-byte chunks per tile
     static constexpr int LDS_BYTES = TILES * STRIDE;
@@ -39,11 +49,10 @@ __device__ __forceinline__ uint4 load16(const uint8_t *p)
     }
 }
 
-template <int G, int ESIZE, bool FULL, bool STREAM = false, int N>
+template <class B, bool FULL, bool STREAM = false, int N>
 __device__ __forceinline__ void load_batch(const void *__restrict__ in, uint64_t j0, uint32_t nvalid, uint4 (&v)[N],
                                            int tid = (int)threadIdx.x)
 {
-    using B = Batch<G, ESIZE>;
     constexpr int THREADS = B::TILES * B::CHUNKS / N;        // N chunks per thread
     const uint8_t *src = static_cast<const uint8_t *>(in) + j0 * B::BYTES;
 #pragma unroll
@@ -58,10 +67,9 @@ __device__ __forceinline__ void load_batch(const void *__restrict__ in, uint64_t
     }
 }
 
-template <int G, int ESIZE, bool FULL, int N>
+template <class B, bool FULL, int N>
 __device__ __forceinline__ void store_batch(const uint4 (&v)[N], uint32_t nvalid, uint8_t *lds, int tid = (int)threadIdx.x)
 {
-    using B = Batch<G, ESIZE>;
     constexpr int THREADS = B::TILES * B::CHUNKS / N;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
@@ -141,13 +149,11 @@ __device__ __forceinline__ void butterfly(float *x)
     }
 }
 
-// How tiles spread over lanes in the entropy kernel, the quantizer and the decoder: LPT lanes per tile, EPL consecutive elements per lane, so
-// that a lane holds at most 128 bytes of the tensor; TILES tiles per wavefront.
-template <int G, int ESIZE>
+// How tiles spread over lanes in the entropy kernel, the quantizer and the decoder: LPT lanes per tile, EPL consecutive
+// elements per lane, at most 128 bytes of the tensor; TILES tiles per wavefront.
+template <int G, int ESIZE, int LPT>
 struct Wave {
-    static constexpr int MAX_EPL = 128 / ESIZE;
-    static constexpr int EPL = G < MAX_EPL ? G : MAX_EPL;                     // elements per lane
-    static constexpr int LPT = G / EPL;                                       // lanes per tile
+    static constexpr int EPL = G / LPT;                                       // elements per lane
     static constexpr int TILES = 64 / LPT;                                    // tiles per wavefront
     static constexpr int LANE_BYTES = EPL * ESIZE;
     static constexpr int CHUNKS = LANE_BYTES / 16;                            // 16-byte chunks per lane
@@ -212,7 +218,7 @@ struct Prologue {
 };
 
 // Thread `gid` of `threads` (at least 64).  The small launches of a call cost more than what they do, so the prologue rides
-// along with the call's first kernel: in front of the entropies (encode of 1024 x 1600 channels: 18.8 -> 17.5 us), or of the
+// along with the call's first kernel, at its end, where nothing waits for it: in front of the entropies (encode of 1024 x 1600 channels: 18.8 -> 17.5 us), or of the
 // quantizer where all tiles have one width (fp32 [1,128,512], encode and decode: 19.7 -> 16.8).
 __device__ __forceinline__ void write_prologue(const Prologue &p, uint32_t gid, uint32_t threads)
 {
@@ -283,22 +289,21 @@ static_assert((1u << kDigit0Bits) == kDigit0Bins, "digit 0 width");
 // linear bins (bin_scale > 0), `hist_stride` bins per unit, accumulated in LDS and flushed with global atomics
 // when the workgroup moves to another unit, in the middle of a batch if need be, and at its end.  A batch may touch two
 // units, not more: `unit_tiles` is at least TILES (the caller checks; otherwise it passes no histogram).
-template <int G, bool BF16>
-__global__ __launch_bounds__((Batch<G, BF16 ? 2 : 4>::TILES * Wave<G, BF16 ? 2 : 4>::LPT))
+template <int G, bool BF16, int LPT>
+__global__ __launch_bounds__(256)
 void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, float eps_l1, float eps_log,
                uint32_t *__restrict__ hist0, uint32_t unit_tiles, uint32_t hist_stride, float bin_scale, Prologue pro)
 {
     constexpr int ES = BF16 ? 2 : 4;
-    using B = Batch<G, ES>;
-    constexpr int LPT = Wave<G, ES>::LPT, THREADS = B::TILES * LPT;
-    write_prologue(pro, blockIdx.x * THREADS + threadIdx.x, gridDim.x * THREADS);
+    using B = Batch<G, ES, LPT>;
+    constexpr int THREADS = B::TILES * LPT;
     __shared__ __attribute__((aligned(16))) uint8_t lds[B::LDS_BYTES];
     static_assert(kLinBins >= kDigit0Bins, "one LDS histogram serves both kinds of bins");
     __shared__ uint32_t lh[kLinBins];
     const int tid = threadIdx.x;
     const uint32_t nfull = T / B::TILES, tail = T % B::TILES;
     const uint32_t tile = (uint32_t)tid / LPT, part = (uint32_t)tid % LPT;
-    const uint8_t *row = lds + tile * B::STRIDE + part * Wave<G, ES>::LANE_BYTES;
+    const uint8_t *row = lds + tile * B::STRIDE + part * (B::BYTES / LPT);
     const uint32_t per = (nfull + gridDim.x - 1) / gridDim.x;
     const uint32_t first = blockIdx.x * per;
     const uint32_t last = first + per < nfull ? first + per : nfull;      // my batches: [first, last)
@@ -319,7 +324,7 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, f
     // non-temporal loads: the tensor is much larger than any cache, and keeping part of it for the second
     // pass measured slower than streaming all of it
     auto load_full = [&](uint32_t batch) {
-        load_batch<G, ES, true, true>(in, (uint64_t)batch * B::TILES, B::TILES, v);
+        load_batch<B, true, true>(in, (uint64_t)batch * B::TILES, B::TILES, v);
     };
     if (first < last) load_full(first);
     float h_prev = 0.0f;
@@ -332,7 +337,7 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, f
     };
     for (uint32_t batch = first; batch < last; ++batch) {
         if (hist0 && batch * B::TILES >= unit_end) { flush(cur_unit); ++cur_unit; unit_end += unit_tiles; }
-        store_batch<G, ES, true>(v, B::TILES, lds);
+        store_batch<B, true>(v, B::TILES, lds);
         __syncthreads();
         if (have_prev && part == 0) H[j_prev] = h_prev;
         if (batch + 1 < last) load_full(batch + 1);
@@ -356,11 +361,12 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, f
     }
     if (have_prev && part == 0) H[j_prev] = h_prev;
     if (hist0 && first < last) flush(cur_unit);
+    write_prologue(pro, blockIdx.x * THREADS + threadIdx.x, gridDim.x * THREADS);
 
     if (tail != 0 && blockIdx.x == gridDim.x - 1) {
         const uint64_t j0 = (uint64_t)nfull * B::TILES;
-        load_batch<G, ES, false>(in, j0, tail, v);
-        store_batch<G, ES, false>(v, tail, lds);
+        load_batch<B, false>(in, j0, tail, v);
+        store_batch<B, false>(v, tail, lds);
         __syncthreads();
         if (tile < tail) {
             const float h = entropy_of_row<G, BF16, LPT>(row, eps_l1, eps_log);
@@ -397,11 +403,11 @@ void k_tile_partial(const void *__restrict__ in, const float *__restrict__ inv_n
     const uint32_t nvalid = left < (uint32_t)B::TILES ? left : (uint32_t)B::TILES;
     uint4 v[B::CHUNKS];
     if (nvalid == (uint32_t)B::TILES) {
-        load_batch<G, ES, true, true>(in, j0, nvalid, v);
-        store_batch<G, ES, true>(v, nvalid, lds);
+        load_batch<B, true, true>(in, j0, nvalid, v);
+        store_batch<B, true>(v, nvalid, lds);
     } else {
-        load_batch<G, ES, false>(in, j0, nvalid, v);
-        store_batch<G, ES, false>(v, nvalid, lds);
+        load_batch<B, false>(in, j0, nvalid, v);
+        store_batch<B, false>(v, nvalid, lds);
     }
     __syncthreads();
     if ((uint32_t)tid >= nvalid) return;
@@ -438,11 +444,11 @@ void k_alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_
     const uint32_t nvalid = left < (uint32_t)B::TILES ? left : (uint32_t)B::TILES;   // a multiple of m
     uint4 v[B::CHUNKS];
     if (nvalid == (uint32_t)B::TILES) {
-        load_batch<G, ES, true, true>(in, j0, nvalid, v);
-        store_batch<G, ES, true>(v, nvalid, lds);
+        load_batch<B, true, true>(in, j0, nvalid, v);
+        store_batch<B, true>(v, nvalid, lds);
     } else {
-        load_batch<G, ES, false>(in, j0, nvalid, v);
-        store_batch<G, ES, false>(v, nvalid, lds);
+        load_batch<B, false>(in, j0, nvalid, v);
+        store_batch<B, false>(v, nvalid, lds);
     }
     __syncthreads();
     const bool valid = (uint32_t)tid < nvalid;
@@ -879,15 +885,15 @@ __device__ __forceinline__ uint32_t quantize_values(const float *x, uint32_t b, 
 // every tile: with a lane per tile such workgroups had 64 or 128 threads of 200 registers, one or two wavefronts per
 // vector unit, where it takes four to issue at the full rate.  bf16 [8,1024,4096] G = 128 at 3 bits: 28.5 -> 24.2 us, fp32
 // [4,512,2048] G = 64: 8.3 -> 6.7.
-template <int G, bool BF16, int LOW, bool RANKED, bool FULL>
+template <int G, bool BF16, int LOW, bool RANKED, int LPT, bool FULL>
 __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, uint8_t *__restrict__ packed, const Layout &lay,
                                                  uint32_t T, float tau, float eps_ratio, uint32_t batch, uint32_t nvalid,
                                                  bool all_wide, uint8_t *lds, uint32_t *info, uint16_t *order, uint32_t *class_count)
 {
     constexpr int ES = BF16 ? 2 : 4;
-    using B = Batch<G, ES>;
+    using B = Batch<G, ES, LPT>;
     using U = typename Unit<G>::type;
-    constexpr int EPL = Wave<G, ES>::EPL, LPT = Wave<G, ES>::LPT, THREADS = B::TILES * LPT;
+    constexpr int EPL = G / LPT, THREADS = B::TILES * LPT;
     constexpr int WAVES = THREADS / 64;
     constexpr uint32_t WIDE = LOW + 1;           // the two code widths are LOW and WIDE bits
     static_assert(sizeof(U) * WIDE * B::TILES <= (size_t)B::LDS_BYTES, "payload buffer must fit in the rows");
@@ -901,21 +907,18 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
     const uint64_t j0 = (uint64_t)batch * B::TILES;
 
     uint4 v[B::CHUNKS / LPT];
-    load_batch<G, ES, FULL, true>(in, j0, nvalid, v, tid);           // second and last read of the tensor
+    load_batch<B, FULL, true>(in, j0, nvalid, v, tid);           // second and last read of the tensor
     BatchMeta<B::TILES> meta;
     if constexpr (RANKED) {
         load_meta<B::TILES>(packed, lay, j0, T, meta);
     } else {
-        // one width for all tiles: the batch's bit map words and rank-table entries are constants, and written here
+        // one width for all tiles: the batch's bit map words and rank-table entries are constants, and written at the end
         const uint64_t w0 = j0 >> 6, words = ((uint64_t)T + 63) >> 6;
 #pragma unroll
         for (int w = 0; w < BatchMeta<B::TILES>::WORDS; ++w) meta.word[w] = w0 + w < words ? constant_word(w0 + w, T, all_wide) : 0ull;
         meta.rank0 = all_wide ? (uint32_t)j0 : 0u;
-        if (tid < BatchMeta<B::TILES>::WORDS && w0 + tid < words)
-            constant_width_word(w0 + tid, T, all_wide, reinterpret_cast<uint64_t *>(packed + lay.bitmap),
-                                reinterpret_cast<uint32_t *>(packed + lay.ranks));
     }
-    store_batch<G, ES, FULL>(v, nvalid, lds, tid);
+    store_batch<B, FULL>(v, nvalid, lds, tid);
     uint32_t b, rel, total4;
     tile_pos<B::TILES, LOW, LPT>(meta, tid, &b, &rel, &total4);
     __syncthreads();
@@ -969,31 +972,39 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
         const uint32_t q = (uint32_t)i * THREADS + tid;
         if (q < span) gdst[q] = pay[q];
     }
+    if constexpr (!RANKED) {
+        const uint64_t w = (j0 >> 6) + tid;
+        if (tid < BatchMeta<B::TILES>::WORDS && w < ((uint64_t)T + 63) >> 6)
+            constant_width_word(w, T, all_wide, reinterpret_cast<uint64_t *>(packed + lay.bitmap),
+                                reinterpret_cast<uint32_t *>(packed + lay.ranks));
+    }
 }
 
 // RANKED: the widths are in the stream's bit map.  Otherwise all tiles have one, and the kernel is the call's only one and
 // writes bit map, rank table and prologue as well.  (A variant of its own: the same as a run-time choice delayed the loads of
 // the ranked case, 126 -> 136 us on bf16 [8,4096,8192].)
-template <int G, bool BF16, int LOW, bool RANKED>
-__global__ __launch_bounds__((Batch<G, BF16 ? 2 : 4>::TILES * Wave<G, BF16 ? 2 : 4>::LPT), 4)
+template <int G, bool BF16, int LOW, bool RANKED, int LPT>
+__global__ __launch_bounds__(256, 4)
 void k_quant_pack(const void *__restrict__ in, uint8_t *__restrict__ packed, Layout lay, uint32_t T, float tau,
                   float eps_ratio, bool all_wide, Prologue pro)
 {
     constexpr int ES = BF16 ? 2 : 4;
-    using B = Batch<G, ES>;
-    constexpr int THREADS = B::TILES * Wave<G, ES>::LPT, WAVES = THREADS / 64;
+    using B = Batch<G, ES, LPT>;
+    constexpr int THREADS = B::TILES * LPT, WAVES = THREADS / 64;
     __shared__ __attribute__((aligned(16))) uint8_t lds[B::LDS_BYTES];
     __shared__ uint32_t info[B::TILES];          // per tile: pivot byte | (b == WIDE) << 8 | rel << 9
     __shared__ uint16_t order[B::TILES];         // tiles in class order
     __shared__ uint32_t class_count[4 * WAVES];  // tiles per class and wavefront, class-major
-    if constexpr (!RANKED) write_prologue(pro, blockIdx.x * THREADS + threadIdx.x, gridDim.x * THREADS);
     const uint32_t nfull = T / B::TILES;        // a workgroup per batch; the last one may be ragged
     if (blockIdx.x < nfull)
-        quant_pack_batch<G, BF16, LOW, RANKED, true>(in, packed, lay, T, tau, eps_ratio, blockIdx.x, B::TILES, all_wide, lds, info,
+        quant_pack_batch<G, BF16, LOW, RANKED, LPT, true>(in, packed, lay, T, tau, eps_ratio, blockIdx.x, B::TILES, all_wide, lds, info,
                                              order, class_count);
     else
-        quant_pack_batch<G, BF16, LOW, RANKED, false>(in, packed, lay, T, tau, eps_ratio, nfull, T % B::TILES, all_wide, lds, info,
+        quant_pack_batch<G, BF16, LOW, RANKED, LPT, false>(in, packed, lay, T, tau, eps_ratio, nfull, T % B::TILES, all_wide, lds, info,
                                               order, class_count);
+    if constexpr (!RANKED) {
+        if (blockIdx.x == 0) write_prologue(pro, threadIdx.x, THREADS);      // (nothing but header and padding)
+    }
 }
 
 // ------------------------------------------------------------- K4: decode
@@ -1098,13 +1109,13 @@ __device__ __forceinline__ void load_codes(const uint8_t *__restrict__ p, bool w
 // Measured (back to back on one box; before -> now): bf16 [8,4096,8192] G = 64 3.25 bits 107.4 -> 92.4 us (667 MB, 7.2 TB/s),
 // [8,2048,8192] G = 128 79.8 -> 51.3, fp32 [4,2048,8192] G = 64 53.1 -> 45.7, G = 128 61.6 -> 45.9, bf16 [4,2048,4096] G = 8
 // 24.4 -> 18.2; half as many elements per lane: 98.8 us where 64 take 92.4.
-template <int G, bool OUT_BF16, int LOW>
+template <int G, bool OUT_BF16, int LOW, int LPT>
 __global__ __launch_bounds__(256, 4)
 void k_decode(const uint8_t *__restrict__ packed, void *__restrict__ out, Layout lay, uint32_t T, uint32_t total_wide)
 {
     constexpr int ES = OUT_BF16 ? 2 : 4;
-    using W = Wave<G, ES>;
-    constexpr int EPL = W::EPL, LPT = W::LPT;
+    using W = Wave<G, ES, LPT>;
+    constexpr int EPL = W::EPL;
     constexpr uint32_t WIDE = LOW + 1;           // the two code widths are LOW and WIDE bits
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * W::LDS_BYTES];
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63u;

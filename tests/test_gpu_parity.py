@@ -586,6 +586,26 @@ def test_single_launch_selection_with_a_crowded_threshold_bin(tahq, crowd):
         check_case(tahq, x, 2, n, G, G, tahq.F32, 3.0 + take / n)
 
 
+@pytest.mark.parametrize("G", (16, 32, 64, 128))
+@pytest.mark.parametrize("dtype_name", ("f32", "bf16"))
+@pytest.mark.parametrize("low", (1, 3, 7))
+def test_more_lanes_per_tile_up_to_the_tensor_sizes_that_take_fewer(tahq, G, dtype_name, low):
+    # tensors of few tiles spread every tile over up to four lanes: a handful of tiles, the last size that the quantizer and
+    # the last that the other kernels take so, and the first that they do not, none a multiple of a wavefront's tiles
+    dtype = tahq.F32 if dtype_name == "f32" else tahq.BF16
+    usual = max(1, G * (4 if dtype_name == "f32" else 2) // 128)
+    few = min(4, G // 8)
+    last = [min((65536 - 1) // usual, (deep * 65536 - 1) // few) for deep in (2, 4)]
+    rng = np.random.default_rng(G + low)
+    for T in sorted({5, 67, last[0] - 1, last[0] + 2, last[1] - 1, last[1] + 2}):
+        x = rng.standard_normal((1, T, G)).astype(np.float32)
+        x[:, ::3, 5] *= 30.0                             # transformed tiles
+        x[:, 1::7, :] *= 1e-3
+        x = x if dtype_name == "f32" else np.ascontiguousarray(workloads.f32_to_bf16_bits(x).reshape(1, T, G))
+        _say(f"[case] {T} tiles G={G} {dtype_name} low={low}")
+        check_case(tahq, x, 1, T, G, G, dtype, low + 0.4, low_bits=low, tau=2.0)
+
+
 @pytest.mark.parametrize("B,n", [(3, 32706), (2, 32769), (2, 49151), (3, 49153), (2, 65535), (5, 40001)])
 @pytest.mark.parametrize("ties", (False, True))
 def test_large_units_off_the_64_tile_boundaries(tahq, B, n, ties):
