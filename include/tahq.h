@@ -161,8 +161,8 @@ enum {
     TAHQ_PHASE_ALL = 15,
     /* Not a phase but an option, OR-ed into `phases`: rank every ranking unit with the general
      * multi-launch selection.  By default one workgroup ranks a unit of up to 32768 tiles in a single
-     * launch, and larger units that start on 64-tile boundaries are ranked in two launches from a
-     * histogram the entropy phase builds.  Same result; meant for tests and timing.  Pass it with
+     * launch, and larger units are ranked in two launches from a histogram the entropy phase builds
+     * (allocation tiles of several quantization tiles excepted).  Same result; meant for tests and timing.  Pass it with
      * every phase of a call sequence, since the prologue and the entropy phase prepare different
      * scratch for each way. */
     TAHQ_SELECT_MULTI_LAUNCH = 16
