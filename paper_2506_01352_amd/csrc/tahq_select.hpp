@@ -597,6 +597,7 @@ struct SmallSelectLds {
     uint32_t wave_total[kSmallUnitThreads / 64], wave_equal[kSmallUnitThreads / 64];
     uint32_t chosen[3];                          // threshold bin, wanted inside it, its tiles
     uint32_t listed;
+    uint32_t above_zero, zero;                   // the lowest bin's entropies above +0.0f and equal to it
 };
 
 // A ranking unit that one workgroup can hold, ranked in one launch, everything in LDS.
@@ -608,7 +609,7 @@ struct SmallSelectLds {
 // The entropies' bit patterns fall into BINS bins of 2^SHIFT neighbouring floats each, four octaves below ln A (`bin0` is
 // the number of the lowest bin); the bins at the ends take what lies beyond.  The bin that holds the k-th largest settles
 // every other tile with one comparison each; its own tiles (about a hundred) are placed directly among each other by (key
-// descending, tile ascending).  A crowded bin (ties) goes through a radix select instead.
+// descending, tile ascending).  A crowded bin goes through a radix select instead, unless its crowd are all-zero tiles.
 //
 // Bound by the instruction issue of its one compute unit, scalar instructions included (a ballot per 64 entropies and what
 // follows it cost three times as much as the carries that collect a lane's four bits here), and by a dozen dependent
@@ -645,7 +646,7 @@ __global__ __launch_bounds__(kSmallUnitThreads) void k_select_small(const float 
 #pragma unroll
     for (uint32_t i = 0; i < PER / 4; ++i)
         reinterpret_cast<uint4 *>(L.hist)[i * kSmallUnitThreads + tid] = make_uint4(0, 0, 0, 0);
-    if (tid == 0) L.listed = 0;
+    if (tid == 0) { L.listed = 0; L.above_zero = 0; L.zero = 0; }
     __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0): my wavefront's entropies are in LDS
     __syncthreads();
     for (uint32_t b = wave; b < nblocks; b += WAVES) {
@@ -767,7 +768,29 @@ __global__ __launch_bounds__(kSmallUnitThreads) void k_select_small(const float 
             }
         };
         uint32_t thr, take, equal;
-        block_radix_select(rem, [&](auto &&visit) {
+        // The usual crowd are the entropies of all-zero tiles, +0.0f, in the lowest bin: if the threshold is among them,
+        // counting tells.
+        bool at_zero = false;
+        if (bstar == 0) {
+            uint32_t above = 0, zero = 0;
+            for (uint32_t b = wave; b < nblocks; b += WAVES) {
+                const int4 q = *reinterpret_cast<const int4 *>(&L.key[b * 256u + 4u * lane]);
+                const int v[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    above += v[c] > 0 && v[c] <= last ? 1u : 0u;
+                    zero += v[c] == 0 ? 1u : 0u;
+                }
+            }
+            above = wave_incl_scan(above);
+            zero = wave_incl_scan(zero);
+            if (lane == 63) { atomicAdd(&L.above_zero, above); atomicAdd(&L.zero, zero); }
+            __syncthreads();
+            at_zero = L.above_zero < rem && rem <= L.above_zero + L.zero;
+            take = rem - L.above_zero;
+        }
+        if (at_zero) thr = order_key(0.0f);
+        else block_radix_select(rem, [&](auto &&visit) {
             each([&](uint32_t, float h) {
                 const int v = (int)__float_as_uint(h);
                 if (v >= first && v <= last) visit(order_key(h));
@@ -972,12 +995,20 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *
     }
     __syncthreads();
     uint32_t pos = chosen[2] + before + incl - count;
-    while (inside != 0) {
-        const uint32_t bit = (uint32_t)__ffs((int)inside) - 1u;
-        inside &= inside - 1u;
-        const uint32_t p = place0 + (BLOCKS - 1u - bit / 4) * (WAVES * 256u) + bit % 4;
-        if (pos < kCandCap) ucand[pos] = make_uint2(order_key(uH[p]), p);
-        ++pos;
+    if (__ballot(inside != 0) != 0) {
+        // (from registers: a lane may hold sixteen of them, where tiles are all zero)
+#pragma unroll
+        for (uint32_t r = 0; r < BLOCKS; ++r) {
+            const int v[4] = {q[r].x, q[r].y, q[r].z, q[r].w};
+#pragma unroll
+            for (uint32_t c = 0; c < 4; ++c) {
+                if ((inside >> (4 * (BLOCKS - 1 - r) + c)) & 1u) {
+                    if (pos < kCandCap)
+                        ucand[pos] = make_uint2(order_key(__uint_as_float((uint32_t)v[c])), place0 + r * (WAVES * 256u) + c);
+                    ++pos;
+                }
+            }
+        }
     }
 }
 
