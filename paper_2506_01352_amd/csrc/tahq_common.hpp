@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include "tahq.h"
+#include "tahq_bins.hpp"
 
 namespace tahq {
 
@@ -32,8 +33,6 @@ constexpr uint32_t kSegTiles = 1024;     // tiles one wavefront handles in the s
 constexpr uint32_t kHistBins = 2048;      // bins of radix digits 1 and 2 (11 bits each)
 constexpr uint32_t kDigit0Bins = 1024;    // bins of radix digit 0 (key bits 31..22)
 constexpr uint32_t kRadixKeysPerBlock = 8192;
-constexpr uint32_t kLinBins = 2048;       // bins of the entropy histogram of the single-launch selection of large units
-constexpr uint32_t kSubBins = 1024;       // sub-bins of the bin that holds the threshold (k_select_resolve)
 constexpr uint32_t kCandCap = 16384;      // tiles of the threshold bin that the selection keeps in a list, per ranking unit
 
 struct Workspace {
@@ -153,38 +152,6 @@ __device__ __forceinline__ float log_contract(float u)
     P = __builtin_fmaf(P, m, 0x1.c4859ep+2f);
     P = __builtin_fmaf(P, m, -0x1.5165a2p+1f);
     return __builtin_fmaf((float)e, kLn2, P);
-}
-
-// Order-preserving 32-bit key of an entropy (larger entropy -> larger key).
-__device__ __forceinline__ uint32_t order_key(float h)
-{
-    const uint32_t u = __float_as_uint(h);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
-// Linear bin of an entropy, 0 .. kLinBins - 1: non-decreasing in the entropy's order-preserving key (so a higher bin
-// means a higher rank), and the same instruction sequence wherever it is evaluated.  Negative values go to bin 0; a NaN
-// goes where its key goes: above +infinity with the sign bit clear, below -infinity with it set.
-__device__ __forceinline__ uint32_t linear_bin(float h, float scale)
-{
-    // the median of three takes a NaN for the smallest of the three (bin 0, where a NaN with the sign bit set belongs)
-    const uint32_t b = (uint32_t)__builtin_amdgcn_fmed3f(h * scale, 0.0f, (float)(kLinBins - 1));
-    return (int32_t)__float_as_uint(h) > 0x7f800000 ? kLinBins - 1 : b;
-}
-
-// Sub-bin of an entropy that lies in linear bin `b`, 0 .. kSubBins - 1: non-decreasing in the entropy's key.  h * scale
-// is the product linear_bin rounds down; its distance to b is exact in fp32, and so is the multiplication by a power of
-// two.
-__device__ __forceinline__ uint32_t linear_sub_bin(float h, float scale, uint32_t b)
-{
-    const uint32_t s = (uint32_t)__builtin_amdgcn_fmed3f((h * scale - (float)b) * (float)kSubBins, 0.0f, (float)(kSubBins - 1));
-    return (int32_t)__float_as_uint(h) > 0x7f800000 ? kSubBins - 1 : s;
-}
-
-// The entropy an order-preserving key was made from.
-__device__ __forceinline__ float key_to_float(uint32_t key)
-{
-    return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
 }
 
 // fp32(1/sqrt(G)), the normalisation of Eq. 4.

@@ -70,7 +70,7 @@ __device__ __forceinline__ uint32_t sum_of_waves_before(const uint32_t *totals, 
 
 // Which of BINS bins holds the `want`-th largest value (bins counted from the top) and how many values are wanted inside it, found
 // by the whole workgroup of 1024 threads: BINS / 1024 bins per thread and a scan.  chosen[0..1] is written before the last of
-// its two barriers; `totals`: 16 words of LDS.  (One wavefront with a sixteenth of the bins per lane, its loads as far apart,
+// its two barriers, and both are 0 where there are fewer than `want` values; `totals`: 16 words of LDS.  (One wavefront with a sixteenth of the bins per lane, its loads as far apart,
 // took 1.5 us longer.)
 template <int BINS>
 __device__ __forceinline__ void block_pick_bin(const uint32_t *hist, uint32_t want, uint32_t *totals, uint32_t *chosen)
@@ -88,6 +88,7 @@ __device__ __forceinline__ void block_pick_bin(const uint32_t *hist, uint32_t wa
     }
     const uint32_t incl = wave_incl_scan(hi + lo);
     if (lane == 63) totals[wave] = incl;
+    if (tid == 0) { chosen[0] = 0; chosen[1] = 0; }
     __syncthreads();
     const uint32_t above = sum_of_waves_before(totals, wave, lane) + incl - (hi + lo);
     const uint32_t top = (uint32_t)(BINS - 1 - PER * tid);
@@ -913,14 +914,6 @@ __device__ __forceinline__ void put_word(uint64_t *word, uint64_t mask, uint64_t
 {
     if (mask == ~0ull) *word = bits;
     else atomicOr(reinterpret_cast<unsigned long long *>(word), (unsigned long long)bits);
-}
-
-// The bit pattern of the smallest entropy in linear bin `b` >= 1: at most a few floats from b / scale.
-__device__ __forceinline__ int linear_bin_edge(uint32_t b, float scale)
-{
-    int e = (int)__float_as_uint((float)b / scale) - 4;
-    while (linear_bin(__uint_as_float((uint32_t)e), scale) < b) ++e;
-    return e;
 }
 
 // A workgroup takes 16384 places, its wavefront w the blocks w, w + 16, .. of 256, four consecutive places per lane.  The

@@ -376,6 +376,20 @@ def test_phase_by_phase_calls_write_the_same_stream(tahq):
         assert np.array_equal(whole.view.cpu().numpy(), o32.encode(ocfg, x))
 
 
+def test_selection_of_a_large_unit_without_its_histogram_ends(tahq):
+    # the selection phase by itself over cleared scratch: no bin of the histogram holds the threshold.  What it writes means
+    # nothing, but it ends, and inside its buffers
+    cfg = tahq.make_config(2, 1024, 1024, 16, tahq.F32, 3.5)
+    d_in = torch.zeros(2 * 1024 * 1024, device="cuda")
+    packed, ws = Guarded(tahq.tahq_packed_size(cfg)), Guarded(tahq.tahq_workspace_size(cfg))
+    ws.view.zero_()
+    _say("[case] selection phase over cleared scratch")
+    tahq.tahq_encode_phases(cfg, d_in, packed.view, ws.view, tahq.PHASE_SELECT)
+    torch.cuda.synchronize()
+    packed.check()
+    ws.check()
+
+
 def test_side_stream(tahq):
     w, x = workloads.generate(2, batch=1, seq=64)
     cfg = tahq.make_config(w.batch, w.seq, w.hidden, w.tile, w.dtype, w.budget_bits)
