@@ -71,8 +71,8 @@ typedef enum {
     TAHQ_ERR_NULL = 1,                 /* a required pointer is NULL                     */
     TAHQ_ERR_INVALID_ARG = 2,          /* zero dimension, hidden % tile != 0, alloc_tile not a multiple of tile dividing hidden,
                                           budget outside [3,4] or NaN, bad enum */
-    TAHQ_ERR_UNSUPPORTED = 3,          /* tile not in {8, 16, 32, 64, 128}, more than 2^31 tiles, or more than
-                                          65535 ranking units of more than 32768 tiles each */
+    TAHQ_ERR_UNSUPPORTED = 3,          /* tile not in {8, 16, 32, 64, 128}, 2^31 tiles or more, or more than
+                                          65535 ranking units with TAHQ_SELECT_MULTI_LAUNCH */
     TAHQ_ERR_BUFFER_TOO_SMALL = 4,     /* packed capacity / packed_bytes below tahq_packed_size */
     TAHQ_ERR_WORKSPACE_TOO_SMALL = 5,  /* workspace capacity below tahq_workspace_size   */
     TAHQ_ERR_MISALIGNED = 6,           /* a device pointer is not 16-byte aligned        */

@@ -43,6 +43,8 @@ void *g_scratch_ptr[kMaxDevices];
 
 inline bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
 
+constexpr uint32_t kMaxGridY = 65535;
+
 inline uint32_t blocks_for(uint64_t threads) { return (uint32_t)((threads + 255) / 256); }
 
 // Dispatch on the tile width G and on a dtype flag (bf16 or not) to a functor template.
@@ -428,8 +430,9 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
     const uint64_t places = s.nA + (!wide && s.n % 64 != 0 ? 63u : 0u);       // counted from a 64-tile boundary
     const bool small_units = select && places <= kSmallUnitMaxKeys && !multi_launch;
 
-    // the selection kernels of large ranking units put the unit into the grid's second dimension
-    if (select && !small_units && s.U > 65535u) return TAHQ_ERR_UNSUPPORTED;
+    // The multi-launch selection puts the unit into the grid's second dimension.  (The two-launch selection does so too, in
+    // slices: 65536 units and more of 32706 to 32767 tiles each are a tensor of fewer than 2^31.)
+    if (select && multi_launch && s.U > kMaxGridY) return TAHQ_ERR_UNSUPPORTED;
 
     // header and section padding
     Prologue pro;
@@ -498,16 +501,19 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
                 launch_entropy(s, cfg, d_in, H, fused ? hist0 : (uint32_t *)nullptr, kDigit0Bins, 0.0f, pro, &q);
         }
         if ((phases & TAHQ_PHASE_SELECT) && fused_select) {
-            const dim3 grid((uint32_t)((places + kFusedKeysPerBlock - 1) / kFusedKeysPerBlock), s.U);
             uint32_t *fused_state = reinterpret_cast<uint32_t *>(wsb + ws.fused);
             uint2 *cand = reinterpret_cast<uint2 *>(wsb + ws.cand);
             uint32_t *block_above = seg;             // fewer entries than the segments it was made for
-            q(k_select_classify, grid, dim3(kFusedThreads), (const float *)H, (uint32_t)s.n,
-                               (uint32_t)s.k, bin_scale, (const uint32_t *)lin_hist, fused_state, cand, block_above,
-                               bitmap);
-            q(k_select_resolve, grid, dim3(kFusedThreads), (const float *)H, (uint32_t)s.n,
-                               (uint32_t)s.k, bin_scale, (const uint32_t *)lin_hist, (const uint32_t *)fused_state,
-                               (const uint2 *)cand, (const uint32_t *)block_above, bitmap, ranks);
+            for (uint32_t u0 = 0; u0 < s.U; u0 += kMaxGridY) {
+                const dim3 grid((uint32_t)((places + kFusedKeysPerBlock - 1) / kFusedKeysPerBlock),
+                                s.U - u0 < kMaxGridY ? s.U - u0 : kMaxGridY);
+                q(k_select_classify, grid, dim3(kFusedThreads), (const float *)H, (uint32_t)s.n,
+                                   (uint32_t)s.k, u0, bin_scale, (const uint32_t *)lin_hist, fused_state, cand, block_above,
+                                   bitmap);
+                q(k_select_resolve, grid, dim3(kFusedThreads), (const float *)H, (uint32_t)s.n,
+                                   (uint32_t)s.k, u0, bin_scale, (const uint32_t *)lin_hist, (const uint32_t *)fused_state,
+                                   (const uint2 *)cand, (const uint32_t *)block_above, bitmap, ranks);
+            }
         } else
         if ((phases & TAHQ_PHASE_SELECT) && small_units) {
             const uint32_t n32 = (uint32_t)s.nA, k32 = (uint32_t)s.kA;

@@ -920,7 +920,7 @@ __device__ __forceinline__ void put_word(uint64_t *word, uint64_t mask, uint64_t
 // threshold bin's edges turn into bit patterns once, so that an entropy costs two comparisons and its two bits; lanes collect
 // them in nibbles (a ballot per 64 entropies, and the bin of every entropy, took 2.5 us longer).
 __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *__restrict__ H, uint32_t n, uint32_t k,
-                                                                   float bin_scale,
+                                                                   uint32_t unit0, float bin_scale,
                                                                    const uint32_t *__restrict__ lin_hist,
                                                                    uint32_t *__restrict__ fused,
                                                                    uint2 *__restrict__ cand,
@@ -930,7 +930,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *
     constexpr uint32_t WAVES = kFusedThreads / 64, BLOCKS = kFusedKeysPerBlock / 256 / WAVES;
     __shared__ uint32_t chosen[3];               // threshold bin, wanted inside it; the workgroup's place in the list
     __shared__ uint32_t wave_cand[WAVES], wave_above[WAVES];
-    const uint32_t u = blockIdx.y;
+    const uint32_t u = unit0 + blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
     const UnitPlaces at(u, n);
@@ -1114,7 +1114,7 @@ __device__ __noinline__ void resolve_unit_alone(const float *__restrict__ uH, ui
 }
 
 __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *__restrict__ H, uint32_t n, uint32_t k,
-                                                                  float bin_scale,
+                                                                  uint32_t unit0, float bin_scale,
                                                                   const uint32_t *__restrict__ lin_hist,
                                                                   const uint32_t *__restrict__ fused,
                                                                   const uint2 *__restrict__ cand,
@@ -1124,7 +1124,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
 {
     __shared__ ResolveLds L;
     constexpr uint32_t GROUPS = kFusedKeysPerBlock / 64;     // 64-tile groups of a block
-    const uint32_t u = blockIdx.y, blk = blockIdx.x;
+    const uint32_t u = unit0 + blockIdx.y, blk = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float *uH = H + (uint64_t)u * n;
     const uint2 *ucand = cand + (uint64_t)u * kCandCap;

@@ -241,3 +241,17 @@ def test_more_than_65535_ranking_units_on_the_multi_launch_selection_are_refused
     assert lib.tahq_encode_phases(C.byref(cfg), 0x10000, 0x20000, big, 0x30000, big, 15 | 16, None) == 3
     cfg = tahq.make_config(65535, 1, 256, 64, tahq.BF16, 3.5)
     assert tahq.tahq_packed_size(cfg) > 0
+
+
+def test_more_than_65535_ranking_units_off_the_64_tile_boundaries_are_taken():
+    # 65536 units of 32706 .. 32767 tiles are the most tiles that a unit can have in a tensor of that many
+    torch = pytest.importorskip("torch")
+    if torch.cuda.device_count() > 0:
+        pytest.skip("the addresses are made up: a call that passes the checks must find no device")
+    lib = binding._load()
+    big = 1 << 42
+    for seq in (32705, 32706, 32767):
+        cfg = tahq.make_config(65536, seq, 8, 8, tahq.BF16, 3.5)
+        assert tahq.tahq_packed_size(cfg) > 0
+        assert lib.tahq_encode(C.byref(cfg), 0x10000, 0x20000, big, 0x30000, big, None) == 7       # the launch fails
+        assert lib.tahq_encode_phases(C.byref(cfg), 0x10000, 0x20000, big, 0x30000, big, 15 | 16, None) == 3

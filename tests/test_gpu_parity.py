@@ -639,6 +639,40 @@ def test_large_units_off_the_64_tile_boundaries(tahq, B, n, ties):
     check_case(tahq, x16, B, n, G, 8, tahq.BF16, 2.6, low_bits=2)
 
 
+def test_65536_units_just_off_the_64_tile_boundaries(tahq):
+    # as many ranking units as a grid's second dimension does not take, of as few tiles as go through the two-launch selection,
+    # 34 GB of them: 1024 times the same 64 units, whose sections are 1024 times the same bytes
+    B, n, G, reps = 64, 32707, 8, 1024
+    cfg1, cfg = (tahq.make_config(b, n, G, G, tahq.BF16, 3.5) for b in (B, B * reps))
+    if torch.cuda.mem_get_info()[0] < 2 * B * reps * n * G + tahq.tahq_packed_size(cfg) + tahq.tahq_workspace_size(cfg) + (4 << 30):
+        pytest.skip("the card has no room for 65536 units")
+    _say("[case] 65536 units x 32707 tiles")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    base = torch.randn(B * n * G, device="cuda", generator=gen).to(torch.bfloat16)
+    base[::16] *= 20.0
+    small = tahq.Codec(cfg1)
+    small.encode(base)
+    x = base.view(1, -1).expand(reps, -1).contiguous()
+    packed = torch.empty(tahq.tahq_packed_size(cfg), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(tahq.tahq_workspace_size(cfg), dtype=torch.uint8, device="cuda")
+    tahq.tahq_encode(cfg, x, packed, ws)
+    torch.cuda.synchronize()
+    T, k = B * n, tahq.tahq_k_per_unit(cfg)
+    one, all_ = o64.section_offsets(T, G, B, k), o64.section_offsets(T * reps, G, B * reps, k)
+    for name, size in (("bitmap", T // 8), ("pivot", T), ("scale", 2 * T), ("zero", 2 * T), ("payload", 3 * T + B * k)):
+        want = small.packed[one[name]:one[name] + size]
+        for r in range(reps):
+            at = all_[name] + r * size
+            assert torch.equal(packed[at:at + size], want), f"{name} of units {r * B} .."
+    want = small.packed[one["ranks"]:one["ranks"] + T // 16].view(torch.int32)
+    got = packed[all_["ranks"]:all_["ranks"] + T // 16 * reps].view(torch.int32).view(reps, -1)
+    steps = torch.arange(reps, device="cuda", dtype=torch.int64).view(-1, 1) * (B * k)
+    assert torch.equal(got.long(), want.long().view(1, -1) + steps)
+    del x, packed, ws, got
+    torch.cuda.empty_cache()
+
+
 def test_many_ranking_units_with_few_tiles_each(tahq):
     # 300 samples of 6 tiles: units smaller than a wavefront, a batch spans many units
     rng = np.random.default_rng(5)
