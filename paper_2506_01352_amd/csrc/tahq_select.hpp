@@ -3,8 +3,9 @@
 // Entropies map to order-preserving 32-bit keys; three ways to find the k-th largest key K*, how many tiles equal to
 // K* are still wanted (`take`), and from them the bit map and the rank table:
 //
-//   * ranking units of at most 32768 tiles: k_select_small, one workgroup per unit in one launch (entropies in
-//     registers, one histogram in LDS, the threshold's bin ranked directly), because at that size several launches cost more than the work;
+//   * ranking units of at most 32768 tiles (32705 where units start off the 64-tile boundaries): k_select_small, one workgroup per
+//     unit in one launch (entropies and a histogram in LDS, the threshold's bin ranked directly), because at that size several
+//     launches cost more than the work;
 //   * larger units: the entropy kernel also counts the entropies over 2048 linear bins per unit; k_select_classify
 //     settles every tile outside the bin that holds K* and lists the tiles inside it, k_select_resolve ranks that list
 //     (further down in this file);
@@ -68,32 +69,45 @@ __device__ __forceinline__ uint32_t sum_of_waves_before(const uint32_t *totals, 
     return (uint32_t)__builtin_amdgcn_readlane((int)(v - own), (int)wave);
 }
 
-// Which of BINS bins holds the `want`-th largest value (bins counted from the top) and how many values are wanted inside it, found
-// by the whole workgroup of 1024 threads: BINS / 1024 bins per thread and a scan.  chosen[0..1] is written before the last of
-// its two barriers, and both are 0 where there are fewer than `want` values; `totals`: 16 words of LDS.  (One wavefront with a sixteenth of the bins per lane, its loads as far apart,
-// took 1.5 us longer.)
+// Which of BINS bins holds the `want`-th largest value (bins counted from the top), how many values are wanted inside it and how
+// many it holds, found by the whole workgroup of 1024 threads: BINS / 1024 bins per thread and a scan.  chosen[0..2] is written
+// before the last of its two barriers, and all three are 0 where there are fewer than `want` values; `totals`: 16 words of LDS.
+// (One wavefront with a sixteenth of the bins per lane, its loads as far apart, took 1.5 us longer.)
 template <int BINS>
 __device__ __forceinline__ void block_pick_bin(const uint32_t *hist, uint32_t want, uint32_t *totals, uint32_t *chosen)
 {
     constexpr int PER = BINS / 1024;
-    static_assert(PER == 1 || PER == 2, "one load per thread");
+    static_assert(PER == 1 || PER == 2 || PER % 4 == 0, "whole loads");
     const int tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
-    uint32_t hi = 0, lo = 0;                     // my bins: top and, if there are two, the one below it
-    if constexpr (PER == 2) {
-        const uint2 q = reinterpret_cast<const uint2 *>(hist)[BINS / 2 - 1 - tid];
-        lo = q.x; hi = q.y;
+    const uint32_t low = (uint32_t)(BINS - PER * (tid + 1));                   // my bins: low .. low + PER - 1
+    uint32_t c[PER], mine = 0;
+    if constexpr (PER == 1) {
+        c[0] = hist[low];
+    } else if constexpr (PER == 2) {
+        const uint2 q = *reinterpret_cast<const uint2 *>(hist + low);
+        c[0] = q.x; c[1] = q.y;
     } else {
-        hi = hist[BINS - 1 - tid];
+#pragma unroll
+        for (int i = 0; i < PER / 4; ++i) {
+            const uint4 q = reinterpret_cast<const uint4 *>(hist + low)[i];
+            c[4 * i] = q.x; c[4 * i + 1] = q.y; c[4 * i + 2] = q.z; c[4 * i + 3] = q.w;
+        }
     }
-    const uint32_t incl = wave_incl_scan(hi + lo);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) mine += c[i];
+    const uint32_t incl = wave_incl_scan(mine);
     if (lane == 63) totals[wave] = incl;
-    if (tid == 0) { chosen[0] = 0; chosen[1] = 0; }
+    if (tid == 0) { chosen[0] = 0; chosen[1] = 0; chosen[2] = 0; }
     __syncthreads();
-    const uint32_t above = sum_of_waves_before(totals, wave, lane) + incl - (hi + lo);
-    const uint32_t top = (uint32_t)(BINS - 1 - PER * tid);
-    if (above < want && want <= above + hi) { chosen[0] = top; chosen[1] = want - above; }
-    else if (PER == 2 && above + hi < want && want <= above + hi + lo) { chosen[0] = top - 1; chosen[1] = want - above - hi; }
+    uint32_t above = sum_of_waves_before(totals, wave, lane) + incl - mine;
+    if (above < want && want <= above + mine) {
+#pragma unroll
+        for (int i = PER; i-- > 0;) {
+            if (above < want && want <= above + c[i]) { chosen[0] = low + i; chosen[1] = want - above; chosen[2] = c[i]; }
+            above += c[i];
+        }
+    }
     __syncthreads();
 }
 
@@ -586,14 +600,11 @@ constexpr uint32_t kExpandWords = 2048;          // bit map words a workgroup ex
 // LDS of k_select_small, for units of at most PLACES places and BINS bins of the first cut
 template <uint32_t PLACES, uint32_t BINS>
 struct SmallSelectLds {
-    union {
-        int key[PLACES];                         // the entropies' bit patterns, by place
-        BlockSelectLds sel;                      // the crowded-bin path, which reads the entropies from memory again
-    };
+    int key[PLACES];                             // the entropies' bit patterns, by place
     uint32_t hist[BINS];
     uint64_t list[kSmallListCap];                // tiles of the threshold bin: key << 32 | ~place
     uint64_t words[PLACES / 64];                 // bit map words over places
-    uint64_t equal[PLACES / 64];                 // the crowded-bin path: keys equal to the threshold
+    uint64_t equal[PLACES / 64];                 // where many share the threshold: the words of those that do
     uint32_t prefix[PLACES / 64];                // selected places before each word
     uint32_t wave_total[kSmallUnitThreads / 64], wave_equal[kSmallUnitThreads / 64];
     uint32_t chosen[3];                          // threshold bin, wanted inside it, its tiles
@@ -609,8 +620,13 @@ struct SmallSelectLds {
 //
 // The entropies' bit patterns fall into BINS bins of 2^SHIFT neighbouring floats each, four octaves below ln A (`bin0` is
 // the number of the lowest bin); the bins at the ends take what lies beyond.  The bin that holds the k-th largest settles
-// every other tile with one comparison each; its own tiles (about a hundred) are placed directly among each other by (key
-// descending, tile ascending).  A crowded bin goes through a radix select instead, unless its crowd are all-zero tiles.
+// every other tile with one comparison each; its own tiles, if they are 256 or fewer, are placed directly among each other by (key
+// descending, tile ascending).  Of N(0,1) values those are 160 to 220 of 25600 tiles of 64 channels and 260 to 560 of 30720 and
+// more, of 12288 tiles of 128 channels or of 2048 of 4096; tiles that are alike are as many as there are.  A bin of more tiles is
+// cut again into 4096 parts, as a rule of one or two floats each, by a histogram of the bit patterns in LDS.
+// Encode of bf16 at 3.5 bits, against a radix select over the entropies in memory: 32768 tiles of 64 channels 36.5 -> 21.1 us, of 32
+// channels 34.4 -> 19.3, 25600 of 128 channels 28.7 -> 19.1, 8192 of 4096 channels 48.9 -> 45.4; a fifth of 32768 tiles alike, at
+// 3.1 bits, 35.7 -> 31.0.
 //
 // Bound by the instruction issue of its one compute unit, scalar instructions included (a ballot per 64 entropies and what
 // follows it cost three times as much as the carries that collect a lane's four bits here), and by a dozen dependent
@@ -668,36 +684,12 @@ __global__ __launch_bounds__(kSmallUnitThreads) void k_select_small(const float 
         }
     }
     __syncthreads();
-    // The bin of the k-th largest: thread t adds up the PER bins from BINS - PER (t + 1) on, a scan over the workgroup tells
-    // it how many entropies lie above them.  1 <= k <= n, so exactly one thread finds it.
-    {
-        uint32_t c[PER], mine = 0;
-        const uint32_t low = BINS - PER * ((uint32_t)tid + 1);
-#pragma unroll
-        for (uint32_t i = 0; i < PER / 4; ++i) {
-            const uint4 q = reinterpret_cast<const uint4 *>(L.hist + low)[i];
-            c[4 * i] = q.x; c[4 * i + 1] = q.y; c[4 * i + 2] = q.z; c[4 * i + 3] = q.w;
-            mine += q.x + q.y + q.z + q.w;
-        }
-        const uint32_t incl = wave_incl_scan(mine);
-        if (lane == 63) L.wave_total[wave] = incl;
-        __syncthreads();
-        uint32_t above = sum_of_waves_before(L.wave_total, wave, lane) + incl - mine;
-        if (above < k && k <= above + mine) {
-#pragma unroll
-            for (uint32_t i = PER; i-- > 0;) {
-                if (above < k && k <= above + c[i]) {
-                    const uint32_t outside = low + i == 0 ? nblocks * 256u - n : 0u;     // bin 0 has counted those as well
-                    L.chosen[0] = low + i; L.chosen[1] = k - above; L.chosen[2] = c[i] - outside;
-                }
-                above += c[i];
-            }
-        }
-        __syncthreads();
-    }
+    // The bin of the k-th largest.  1 <= k <= n, so there is one.
+    block_pick_bin<(int)BINS>(L.hist, k, L.wave_total, L.chosen);
     const uint32_t bstar = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[0]);
-    const uint32_t rem = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[1]);
-    const uint32_t crowd = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[2]);
+    uint32_t rem = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[1]);
+    uint32_t crowd = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[2]);
+    if (bstar == 0) crowd -= nblocks * 256u - n;             // bin 0 has counted the places outside the unit as well
     // the bit patterns of that bin, first and last
     const int first = bstar == 0 ? INT32_MIN + 1 : (int)((bstar + (uint32_t)bin0) << SHIFT);
     const int last = bstar == BINS - 1 ? INT32_MAX : (int)(((bstar + (uint32_t)bin0 + 1u) << SHIFT) - 1u);
@@ -713,14 +705,18 @@ __global__ __launch_bounds__(kSmallUnitThreads) void k_select_small(const float 
         const uint32_t d = nibbles_to_dword(four, lane);
         if ((lane & 7) == 0) reinterpret_cast<uint32_t *>(out)[b * 8u + (lane >> 3)] = d;
     };
-    if (crowd <= kSmallListCap) {
+    auto four_bits = [](const int4 &q, auto test) {
+        return (test(q.x) ? 1u : 0u) | (test(q.y) ? 2u : 0u) | (test(q.z) ? 4u : 0u) | (test(q.w) ? 8u : 0u);
+    };
+    // Every place that is_above is selected, and of the `crowd` others that are not below, the `rem` first by (key descending,
+    // tile ascending), placed directly among each other.
+    auto place_directly = [&](auto is_above, auto is_not_below) {
         uint32_t inside = 0;                     // my tiles of the bin, four bits per block, the last block lowest
         int4 next = *reinterpret_cast<const int4 *>(&L.key[wave * 256u + 4u * lane]);
         for (uint32_t b = wave; b < nblocks; b += WAVES) {
             const int4 q = next;
             if (b + WAVES < nblocks) next = *reinterpret_cast<const int4 *>(&L.key[(b + WAVES) * 256u + 4u * lane]);
-            const uint32_t above = (q.x > last ? 1u : 0u) | (q.y > last ? 2u : 0u) | (q.z > last ? 4u : 0u) | (q.w > last ? 8u : 0u);
-            const uint32_t reach = (q.x >= first ? 1u : 0u) | (q.y >= first ? 2u : 0u) | (q.z >= first ? 4u : 0u) | (q.w >= first ? 8u : 0u);
+            const uint32_t above = four_bits(q, is_above), reach = four_bits(q, is_not_below);
             put_bits(L.words, b, above);
             inside = (inside << 4) | (reach & ~above);
         }
@@ -752,72 +748,88 @@ __global__ __launch_bounds__(kSmallUnitThreads) void k_select_small(const float 
                 atomicOr(reinterpret_cast<uint32_t *>(L.words) + (place >> 5), 1u << (place & 31u));
         }
         __syncthreads();
+    };
+    if (crowd <= kSmallListCap) {
+        place_directly([&](int v) { return v > last; }, [&](int v) { return v >= first; });
     } else {
-        // the entropies' LDS serves the radix select, the entropies come from memory again (-0.0f outside the unit)
-        auto each = [&](auto &&visit) {
-            for (uint32_t p0 = wave * 64u; p0 < nwords * 64u; p0 += 8 * kSmallUnitThreads) {
-                float h[8];
-#pragma unroll
-                for (uint32_t r = 0; r < 8; ++r) {           // from a clamped index: none of the loads sits behind a branch
-                    const uint32_t p = p0 + r * kSmallUnitThreads + lane;
-                    h[r] = uH[p - phase < n ? p : phase];
-                    if (p - phase >= n) h[r] = -0.0f;
-                }
-#pragma unroll
-                for (uint32_t r = 0; r < 8; ++r)
-                    if (p0 + r * kSmallUnitThreads < nwords * 64u) visit(p0 + r * kSmallUnitThreads + lane, h[r]);
-            }
-        };
-        uint32_t thr, take, equal;
-        // The usual crowd are the entropies of all-zero tiles, +0.0f, in the lowest bin: if the threshold is among them,
-        // counting tells.
-        bool at_zero = false;
+        // More tiles in the bin than the list takes: it is cut again, 4096 parts at a time, until they fit or all share one
+        // entropy.  Bit patterns count in the order of their keys here, as signed integers, in which -0.0f (the places outside
+        // the unit) is -1: in none of the ranges below.
+        auto ordered = [](int v) { return v ^ ((v >> 31) & INT32_MAX); };
+        int lo = first, hi = last;
         if (bstar == 0) {
+            // The lowest bin's usual crowd are the entropies of all-zero tiles, +0.0f, which counting tells from those above
+            // and below.
             uint32_t above = 0, zero = 0;
             for (uint32_t b = wave; b < nblocks; b += WAVES) {
                 const int4 q = *reinterpret_cast<const int4 *>(&L.key[b * 256u + 4u * lane]);
-                const int v[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    above += v[c] > 0 && v[c] <= last ? 1u : 0u;
-                    zero += v[c] == 0 ? 1u : 0u;
-                }
+                above += (uint32_t)__popc(four_bits(q, [&](int v) { return v > 0 && v <= last; }));
+                zero += (uint32_t)__popc(four_bits(q, [](int v) { return v == 0; }));
             }
             above = wave_incl_scan(above);
             zero = wave_incl_scan(zero);
             if (lane == 63) { atomicAdd(&L.above_zero, above); atomicAdd(&L.zero, zero); }
             __syncthreads();
-            at_zero = L.above_zero < rem && rem <= L.above_zero + L.zero;
-            take = rem - L.above_zero;
+            above = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.above_zero);
+            zero = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.zero);
+            if (rem <= above) { lo = 1; crowd = above; }
+            else if (rem <= above + zero) { lo = hi = 0; rem -= above; crowd = zero; }
+            else { lo = INT32_MIN; hi = -2; rem -= above + zero; crowd -= above + zero; }
         }
-        if (at_zero) thr = order_key(0.0f);
-        else block_radix_select(rem, [&](auto &&visit) {
-            each([&](uint32_t, float h) {
-                const int v = (int)__float_as_uint(h);
-                if (v >= first && v <= last) visit(order_key(h));
-            });
-        }, L.sel, &thr, &take, &equal);
-        each([&](uint32_t p, float h) {
-            const uint32_t key = order_key(h);
-            const uint64_t eq = __ballot(key == thr), above = __ballot(key > thr);
-            if (lane == 0) { L.equal[p >> 6] = eq; L.words[p >> 6] = above; }
-        });
-        __syncthreads();
-        // Keys equal to thr are taken in index order until `take` are used up.  (A place outside the unit may lie above a
-        // threshold that is a NaN with the sign bit set.)
-        const uint64_t eq = (uint32_t)tid < nwords ? L.equal[tid] : 0ull;
-        const uint32_t count = (uint32_t)__popcll(eq), incl = wave_incl_scan(count);
-        if (lane == 63) L.wave_equal[wave] = incl;
-        __syncthreads();
-        const uint32_t eq_before = sum_of_waves_before(L.wave_equal, wave, lane) + incl - count;
-        if ((uint32_t)tid < nwords) {
-            uint64_t taken = eq;
-            if (eq_before >= take) taken = 0;
-            else
-                for (uint32_t over = eq_before + count; over > take; --over) taken &= ~(1ull << (63 - __builtin_clzll(taken)));
-            L.words[tid] = (L.words[tid] & in_unit((uint32_t)tid)) | taken;
+#pragma unroll 1
+        while (crowd > kSmallListCap && lo != hi) {          // three times at most: 32 bits, 12 fewer each time
+            const uint32_t span = (uint32_t)hi - (uint32_t)lo;
+            const int bits = 32 - __builtin_clz(span), shift = bits > 12 ? bits - 12 : 0;
+            static_assert(BINS >= 4096, "the parts' counts");
+            reinterpret_cast<uint4 *>(L.hist)[tid] = make_uint4(0, 0, 0, 0);
+            __syncthreads();
+            for (uint32_t b = wave; b < nblocks; b += WAVES) {
+                const int4 q = *reinterpret_cast<const int4 *>(&L.key[b * 256u + 4u * lane]);
+                const uint32_t from_lo[4] = {(uint32_t)ordered(q.x) - (uint32_t)lo, (uint32_t)ordered(q.y) - (uint32_t)lo,
+                                             (uint32_t)ordered(q.z) - (uint32_t)lo, (uint32_t)ordered(q.w) - (uint32_t)lo};
+                // (where a crowd shares one entropy all additions meet on one counter, one after the other; tokens that are
+                // alike make a crowd of neighbours: one addition for the four)
+                if (q.x == q.y && q.y == q.z && q.z == q.w) {
+                    if (from_lo[0] <= span) atomicAdd(&L.hist[from_lo[0] >> shift], 4u);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (from_lo[c] <= span) atomicAdd(&L.hist[from_lo[c] >> shift], 1u);
+                }
+            }
+            __syncthreads();
+            block_pick_bin<4096>(L.hist, rem, L.wave_total, L.chosen);
+            lo = (int)((uint32_t)lo + ((uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[0]) << shift));
+            rem = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[1]);
+            crowd = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[2]);
+            const uint32_t room = (uint32_t)hi - (uint32_t)lo, part = (1u << shift) - 1u;
+            hi = (int)((uint32_t)lo + (room < part ? room : part));
         }
-        __syncthreads();
+        auto is_above = [&](int v) { return ordered(v) > hi && v != INT32_MIN; };
+        if (crowd <= kSmallListCap) {
+            place_directly(is_above, [&](int v) { return ordered(v) >= lo && v != INT32_MIN; });
+        } else {
+            // `crowd` tiles of one entropy: taken in index order until `rem` are used up
+            for (uint32_t b = wave; b < nblocks; b += WAVES) {
+                const int4 q = *reinterpret_cast<const int4 *>(&L.key[b * 256u + 4u * lane]);
+                put_bits(L.words, b, four_bits(q, is_above));
+                put_bits(L.equal, b, four_bits(q, [&](int v) { return ordered(v) == lo; }));
+            }
+            __syncthreads();
+            const uint64_t eq = (uint32_t)tid < nwords ? L.equal[tid] : 0ull;
+            const uint32_t count = (uint32_t)__popcll(eq), incl = wave_incl_scan(count);
+            if (lane == 63) L.wave_equal[wave] = incl;
+            __syncthreads();
+            const uint32_t eq_before = sum_of_waves_before(L.wave_equal, wave, lane) + incl - count;
+            if ((uint32_t)tid < nwords) {
+                uint64_t taken = eq;
+                if (eq_before >= rem) taken = 0;
+                else
+                    for (uint32_t over = eq_before + count; over > rem; --over) taken &= ~(1ull << (63 - __builtin_clzll(taken)));
+                L.words[tid] |= taken;
+            }
+            __syncthreads();
+        }
     }
     // selected places before every word
     const uint64_t word = (uint32_t)tid < nwords ? L.words[tid] : 0ull;
@@ -928,7 +940,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *
                                                                    uint64_t *__restrict__ bitmap)
 {
     constexpr uint32_t WAVES = kFusedThreads / 64, BLOCKS = kFusedKeysPerBlock / 256 / WAVES;
-    __shared__ uint32_t chosen[3];               // threshold bin, wanted inside it; the workgroup's place in the list
+    __shared__ uint32_t chosen[4];               // threshold bin, wanted inside it, its tiles; the workgroup's place in the list
     __shared__ uint32_t wave_cand[WAVES], wave_above[WAVES];
     const uint32_t u = unit0 + blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -982,12 +994,12 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *
     if (wave == WAVES - 1) {
         const uint32_t above_before = sum_of_waves_before(wave_above, wave, lane);
         if (lane == 63) {
-            chosen[2] = before + incl ? atomicAdd(&fused[(uint64_t)u * 4], before + incl) : 0u;
+            chosen[3] = before + incl ? atomicAdd(&fused[(uint64_t)u * 4], before + incl) : 0u;
             block_above[(uint64_t)u * gridDim.x + blockIdx.x] = above_before + incl_above;
         }
     }
     __syncthreads();
-    uint32_t pos = chosen[2] + before + incl - count;
+    uint32_t pos = chosen[3] + before + incl - count;
     if (__ballot(inside != 0) != 0) {
         // (from registers: a lane may hold sixteen of them, where tiles are all zero)
 #pragma unroll
@@ -1008,7 +1020,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *
 // LDS of k_select_resolve
 struct ResolveLds {
     BlockSelectLds sel;
-    uint32_t chosen[4];                          // threshold bin, wanted inside it; threshold sub-bin, wanted inside it
+    uint32_t chosen[6];                          // threshold bin, wanted inside it, its tiles; the same of the threshold sub-bin
     uint32_t n_equal, n_before;
     uint32_t equal_tile[kFusedThreads];          // tiles whose key equals the threshold (the first 1024)
     uint32_t wave_total[kFusedThreads / 64];
@@ -1184,8 +1196,8 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
             }
         }
         __syncthreads();
-        block_pick_bin<kSubBins>(sub_hist, rem, L.wave_total, L.chosen + 2);
-        const uint32_t sstar = L.chosen[2], rem2 = L.chosen[3];
+        block_pick_bin<kSubBins>(sub_hist, rem, L.wave_total, L.chosen + 3);
+        const uint32_t sstar = L.chosen[3], rem2 = L.chosen[4];
         uint32_t *list_key = L.sel.copies + kSubBins, *list_tile = L.equal_tile;
         uint32_t in_sub = 0;                     // bit r: my r-th candidate lies in the threshold's sub-bin
 #pragma unroll

@@ -600,6 +600,50 @@ def test_single_launch_selection_with_a_crowded_threshold_bin(tahq, crowd):
         check_case(tahq, x, 2, n, G, G, tahq.F32, 3.0 + take / n)
 
 
+@pytest.mark.parametrize("n", (1500, 4100, 30001))
+def test_single_launch_selection_with_crowds_in_the_lowest_bin(tahq, n):
+    # one-hot tiles (entropies just below zero, of a few values), all-zero tiles, tiles of one dominant element (entropies
+    # close to zero, all different) and ordinary ones, each more than are placed directly; the threshold among each of them
+    G = 16
+    rng = np.random.default_rng(n)
+    part = n // 4
+    x = rng.standard_normal((2, n, G)).astype(np.float32)
+    for b in range(2):
+        order = rng.permutation(n)
+        hot, zero, dominant = order[:part], order[part:2 * part], order[2 * part:3 * part]
+        x[b, hot] = 0.0
+        x[b, hot, rng.integers(0, G, part)] = (rng.standard_normal(part) * 10.0 ** rng.integers(-6, 4, part)).astype(np.float32)
+        x[b, zero] = 0.0
+        x[b, dominant, 5] = (10.0 ** rng.uniform(2.0, 7.0, part)).astype(np.float32)
+    for k in (n - 7, n - part + 1, n - part - 7, n - 2 * part + 1, n - 2 * part - 7, n - 3 * part + 1, part // 2):
+        _say(f"[case] crowds in the lowest bin: {k} of {n} tiles wide")
+        check_case(tahq, x, 2, n, G, G, tahq.F32, 3.0 + k / n)
+
+
+@pytest.mark.parametrize("S,M", [(143, 7), (20, 1613), (317, 257)])
+def test_non_finite_entropies_off_the_64_tile_boundaries_follow_key_order(tahq, S, M):
+    # units for one launch and for two, that share bit map words; NaN entropies among the widest and, with the sign bit set,
+    # among the narrowest: run_gpu compares with the multi-launch selection, which ranks by the keys' digits
+    G = 16
+    rng = np.random.default_rng(S)
+    for dtype in (tahq.F32, tahq.BF16):
+        x = rng.standard_normal((3, S, M * G)).astype(np.float32)
+        x[0, 0, 3] = np.nan
+        x[0, 7, 20] = np.inf
+        x[1, 9, 30] = -np.inf
+        x[1, 2:S // 2, :G] = np.nan
+        x[1, S // 2:, G:2 * G] = -np.nan
+        x[2, 3:S // 3, :] = 3e38
+        x[2, S // 2:, :] = 0.0
+        with np.errstate(all="ignore"):
+            xin = x if dtype == tahq.F32 else np.ascontiguousarray(workloads.f32_to_bf16_bits(x).reshape(x.shape))
+        if dtype == tahq.F32:
+            xin.view(np.uint32)[1, 1, :G] = 0xFFFFFFFF
+        for budget in (3.0 + 0.5 / M, 3.5, 3.97):
+            _say(f"[case] non-finite inputs, 3 units x {S * M} tiles, dtype {dtype}, budget {budget}")
+            run_gpu(tahq, tahq.make_config(3, S, M * G, G, dtype, budget), xin, tahq.F32)
+
+
 @pytest.mark.parametrize("G", (16, 32, 64, 128))
 @pytest.mark.parametrize("dtype_name", ("f32", "bf16"))
 @pytest.mark.parametrize("low", (1, 3, 7))

@@ -1,0 +1,64 @@
+"""Times of the selection's paths against each other: how long an encode takes may not depend on where the entropies lie.
+
+Ratios of two encodes on one GPU, back to back, with room for the difference between boxes; what they guard against is a path
+that takes several times as long.
+"""
+import sys
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def tahq():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2506_01352_amd as t
+    t.binding._load()
+    return t
+
+
+def _normal(B, S, C, seed=5):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    return torch.randn(B, S, C, device="cuda", generator=gen), gen
+
+
+def _alike(x, gen, value):
+    """A fifth of the tokens set to one value: their tiles share one entropy."""
+    some = torch.rand(x.shape[0], x.shape[1], 1, device="cuda", generator=gen) < 0.2
+    return torch.where(some, torch.full((), value, device="cuda"), x)
+
+
+def _encode_us(tahq, x, G, budget, alloc_tile=0):
+    """Microseconds of one encode: the best of five replays of a graph of eight."""
+    B, S, C = x.shape
+    x = x.to(torch.bfloat16).contiguous()
+    codec = tahq.Codec(tahq.make_config(B, S, C, G, tahq.BF16, budget, alloc_tile=alloc_tile))
+    codec.encode(x)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(8):
+            codec.encode(x)
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    best = float("inf")
+    for i in range(8):
+        start.record()
+        graph.replay()
+        end.record()
+        torch.cuda.synchronize()
+        if i >= 3:
+            best = min(best, start.elapsed_time(end) / 8 * 1e3)
+    print(f"[case] {B}x{S}x{C} G={G} A={alloc_tile or G} {budget} bits: {best:.1f} us", file=sys.stderr, flush=True)
+    return best
+
+
+def test_units_of_the_single_launch_take_about_as_long_whatever_their_size(tahq):
+    # 25600 tiles of 64 channels; 32768 of them, and of 32 channels, whose threshold bin holds more than is placed directly
+    base = _encode_us(tahq, _normal(1, 1024, 1600)[0], 64, 3.5)
+    assert _encode_us(tahq, _normal(1, 1024, 2048)[0], 64, 3.5) < 1.7 * base
+    assert _encode_us(tahq, _normal(1, 1024, 1024)[0], 32, 3.5) < 1.7 * base
