@@ -464,7 +464,7 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
     const bool with_entropy = select && !histograms && (phases & (uint32_t)TAHQ_PHASE_PROLOGUE) && (phases & (uint32_t)TAHQ_PHASE_ENTROPY);
     if (phases & TAHQ_PHASE_PROLOGUE) pro.packed = packed;
     if ((phases & TAHQ_PHASE_PROLOGUE) && !all_in_quant && !with_entropy) {
-        const uint64_t zero_from = multi_launch || wide ? ws.hist0 : ws.lin_hist;        // what this selection counts in
+        const uint64_t zero_from = multi_launch || wide ? ws.coarse : ws.hist0;          // what this selection counts in
         const uint32_t zero_words = histograms ? (uint32_t)((ws.zero_bytes - zero_from) / 4) : 0u;
         const uint32_t zero_blocks = blocks_for(zero_words) < 256u ? blocks_for(zero_words) : 256u;
         q(k_prologue, dim3(zero_blocks ? zero_blocks : 1u), dim3(256), pro, reinterpret_cast<uint32_t *>(wsb + zero_from), zero_words);
@@ -509,10 +509,11 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
                                 s.U - u0 < kMaxGridY ? s.U - u0 : kMaxGridY);
                 q(k_select_classify, grid, dim3(kFusedThreads), (const float *)H, (uint32_t)s.n,
                                    (uint32_t)s.k, u0, bin_scale, (const uint32_t *)lin_hist, fused_state, cand, block_above,
-                                   bitmap);
+                                   hist0, bitmap);
                 q(k_select_resolve, grid, dim3(kFusedThreads), (const float *)H, (uint32_t)s.n,
-                                   (uint32_t)s.k, u0, bin_scale, (const uint32_t *)lin_hist, (const uint32_t *)fused_state,
-                                   (const uint2 *)cand, (const uint32_t *)block_above, bitmap, ranks);
+                                   (uint32_t)s.k, u0, bin_scale, (const uint32_t *)lin_hist, fused_state, cand,
+                                   (const uint32_t *)block_above, (const uint32_t *)hist0, reinterpret_cast<uint64_t *>(sel),
+                                   bitmap, ranks);
             }
         } else
         if ((phases & TAHQ_PHASE_SELECT) && small_units) {

@@ -34,6 +34,16 @@ __device__ __forceinline__ uint32_t linear_sub_bin(float h, float scale, uint32_
     return (int32_t)__float_as_uint(h) > 0x7f800000 ? kSubBins - 1 : s;
 }
 
+// The same for a bin that many tiles share: most of them may be alike, and the usual ones are all-zero tiles.  In the lowest bin
+// their entropy, +0.0f, has sub-bin 1 to itself, with whatever is negative below it.
+__device__ __forceinline__ uint32_t crowd_sub_bin(float h, float scale, uint32_t b)
+{
+    const uint32_t s = linear_sub_bin(h, scale, b);
+    if (b != 0) return s;
+    const int32_t v = (int32_t)__float_as_uint(h);
+    return v == 0 ? 1u : v < 0 ? 0u : s < 2u ? 2u : s;
+}
+
 // The entropy an order-preserving key was made from.
 __device__ __forceinline__ float key_to_float(uint32_t key)
 {

@@ -37,18 +37,20 @@ constexpr uint32_t kCandCap = 16384;      // tiles of the threshold bin that the
 
 struct Workspace {
     // offsets in bytes from the workspace base
-    uint64_t hist0;      // uint32[U][kDigit0Bins]: first-digit histogram      (zeroed per call)
     uint64_t coarse;     // uint32[U][2][64]: super-bin totals of digits 1, 2   (zeroed per call)
     uint64_t state;      // uint32[U][8] selection state
+    uint64_t hist0;      // uint32[U][kDigit0Bins]: first-digit histogram; the two-launch selection: a crowded threshold
+                         // bin's tiles by sub-bin                                        (zeroed per call)
     uint64_t lin_hist;   // uint32[U][kLinBins]: entropies by linear bin                  (zeroed per call)
-    uint64_t fused;      // uint32[U][4]: candidates listed, workgroups done              (zeroed per call)
-    uint64_t zero_bytes; // bytes from `hist0` that must be zero before the selection starts
+    uint64_t fused;      // uint32[U][4]: candidates listed, workgroups done, key range   (zeroed per call)
+    uint64_t zero_bytes; // end of what must be zero before the selection starts
     uint64_t partial;    // uint32[U][2][hb][kHistBins]: per-workgroup histograms of digits 1, 2
     uint64_t keys;       // float[T] entropies
     uint64_t cand;       // uint2[U][kCandCap]: (key, tile) of the tiles in the threshold bin
     uint64_t seg;        // uint32[U][nseg][2]: keys equal to / above the threshold, per segment; the two-launch
                          // selection: tiles above the threshold bin, per block of 16384 places
-    uint64_t sel;        // uint8[T] (only when n % 64 != 0, or A > G)
+    uint64_t sel;        // uint8[T] (multi-launch selection, only when n % 64 != 0, or A > G); two-launch selection:
+                         // uint64[U][n / 64 + 2], the words of the tiles that share a crowded threshold's sub-bin
     uint64_t part;       // float[T]: per-quantization-tile partial sums            (only when A > G)
     uint64_t inv_norm;   // float[T/m]: 1 / (L1 norm + eps) of every allocation tile (only when A > G)
     uint64_t ranks_a;    // uint32[ceil(U*nA/64)]: rank table over allocation tiles  (only when A > G)
@@ -113,9 +115,9 @@ void make_workspace(const Shape &s, Workspace *w)
     uint64_t hb = (s.nA + kRadixKeysPerBlock - 1) / kRadixKeysPerBlock;
     w->hb = (uint32_t)(hb > 64 ? 64 : hb);
     uint64_t off = 0;
-    w->hist0 = off;  off += (uint64_t)s.U * kDigit0Bins * 4;
     w->coarse = off; off += (uint64_t)s.U * 2 * 64 * 4;
     w->state = off;  off += (uint64_t)s.U * 8 * 4;
+    w->hist0 = off;  off += (uint64_t)s.U * kDigit0Bins * 4;
     w->lin_hist = off; off += (uint64_t)s.U * kLinBins * 4;
     w->fused = off;  off += (uint64_t)s.U * 4 * 4;
     w->zero_bytes = off;

@@ -57,6 +57,17 @@ __device__ __forceinline__ uint32_t nibbles_to_dword(uint32_t four, int lane)
     return d;
 }
 
+// The largest a and the largest b of the wavefront, in every lane.
+__device__ __forceinline__ void wave_max(uint32_t &a, uint32_t &b)
+{
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        const uint32_t oa = (uint32_t)__shfl_xor((int)a, off, 64), ob = (uint32_t)__shfl_xor((int)b, off, 64);
+        a = oa > a ? oa : a;
+        b = ob > b ? ob : b;
+    }
+}
+
 // The 16 wavefronts' entries of `totals` that come before mine, added up.
 __device__ __forceinline__ uint32_t sum_of_waves_before(const uint32_t *totals, uint32_t wave, int lane)
 {
@@ -67,6 +78,19 @@ __device__ __forceinline__ uint32_t sum_of_waves_before(const uint32_t *totals, 
     v += dpp_or_zero<0x114, 0xF>(v);
     v += dpp_or_zero<0x118, 0xF>(v);
     return (uint32_t)__builtin_amdgcn_readlane((int)(v - own), (int)wave);
+}
+
+// hist[bin] += 1 in LDS for every lane that is `active`.  Where many tiles are alike whole wavefronts meet on one address, whose
+// additions would follow one another: then it is one addition.  (Adding up the lanes of one bin beforehand in every case cost a
+// selection from 7000 different candidates 1.5 us.)
+__device__ __forceinline__ void add_one_each(uint32_t *hist, uint32_t bin, bool active)
+{
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)bin);
+    if (__ballot(active && bin == first) == ~0ull) {
+        if ((threadIdx.x & 63) == 0) atomicAdd(&hist[first], 64u);
+    } else if (active) {
+        atomicAdd(&hist[bin], 1u);
+    }
 }
 
 // Which of BINS bins holds the `want`-th largest value (bins counted from the top), how many values are wanted inside it and how
@@ -477,118 +501,9 @@ __global__ __launch_bounds__(256) void k_expand_alloc(const uint8_t *__restrict_
     }
 }
 
-constexpr uint32_t kBlockSelectThreads = 1024;
-
-// LDS scratch of block_radix_select.
-struct BlockSelectLds {
-    uint32_t copies[8192];                       // the histogram of one digit, several copies of every bin
-    uint32_t lh[4096 + 64];                      // its bins added up; bin b at b + b/64: a lane that reads bin l of a chunk
-                                                 // of 64 bins while its neighbours read theirs meets no bank conflict
-    uint32_t chunk_total[64];                    // totals of the chunks of 64 bins
-    uint32_t chosen[5];                          // bin, wanted inside it, its count; smallest and largest value
-};
-
-// Run by the first wavefront: the bin of L.lh that holds the `want`-th largest value, in two levels -- the chunk of 64
-// bins from the top (totals in L.chunk_total; chunks that are not in use hold 0), then the bin inside it.  Leaves the
-// bin, the number still wanted inside it and its count in L.chosen[0..2].
-__device__ __forceinline__ void pick_from_chunks(BlockSelectLds &L, uint32_t want, int lane)
-{
-    const uint32_t cs = L.chunk_total[63 - lane];                           // lane l: chunk 63 - l, from the top
-    const uint32_t above = wave_incl_scan(cs) - cs;
-    const uint64_t who = __ballot(above < want && want <= above + cs);
-    const int src = who ? (int)__ffsll((unsigned long long)who) - 1 : 0;
-    const uint32_t chunk = 63u - (uint32_t)src;
-    const uint32_t want2 = want - (uint32_t)__shfl((int)above, src, 64);
-    const uint32_t bs = L.lh[chunk * 65 + (63 - lane)];                     // lane l: bin 63 - l of the chunk
-    const uint32_t above2 = wave_incl_scan(bs) - bs;
-    const uint64_t who2 = __ballot(above2 < want2 && want2 <= above2 + bs);
-    const int src2 = who2 ? (int)__ffsll((unsigned long long)who2) - 1 : 0;
-    if (lane == src2) {
-        L.chosen[0] = chunk * 64 + (63u - (uint32_t)src2);
-        L.chosen[1] = want2 - above2;
-        L.chosen[2] = bs;
-    }
-}
-
-// Workgroup-wide radix select over the values that `each` hands to its argument (every thread visits its own share
-// of the values; each(g) calls g(value) for each of them): the `want`-th largest value (1 <= want <= number of values),
-// how many values equal to it belong to the `want` largest, and how many values equal to it there are.  The values of
-// one selection lie close together (the entropies of one sample, or the keys of one histogram bin), so the digits are
-// taken from value - minimum: 12 bits at a time from the top of max - min, usually two passes.  Called by all 1024
-// threads; the result is the same in every thread.
-template <class Each>
-__device__ __forceinline__ void block_radix_select(uint32_t want, Each each, BlockSelectLds &L, uint32_t *thr_out,
-                                                   uint32_t *take_out, uint32_t *equal_out)
-{
-    constexpr int kBins = 4096;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (tid == 0) { L.chosen[3] = 0xffffffffu; L.chosen[4] = 0u; }
-    __syncthreads();
-    {
-        uint32_t lo = 0xffffffffu, hi = 0u;
-        each([&](uint32_t val) { lo = val < lo ? val : lo; hi = val > hi ? val : hi; });
-        // per wavefront first: a thousand atomics on one LDS address would take longer than the rest of the selection
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            const uint32_t olo = (uint32_t)__shfl_xor((int)lo, off, 64), ohi = (uint32_t)__shfl_xor((int)hi, off, 64);
-            lo = olo < lo ? olo : lo;
-            hi = ohi > hi ? ohi : hi;
-        }
-        if (lane == 0 && lo <= hi) { atomicMin(&L.chosen[3], lo); atomicMax(&L.chosen[4], hi); }
-    }
-    __syncthreads();
-    const uint32_t vmin = L.chosen[3], span = L.chosen[4] - vmin;
-    int bits = 32 - __builtin_clz(span | 1u);    // digits cover bits [0, bits) of value - vmin
-    uint32_t prefix = 0;                         // the digits found so far, as the top bits of value - vmin
-    uint32_t equal = 0;
-#pragma unroll 1
-    while (true) {
-        const int shift = bits > 12 ? bits - 12 : 0;         // this pass: bits [shift, bits)
-        const uint32_t mask = (1u << (bits - shift)) - 1u;
-        // Several copies of every bin, indexed by the lane, as many as the 8192 words hold (2 for a 12-bit digit, at
-        // most 32): a wavefront's atomics on one LDS address are serialized, and under massive ties a digit takes
-        // one or two values.
-        const int copy_bits = 13 - (bits - shift) > 5 ? 5 : 13 - (bits - shift);
-        const uint32_t my_copy = (uint32_t)lane & ((1u << copy_bits) - 1u);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) L.copies[i * (int)kBlockSelectThreads + tid] = 0;
-        __syncthreads();
-        each([&](uint32_t val) {
-            const uint32_t d = val - vmin;
-            if (bits == 32 || (d >> bits) == prefix) atomicAdd(&L.copies[(((d >> shift) & mask) << copy_bits) | my_copy], 1u);
-        });
-        __syncthreads();
-        // thread t adds up the copies of bins t, t + 1024, ...; the 64 bins of a wavefront are one chunk, whose total
-        // the wavefront leaves beside them
-#pragma unroll
-        for (int part = 0; part < kBins / (int)kBlockSelectThreads; ++part) {
-            const uint32_t bin = (uint32_t)tid + kBlockSelectThreads * part;
-            uint32_t sum = 0;
-            if (bin <= mask) {
-                for (int c = 0; c < (1 << copy_bits); ++c) sum += L.copies[(bin << copy_bits) + c];
-            }
-            L.lh[bin + (bin >> 6)] = sum;
-            const uint32_t upto = wave_incl_scan(sum);
-            if (lane == 63) L.chunk_total[(kBlockSelectThreads / 64) * part + wave] = upto;
-        }
-        __syncthreads();
-        if (tid < 64) pick_from_chunks(L, want, lane);
-        __syncthreads();
-        prefix = (bits - shift == 32) ? L.chosen[0] : ((prefix << (bits - shift)) | L.chosen[0]);
-        want = L.chosen[1];
-        equal = L.chosen[2];
-        __syncthreads();
-        if (shift == 0) break;
-        bits = shift;
-    }
-    *thr_out = vmin + prefix;
-    *take_out = want;
-    *equal_out = equal;
-}
-
 // ---- small ranking units: the whole selection in one launch
 
-constexpr uint32_t kSmallUnitThreads = kBlockSelectThreads;
+constexpr uint32_t kSmallUnitThreads = 1024;
 #ifndef TAHQ_SMALL_UNIT_MAX
 #define TAHQ_SMALL_UNIT_MAX 32768
 #endif
@@ -884,19 +799,31 @@ __global__ __launch_bounds__(kSmallUnitThreads) void k_select_small(const float 
 //   k_select_classify (workgroups of 1024 threads over blocks of 16384 tiles): find b*; write the bit map words with
 //     the tiles above b* and the block's count of them; append (key, tile) of the tiles in b* to the unit's
 //     candidate list.
-//   k_select_resolve (same grid): every workgroup ranks the unit's candidates exactly for itself -- radix select on
-//     the keys, then, among the keys equal to the threshold, by tile index, so that ties go to the lower index
+//   k_select_resolve (same grid): every workgroup ranks the unit's candidates exactly for itself -- a histogram over
+//     parts of the bin leaves a handful that are placed directly, ties by tile index, so that they go to the lower index
 //     whatever order the list came in -- adds the selected candidates of its own block to the block's bit map
 //     words, and writes the block's part of the rank table (tiles above b* in the blocks before it, from the
 //     counts; selected candidates before it, counted while ranking).  Ranking a few thousand candidates sixteen to
 //     thirty-two times over costs less than one workgroup walking the unit's whole bit map.
-// If a unit's bin b* holds more tiles than the list does (massive ties), the unit's first workgroup of the second
-// kernel does all of it alone, straight from the entropies: slower but as exact.
-// (One launch, with the last workgroup of every unit doing the second part, measured ten times slower: what a
-// workgroup wrote becomes visible to a workgroup on another XCD only through fences that write back the L2.)
+// If b* holds a crowd, more tiles than the list or than a sixteenth of the unit, nothing is listed:
+//   k_select_classify counts b*'s tiles over the sub-bins of b*;
+//   k_select_resolve, in the place of the ranking above: every workgroup settles its own tiles but those in the threshold's
+//     sub-bin, whose places it leaves in words of their own; the unit's last workgroup to get there settles those, as a rule
+//     by index alone, because they are all alike, or from a list, because they are few.
+// (Ordinary values put up to 3 % of a unit into one bin, so more than a sixteenth are tiles that are alike.  From the list those take
+// longer than the crowd's way does, three units of 77700 tiles with 15500 all-zero ones each 49 against 40 us for the encode, and
+// tiles that are not the other way round, 655520 tiles of 32 channels 74 against 59.)
+// Encode, against one workgroup that did all of such a unit from the entropies: 655520 tiles of 32 channels, a fifth of them all zero,
+// 1477 -> 72 us, 1056897 tiles of 64 channels 1480 -> 127, a fifth of them all zero 3013 -> 121.
+// (Without a crowd, one launch, with the last workgroup of every unit doing the second part, measured ten times slower.  What a
+// workgroup wrote becomes visible to a workgroup on another XCD only when the L2 is written back: in the crowd's way one thread
+// per workgroup sees to that, in under 1 us; the last workgroup's work takes ten.)
 
-constexpr uint32_t kFusedThreads = kBlockSelectThreads;
+constexpr uint32_t kFusedThreads = 1024;
 constexpr uint32_t kFusedKeysPerBlock = 16 * kFusedThreads;
+
+// A threshold bin of more tiles than this is a crowd.
+__device__ __forceinline__ uint32_t crowd_from(uint32_t n) { return n / 16 < kCandCap ? n / 16 : kCandCap; }
 
 // A ranking unit in places: a place is a tile's index counted from the 64-tile boundary at or before the unit's first tile, so
 // that 64 places are one word of the bit map, which the unit may share with a neighbour at either end.
@@ -937,9 +864,12 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *
                                                                    uint32_t *__restrict__ fused,
                                                                    uint2 *__restrict__ cand,
                                                                    uint32_t *__restrict__ block_above,
+                                                                   uint32_t *__restrict__ crowd_hist,
                                                                    uint64_t *__restrict__ bitmap)
 {
     constexpr uint32_t WAVES = kFusedThreads / 64, BLOCKS = kFusedKeysPerBlock / 256 / WAVES;
+    static_assert(kSubBins == kFusedThreads, "one sub-bin per thread");
+    __shared__ uint32_t sub_hist[kSubBins];
     __shared__ uint32_t chosen[4];               // threshold bin, wanted inside it, its tiles; the workgroup's place in the list
     __shared__ uint32_t wave_cand[WAVES], wave_above[WAVES];
     const uint32_t u = unit0 + blockIdx.y;
@@ -985,6 +915,29 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *
             else atomicOr(&ubits[p >> 5], d);    // (a word that units share: cleared by an earlier kernel)
         }
     }
+    if (chosen[2] > crowd_from(n)) {             // (the same for all of the unit's workgroups)
+        sub_hist[tid] = 0;
+        __syncthreads();
+        if (inside != 0) {
+#pragma unroll
+            for (uint32_t r = 0; r < BLOCKS; ++r) {
+                const uint32_t four = (inside >> (4 * (BLOCKS - 1 - r))) & 15u;
+                const int v[4] = {q[r].x, q[r].y, q[r].z, q[r].w};
+                auto sub_bin = [&](int bits) { return crowd_sub_bin(__uint_as_float((uint32_t)bits), bin_scale, bstar); };
+                // (tiles that are alike meet on one counter; where they are neighbours, with one addition for four)
+                if (four == 15u && v[0] == v[1] && v[1] == v[2] && v[2] == v[3]) {
+                    atomicAdd(&sub_hist[sub_bin(v[0])], 4u);
+                } else {
+#pragma unroll
+                    for (uint32_t c = 0; c < 4; ++c)
+                        if ((four >> c) & 1u) atomicAdd(&sub_hist[sub_bin(v[c])], 1u);
+                }
+            }
+        }
+        __syncthreads();
+        if (sub_hist[tid] != 0) atomicAdd(&crowd_hist[(uint64_t)u * kSubBins + tid], sub_hist[tid]);
+        return;
+    }
     // one place in the list for the whole workgroup (a unit's workgroups all add to one counter: few, large additions)
     const uint32_t count = (uint32_t)__popc(inside), incl = wave_incl_scan(count), incl_above = wave_incl_scan(n_above);
     __syncthreads();                             // everybody has the threshold bin: `wave_above` is used again
@@ -1019,118 +972,324 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *
 
 // LDS of k_select_resolve
 struct ResolveLds {
-    BlockSelectLds sel;
+    uint32_t hist[4096];
+    uint64_t list[kFusedThreads];                // candidates that are placed directly: key << 32 | ~tile
     uint32_t chosen[6];                          // threshold bin, wanted inside it, its tiles; the same of the threshold sub-bin
-    uint32_t n_equal, n_before;
-    uint32_t equal_tile[kFusedThreads];          // tiles whose key equals the threshold (the first 1024)
+    uint32_t listed, n_before;
     uint32_t wave_total[kFusedThreads / 64];
     uint32_t words[2 * (kFusedKeysPerBlock / 64)];           // the block's bit map words, as dwords
 };
 
-// Which of the candidates f visits are selected: `rem` of them, by (key descending, tile ascending).  each_candidate(f)
-// calls f(key, tile) for my share of the tiles in bin b*; take_it(tile) is called for every selected one.  All 1024
-// threads.
-template <class EachCandidate, class TakeIt>
-__device__ __forceinline__ void rank_candidates(uint32_t rem, EachCandidate each_candidate, TakeIt take_it, ResolveLds &L)
+// The first `rem` of the `count` candidates in L.list, by (key descending, tile ascending), thread t placing the t-th.
+template <class TakeIt>
+__device__ __forceinline__ void place_listed(uint32_t rem, uint32_t count, TakeIt take_it, const ResolveLds &L)
 {
-    const int tid = threadIdx.x;
-    if (tid == 0) L.n_equal = 0;
-    uint32_t thr, take, equal;
-    block_radix_select(rem, [&](auto g) { each_candidate([&](uint32_t key, uint32_t) { g(key); }); }, L.sel, &thr, &take,
-                       &equal);
-    if (take == equal) {                         // every tile equal to the threshold is taken (one, as a rule)
-        each_candidate([&](uint32_t key, uint32_t tile) { if (key >= thr) take_it(tile); });
-        return;
-    }
-    // tiles above the threshold are taken; of those equal to it, the `take` with the lowest tile indices
-    each_candidate([&](uint32_t key, uint32_t tile) {
-        if (key > thr) take_it(tile);
-        else if (key == thr) {
-            const uint32_t at = atomicAdd(&L.n_equal, 1u);
-            if (at < kFusedThreads) L.equal_tile[at] = tile;
-        }
-    });
-    __syncthreads();
-    const uint32_t ne = L.n_equal;
-    if (ne <= kFusedThreads) {
-        // a handful, as a rule: thread t ranks the t-th of them among all of them
-        if ((uint32_t)tid < ne) {
-            const uint32_t mine = L.equal_tile[tid];
-            uint32_t lower = 0;
-            for (uint32_t i = 0; i < ne; ++i) lower += L.equal_tile[i] < mine ? 1u : 0u;
-            if (lower < take) take_it(mine);
-        }
-    } else {
-        uint32_t thr_index, unused, unused2;     // a tile with key == thr is taken iff ~tile >= thr_index
-        block_radix_select(take, [&](auto g) {
-            each_candidate([&](uint32_t key, uint32_t tile) { if (key == thr) g(~tile); });
-        }, L.sel, &thr_index, &unused, &unused2);
-        each_candidate([&](uint32_t key, uint32_t tile) { if (key == thr && ~tile >= thr_index) take_it(tile); });
+    if (threadIdx.x < count) {
+        const uint64_t mine = L.list[threadIdx.x];
+        uint32_t ahead = 0;
+        for (uint32_t i = 0; i < count; ++i) ahead += L.list[i] > mine ? 1u : 0u;
+        if (ahead < rem) take_it(~(uint32_t)mine);
     }
 }
 
-// The overflow path: one workgroup resolves a whole unit from the entropies (bin b* holds more tiles than the list).
-__device__ __noinline__ void resolve_unit_alone(const float *__restrict__ uH, uint32_t n, const UnitPlaces &at, uint32_t rank_base,
-                                                float bin_scale, uint32_t bstar, uint32_t rem,
-                                                uint64_t *__restrict__ ubitmap, uint32_t *__restrict__ uranks,
-                                                ResolveLds &L)
+// The same for `count` candidates, keys lo .. hi, tiles below `places`, that are too many for the list: each(f) calls f(key, tile)
+// for my share of them.  A histogram over 4096 parts of the keys' range narrows them down until they fit the list or share one
+// key, and then one over 4096 parts of the tiles.  All 1024 threads.  (Encode of 655520 tiles of 32 channels with 16000 alike at the
+// threshold: 89 us when both were radix selects, 69 now.)
+template <class Each, class TakeIt>
+__device__ __forceinline__ void rank_candidates(uint32_t rem, uint32_t count, uint32_t lo, uint32_t hi, uint32_t places, Each each,
+                                                TakeIt take_it, ResolveLds &L)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    uint32_t *ubits32 = reinterpret_cast<uint32_t *>(ubitmap);
-    if (rem != 0) {
-        rank_candidates(rem, [&](auto f) {
-            for (uint32_t i = tid; i < n; i += kFusedThreads) {
-                const float hv = uH[i];
-                if (linear_bin(hv, bin_scale) == bstar) f(order_key(hv), i + at.phase);
-            }
-        }, [&](uint32_t tile) { atomicOr(&ubits32[tile >> 5], 1u << (tile & 31u)); }, L);
+    const int tid = threadIdx.x;
+    if (tid == 0) L.listed = 0;
+    uint32_t tile0 = 0;                          // of the candidates with one key: tiles from here on
+    int tile_bits = 32 - __builtin_clz(places | 1u);         // ... that differ in so many bits
+    __syncthreads();
+#pragma unroll 1
+    while (count > kFusedThreads && (lo != hi || tile_bits != 0)) {          // each part has 12 bits fewer: six times at most
+        const bool by_key = lo != hi;
+        const uint32_t span = hi - lo;
+        const int bits = by_key ? 32 - __builtin_clz(span) : tile_bits, shift = bits > 12 ? bits - 12 : 0;
+        reinterpret_cast<uint4 *>(L.hist)[tid] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+        each([&](uint32_t key, uint32_t tile) {
+            // (the lowest tiles come first: their parts are counted from the top)
+            const uint32_t at = by_key ? (key - lo) >> shift : 4095u - ((tile - tile0) >> shift);
+            const bool inside = by_key ? key - lo <= span : key == lo && (uint64_t)(tile - tile0) >> tile_bits == 0;
+            add_one_each(L.hist, at & 4095u, inside);
+        });
+        __syncthreads();
+        block_pick_bin<4096>(L.hist, rem, L.wave_total, L.chosen);
+        const uint32_t part = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[0]);
+        rem = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[1]);
+        count = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[2]);
+        if (by_key) {
+            lo += part << shift;
+            const uint32_t width = (1u << shift) - 1u;
+            hi = hi - lo < width ? hi : lo + width;
+        } else {
+            tile0 += (4095u - part) << shift;
+            tile_bits = shift;
+        }
     }
-    // every wavefront's atomics have been performed (acknowledged by the L2, where the loads below read) before
-    // anybody reads the words
+    each([&](uint32_t key, uint32_t tile) {
+        if (key > hi || (key >= lo && tile < tile0)) take_it(tile);
+        else if (key >= lo && (uint64_t)(tile - tile0) >> tile_bits == 0) {
+            const uint32_t at = atomicAdd(&L.listed, 1u);
+            if (at < kFusedThreads) L.list[at] = ((uint64_t)key << 32) | (uint32_t)~tile;
+        }
+    });
+    __syncthreads();
+    place_listed(rem, count < kFusedThreads ? count : kFusedThreads, take_it, L);
+}
+
+// A unit whose threshold bin holds more tiles than the candidate list: workgroup `blk` of `blocks`, each of 16384 places.
+// Every workgroup first settles its own tiles: those above the threshold's sub-bin into the bit map, those in it (`crowd`, of which
+// `rem` are selected) into `equal`, words over places that only this unit has; it finds the range of their keys and, where they
+// fit, lists them.  The last of the unit's workgroups to finish then knows them all.
+__device__ __forceinline__ void resolve_crowd(const float *__restrict__ H, uint32_t n, uint32_t k, uint32_t u, uint32_t blk,
+                                              uint32_t blocks, float bin_scale, uint32_t bstar, uint32_t rem,
+                                              const uint32_t *crowd_hist, uint32_t *state, uint2 *ucand, uint64_t *equal,
+                                              uint64_t *bitmap, uint32_t *ranks, ResolveLds &L)
+{
+    constexpr uint32_t WAVES = kFusedThreads / 64, BLOCKS = kFusedKeysPerBlock / 256 / WAVES;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    const UnitPlaces at(u, n);
+    const float *uH = H + ((uint64_t)u * n - at.phase);      // by place
+    uint64_t *ubitmap = bitmap + at.word0;
+    uint32_t *ubits = reinterpret_cast<uint32_t *>(ubitmap), *equal32 = reinterpret_cast<uint32_t *>(equal);
+    const uint32_t top = at.nwords * 64u - 4u;
+    // four neighbouring entropies' bit patterns, -0.0f (no entropy's) outside the unit
+    auto four_at = [&](uint32_t p) {
+        int4 q = *reinterpret_cast<const int4 *>(uH + (p < top ? p : top));
+        q.x = p - at.phase < n ? q.x : INT32_MIN; q.y = p + 1u - at.phase < n ? q.y : INT32_MIN;
+        q.z = p + 2u - at.phase < n ? q.z : INT32_MIN; q.w = p + 3u - at.phase < n ? q.w : INT32_MIN;
+        return q;
+    };
+    int4 q[BLOCKS];
+#pragma unroll
+    for (uint32_t r = 0; r < BLOCKS; ++r) q[r] = four_at(blk * kFusedKeysPerBlock + (r * WAVES + wave) * 256u + 4u * lane);
+    block_pick_bin<kSubBins>(crowd_hist + (uint64_t)u * kSubBins, rem, L.wave_total, L.chosen + 3);
+    const uint32_t sstar = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[3]);
+    rem = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[4]);
+    uint32_t crowd = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[5]);
+    const bool list_them = crowd <= kCandCap;
+    const int first = bstar == 0 ? INT32_MIN + 1 : linear_bin_edge(bstar, bin_scale);
+    const int last = bstar == kLinBins - 1 ? INT32_MAX : linear_bin_edge(bstar + 1, bin_scale) - 1;
+
+    uint32_t inside = 0, key_max = 0, not_key_min = 0;
+#pragma unroll
+    for (uint32_t r = 0; r < BLOCKS; ++r) {
+        const int v[4] = {q[r].x, q[r].y, q[r].z, q[r].w};
+        uint32_t above = 0, four = 0;
+#pragma unroll
+        for (uint32_t c = 0; c < 4; ++c) {
+            const float h = __uint_as_float((uint32_t)v[c]);
+            const uint32_t s = crowd_sub_bin(h, bin_scale, bstar), key = order_key(h);
+            const bool in_bin = v[c] >= first && v[c] <= last, in_sub = in_bin && s == sstar;
+            above |= v[c] > last || (in_bin && s > sstar) ? 1u << c : 0u;
+            four |= in_sub ? 1u << c : 0u;
+            key_max = in_sub && key > key_max ? key : key_max;
+            not_key_min = in_sub && ~key > not_key_min ? ~key : not_key_min;
+        }
+        inside = (inside << 4) | four;
+        const uint32_t p = blk * kFusedKeysPerBlock + (r * WAVES + wave) * 256u + 4u * lane;
+        const uint32_t d_above = nibbles_to_dword(above, lane), d_equal = nibbles_to_dword(four, lane);
+        if ((lane & 7) == 0 && p < at.nwords * 64u) {
+            equal32[p >> 5] = d_equal;
+            if (p >= at.phase && p + 32u <= at.end) ubits[p >> 5] = d_above;
+            else atomicOr(&ubits[p >> 5], d_above);          // (a word that units share)
+        }
+    }
+    wave_max(key_max, not_key_min);
+    const uint32_t count = (uint32_t)__popc(inside), incl = wave_incl_scan(count);
+    __syncthreads();                             // everybody has the sub-bin: `chosen` and `wave_total` are used again
+    if (lane == 63) {
+        L.wave_total[wave] = incl;
+        if (incl != 0) { atomicMax(&L.n_before, key_max); atomicMax(&L.listed, not_key_min); }       // both start at 0
+    }
+    __syncthreads();
+    const uint32_t before = sum_of_waves_before(L.wave_total, wave, lane);
+    if (wave == WAVES - 1 && lane == 63 && before + incl != 0) {
+        L.chosen[0] = list_them ? atomicAdd(&state[0], before + incl) : 0u;
+        atomicMax(&state[2], L.n_before);
+        atomicMax(&state[3], L.listed);
+    }
+    __syncthreads();
+    if (list_them) {
+        uint32_t pos = L.chosen[0] + before + incl - count;
+#pragma unroll
+        for (uint32_t r = 0; r < BLOCKS; ++r) {
+            const int v[4] = {q[r].x, q[r].y, q[r].z, q[r].w};
+#pragma unroll
+            for (uint32_t c = 0; c < 4; ++c) {
+                if ((inside >> (4 * (BLOCKS - 1 - r) + c)) & 1u) {
+                    if (pos < kCandCap)
+                        ucand[pos] = make_uint2(order_key(__uint_as_float((uint32_t)v[c])),
+                                                blk * kFusedKeysPerBlock + (r * WAVES + wave) * 256u + 4u * lane + c);
+                    ++pos;
+                }
+            }
+        }
+    }
+    // Who is last?  Every wavefront's stores have reached the L2 before the workgroup counts itself, and the one thread that
+    // counts writes the L2 back where another XCD could not see it otherwise.
     __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0)
     __syncthreads();
-    // the unit's rank table from the finished bit map (read where the atomics were performed, in the L2: this
-    // workgroup's L1 may hold older copies of some words); a thread takes eight consecutive groups per sweep
-    constexpr int GPT = 8;
-    uint32_t running = rank_base;
-    for (uint32_t g0 = 0; g0 < at.nwords; g0 += GPT * kFusedThreads) {
-        const uint32_t first = g0 + (uint32_t)tid * GPT;
-        uint32_t c[GPT], mine = 0;
+    if (tid == 0) L.chosen[0] = __hip_atomic_fetch_add(&state[1], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (L.chosen[0] != blocks - 1) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+
+    // The unit's words in order, 256 consecutive ones per wavefront and sweep, the first of them requested right away.
+    constexpr int WPT = 4;
+    uint64_t word[WPT], eq[WPT];
+    auto load_words = [&](uint32_t sweep, uint64_t (&w)[WPT], uint64_t (&e)[WPT]) {
 #pragma unroll
-        for (int i = 0; i < GPT; ++i) {
-            const uint32_t g = first + i < at.nwords ? first + i : at.nwords - 1;      // clamped, masked below
-            const uint32_t lo = __hip_atomic_load(&ubits32[2 * g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint32_t hi = __hip_atomic_load(&ubits32[2 * g + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            c[i] = first + i < at.nwords ? (uint32_t)__popcll((((uint64_t)hi << 32) | lo) & at.mask(g)) : 0u;
-            mine += c[i];
+        for (int i = 0; i < WPT; ++i) {
+            const uint32_t g = sweep + wave * (64u * WPT) + 64u * i + lane, c = g < at.nwords ? g : at.nwords - 1;
+            w[i] = ubitmap[c];                   // (clamped, masked where they are used)
+            e[i] = equal[c];
         }
-        const uint32_t incl = wave_incl_scan(mine);
-        if (lane == 63) L.wave_total[wave] = incl;
+    };
+    load_words(0, word, eq);
+    uint32_t hi = __hip_atomic_load(&state[2], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t lo = ~__hip_atomic_load(&state[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool by_index = lo == hi || rem == crowd || !list_them;        // the first `rem` places of `equal` are selected
+    auto take_it = [&](uint32_t tile) {
+        if (tile < at.nwords * 64u) atomicOr(&ubits[tile >> 5], 1u << (tile & 31u));
+    };
+    const bool changed = lo != hi && rem != crowd;           // otherwise the words are what has been requested
+    if (!by_index) {
+        rank_candidates(rem, crowd, lo, hi, at.nwords * 64u, [&](auto f) {
+#pragma unroll 1
+            for (uint32_t i = tid; i < crowd; i += kFusedThreads) {
+                const uint2 c = ucand[i];
+                f(c.x, c.y);
+            }
+        }, take_it, L);
+    } else if (changed) {
+        // A crowd of several entropies that lie within one sub-bin: the range of their keys is cut into 4096 parts until one
+        // entropy is left (three times at most), by passes over the unit.
+        const uint32_t largest = hi;
+        auto each_four = [&](auto visit) {       // (four loads in flight; every wavefront takes whole blocks of 256 places)
+            for (uint32_t b = wave; b * 256u < at.nwords * 64u; b += 4 * WAVES) {
+                int4 w[4];
+#pragma unroll
+                for (uint32_t i = 0; i < 4; ++i) w[i] = four_at((b + i * WAVES) * 256u + 4u * lane);
+#pragma unroll
+                for (uint32_t i = 0; i < 4; ++i) visit((b + i * WAVES) * 256u + 4u * lane, w[i]);
+            }
+        };
+        auto key_of = [](int v) { return order_key(__uint_as_float((uint32_t)v)); };     // (-0.0f lies in no range: no entropy is)
+#pragma unroll 1
+        while (lo != hi) {
+            const uint32_t span = hi - lo;
+            const int bits = 32 - __builtin_clz(span), shift = bits > 12 ? bits - 12 : 0;
+            reinterpret_cast<uint4 *>(L.hist)[tid] = make_uint4(0, 0, 0, 0);
+            __syncthreads();
+            each_four([&](uint32_t, const int4 &w) {
+                const int v[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const uint32_t from_lo = key_of(v[c]) - lo;
+                    if (from_lo <= span && v[c] != INT32_MIN) atomicAdd(&L.hist[from_lo >> shift], 1u);
+                }
+            });
+            __syncthreads();
+            block_pick_bin<4096>(L.hist, rem, L.wave_total, L.chosen);
+            lo += (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[0]) << shift;
+            rem = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[1]);
+            const uint32_t part = (1u << shift) - 1u;
+            hi = hi - lo < part ? hi : lo + part;
+        }
+        each_four([&](uint32_t p, const int4 &w) {
+            const int v[4] = {w.x, w.y, w.z, w.w};
+            uint32_t above = 0, four = 0;
+#pragma unroll
+            for (uint32_t c = 0; c < 4; ++c) {
+                const uint32_t key = key_of(v[c]);
+                above |= key > lo && key <= largest && v[c] != INT32_MIN ? 1u << c : 0u;
+                four |= key == lo && v[c] != INT32_MIN ? 1u << c : 0u;
+            }
+            const uint32_t d_above = nibbles_to_dword(above, lane), d_equal = nibbles_to_dword(four, lane);
+            if ((lane & 7) == 0 && p < at.nwords * 64u) {
+                equal32[p >> 5] = d_equal;
+                if (d_above != 0) atomicOr(&ubits[p >> 5], d_above);
+            }
+        });
+    }
+    if (changed) {
+        __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0): all wavefronts' words are in the L2
         __syncthreads();
-        uint32_t before = 0, total = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        load_words(0, word, eq);
+    }
+    // How many of `equal` come before each word, which of them are taken, and how many selected tiles come before.
+    uint32_t equal_run = 0, rank_run = u * k;    // (every earlier unit holds exactly k wide tiles)
+    // ahead[i] = the sum of count over all words before my i-th, and `run` moved on by the sum of all
+    auto scan_words = [&](const uint32_t (&count)[WPT], uint32_t (&ahead)[WPT], uint32_t *run) {
+        uint32_t sum = 0;
 #pragma unroll
-        for (int w = 0; w < (int)(kFusedThreads / 64); ++w) {
-            const uint32_t wt = L.wave_total[w];
-            if (w < wave) before += wt;
-            total += wt;
+        for (int i = 0; i < WPT; ++i) {
+            const uint32_t upto = wave_incl_scan(count[i]);
+            ahead[i] = sum + upto - count[i];
+            sum += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
         }
-        uint32_t rank = running + before + incl - mine;
-#pragma unroll
-        for (int i = 0; i < GPT; ++i) {
-            if (first + i < at.nwords && (first + i != 0 || at.phase == 0)) uranks[first + i] = rank;
-            rank += c[i];
-        }
-        running += total;
         __syncthreads();
+        if (lane == 0) L.wave_total[wave] = sum;
+        __syncthreads();
+        const uint32_t before = *run + sum_of_waves_before(L.wave_total, wave, lane);
+#pragma unroll
+        for (int i = 0; i < WPT; ++i) ahead[i] += before;
+        uint32_t total = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < WAVES; ++w) total += L.wave_total[w];
+        *run += total;
+    };
+    for (uint32_t sweep = 0; sweep < at.nwords; sweep += WPT * kFusedThreads) {
+        const uint32_t g0 = sweep + wave * (64u * WPT) + lane;
+        uint64_t next_word[WPT], next_eq[WPT];
+        load_words(sweep + WPT * kFusedThreads, next_word, next_eq);
+        uint32_t count[WPT], ahead[WPT];
+#pragma unroll
+        for (int i = 0; i < WPT; ++i) {
+            const uint32_t g = g0 + 64u * i;
+            word[i] = g < at.nwords ? word[i] & at.mask(g) : 0ull;
+            eq[i] = g < at.nwords && by_index ? eq[i] : 0ull;
+            count[i] = (uint32_t)__popcll(eq[i]);
+        }
+        scan_words(count, ahead, &equal_run);
+#pragma unroll
+        for (int i = 0; i < WPT; ++i) {
+            uint64_t taken = ahead[i] < rem ? eq[i] : 0ull;
+            for (uint32_t over = ahead[i] + count[i]; taken != 0 && over > rem; --over) taken &= ~(1ull << (63 - __builtin_clzll(taken)));
+            word[i] |= taken;
+            count[i] = (uint32_t)__popcll(word[i]);
+        }
+        scan_words(count, ahead, &rank_run);
+#pragma unroll
+        for (int i = 0; i < WPT; ++i) {
+            const uint32_t g = g0 + 64u * i;
+            if (g < at.nwords) {
+                put_word(&ubitmap[g], at.mask(g), word[i]);
+                if (g != 0 || at.phase == 0) ranks[at.word0 + g] = ahead[i];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < WPT; ++i) { word[i] = next_word[i]; eq[i] = next_eq[i]; }
     }
 }
 
 __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *__restrict__ H, uint32_t n, uint32_t k,
                                                                   uint32_t unit0, float bin_scale,
                                                                   const uint32_t *__restrict__ lin_hist,
-                                                                  const uint32_t *__restrict__ fused,
-                                                                  const uint2 *__restrict__ cand,
+                                                                  uint32_t *__restrict__ fused,
+                                                                  uint2 *__restrict__ cand,
                                                                   const uint32_t *__restrict__ block_above,
+                                                                  const uint32_t *__restrict__ crowd_hist,
+                                                                  uint64_t *__restrict__ equal,
                                                                   uint64_t *__restrict__ bitmap,
                                                                   uint32_t *__restrict__ ranks)
 {
@@ -1138,8 +1297,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
     constexpr uint32_t GROUPS = kFusedKeysPerBlock / 64;     // 64-tile groups of a block
     const uint32_t u = unit0 + blockIdx.y, blk = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const float *uH = H + (uint64_t)u * n;
-    const uint2 *ucand = cand + (uint64_t)u * kCandCap;
+    uint2 *ucand = cand + (uint64_t)u * kCandCap;
     const UnitPlaces at(u, n);
     uint64_t *ubitmap = bitmap + at.word0;
     uint32_t *uranks = ranks + at.word0;
@@ -1158,16 +1316,17 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
     if ((uint32_t)tid < mygroups) my_word = ubitmap[group0 + tid] & at.mask(group0 + tid);
     uint32_t above_before = 0;
     for (uint32_t b = tid; b < blk; b += kFusedThreads) above_before += block_above[(uint64_t)u * gridDim.x + b];
-    if (tid == 0) { L.n_before = 0; L.n_equal = 0; }
+    if (tid == 0) { L.n_before = 0; L.listed = 0; }
     static_assert(kSubBins == kFusedThreads, "one sub-bin per thread");
-    uint32_t *sub_hist = L.sel.copies;           // the threshold bin's candidates by sub-bin
+    uint32_t *sub_hist = L.hist;                 // the threshold bin's candidates by sub-bin
     sub_hist[tid] = 0;
     if ((uint32_t)tid < GROUPS) { L.words[2 * tid] = (uint32_t)my_word; L.words[2 * tid + 1] = (uint32_t)(my_word >> 32); }
     block_pick_bin<kLinBins>(lin_hist + (uint64_t)u * kLinBins, k, L.wave_total, L.chosen);
     const uint32_t bstar = L.chosen[0], rem = L.chosen[1];
 
-    if (listed > kCandCap) {
-        if (blk == 0) resolve_unit_alone(uH, n, at, u * k, bin_scale, bstar, rem, ubitmap, uranks, L);
+    if (L.chosen[2] > crowd_from(n)) {           // (the same for all of the unit's workgroups)
+        resolve_crowd(H, n, k, u, blk, gridDim.x, bin_scale, bstar, rem, crowd_hist, fused + (uint64_t)u * 4, ucand,
+                      equal + (uint64_t)u * (n / 64 + 2), bitmap, ranks, L);
         return;
     }
     // the selected candidates: those of my block go into its words, those before it are counted
@@ -1192,13 +1351,14 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
             if ((uint32_t)r * kFusedThreads >= listed) continue;         // (the same for all threads)
             if ((uint32_t)r * kFusedThreads + tid < listed) {
                 sub[r] = linear_sub_bin(key_to_float(c[r].x), bin_scale, bstar);
-                atomicAdd(&sub_hist[sub[r]], 1u);
             }
+            // (many candidates are a crowd of tiles that are alike, as a rule)
+            if (listed > (uint32_t)AHEAD * kFusedThreads) add_one_each(sub_hist, sub[r], sub[r] != 0xffffffffu);
+            else if (sub[r] != 0xffffffffu) atomicAdd(&sub_hist[sub[r]], 1u);
         }
         __syncthreads();
         block_pick_bin<kSubBins>(sub_hist, rem, L.wave_total, L.chosen + 3);
-        const uint32_t sstar = L.chosen[3], rem2 = L.chosen[4];
-        uint32_t *list_key = L.sel.copies + kSubBins, *list_tile = L.equal_tile;
+        const uint32_t sstar = L.chosen[3], rem2 = L.chosen[4], nl = L.chosen[5];
         uint32_t in_sub = 0;                     // bit r: my r-th candidate lies in the threshold's sub-bin
 #pragma unroll
         for (int r = 0; r < CPT; ++r) {
@@ -1207,26 +1367,31 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
                 if (sub[r] > sstar) take_it(c[r].y);
                 else if (sub[r] == sstar) {
                     in_sub |= 1u << r;
-                    const uint32_t at = atomicAdd(&L.n_equal, 1u);
-                    if (at < kFusedThreads) { list_key[at] = c[r].x; list_tile[at] = c[r].y; }
+                    if (nl <= kFusedThreads) {
+                        const uint32_t at = atomicAdd(&L.listed, 1u);
+                        if (at < kFusedThreads) L.list[at] = ((uint64_t)c[r].x << 32) | (uint32_t)~c[r].y;
+                    }
                 }
             }
         }
-        __syncthreads();
-        const uint32_t nl = L.n_equal;
         if (nl <= kFusedThreads) {
-            if ((uint32_t)tid < nl) {
-                const uint32_t key = list_key[tid], tile = list_tile[tid];
-                uint32_t ahead = 0;
-                for (uint32_t i = 0; i < nl; ++i) {
-                    const uint32_t ki = list_key[i];
-                    ahead += (ki > key || (ki == key && list_tile[i] < tile)) ? 1u : 0u;
-                }
-                if (ahead < rem2) take_it(tile);
-            }
+            __syncthreads();
+            place_listed(rem2, nl, take_it, L);
         } else {
-            __syncthreads();                     // the list is dropped: its memory serves the radix select
-            rank_candidates(rem2, [&](auto f) {
+            uint32_t key_max = 0, not_key_min = 0;
+#pragma unroll
+            for (int r = 0; r < CPT; ++r) {
+                const bool mine = (in_sub >> r) & 1u;
+                key_max = mine && c[r].x > key_max ? c[r].x : key_max;
+                not_key_min = mine && ~c[r].x > not_key_min ? ~c[r].x : not_key_min;
+            }
+            wave_max(key_max, not_key_min);
+            __syncthreads();                     // (L.chosen has been read)
+            if (tid == 0) { L.chosen[0] = 0; L.chosen[1] = 0; }
+            __syncthreads();
+            if (lane == 0) { atomicMax(&L.chosen[0], key_max); atomicMax(&L.chosen[1], not_key_min); }
+            __syncthreads();
+            rank_candidates(rem2, nl, ~L.chosen[1], L.chosen[0], at.nwords * 64u, [&](auto f) {
 #pragma unroll
                 for (int r = 0; r < CPT; ++r)
                     if ((in_sub >> r) & 1u) f(c[r].x, c[r].y);

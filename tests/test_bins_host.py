@@ -67,6 +67,8 @@ int main()
         const uint32_t bp = linear_bin(p, scale), bq = linear_bin(q, scale);
         check(bp <= bq && bq < kLinBins, "bins in key order", q, bq);
         if (bp == bq) check(linear_sub_bin(p, scale, bp) <= linear_sub_bin(q, scale, bq), "sub-bins in key order", q, bq);
+        if (bp == bq) check(crowd_sub_bin(p, scale, bp) <= crowd_sub_bin(q, scale, bq) && crowd_sub_bin(q, scale, bq) < kSubBins, "a crowd's sub-bins in key order", q, bq);
+        if (bq == 0 && v[i] != 0x80000000u) check((crowd_sub_bin(q, scale, 0) == 1) == (v[i] == 0), "all-zero tiles by themselves", q, bq);
         check(__float_as_uint(key_to_float(order_key(q))) == v[i], "a key turns back into its entropy", q, bq);
     }
     return 0;

@@ -376,6 +376,33 @@ def test_phase_by_phase_calls_write_the_same_stream(tahq):
         assert np.array_equal(whole.view.cpu().numpy(), o32.encode(ocfg, x))
 
 
+@pytest.mark.parametrize("S,M,A,alike", [(77, 13, 0, False), (77, 13, 0, True), (61, 15, 80, False), (401, 101, 0, False),
+                                         (401, 101, 0, True), (1201, 99, 0, True)])
+def test_phase_by_phase_calls_off_the_64_tile_boundaries(tahq, S, M, A, alike):
+    # units that share bit map words, which the entropy phase clears and the selection phase adds to, over buffers full of ones:
+    # one launch, one with allocation tiles, two launches; `alike`: more tiles of one entropy at the threshold than are listed
+    G, B = 16, 3
+    rng = np.random.default_rng(S + M)
+    x = rng.standard_normal((B, S, M * G)).astype(np.float32)
+    if alike:
+        x[:, rng.permutation(S)[:S // 2], :] = 0.0
+    d_in = to_device(x)
+    for budget in (3.3, 3.8):
+        _say(f"[case] phases one by one, 3 units x {S * M} tiles, A={A or G}, alike={alike}, budget {budget}")
+        cfg = tahq.make_config(B, S, M * G, G, tahq.F32, budget, alloc_tile=A)
+        parts, ws = Guarded(tahq.tahq_packed_size(cfg)), Guarded(tahq.tahq_workspace_size(cfg))
+        parts.view.fill_(0xFF)
+        ws.view.fill_(0xFF)
+        for phase in (tahq.PHASE_PROLOGUE, tahq.PHASE_ENTROPY, tahq.PHASE_SELECT, tahq.PHASE_QUANT):
+            tahq.tahq_encode_phases(cfg, d_in, parts.view, ws.view, phase)
+        torch.cuda.synchronize()
+        parts.check()
+        ws.check()
+        ocfg = o32.make_cfg(B, S, M * G, G, tahq.F32, budget, alloc_tile=A)
+        compare_streams(parts.view.cpu().numpy(), o32.encode(ocfg, x), B * S * M, G, B,
+                        o32.k_per_unit(ocfg) * o32.tiles_per_alloc(ocfg))
+
+
 def test_selection_of_a_large_unit_without_its_histogram_ends(tahq):
     # the selection phase by itself over cleared scratch: no bin of the histogram holds the threshold.  What it writes means
     # nothing, but it ends, and inside its buffers
@@ -681,6 +708,38 @@ def test_large_units_off_the_64_tile_boundaries(tahq, B, n, ties):
         check_case(tahq, x, B, n, G, G, tahq.F32, budget)
     x16 = np.ascontiguousarray(workloads.f32_to_bf16_bits(x).reshape(B, n, G))
     check_case(tahq, x16, B, n, G, 8, tahq.BF16, 2.6, low_bits=2)
+
+
+@pytest.mark.parametrize("B,n", [(2, 40001), (1, 131072), (2, 98305)])
+@pytest.mark.parametrize("spread", (0.05, 0.01, 0.003, 1e-3))
+def test_large_units_of_nearly_equal_tiles(tahq, B, n, spread):
+    # entropies within a few bins, a few sub-bins or one sub-bin below ln G: the crowd's way with a short list of candidates, with
+    # a long one, and with too many for a list that are not all alike
+    G = 16
+    rng = np.random.default_rng(n)
+    x = (1.0 + spread * rng.standard_normal((B, n, G))).astype(np.float32)
+    _say(f"[case] {B} units x {n} nearly equal tiles, spread {spread}")
+    for budget in (3.02, 3.4, 3.97):
+        check_case(tahq, x, B, n, G, G, tahq.F32, budget)
+
+
+@pytest.mark.parametrize("n,alike", [(40001, 1024), (40001, 1025), (40001, 2400), (40001, 2600), (300001, 16000), (300001, 19000)])
+def test_large_units_with_alike_tiles_at_the_threshold(tahq, n, alike):
+    # tiles of one entropy in a bin of their own, or with a one-hot tile and one of a single dominant element beside them: placed
+    # from the candidate list one by one or by runs of places, or as a crowd by index alone
+    G = 16
+    rng = np.random.default_rng(alike)
+    for value in (1.5, 0.0):
+        x = rng.standard_normal((1, n, G)).astype(np.float32)
+        x[0, rng.permutation(n)[:alike]] = value
+        if value == 0.0:
+            x[0, :40] = 0.0
+            x[0, :20, 3] = 7.0
+            x[0, 20:40, 3:5] = (1e6, 1.0)
+        below = 0 if value else n - alike - 40                # tiles ahead of them: none, or nearly all others
+        for k in (below + 1, below + alike // 2, below + alike - 60):
+            _say(f"[case] {alike} of {n} tiles alike ({value}), {k} wide")
+            check_case(tahq, x, 1, n, G, G, tahq.F32, 3.0 + k / n)
 
 
 def test_65536_units_just_off_the_64_tile_boundaries(tahq):

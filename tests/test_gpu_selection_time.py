@@ -62,3 +62,19 @@ def test_units_of_the_single_launch_take_about_as_long_whatever_their_size(tahq)
     base = _encode_us(tahq, _normal(1, 1024, 1600)[0], 64, 3.5)
     assert _encode_us(tahq, _normal(1, 1024, 2048)[0], 64, 3.5) < 1.7 * base
     assert _encode_us(tahq, _normal(1, 1024, 1024)[0], 32, 3.5) < 1.7 * base
+
+
+@pytest.mark.parametrize("B,S,C,G", [(3, 777, 1600, 16), (1, 4097, 5120, 32)])
+def test_tiles_that_are_alike_do_not_slow_the_two_launch_selection(tahq, B, S, C, G):
+    # units of 77700 and of 655520 tiles, a fifth of them with one entropy, which holds the threshold: 0 and ln G
+    x, gen = _normal(B, S, C)
+    base = _encode_us(tahq, x, G, 3.5)
+    zero, level = _encode_us(tahq, _alike(x, gen, 0.0), G, 3.9), _encode_us(tahq, _alike(x, gen, 1.5), G, 3.1)
+    assert zero < 1.7 * base and level < 1.7 * base
+
+
+def test_a_million_ordinary_tiles_do_not_overwhelm_the_two_launch_selection(tahq):
+    # N(0,1) tiles of 64 channels put 1.6 % of a unit into one bin: more than the list of candidates takes
+    base = _encode_us(tahq, _normal(1, 4097, 8256)[0], 64, 3.5)
+    twice = _encode_us(tahq, _normal(1, 8193, 8256)[0], 64, 3.5)
+    assert twice < 3.0 * base

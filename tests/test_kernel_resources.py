@@ -42,8 +42,8 @@ def kernels():
     return k
 
 
-def test_no_kernel_spills_vector_registers(kernels):
-    assert not [n for n, k in kernels.items() if k[".vgpr_spill_count"]]
+def test_no_kernel_needs_scratch_memory(kernels):
+    assert not [n for n, k in kernels.items() if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]]
 
 
 def test_allocation_tile_entropies_keep_their_wavefronts(kernels):
