@@ -95,7 +95,7 @@ __device__ __forceinline__ void add_one_each(uint32_t *hist, uint32_t bin, bool 
 
 // Which of BINS bins holds the `want`-th largest value (bins counted from the top), how many values are wanted inside it and how
 // many it holds, found by the whole workgroup of 1024 threads: BINS / 1024 bins per thread and a scan.  chosen[0..2] is written
-// before the last of its two barriers, and all three are 0 where there are fewer than `want` values; `totals`: 16 words of LDS.
+// before the last of its two barriers, and left as it was where there are fewer than `want` values; `totals`: 16 words of LDS.
 // (One wavefront with a sixteenth of the bins per lane, its loads as far apart, took 1.5 us longer.)
 template <int BINS>
 __device__ __forceinline__ void block_pick_bin(const uint32_t *hist, uint32_t want, uint32_t *totals, uint32_t *chosen)
@@ -122,7 +122,6 @@ __device__ __forceinline__ void block_pick_bin(const uint32_t *hist, uint32_t wa
     for (int i = 0; i < PER; ++i) mine += c[i];
     const uint32_t incl = wave_incl_scan(mine);
     if (lane == 63) totals[wave] = incl;
-    if (tid == 0) { chosen[0] = 0; chosen[1] = 0; chosen[2] = 0; }
     __syncthreads();
     uint32_t above = sum_of_waves_before(totals, wave, lane) + incl - mine;
     if (above < want && want <= above + mine) {
@@ -664,7 +663,7 @@ __global__ __launch_bounds__(kSmallUnitThreads) void k_select_small(const float 
         }
         __syncthreads();
     };
-    if (crowd <= kSmallListCap) {
+    if (__builtin_expect(crowd <= kSmallListCap, 1)) {
         place_directly([&](int v) { return v > last; }, [&](int v) { return v >= first; });
     } else {
         // More tiles in the bin than the list takes: it is cut again, 4096 parts at a time, until they fit or all share one
@@ -889,6 +888,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *
         const uint32_t p = place0 + r * (WAVES * 256u);
         q[r] = *reinterpret_cast<const int4 *>(uH + (p < top ? p : top));
     }
+    if (tid == 0) { chosen[0] = 0; chosen[1] = 0; chosen[2] = 0; }           // (for a histogram that does not hold k)
     block_pick_bin<kLinBins>(lin_hist + (uint64_t)u * kLinBins, k, wave_above, chosen);
     const uint32_t bstar = (uint32_t)__builtin_amdgcn_readfirstlane((int)chosen[0]);
     // the bit patterns of that bin, first and last, as signed integers (negative values and NaN with the sign bit set lowest)
@@ -915,7 +915,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *
             else atomicOr(&ubits[p >> 5], d);    // (a word that units share: cleared by an earlier kernel)
         }
     }
-    if (chosen[2] > crowd_from(n)) {             // (the same for all of the unit's workgroups)
+    if (__builtin_expect(chosen[2] > crowd_from(n), 0)) {    // (the same for all of the unit's workgroups)
         sub_hist[tid] = 0;
         __syncthreads();
         if (inside != 0) {
@@ -1316,6 +1316,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
     if ((uint32_t)tid < mygroups) my_word = ubitmap[group0 + tid] & at.mask(group0 + tid);
     uint32_t above_before = 0;
     for (uint32_t b = tid; b < blk; b += kFusedThreads) above_before += block_above[(uint64_t)u * gridDim.x + b];
+    if (tid < 6) L.chosen[tid] = 0;              // (for histograms that do not hold as many as are wanted)
     if (tid == 0) { L.n_before = 0; L.listed = 0; }
     static_assert(kSubBins == kFusedThreads, "one sub-bin per thread");
     uint32_t *sub_hist = L.hist;                 // the threshold bin's candidates by sub-bin
@@ -1324,7 +1325,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
     block_pick_bin<kLinBins>(lin_hist + (uint64_t)u * kLinBins, k, L.wave_total, L.chosen);
     const uint32_t bstar = L.chosen[0], rem = L.chosen[1];
 
-    if (L.chosen[2] > crowd_from(n)) {           // (the same for all of the unit's workgroups)
+    if (__builtin_expect(L.chosen[2] > crowd_from(n), 0)) {  // (the same for all of the unit's workgroups)
         resolve_crowd(H, n, k, u, blk, gridDim.x, bin_scale, bstar, rem, crowd_hist, fused + (uint64_t)u * 4, ucand,
                       equal + (uint64_t)u * (n / 64 + 2), bitmap, ranks, L);
         return;
