@@ -6,7 +6,8 @@
 // (dequantize); and, for the backward direction, Sec. 3.5 / Alg. 1 steps 6-7 with the appendix's gradient
 // scaling (fixed-point compressor, tahq_naive_*).
 //
-// Numerics contract (identical results on any mapping of tiles to lanes):
+// Numerics contract (identical results on any mapping of tiles to lanes; a signalling NaN in the input, which no arithmetic
+// produces, is the exception: the minimum and maximum of its tile depend on the lanes that share it):
 //   * all arithmetic is IEEE binary32, no contraction (-ffp-contract=off); fused multiply-adds
 //     only where written (__builtin_fmaf);
 //   * sums over a tile use the adjacent-pair binary tree; an allocation tile of several quantization

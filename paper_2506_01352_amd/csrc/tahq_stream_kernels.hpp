@@ -1,11 +1,12 @@
 // Streaming kernels: entropy (Eq. 1-2), transform + quantize + pack (Eq. 3-4, Sec. 3.4),
 // decode (Alg. 1 step 5).
 //
-// Mapping: ONE LANE OWNS ONE TILE.  The codec is bound by vector-ALU issue as much as by HBM, so the
-// per-tile work (reductions, butterflies, quantizer parameters) is kept free of cross-lane traffic
-// and of lane-redundant scalar work: a workgroup stages TILES consecutive tiles through LDS with
-// coalesced 128-bit global accesses, then every lane pulls its whole tile into registers.  LDS rows
-// are padded by 16 bytes so that the lane-per-row 128-bit reads are bank-conflict free.
+// Mapping: A LANE OWNS A TILE, or, of a tile of more than 128 bytes or in a tensor of few tiles, one part of two or four.  The
+// codec is bound by vector-ALU issue as much as by HBM, so the per-tile work (reductions, butterflies, quantizer
+// parameters) crosses lanes in its last one or two levels only, inside a quad.  A workgroup stages TILES consecutive tiles
+// through LDS with coalesced 128-bit global accesses, then every lane pulls its part into registers; LDS rows are padded by
+// 16 bytes so that the lane-per-row 128-bit reads are bank-conflict free.  (The decoder: a wavefront by itself, see there.  The
+// entropies of allocation tiles of several quantization tiles: always one lane per quantization tile.)
 #pragma once
 #include "tahq_common.hpp"
 
@@ -218,8 +219,9 @@ struct Prologue {
 };
 
 // Thread `gid` of `threads` (at least 64).  The small launches of a call cost more than what they do, so the prologue rides
-// along with the call's first kernel, at its end, where nothing waits for it: in front of the entropies (encode of 1024 x 1600 channels: 18.8 -> 17.5 us), or of the
-// quantizer where all tiles have one width (fp32 [1,128,512], encode and decode: 19.7 -> 16.8).
+// along with the call's first kernel, at its end, where nothing waits for it: instead of a launch in front of the entropies
+// (encode of 1024 x 1600 channels: 18.8 -> 17.5 us), or of the quantizer where all tiles have one width (fp32 [1,128,512],
+// encode and decode: 19.7 -> 16.8).
 __device__ __forceinline__ void write_prologue(const Prologue &p, uint32_t gid, uint32_t threads)
 {
     if (p.packed != nullptr && gid < 64) {
