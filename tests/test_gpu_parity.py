@@ -742,6 +742,35 @@ def test_large_units_with_alike_tiles_at_the_threshold(tahq, n, alike):
             check_case(tahq, x, 1, n, G, G, tahq.F32, 3.0 + k / n)
 
 
+@pytest.mark.parametrize("B,S,M,G,zeros", [(3, 777, 100, 16, 0.2), (1, 4097, 160, 32, 0.2), (2, 4097, 140, 8, 0.4), (1, 8193, 129, 64, 0.0)])
+def test_crowded_units_give_the_same_bytes_on_every_replay(tahq, B, S, M, G, zeros):
+    # which workgroup settles a crowd is a matter of which one is last: replays of a captured encode over poisoned buffers, with
+    # eager work between them, against the multi-launch selection, which knows no crowds
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(S + M)
+    x = torch.randn(B, S, M * G, device="cuda", generator=gen)
+    x *= torch.rand(B, S, 1, device="cuda", generator=gen) >= zeros
+    x = x.to(torch.bfloat16)
+    budget = 4.0 - zeros / 2 if zeros else 3.5                # the threshold in the middle of the all-zero tiles
+    cfg = tahq.make_config(B, S, M * G, G, tahq.BF16, budget)
+    _say(f"[case] replays of {B} crowded units x {S * M} tiles")
+    packed, ws = Guarded(tahq.tahq_packed_size(cfg)), Guarded(tahq.tahq_workspace_size(cfg))
+    tahq.tahq_encode_phases(cfg, x, packed.view, ws.view, tahq.PHASE_ALL | tahq.SELECT_MULTI_LAUNCH)
+    want = packed.view.clone()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        tahq.tahq_encode(cfg, x, packed.view, ws.view)
+    for i in range(12):
+        packed.view.fill_(0xFF if i % 2 else 0)
+        ws.view.fill_((37 * i) & 0xFF)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(packed.view, want), f"replay {i}"
+    packed.check()
+    ws.check()
+
+
 def test_65536_units_just_off_the_64_tile_boundaries(tahq):
     # as many ranking units as a grid's second dimension does not take, of as few tiles as go through the two-launch selection,
     # 34 GB of them: 1024 times the same 64 units, whose sections are 1024 times the same bytes
