@@ -70,7 +70,7 @@ def test_tiles_that_are_alike_do_not_slow_the_two_launch_selection(tahq, B, S, C
     x, gen = _normal(B, S, C)
     base = _encode_us(tahq, x, G, 3.5)
     zero, level = _encode_us(tahq, _alike(x, gen, 0.0), G, 3.9), _encode_us(tahq, _alike(x, gen, 1.5), G, 3.1)
-    assert zero < 1.7 * base and level < 1.7 * base
+    assert zero < 1.9 * base and level < 1.9 * base          # 1.5 and 1.25 as measured; 2.2 and 25 for what it guards against
 
 
 def test_a_million_ordinary_tiles_do_not_overwhelm_the_two_launch_selection(tahq):
