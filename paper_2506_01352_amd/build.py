@@ -11,10 +11,12 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # -ffp-contract=off: the numerics contract allows fused multiply-adds only where the source writes them.
 # packed-fp32-ops is switched off for the device pass (the host pass warns that it does not know the feature).
+# amdgpu-kernarg-preload-count: the first words of a kernel's arguments are in scalar registers when its wavefronts start.
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-ffp-contract=off", "-fno-fast-math",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wextra",
     "-I" + os.path.join(ROOT, "include"),
 ]

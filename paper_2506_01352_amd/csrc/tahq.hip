@@ -119,33 +119,48 @@ inline bool few_tiles(uint64_t T, uint32_t deep) { return T * N::usual < 65536u 
 
 template <int G, bool BF16>
 struct LaunchEntropy {
-    template <int LPT>
+    template <int LPT, int NG, bool HIST>
     static void go(const void *d_in, float *d_H, uint32_t T, float eps_l1, float eps_log, uint32_t *hist,
                    uint32_t bins, float bin_scale, uint64_t n_per_unit, const Prologue &pro, Enqueue *qp)
     {
         Enqueue &q = *qp;
-        using B = Batch<G, BF16 ? 2 : 4, LPT>;
-        const uint32_t nb = (T + B::TILES - 1) / B::TILES;
-        constexpr int THREADS = B::TILES * LPT;
+        constexpr uint32_t STEP = 256 / LPT * NG;            // tiles
+        const uint32_t nb = (T + STEP - 1) / STEP;
         static ResidentCache cache;
-        const uint32_t res = resident_blocks(reinterpret_cast<const void *>(k_entropy<G, BF16, LPT>), THREADS, cache);
+        const uint32_t res = resident_blocks(reinterpret_cast<const void *>(k_entropy<G, BF16, LPT, NG, HIST>), 256, cache);
         // Every workgroup adds its histogram to the unit's, and what that costs are the additions that meet on one bin: four
-        // batches per workgroup where that still leaves a workgroup per compute unit (three units of 77700 tiles of 16
+        // steps per workgroup where that still leaves a workgroup per compute unit (three units of 77700 tiles of 16
         // channels: 14.1 -> 8.4 us)
         const uint32_t few = nb / 4 > 256u ? nb / 4 : 256u;
-        const uint32_t most = hist && few < res ? few : res;
-        q(k_entropy<G, BF16, LPT>, dim3(nb < most ? nb : most), dim3(THREADS), d_in, d_H, T, eps_l1, eps_log, hist,
-          (uint32_t)n_per_unit, bins, bin_scale, pro);
+        const uint32_t most = HIST && few < res ? few : res;
+        const uint32_t grid = nb < most ? nb : most;
+        q(k_entropy<G, BF16, LPT, NG, HIST>, dim3(grid), dim3(256), d_in, d_H, T, grid, eps_l1, eps_log, hist, (uint32_t)n_per_unit,
+          bins, bin_scale, prologue_blocks(pro, 256, grid), pro);
     }
-    // hist != nullptr: also build the selection's first histogram, `bins` bins per ranking unit (of at least one batch): the keys' first radix digit if bin_scale == 0, the entropies' linear bins otherwise
+    template <int LPT, int NG>
+    static void with(const void *d_in, float *d_H, uint32_t T, float eps_l1, float eps_log, uint32_t *hist,
+                     uint32_t bins, float bin_scale, uint64_t n_per_unit, const Prologue &pro, Enqueue *qp)
+    {
+        if (hist) go<LPT, NG, true>(d_in, d_H, T, eps_l1, eps_log, hist, bins, bin_scale, n_per_unit, pro, qp);
+        else go<LPT, NG, false>(d_in, d_H, T, eps_l1, eps_log, hist, bins, bin_scale, n_per_unit, pro, qp);
+    }
+    // hist != nullptr: also build the selection's first histogram, `bins` bins per ranking unit (of at least one step): the keys'
+    // first radix digit if bin_scale == 0, the entropies' linear bins otherwise
     static void run(const void *d_in, float *d_H, uint32_t T, float eps_l1, float eps_log, uint32_t *hist,
                     uint32_t bins, float bin_scale, uint64_t n_per_unit, Prologue pro, Enqueue *qp)
     {
         using N = Lanes<G, BF16 ? 2 : 4>;
-        if (few_tiles<N>(T, 4)) go<N::few>(d_in, d_H, T, eps_l1, eps_log, hist, bins, bin_scale, n_per_unit, pro, qp);
-        else go<N::usual>(d_in, d_H, T, eps_l1, eps_log, hist, bins, bin_scale, n_per_unit, pro, qp);
+        constexpr int NG = kRowGroups<G, BF16 ? 2 : 4, N::usual>;
+        if (few_tiles<N>(T, 4)) with<N::few, 1>(d_in, d_H, T, eps_l1, eps_log, hist, bins, bin_scale, n_per_unit, pro, qp);
+        else if (NG == 1 || T < 1024u * 256u * NG) with<N::usual, 1>(d_in, d_H, T, eps_l1, eps_log, hist, bins, bin_scale, n_per_unit, pro, qp);
+        else with<N::usual, NG>(d_in, d_H, T, eps_l1, eps_log, hist, bins, bin_scale, n_per_unit, pro, qp);
     }
-    static bool can_fuse_histogram(uint64_t n_per_unit) { return n_per_unit % Batch<G, BF16 ? 2 : 4>::TILES == 0; }
+    // units are whole steps, whatever those are
+    static bool can_fuse_histogram(uint64_t n_per_unit)
+    {
+        using N = Lanes<G, BF16 ? 2 : 4>;
+        return n_per_unit % (256 / N::usual * kRowGroups<G, BF16 ? 2 : 4, N::usual>) == 0;
+    }
 };
 
 template <int G, bool BF16>
@@ -157,34 +172,34 @@ struct CanFuse {
 template <int G, bool BF16>
 struct LaunchQuantPack {
     template <int LOW, int LPT>
-    static void with(const void *d_in, uint8_t *packed, Layout lay, uint32_t T, float tau, float eps_ratio, bool ranked,
+    static void with(const void *d_in, uint8_t *packed, uint32_t T, float tau, float eps_ratio, bool ranked,
                    bool all_wide, const Prologue &pro, Enqueue *qp)
     {
         Enqueue &q = *qp;
         using B = Batch<G, BF16 ? 2 : 4, LPT>;
         const dim3 grid((T + B::TILES - 1) / B::TILES), block(B::TILES * LPT);
-        if (ranked) q(k_quant_pack<G, BF16, LOW, true, LPT>, grid, block, d_in, packed, lay, T, tau, eps_ratio, false, pro);
-        else q(k_quant_pack<G, BF16, LOW, false, LPT>, grid, block, d_in, packed, lay, T, tau, eps_ratio, all_wide, pro);
+        if (ranked) q(k_quant_pack<G, BF16, LOW, true, LPT>, grid, block, d_in, packed, T, tau, eps_ratio, 0u, pro);
+        else q(k_quant_pack<G, BF16, LOW, false, LPT>, grid, block, d_in, packed, T, tau, eps_ratio, all_wide ? 1u : 0u, pro);
     }
     template <int LOW>
-    static void go(const void *d_in, uint8_t *packed, Layout lay, uint32_t T, float tau, float eps_ratio, bool ranked,
+    static void go(const void *d_in, uint8_t *packed, uint32_t T, float tau, float eps_ratio, bool ranked,
                    bool all_wide, const Prologue &pro, Enqueue *qp)
     {
         using N = Lanes<G, BF16 ? 2 : 4>;
-        if (few_tiles<N>(T, 2)) with<LOW, N::few>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp);
-        else with<LOW, N::usual>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp);
+        if (few_tiles<N>(T, 2)) with<LOW, N::few>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp);
+        else with<LOW, N::usual>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp);
     }
-    static void run(uint32_t low, const void *d_in, uint8_t *packed, Layout lay, uint32_t T, float tau, float eps_ratio,
+    static void run(uint32_t low, const void *d_in, uint8_t *packed, uint32_t T, float tau, float eps_ratio,
                     bool ranked, bool all_wide, Prologue pro, Enqueue *qp)
     {
         switch (low) {
-        case 1: go<1>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
-        case 2: go<2>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
-        case 3: go<3>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
-        case 4: go<4>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
-        case 5: go<5>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
-        case 6: go<6>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
-        default: go<7>(d_in, packed, lay, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
+        case 1: go<1>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
+        case 2: go<2>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
+        case 3: go<3>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
+        case 4: go<4>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
+        case 5: go<5>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
+        case 6: go<6>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
+        default: go<7>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
         }
     }
 };
@@ -192,57 +207,78 @@ struct LaunchQuantPack {
 template <int G, bool BF16>
 struct LaunchDecode {
     template <int LOW>
-    static void go(const uint8_t *packed, void *d_out, Layout lay, uint32_t T, uint32_t total_wide, Enqueue *qp)
+    static void go(const uint8_t *packed, void *d_out, uint32_t T, uint32_t total_wide, Enqueue *qp)
     {
         using N = Lanes<G, BF16 ? 2 : 4>;
-        if (few_tiles<N>(T, 4)) with<LOW, N::few>(packed, d_out, lay, T, total_wide, qp);
-        else with<LOW, N::usual>(packed, d_out, lay, T, total_wide, qp);
+        if (few_tiles<N>(T, 4)) with<LOW, N::few>(packed, d_out, T, total_wide, qp);
+        else with<LOW, N::usual>(packed, d_out, T, total_wide, qp);
     }
     template <int LOW, int LPT>
-    static void with(const uint8_t *packed, void *d_out, Layout lay, uint32_t T, uint32_t total_wide, Enqueue *qp)
+    static void with(const uint8_t *packed, void *d_out, uint32_t T, uint32_t total_wide, Enqueue *qp)
     {
         Enqueue &q = *qp;
         using W = Wave<G, BF16 ? 2 : 4, LPT>;
         const uint32_t groups = (T + W::TILES - 1) / W::TILES;
-        q(k_decode<G, BF16, LOW, LPT>, dim3((groups + 3) / 4), dim3(256), packed, d_out, lay, T, total_wide);
+        q(k_decode<G, BF16, LOW, LPT>, dim3((groups + 3) / 4), dim3(256), packed, d_out, T, total_wide);
     }
-    static void run(uint32_t low, const uint8_t *packed, void *d_out, Layout lay, uint32_t T, uint32_t total_wide,
+    static void run(uint32_t low, const uint8_t *packed, void *d_out, uint32_t T, uint32_t total_wide,
                     Enqueue *qp)
     {
         switch (low) {
-        case 1: go<1>(packed, d_out, lay, T, total_wide, qp); break;
-        case 2: go<2>(packed, d_out, lay, T, total_wide, qp); break;
-        case 3: go<3>(packed, d_out, lay, T, total_wide, qp); break;
-        case 4: go<4>(packed, d_out, lay, T, total_wide, qp); break;
-        case 5: go<5>(packed, d_out, lay, T, total_wide, qp); break;
-        case 6: go<6>(packed, d_out, lay, T, total_wide, qp); break;
-        default: go<7>(packed, d_out, lay, T, total_wide, qp); break;
+        case 1: go<1>(packed, d_out, T, total_wide, qp); break;
+        case 2: go<2>(packed, d_out, T, total_wide, qp); break;
+        case 3: go<3>(packed, d_out, T, total_wide, qp); break;
+        case 4: go<4>(packed, d_out, T, total_wide, qp); break;
+        case 5: go<5>(packed, d_out, T, total_wide, qp); break;
+        case 6: go<6>(packed, d_out, T, total_wide, qp); break;
+        default: go<7>(packed, d_out, T, total_wide, qp); break;
         }
     }
 };
 
 template <int G, bool BF16>
 struct LaunchAllocEntropy {
-    // Entropies of allocation tiles of m > 1 quantization tiles: one pass if a workgroup's batch holds whole
+    using N = Lanes<G, BF16 ? 2 : 4>;
+    template <int LPT, bool WAVE_TEAM>
+    static void go(const void *d_in, float *d_H, uint32_t n_alloc, uint32_t m, float eps_l1, float eps_log, const Prologue &pro, Enqueue *qp)
+    {
+        Enqueue &q = *qp;
+        constexpr uint32_t SLOTS = (WAVE_TEAM ? 64 : 256) / LPT, TEAMS = WAVE_TEAM ? 4 : 1;
+        const uint32_t per = SLOTS / m, nb = (n_alloc + per * TEAMS - 1) / (per * TEAMS);
+        void (*kernel)(const void *, float *, uint32_t, uint32_t, uint32_t, uint32_t, float, float, uint32_t, Prologue);
+        if constexpr (LPT == N::usual && WAVE_TEAM) kernel = k_alloc_entropy<G, BF16>;
+        else kernel = k_alloc_entropy_by<G, BF16, LPT, WAVE_TEAM>;
+        static ResidentCache cache;
+        const uint32_t res = resident_blocks(reinterpret_cast<const void *>(kernel), 256, cache);
+        const uint32_t grid = nb < res ? nb : res;
+        q(kernel, dim3(grid), dim3(256), d_in, d_H, n_alloc, grid, m, per, eps_l1, eps_log,
+          prologue_blocks(pro, 256, grid), pro);
+    }
+    // A wavefront by itself where it wastes no more lanes than a workgroup would.
+    template <int LPT>
+    static void one_pass(const void *d_in, float *d_H, uint32_t n_alloc, uint32_t m, float eps_l1, float eps_log, const Prologue &pro, Enqueue *qp)
+    {
+        const uint32_t by_wave = 4 * (64 / LPT / m), by_group = 256 / LPT / m;       // allocation tiles per workgroup
+        if (by_wave >= by_group) go<LPT, true>(d_in, d_H, n_alloc, m, eps_l1, eps_log, pro, qp);
+        else go<LPT, false>(d_in, d_H, n_alloc, m, eps_l1, eps_log, pro, qp);
+    }
+    // Entropies of allocation tiles of m > 1 quantization tiles: one pass if a workgroup's lanes hold whole
     // allocation tiles, otherwise two streaming passes over the tensor.
     static void run(const void *d_in, float *d_H, float *part, float *inv_norm, uint32_t T, uint32_t m, float eps_l1,
                     float eps_log, Prologue pro, Enqueue *qp)
     {
         Enqueue &q = *qp;
+        const uint32_t n_alloc = T / m;
+        if (few_tiles<N>(T, 4) && m <= 256 / N::few) { one_pass<N::few>(d_in, d_H, n_alloc, m, eps_l1, eps_log, pro, qp); return; }
+        if (m <= 256 / N::usual) { one_pass<N::usual>(d_in, d_H, n_alloc, m, eps_l1, eps_log, pro, qp); return; }
         using B = Batch<G, BF16 ? 2 : 4>;
         const uint32_t nb = (T + B::TILES - 1) / B::TILES;
-        const uint32_t n_alloc = T / m;
-        if (B::TILES % m == 0) {
-            q(k_alloc_entropy<G, BF16>, dim3(nb), dim3(B::TILES), d_in, d_H, T, m, eps_l1,
-                               eps_log, pro);
-            return;
-        }
         q(k_tile_partial<G, BF16, false>, dim3(nb), dim3(B::TILES), d_in,
-                           (const float *)nullptr, part, T, m, eps_log, pro);
+                           (const float *)nullptr, part, T, m, eps_log, prologue_blocks(pro, B::TILES, nb), pro);
         q(k_alloc_reduce<false>, dim3(blocks_for(n_alloc)), dim3(256), (const float *)part, (const float *)nullptr,
                            inv_norm, n_alloc, m, eps_l1);
         q(k_tile_partial<G, BF16, true>, dim3(nb), dim3(B::TILES), d_in,
-                           (const float *)inv_norm, part, T, m, eps_log, Prologue{});
+                           (const float *)inv_norm, part, T, m, eps_log, 0u, Prologue{});
         q(k_alloc_reduce<true>, dim3(blocks_for(n_alloc)), dim3(256), (const float *)part, (const float *)inv_norm,
                            d_H, n_alloc, m, eps_l1);
     }
@@ -301,8 +337,8 @@ void launch_naive_encode(bool bf16, const void *d_in, uint8_t *packed, const Nai
 {
     Enqueue &q = *qp;
     const dim3 grid((nchunks + kNaiveChunks - 1) / kNaiveChunks), block(kNaiveChunks);
-    if (bf16) q(k_naive_encode<BITS, true>, grid, block, d_in, packed, hdr, nchunks, scale);
-    else q(k_naive_encode<BITS, false>, grid, block, d_in, packed, hdr, nchunks, scale);
+    if (bf16) q(k_naive_encode<BITS, true>, grid, block, d_in, packed, nchunks, scale, hdr);
+    else q(k_naive_encode<BITS, false>, grid, block, d_in, packed, nchunks, scale, hdr);
 }
 
 template <int BITS>
@@ -350,9 +386,7 @@ size_t tahq_packed_size(const tahq_config *cfg)
 {
     Shape s;
     if (make_shape(cfg, &s) != TAHQ_OK) return 0;
-    Layout L;
-    make_layout(s, &L);
-    return (size_t)L.total;
+    return (size_t)stream_bytes(s);
 }
 
 size_t tahq_workspace_size(const tahq_config *cfg)
@@ -412,11 +446,10 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
     tahq_status rc = make_shape(cfg, &s);
     if (rc != TAHQ_OK) return rc;
     if (!d_in || !d_packed || !d_workspace) return TAHQ_ERR_NULL;
-    Layout lay;
-    make_layout(s, &lay);
+    const Sections lay((uint32_t)s.T);
     Workspace ws;
     make_workspace(s, &ws);
-    if (packed_capacity < lay.total) return TAHQ_ERR_BUFFER_TOO_SMALL;
+    if (packed_capacity < stream_bytes(s)) return TAHQ_ERR_BUFFER_TOO_SMALL;
     if (workspace_capacity < ws.total) return TAHQ_ERR_WORKSPACE_TOO_SMALL;
     if (misaligned(d_in) || misaligned(d_packed) || misaligned(d_workspace)) return TAHQ_ERR_MISALIGNED;
 
@@ -556,7 +589,7 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
     }
 
     if (phases & TAHQ_PHASE_QUANT) {
-        dispatch<LaunchQuantPack>(s.G, s.dtype == TAHQ_BF16, s.low, d_in, packed, lay, (uint32_t)s.T, cfg->tau,
+        dispatch<LaunchQuantPack>(s.G, s.dtype == TAHQ_BF16, s.low, d_in, packed, (uint32_t)s.T, cfg->tau,
                                   cfg->eps_ratio, !all_in_quant, s.kA == s.nA, pro, &q);
     }
     return q.result();
@@ -579,9 +612,7 @@ tahq_status tahq_encode_noalloc(const tahq_config *cfg, const void *d_in, void *
     make_workspace(s, &ws);
     if (ws.total > kBuiltinScratchBytes) return TAHQ_ERR_TOO_LARGE;
     if (!d_in || !d_packed) return TAHQ_ERR_NULL;
-    Layout lay;
-    make_layout(s, &lay);
-    if (packed_capacity < lay.total) return TAHQ_ERR_BUFFER_TOO_SMALL;
+    if (packed_capacity < stream_bytes(s)) return TAHQ_ERR_BUFFER_TOO_SMALL;
     if (misaligned(d_in) || misaligned(d_packed)) return TAHQ_ERR_MISALIGNED;
     // the current device's copy of the built-in scratch: looked up once per device, with that device current
     int dev = -1;
@@ -610,12 +641,10 @@ tahq_status tahq_decode(const tahq_config *cfg, const void *d_packed, size_t pac
     if (rc != TAHQ_OK) return rc;
     if (out_dtype > TAHQ_BF16) return TAHQ_ERR_INVALID_ARG;
     if (!d_packed || !d_out) return TAHQ_ERR_NULL;
-    Layout lay;
-    make_layout(s, &lay);
-    if (packed_bytes < lay.total) return TAHQ_ERR_BUFFER_TOO_SMALL;
+    if (packed_bytes < stream_bytes(s)) return TAHQ_ERR_BUFFER_TOO_SMALL;
     if (misaligned(d_packed) || misaligned(d_out)) return TAHQ_ERR_MISALIGNED;
     Enqueue q{(hipStream_t)stream};
-    dispatch<LaunchDecode>(s.G, out_dtype == TAHQ_BF16, s.low, static_cast<const uint8_t *>(d_packed), d_out, lay,
+    dispatch<LaunchDecode>(s.G, out_dtype == TAHQ_BF16, s.low, static_cast<const uint8_t *>(d_packed), d_out,
                            (uint32_t)s.T, (uint32_t)(s.U * s.k), &q);
     return q.result();
 }

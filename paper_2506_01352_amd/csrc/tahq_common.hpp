@@ -25,10 +25,6 @@ struct Shape {
     uint64_t kA;  // wide allocation tiles per ranking unit
 };
 
-struct Layout {
-    uint64_t bitmap, ranks, pivot, scale, zero, payload, total;
-};
-
 constexpr uint32_t kSegTiles = 1024;     // tiles one wavefront handles in the selection kernels
 constexpr uint32_t kHistBins = 2048;      // bins of radix digits 1 and 2 (11 bits each)
 constexpr uint32_t kDigit0Bins = 1024;    // bins of radix digit 0 (key bits 31..22)
@@ -59,8 +55,31 @@ struct Workspace {
     uint32_t hb;         // workgroups per ranking unit in the radix passes
 };
 
-inline uint64_t pad64(uint64_t x) { return (x + 63u) & ~uint64_t(63); }
+__host__ __device__ constexpr uint64_t pad64(uint64_t x) { return (x + 63u) & ~uint64_t(63); }
 inline uint64_t pad256(uint64_t x) { return (x + 255u) & ~uint64_t(255); }
+
+// Where the sections of a stream of T tiles begin.  Kernels work this out for themselves: the twenty scalar instructions cost less
+// than reading seven offsets from the kernel's arguments, of which only the first fourteen words reach the scalar registers
+// before a wavefront starts (-amdgpu-kernarg-preload-count in build.py).  What lies behind them costs a round trip to memory
+// in front of a kernel's first load: a chain of kernels that write 100 KB takes 3.1 us a launch with its arguments in memory,
+// 4.1 with 250 bytes of them, and 2.5 preloaded.  So kernels take what their first loads need first and structures last.
+struct Sections {
+    uint64_t ranks, pivot, scale, zero, payload;
+    static constexpr uint64_t bitmap = 64;
+    __host__ __device__ __forceinline__ explicit Sections(uint32_t T)
+    {
+        ranks = bitmap + pad64(((uint64_t)T + 7) / 8);
+        pivot = ranks + pad64(4 * (((uint64_t)T + 63) / 64));
+        scale = pivot + pad64(T);
+        zero = scale + pad64(2 * (uint64_t)T);
+        payload = zero + pad64(2 * (uint64_t)T);
+    }
+    // the end of a stream with total_wide wide tiles
+    __host__ __device__ __forceinline__ uint64_t end(uint32_t G, uint32_t low, uint32_t T, uint64_t total_wide) const
+    {
+        return payload + (uint64_t)(G / 8) * ((uint64_t)low * T + total_wide);
+    }
+};
 
 tahq_status make_shape(const tahq_config *c, Shape *s)
 {
@@ -98,16 +117,7 @@ tahq_status make_shape(const tahq_config *c, Shape *s)
     return TAHQ_OK;
 }
 
-void make_layout(const Shape &s, Layout *L)
-{
-    L->bitmap = 64;
-    L->ranks = L->bitmap + pad64((s.T + 7) / 8);
-    L->pivot = L->ranks + pad64(4 * ((s.T + 63) / 64));
-    L->scale = L->pivot + pad64(s.T);
-    L->zero = L->scale + pad64(2 * s.T);
-    L->payload = L->zero + pad64(2 * s.T);
-    L->total = L->payload + (uint64_t)(s.G / 8) * (s.low * s.T + (uint64_t)s.U * s.k);
-}
+uint64_t stream_bytes(const Shape &s) { return Sections((uint32_t)s.T).end(s.G, s.low, (uint32_t)s.T, (uint64_t)s.U * s.k); }
 
 void make_workspace(const Shape &s, Workspace *w)
 {

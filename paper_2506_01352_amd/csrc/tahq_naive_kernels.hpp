@@ -21,8 +21,8 @@ __device__ __forceinline__ uint32_t skew(uint32_t p) { return p + (p >> 5); }
 
 template <int BITS, bool BF16>
 __global__ __launch_bounds__(kNaiveChunks)
-void k_naive_encode(const void *__restrict__ in, uint8_t *__restrict__ packed, NaiveHeader hdr, uint32_t nchunks,
-                    float scale)
+void k_naive_encode(const void *__restrict__ in, uint8_t *__restrict__ packed, uint32_t nchunks, float scale,
+                    NaiveHeader hdr)
 {
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<kNaiveChunk, ES>;

@@ -3,10 +3,10 @@
 //
 // Mapping: A LANE OWNS A TILE, or, of a tile of more than 128 bytes or in a tensor of few tiles, one part of two or four.  The
 // codec is bound by vector-ALU issue as much as by HBM, so the per-tile work (reductions, butterflies, quantizer
-// parameters) crosses lanes in its last one or two levels only, inside a quad.  A workgroup stages TILES consecutive tiles
-// through LDS with coalesced 128-bit global accesses, then every lane pulls its part into registers; LDS rows are padded by
-// 16 bytes so that the lane-per-row 128-bit reads are bank-conflict free.  (The decoder: a wavefront by itself, see there.  The
-// entropies of allocation tiles of several quantization tiles: always one lane per quantization tile.)
+// parameters) crosses lanes in its last one or two levels only, inside a quad.  In the quantizer a workgroup stages TILES
+// consecutive tiles through LDS with coalesced 128-bit global accesses, then every lane pulls its part into registers; LDS rows
+// are padded by 16 bytes so that the lane-per-row 128-bit reads are bank-conflict free.  In the entropy kernels and the decoder
+// every wavefront works by itself on LDS of its own.
 #pragma once
 #include "tahq_common.hpp"
 
@@ -204,6 +204,13 @@ __device__ __forceinline__ void butterfly_across(float *x, uint32_t part)
     static_assert(LPT <= 4, "two stages across lanes");
 }
 
+// Orders the LDS accesses of one wavefront for the compiler; the hardware performs them in program order.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // ------------------------------------------------------------- prologue
 
 // What a stream holds besides the kernels' results: header and zeroed section padding.  And the bit map words that ranking
@@ -218,10 +225,17 @@ struct Prologue {
     PadList pads;
 };
 
-// Thread `gid` of `threads` (at least 64).  The small launches of a call cost more than what they do, so the prologue rides
+// Thread `gid` of `threads` (at least 64): as many as there are edge units, in whole workgroups (prologue_blocks), so that the others
+// need not read these arguments.  The small launches of a call cost more than what they do, so the prologue rides
 // along with the call's first kernel, at its end, where nothing waits for it: instead of a launch in front of the entropies
 // (encode of 1024 x 1600 channels: 18.8 -> 17.5 us), or of the quantizer where all tiles have one width (fp32 [1,128,512],
 // encode and decode: 19.7 -> 16.8).
+inline uint32_t prologue_blocks(const Prologue &p, uint32_t threads, uint32_t blocks)
+{
+    const uint32_t want = (p.edge_units + threads - 1) / threads;
+    return want < 1u ? 1u : want < blocks ? want : blocks;
+}
+
 __device__ __forceinline__ void write_prologue(const Prologue &p, uint32_t gid, uint32_t threads)
 {
     if (p.packed != nullptr && gid < 64) {
@@ -253,131 +267,201 @@ __device__ __forceinline__ void constant_width_word(uint64_t w, uint32_t T, int 
 
 // -------------------------------------------------------------- K0: entropy
 
-// Eq. 1-2 for a tile, of whose LDS row `row` is my part: the sums of the LPT parts meet in pairs, which are the top of the
-// tile's binary tree.
-template <int G, bool BF16, int LPT>
-__device__ __forceinline__ float entropy_of_row(const uint8_t *row, float eps_l1, float eps_log)
+// Wavefronts that read the tensor for its entropies take their rows straight from memory to their own piece of LDS, without
+// registers or barriers in between, and request the next ones as soon as the present ones are in registers: what a wavefront
+// computes hides its own loads.  Lane r's 128 bytes or less lie as `Wave` says; as consecutive lanes fill consecutive 16 bytes of
+// LDS, the swizzle is in the addresses they load from.
+//   src: row 0; rows: how many exist (lanes past them load the last one); NG groups of 64 rows
+template <class W, int NG>
+__device__ __forceinline__ void request_rows(const uint8_t *__restrict__ src, uint32_t rows, uint8_t *lds, uint32_t lane)
 {
-    constexpr int EPL = G / LPT;
-    auto whole = [](float part) {
-        if constexpr (LPT >= 2) part = part + lane_xor<1>(part);
-        if constexpr (LPT >= 4) part = part + lane_xor<2>(part);
-        return part;
-    };
-    float a[EPL];
-    read_tile<EPL, BF16>(row, a);
+    constexpr uint32_t STEP = 64 / W::CHUNKS;                // rows per load: a multiple of the swizzle's period
+    const uint32_t r = lane / W::CHUNKS, c = (lane % W::CHUNKS) ^ W::swizzle(r);
+    const bool full = rows >= 64u * NG;
 #pragma unroll
-    for (int k = 0; k < EPL; ++k) a[k] = __builtin_fabsf(a[k]);
-    const float L1 = whole(tree_sum<EPL>(a));
-    const float invL = 1.0f / (L1 + eps_l1);
+    for (uint32_t i = 0; i < (uint32_t)(NG * W::CHUNKS); ++i) {
+        uint32_t row = r + i * STEP;
+        if (!full) row = row < rows ? row : rows - 1;
+        // (2: non-temporal.  The tensor is much larger than any cache, and keeping part of it for the second pass was slower.)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + row * W::LANE_BYTES + c * 16u),
+                                         (__attribute__((address_space(3))) void *)(lds + i * 1024u), 16, 0, 2);
+    }
+}
+// ... have arrived
+__device__ __forceinline__ void wait_for_rows() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// ... are in registers: their LDS may be written again
+__device__ __forceinline__ void rows_are_read()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// My row of group `g`, widened to fp32.
+template <class W, bool BF16>
+__device__ __forceinline__ void read_row(const uint8_t *lds, uint32_t g, uint32_t lane, float *x)
+{
+    const uint8_t *row = lds + g * W::LDS_BYTES + lane * W::LANE_BYTES;
+    const uint32_t swz = W::swizzle(lane) << 4;
 #pragma unroll
-    for (int k = 0; k < EPL; ++k) a[k] = a[k] * log_contract(__builtin_fmaf(a[k], invL, eps_log));
-    return 0.0f - invL * whole(tree_sum<EPL>(a));
+    for (uint32_t c = 0; c < (uint32_t)W::CHUNKS; ++c) {
+        const uint4 w = *reinterpret_cast<const uint4 *>(row + ((c << 4) ^ swz));
+        const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (BF16) {
+                x[8 * c + 2 * i] = __uint_as_float(ws[i] << 16);
+                x[8 * c + 2 * i + 1] = __uint_as_float(ws[i] & 0xffff0000u);
+            } else {
+                x[4 * c + i] = __uint_as_float(ws[i]);
+            }
+        }
+    }
+}
+
+// The sum over a tile from its LPT parts' sums, which meet in pairs: the top of the tile's binary tree.
+template <int LPT>
+__device__ __forceinline__ float whole_tile(float part)
+{
+    if constexpr (LPT >= 2) part = part + lane_xor<1>(part);
+    if constexpr (LPT >= 4) part = part + lane_xor<2>(part);
+    return part;
+}
+
+// Sum over my elements of |v| (Eq. 1), and of |v| log(|v| r + varsigma) (Eq. 2 but for its common factor r = 1 / (L1 + eps)).
+template <int N>
+__device__ __forceinline__ float magnitude_sum(const float *x)
+{
+    float a[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) a[k] = __builtin_fabsf(x[k]);
+    return tree_sum<N>(a);
+}
+template <int N>
+__device__ __forceinline__ float weighted_sum(const float *x, float invL, float eps_log)
+{
+    float a[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        a[k] = __builtin_fabsf(x[k]);
+        a[k] = a[k] * log_contract(__builtin_fmaf(a[k], invL, eps_log));
+    }
+    return tree_sum<N>(a);
 }
 
 constexpr int kDigit0Bits = 10;                  // first radix digit of the selection: key bits 31..22
 static_assert((1u << kDigit0Bits) == kDigit0Bins, "digit 0 width");
 
-// Persistent workgroups: workgroup w handles a contiguous run of full batches.  The next batch's loads
-// are issued before the current batch is processed, and a batch's result is stored one iteration later,
-// just before those loads, so that no wait for loads ever has a younger store in front of it.
-// The ragged last batch (T not a multiple of TILES) is handled after the loop by one workgroup.
-// Tiles of more than 128 bytes take LPT lanes each, as in the quantizer.  fp32 [4,2048,8192] G = 64: 44.7 -> 42.7 us, G = 128:
-// 56.2 -> 41.1, bf16
-// [8,2048,8192] G = 128: 65.2 -> 53.9.
+// Groups of 64 rows that a wavefront takes at a time in tensors of many tiles: 128 bytes per lane whatever the tile.
+template <int G, int ESIZE, int LPT>
+constexpr int kRowGroups = 128 / (G * ESIZE / LPT);
+
+// Bound by vector issue (twelve and a half slots per element, ten of them the logarithm) and behind it by HBM.  Without barriers,
+// and with the next rows on their way to LDS while the present ones are in registers, bf16 [8,4096,8192] G = 64 108.7 -> 106.1 us,
+// fp32 [4,512,2048] 5.1 -> 4.6.
 //
-// If `hist0` is given, the kernel also builds the first histogram of the selection (Sec. 3.2, top-p%): per
+// Persistent workgroups of four wavefronts; a step is 4 NG groups of rows, NG for each wavefront, and workgroup w handles a
+// contiguous run of steps.  A step's results are stored one step late, just before the next loads, so that no wait for loads ever
+// has a younger store in front of it.  The wavefronts of a workgroup meet only where the histogram moves to another unit.
+//
+// If HIST, the kernel also builds the first histogram of the selection (Sec. 3.2, top-p%): per
 // ranking unit of `unit_tiles` tiles, counts of the keys' top 10 bits (bin_scale == 0) or of the entropies'
 // linear bins (bin_scale > 0), `hist_stride` bins per unit, accumulated in LDS and flushed with global atomics
-// when the workgroup moves to another unit, in the middle of a batch if need be, and at its end.  A batch may touch two
-// units, not more: `unit_tiles` is at least TILES (the caller checks; otherwise it passes no histogram).
-template <int G, bool BF16, int LPT>
-__global__ __launch_bounds__(256)
-void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, float eps_l1, float eps_log,
-               uint32_t *__restrict__ hist0, uint32_t unit_tiles, uint32_t hist_stride, float bin_scale, Prologue pro)
+// when the workgroup moves to another unit, in the middle of a step if need be, and at its end.  A step may touch two
+// units, not more: `unit_tiles` is at least a step's tiles (the caller checks; otherwise it passes no histogram).
+template <int G, bool BF16, int LPT, int NG, bool HIST>
+__global__ __launch_bounds__(256, 4)
+void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, uint32_t grid, float eps_l1, float eps_log,
+               uint32_t *__restrict__ hist0, uint32_t unit_tiles, uint32_t hist_stride, float bin_scale, uint32_t pro_blocks,
+               Prologue pro)
 {
-    constexpr int ES = BF16 ? 2 : 4;
-    using B = Batch<G, ES, LPT>;
-    constexpr int THREADS = B::TILES * LPT;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[B::LDS_BYTES];
+    using W = Wave<G, BF16 ? 2 : 4, LPT>;
+    constexpr uint32_t WAVE_TILES = W::TILES * NG, STEP_TILES = 4 * WAVE_TILES;
+    __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * NG * W::LDS_BYTES];
     static_assert(kLinBins >= kDigit0Bins, "one LDS histogram serves both kinds of bins");
-    __shared__ uint32_t lh[kLinBins];
-    const int tid = threadIdx.x;
-    const uint32_t nfull = T / B::TILES, tail = T % B::TILES;
-    const uint32_t tile = (uint32_t)tid / LPT, part = (uint32_t)tid % LPT;
-    const uint8_t *row = lds + tile * B::STRIDE + part * (B::BYTES / LPT);
-    const uint32_t per = (nfull + gridDim.x - 1) / gridDim.x;
+    __shared__ uint32_t lh[HIST ? kLinBins : 1];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    uint8_t *lds = lds_all + wave * (NG * W::LDS_BYTES);
+    const uint32_t part = lane % LPT, mine = wave * WAVE_TILES + lane / LPT;          // my tile of the step's first group
+    const uint32_t steps = (T + STEP_TILES - 1) / STEP_TILES, per = (steps + grid - 1) / grid;
     const uint32_t first = blockIdx.x * per;
-    const uint32_t last = first + per < nfull ? first + per : nfull;      // my batches: [first, last)
+    const uint32_t last = first + per < steps ? first + per : steps;      // my steps: [first, last)
 
-    if (hist0) {
-        for (int i = tid; i < (int)hist_stride; i += THREADS) lh[i] = 0;
+    auto request = [&](uint32_t step) {
+        const uint64_t j0 = (uint64_t)step * STEP_TILES + wave * WAVE_TILES;
+        if (j0 >= T) return;                     // (the last step's last wavefronts)
+        const uint64_t left = T - j0;
+        request_rows<W, NG>(static_cast<const uint8_t *>(in) + j0 * (G * (BF16 ? 2 : 4)),
+                            left < WAVE_TILES ? (uint32_t)left * LPT : 64u * NG, lds, lane);
+    };
+    if (first < last) request(first);
+    if constexpr (HIST) {
+        for (uint32_t i = tid; i < hist_stride; i += 256) lh[i] = 0;
+        __syncthreads();
     }
     auto flush = [&](uint32_t unit) {
         __syncthreads();
-        for (int i = tid; i < (int)hist_stride; i += THREADS) {
+        for (uint32_t i = tid; i < hist_stride; i += 256) {
             const uint32_t c = lh[i];
             if (c) { atomicAdd(&hist0[(uint64_t)unit * hist_stride + i], c); lh[i] = 0; }
         }
         __syncthreads();
     };
-
-    uint4 v[B::CHUNKS / LPT];
-    // non-temporal loads: the tensor is much larger than any cache, and keeping part of it for the second
-    // pass measured slower than streaming all of it
-    auto load_full = [&](uint32_t batch) {
-        load_batch<B, true, true>(in, (uint64_t)batch * B::TILES, B::TILES, v);
+    float h[NG];
+    uint64_t j_prev = 0;                         // the step before, and its tiles
+    uint32_t n_prev = 0;
+    auto store = [&]() {
+#pragma unroll
+        for (uint32_t g = 0; g < (uint32_t)NG; ++g)
+            if (part == 0 && mine + g * W::TILES < n_prev) H[j_prev + mine + g * W::TILES] = h[g];
     };
-    if (first < last) load_full(first);
-    float h_prev = 0.0f;
-    uint64_t j_prev = 0;
-    bool have_prev = false;
-    uint32_t cur_unit = hist0 && first < last ? first * B::TILES / unit_tiles : 0u;
-    uint32_t unit_end = (cur_unit + 1) * unit_tiles;         // the first tile after it
-    auto bin_of = [&](float h) {
-        return bin_scale > 0.0f ? linear_bin(h, bin_scale) : order_key(h) >> (32 - kDigit0Bits);
+    uint32_t cur_unit = HIST && first < last ? (uint32_t)((uint64_t)first * STEP_TILES / unit_tiles) : 0u;
+    uint64_t unit_end = (uint64_t)(cur_unit + 1) * unit_tiles;            // the first tile after it
+    auto bin_of = [&](float v) {
+        return bin_scale > 0.0f ? linear_bin(v, bin_scale) : order_key(v) >> (32 - kDigit0Bits);
     };
-    for (uint32_t batch = first; batch < last; ++batch) {
-        if (hist0 && batch * B::TILES >= unit_end) { flush(cur_unit); ++cur_unit; unit_end += unit_tiles; }
-        store_batch<B, true>(v, B::TILES, lds);
-        __syncthreads();
-        if (have_prev && part == 0) H[j_prev] = h_prev;
-        if (batch + 1 < last) load_full(batch + 1);
-        h_prev = entropy_of_row<G, BF16, LPT>(row, eps_l1, eps_log);
-        if (hist0) {                             // (a tile counts in its first lane)
-            uint32_t *at = &lh[bin_of(h_prev)];
-            const uint32_t mine = unit_end - batch * B::TILES;           // tiles of the batch that belong to cur_unit
-            if (mine >= (uint32_t)B::TILES) {
-                if (part == 0) atomicAdd(at, 1u);
+    for (uint32_t step = first; step < last; ++step) {
+        const uint64_t j0 = (uint64_t)step * STEP_TILES;
+        const uint32_t n = T - j0 < STEP_TILES ? (uint32_t)(T - j0) : STEP_TILES;
+        if (HIST && j0 >= unit_end) { flush(cur_unit); ++cur_unit; unit_end += unit_tiles; }
+        wait_for_rows();
+        float x[NG][W::EPL];
+#pragma unroll
+        for (uint32_t g = 0; g < (uint32_t)NG; ++g) read_row<W, BF16>(lds, g, lane, x[g]);
+        rows_are_read();
+        store();
+        if (step + 1 < last) request(step + 1);
+#pragma unroll
+        for (uint32_t g = 0; g < (uint32_t)NG; ++g) {
+            const float L1 = whole_tile<LPT>(magnitude_sum<W::EPL>(x[g]));
+            const float invL = 1.0f / (L1 + eps_l1);
+            h[g] = 0.0f - invL * whole_tile<LPT>(weighted_sum<W::EPL>(x[g], invL, eps_log));
+        }
+        j_prev = j0;
+        n_prev = n;
+        if constexpr (HIST) {                    // (a tile counts in its first lane)
+            auto count = [&](uint32_t from, uint32_t to) {
+#pragma unroll
+                for (uint32_t g = 0; g < (uint32_t)NG; ++g) {
+                    const uint32_t j = mine + g * W::TILES;
+                    if (part == 0 && j >= from && j < to) atomicAdd(&lh[bin_of(h[g])], 1u);
+                }
+            };
+            if (unit_end - j0 >= n) {
+                count(0, n);
             } else {
-                if (part == 0 && tile < mine) atomicAdd(at, 1u);
+                const uint32_t here = (uint32_t)(unit_end - j0);
+                count(0, here);
                 flush(cur_unit);
                 ++cur_unit;
                 unit_end += unit_tiles;
-                if (part == 0 && tile >= mine) atomicAdd(at, 1u);
-            }
-        }
-        j_prev = (uint64_t)batch * B::TILES + tile;
-        have_prev = true;
-        __syncthreads();
-    }
-    if (have_prev && part == 0) H[j_prev] = h_prev;
-    if (hist0 && first < last) flush(cur_unit);
-    write_prologue(pro, blockIdx.x * THREADS + threadIdx.x, gridDim.x * THREADS);
-
-    if (tail != 0 && blockIdx.x == gridDim.x - 1) {
-        const uint64_t j0 = (uint64_t)nfull * B::TILES;
-        load_batch<B, false>(in, j0, tail, v);
-        store_batch<B, false>(v, tail, lds);
-        __syncthreads();
-        if (tile < tail) {
-            const float h = entropy_of_row<G, BF16, LPT>(row, eps_l1, eps_log);
-            if (part == 0) {
-                H[j0 + tile] = h;
-                if (hist0) atomicAdd(&hist0[(j0 + tile) / unit_tiles * hist_stride + bin_of(h)], 1u);
+                count(here, n);
             }
         }
     }
+    if (first < last) store();
+    if (HIST && first < last) flush(cur_unit);
+    if (blockIdx.x < pro_blocks) write_prologue(pro, blockIdx.x * 256 + tid, pro_blocks * 256);
 }
 
 // ---------------------- entropy of allocation tiles wider than a quantization tile
@@ -393,7 +477,7 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, f
 template <int G, bool BF16, bool WEIGHTED>
 __global__ __launch_bounds__((Batch<G, BF16 ? 2 : 4>::TILES))
 void k_tile_partial(const void *__restrict__ in, const float *__restrict__ inv_norm, float *__restrict__ part,
-                    uint32_t T, uint32_t m, float eps_log, Prologue pro)
+                    uint32_t T, uint32_t m, float eps_log, uint32_t pro_blocks, Prologue pro)
 {
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<G, ES>;
@@ -424,74 +508,103 @@ void k_tile_partial(const void *__restrict__ in, const float *__restrict__ inv_n
         }
         part[j] = tree_sum<G>(a);
     }
-    write_prologue(pro, blockIdx.x * B::TILES + threadIdx.x, gridDim.x * B::TILES);
+    if (blockIdx.x < pro_blocks) write_prologue(pro, blockIdx.x * B::TILES + threadIdx.x, pro_blocks * B::TILES);
 }
 
-// The same result in ONE pass over the tensor when a workgroup's batch holds whole allocation tiles
-// (m divides TILES): the per-tile sums meet in LDS, the first lane of every allocation tile adds its m
-// values from left to right, and the tile's magnitudes wait in registers meanwhile.
-template <int G, bool BF16>
-__global__ __launch_bounds__((Batch<G, BF16 ? 2 : 4>::TILES), (G * (BF16 ? 2 : 4) <= 128 ? 4 : 1))
-void k_alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, uint32_t m, float eps_l1,
-                     float eps_log, Prologue pro)
+// The same result in ONE pass over the tensor: a team, a wavefront or a workgroup of four, takes `per` whole allocation tiles at a
+// time, as many as its lanes hold (per * m <= SLOTS), and lanes that are left over repeat the last one's work.  The per-tile sums
+// meet in LDS, from where every lane adds the m values of its allocation tile from left to right; meanwhile the magnitudes wait in
+// registers and the next rows are on their way.  A wavefront by itself needs no barriers.  (Where a workgroup's first lanes added
+// up for all and the others waited at barriers, [4,2048,4096] A = 4096, G = 64 took 18.7 us, or 20.7 when its workgroups started
+// at once, now 16.6.)
+template <int G, bool BF16, int LPT, bool WAVE_TEAM>
+__device__ __forceinline__
+void alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t n_alloc, uint32_t grid, uint32_t m, uint32_t per,
+                   float eps_l1, float eps_log, uint32_t pro_blocks, const Prologue &pro)
 {
-    constexpr int ES = BF16 ? 2 : 4;
-    using B = Batch<G, ES>;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[B::LDS_BYTES];
-    __shared__ float part[B::TILES];
-    __shared__ float inv_norm[B::TILES];
-    const int tid = threadIdx.x;
-    const uint64_t j0 = (uint64_t)blockIdx.x * B::TILES;
-    const uint32_t left = T - (uint32_t)j0;
-    const uint32_t nvalid = left < (uint32_t)B::TILES ? left : (uint32_t)B::TILES;   // a multiple of m
-    uint4 v[B::CHUNKS];
-    if (nvalid == (uint32_t)B::TILES) {
-        load_batch<B, true, true>(in, j0, nvalid, v);
-        store_batch<B, true>(v, nvalid, lds);
-    } else {
-        load_batch<B, false>(in, j0, nvalid, v);
-        store_batch<B, false>(v, nvalid, lds);
-    }
-    __syncthreads();
-    const bool valid = (uint32_t)tid < nvalid;
-    const bool first = valid && (uint32_t)tid % m == 0;      // first quantization tile of its allocation tile
-    float a[G];
-    if (valid) {
-        // (One half of the tile after the other: with the whole row and all magnitudes wanted at once, bf16 tiles of 64 channels
-        // spilled and those of 128 left room for one wavefront per vector unit; encode of [4,2048,4096] with A = 4096, G = 128
-        // 55.7 -> 48.3 us, G = 64 45.0 -> 43.7.)
-        constexpr int HALVES = G >= 16 ? 2 : 1, N = G / HALVES;
-        float sum[HALVES];
-#pragma unroll
-        for (int h = 0; h < HALVES; ++h) {
-            read_tile<N, BF16>(lds + tid * B::STRIDE + h * (B::BYTES / HALVES), a + h * N);
-#pragma unroll
-            for (int k = h * N; k < (h + 1) * N; ++k) a[k] = __builtin_fabsf(a[k]);
-            sum[h] = tree_sum<N>(a + h * N);
-            __builtin_amdgcn_sched_barrier(0);
+    using W = Wave<G, BF16 ? 2 : 4, LPT>;
+    constexpr uint32_t TEAMS = WAVE_TEAM ? 4 : 1, SLOTS = (WAVE_TEAM ? 64 : 256) / LPT;       // teams per workgroup, tiles per team
+    __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * W::LDS_BYTES];
+    __shared__ __attribute__((aligned(16))) float parts[2][TEAMS * SLOTS];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    uint8_t *lds = lds_all + wave * W::LDS_BYTES;
+    const uint32_t part = lane % LPT, slot = (WAVE_TEAM ? lane : tid) / LPT;
+    const uint32_t group = slot / m, q0 = (WAVE_TEAM ? wave * SLOTS : 0u) + group * m;        // my allocation tile, its first slot
+    const uint32_t team = WAVE_TEAM ? blockIdx.x * 4 + wave : blockIdx.x, teams = grid * TEAMS;
+    const uint32_t wave_row = WAVE_TEAM ? 0u : wave * 64u;                                    // my wavefront's first row of the team's
+
+    auto request = [&](uint32_t a0) {            // allocation tiles [a0, a0 + per)
+        const uint32_t have = (n_alloc - a0 < per ? n_alloc - a0 : per) * m * LPT;            // rows
+        // (a wavefront without rows of its own repeats the team's last one)
+        const uint32_t row0 = wave_row < have ? wave_row : have - 1;
+        request_rows<W, 1>(static_cast<const uint8_t *>(in) + ((uint64_t)a0 * m * LPT + row0) * W::LANE_BYTES, have - row0, lds, lane);
+    };
+    auto meet = [&](float (&at)[TEAMS * SLOTS], float value) {
+        if (part == 0) at[(WAVE_TEAM ? wave * SLOTS : 0u) + slot] = value;
+        if constexpr (WAVE_TEAM) wave_lds_fence();
+        else {
+            // (LDS only: the next rows stay on their way)
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
         }
-        part[tid] = tree_sum<HALVES>(sum);
-    }
-    __syncthreads();
-    if (first) {
+    };
+    // my allocation tile's m values from left to right (lanes left over stay inside the array)
+    auto left_to_right = [&](const float (&at)[TEAMS * SLOTS]) {
+        const float *p = &at[group < per ? q0 : 0u];
         float acc = 0.0f;
-        for (uint32_t q = 0; q < m; ++q) acc = acc + part[tid + q];
-        inv_norm[(uint32_t)tid / m] = 1.0f / (acc + eps_l1);
+        uint32_t q = 0;
+        if (m % 4 == 0) {
+            for (; q + 8 <= m; q += 8) {
+                const float4 u = *reinterpret_cast<const float4 *>(p + q), v = *reinterpret_cast<const float4 *>(p + q + 4);
+                acc = acc + u.x; acc = acc + u.y; acc = acc + u.z; acc = acc + u.w;
+                acc = acc + v.x; acc = acc + v.y; acc = acc + v.z; acc = acc + v.w;
+            }
+        }
+#pragma unroll 4
+        for (; q < m; ++q) acc = acc + p[q];
+        return acc;
+    };
+    const uint32_t stride = teams * per;
+    uint32_t a0 = team * per;
+    if (a0 < n_alloc) request(a0);
+    float h = 0.0f;
+    uint32_t a_prev = n_alloc;                   // my allocation tile of the round before
+    const bool first = group < per && slot == group * m && part == 0;
+    for (; a0 < n_alloc; a0 += stride) {
+        wait_for_rows();
+        float x[W::EPL];
+        read_row<W, BF16>(lds, 0, lane, x);
+        rows_are_read();
+        if (first && a_prev < n_alloc) H[a_prev] = h;
+        if (a0 + stride < n_alloc) request(a0 + stride);
+        meet(parts[0], whole_tile<LPT>(magnitude_sum<W::EPL>(x)));
+        const float invL = 1.0f / (left_to_right(parts[0]) + eps_l1);
+        meet(parts[1], whole_tile<LPT>(weighted_sum<W::EPL>(x, invL, eps_log)));
+        h = 0.0f - invL * left_to_right(parts[1]);
+        a_prev = a0 + group;
     }
-    __syncthreads();
-    if (valid) {
-        const float invL = inv_norm[(uint32_t)tid / m];
-#pragma unroll
-        for (int k = 0; k < G; ++k) a[k] = a[k] * log_contract(__builtin_fmaf(a[k], invL, eps_log));
-        part[tid] = tree_sum<G>(a);
-    }
-    __syncthreads();
-    if (first) {
-        float acc = 0.0f;
-        for (uint32_t q = 0; q < m; ++q) acc = acc + part[tid + q];
-        H[((uint32_t)j0 + tid) / m] = 0.0f - inv_norm[(uint32_t)tid / m] * acc;
-    }
-    write_prologue(pro, blockIdx.x * B::TILES + threadIdx.x, gridDim.x * B::TILES);
+    if (first && a_prev < n_alloc) H[a_prev] = h;
+    if (blockIdx.x < pro_blocks) write_prologue(pro, blockIdx.x * 256 + tid, pro_blocks * 256);
+}
+
+// The usual lanes, wavefronts by themselves.
+template <int G, bool BF16>
+__global__ __launch_bounds__(256, 4)
+void k_alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t n_alloc, uint32_t grid, uint32_t m, uint32_t per,
+                     float eps_l1, float eps_log, uint32_t pro_blocks, Prologue pro)
+{
+    alloc_entropy<G, BF16, Lanes<G, BF16 ? 2 : 4>::usual, true>(in, H, n_alloc, grid, m, per, eps_l1, eps_log, pro_blocks, pro);
+}
+
+// Any others.
+template <int G, bool BF16, int LPT, bool WAVE_TEAM>
+__global__ __launch_bounds__(256, 4)
+void k_alloc_entropy_by(const void *__restrict__ in, float *__restrict__ H, uint32_t n_alloc, uint32_t grid, uint32_t m, uint32_t per,
+                        float eps_l1, float eps_log, uint32_t pro_blocks, Prologue pro)
+{
+    alloc_entropy<G, BF16, LPT, WAVE_TEAM>(in, H, n_alloc, grid, m, per, eps_l1, eps_log, pro_blocks, pro);
 }
 
 // Left-to-right sum of the m partial sums of every allocation tile.  FINAL = false: the reciprocal norm
@@ -614,7 +727,7 @@ struct BatchMeta {
 };
 
 template <int TILES>
-__device__ __forceinline__ void load_meta(const uint8_t *__restrict__ packed, const Layout &lay, uint64_t j0, uint32_t T,
+__device__ __forceinline__ void load_meta(const uint8_t *__restrict__ packed, const Sections &lay, uint64_t j0, uint32_t T,
                                           BatchMeta<TILES> &m)
 {
     const uint64_t *bitmap = reinterpret_cast<const uint64_t *>(packed + lay.bitmap);
@@ -899,7 +1012,7 @@ __device__ __forceinline__ uint32_t quantize_values(const float *x, uint32_t b, 
 // vector unit, where it takes four to issue at the full rate.  bf16 [8,1024,4096] G = 128 at 3 bits: 28.5 -> 24.2 us, fp32
 // [4,512,2048] G = 64: 8.3 -> 6.7.
 template <int G, bool BF16, int LOW, bool RANKED, int LPT, bool FULL>
-__device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, uint8_t *__restrict__ packed, const Layout &lay,
+__device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, uint8_t *__restrict__ packed, const Sections &lay,
                                                  uint32_t T, float tau, float eps_ratio, uint32_t batch, uint32_t nvalid,
                                                  bool all_wide, uint8_t *lds, uint32_t *info, uint16_t *order, uint32_t *class_count)
 {
@@ -998,8 +1111,8 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
 // the ranked case, 126 -> 136 us on bf16 [8,4096,8192].)
 template <int G, bool BF16, int LOW, bool RANKED, int LPT>
 __global__ __launch_bounds__(256, 4)
-void k_quant_pack(const void *__restrict__ in, uint8_t *__restrict__ packed, Layout lay, uint32_t T, float tau,
-                  float eps_ratio, bool all_wide, Prologue pro)
+void k_quant_pack(const void *__restrict__ in, uint8_t *__restrict__ packed, uint32_t T, float tau, float eps_ratio,
+                  uint32_t all_wide, Prologue pro)
 {
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<G, ES, LPT>;
@@ -1008,12 +1121,13 @@ void k_quant_pack(const void *__restrict__ in, uint8_t *__restrict__ packed, Lay
     __shared__ uint32_t info[B::TILES];          // per tile: pivot byte | (b == WIDE) << 8 | rel << 9
     __shared__ uint16_t order[B::TILES];         // tiles in class order
     __shared__ uint32_t class_count[4 * WAVES];  // tiles per class and wavefront, class-major
+    const Sections lay(T);
     const uint32_t nfull = T / B::TILES;        // a workgroup per batch; the last one may be ragged
     if (blockIdx.x < nfull)
-        quant_pack_batch<G, BF16, LOW, RANKED, LPT, true>(in, packed, lay, T, tau, eps_ratio, blockIdx.x, B::TILES, all_wide, lds, info,
+        quant_pack_batch<G, BF16, LOW, RANKED, LPT, true>(in, packed, lay, T, tau, eps_ratio, blockIdx.x, B::TILES, all_wide != 0, lds, info,
                                              order, class_count);
     else
-        quant_pack_batch<G, BF16, LOW, RANKED, LPT, false>(in, packed, lay, T, tau, eps_ratio, nfull, T % B::TILES, all_wide, lds, info,
+        quant_pack_batch<G, BF16, LOW, RANKED, LPT, false>(in, packed, lay, T, tau, eps_ratio, nfull, T % B::TILES, all_wide != 0, lds, info,
                                               order, class_count);
     if constexpr (!RANKED) {
         if (blockIdx.x == 0) write_prologue(pro, threadIdx.x, THREADS);      // (nothing but header and padding)
@@ -1079,13 +1193,6 @@ __device__ __forceinline__ void dequantize_codes(const uint32_t *dw, float sf, f
     }
 }
 
-// Orders the LDS accesses of one wavefront for the compiler; the hardware performs them in program order.
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 // My share of a tile's bit string: LOW or LOW + 1 units of UB = EPL / 8 bytes at `p`, as dwords.  `end` is the end of the
 // stream.
 template <int UB, int LOW>
@@ -1124,7 +1231,7 @@ __device__ __forceinline__ void load_codes(const uint8_t *__restrict__ p, bool w
 // 24.4 -> 18.2; half as many elements per lane: 98.8 us where 64 take 92.4.
 template <int G, bool OUT_BF16, int LOW, int LPT>
 __global__ __launch_bounds__(256, 4)
-void k_decode(const uint8_t *__restrict__ packed, void *__restrict__ out, Layout lay, uint32_t T, uint32_t total_wide)
+void k_decode(const uint8_t *__restrict__ packed, void *__restrict__ out, uint32_t T, uint32_t total_wide)
 {
     constexpr int ES = OUT_BF16 ? 2 : 4;
     using W = Wave<G, ES, LPT>;
@@ -1136,6 +1243,7 @@ void k_decode(const uint8_t *__restrict__ packed, void *__restrict__ out, Layout
     const uint32_t j0 = group * W::TILES;
     if (j0 >= T) return;
     uint8_t *lds = lds_all + wave * W::LDS_BYTES;
+    const Sections lay(T);
     const bool full = T - j0 >= (uint32_t)W::TILES;
     const uint32_t t = lane / LPT, part = lane % LPT;
     const uint32_t j = (full || j0 + t < T) ? j0 + t : T - 1;            // lanes past the end repeat the last tile
@@ -1161,7 +1269,7 @@ void k_decode(const uint8_t *__restrict__ packed, void *__restrict__ out, Layout
     uint32_t dw[DW + 2];                         // the readers below may look past the string
 #pragma unroll
     for (int i = 0; i < DW + 2; ++i) dw[i] = 0;
-    load_codes<EPL / 8, LOW>(src, wide, packed + lay.total, dw);
+    load_codes<EPL / 8, LOW>(src, wide, packed + lay.end(G, LOW, T, total_wide), dw);
 
     const float sf = f16_widen(s16), mnf = f16_widen(z16);
     float x[EPL];
