@@ -117,43 +117,69 @@ inline uint32_t resident_blocks(const void *kernel, int threads, ResidentCache &
 template <class N>
 inline bool few_tiles(uint64_t T, uint32_t deep) { return T * N::usual < 65536u && T * N::few < deep * 65536u; }
 
+// Streams from here on pass the caches by.  Written through them, a large stream is not there any more when the decoder reads it and
+// comes out as dirty lines in the middle of the reads of the next kernels.  bf16 [8,S,8192] on three sets of buffers in turn, encode
+// and decode in us, through the caches and past them: G = 64 at 3.25 bits: 62 MiB 180 and 183, 125 MiB 363 and 341 (encode
+// alone 261 and 234); at 4 bits: 74 MiB 117 and 120, 149 MiB 238 and 231; G = 128 at 3 bits: 106 MiB 233 and 244; G = 32 at 4 bits: 85 MiB
+// 118 and 123, 170 MiB 242 and 238.
+constexpr uint64_t kStreamingFrom = 112ull << 20;
+
+// What the entropy pass computes by: Eq. 1-2, and Eq. 3 where it decides that as well.
+struct EntropyParams {
+    float eps_l1, eps_log, tau, eps_ratio;
+    bool approx;                                 // entropies to within kEntropySlack will do (and are to be had)
+};
+
+inline EntropyParams entropy_params(const tahq_config *c) { return {c->eps_l1, c->eps_log, c->tau, c->eps_ratio, false}; }
+
+// Whether the two-launch selection works from approximate entropies: for bf16 tensors of 2^25 elements and more, where what
+// the entropy pass saves is more than what the selection spends on exact ones, and constants that the bound covers.
+inline bool approximate_entropies(const Shape &s, const tahq_config *c)
+{
+    return s.dtype == TAHQ_BF16 && s.T * s.G >= (1u << 25) && c->eps_log >= kApproxLogMin && c->eps_log <= kApproxLogMax &&
+           c->eps_l1 >= 1e-30f && c->eps_l1 <= 1e30f;
+}
+
 template <int G, bool BF16>
 struct LaunchEntropy {
-    template <int LPT, int NG, bool HIST>
-    static void go(const void *d_in, float *d_H, uint32_t T, float eps_l1, float eps_log, uint32_t *hist,
+    template <int LPT, int NG, bool HIST, bool APPROX>
+    static void go(const void *d_in, float *d_H, uint8_t *pivot, uint32_t T, const EntropyParams &p, uint32_t *hist,
                    uint32_t bins, float bin_scale, uint64_t n_per_unit, const Prologue &pro, Enqueue *qp)
     {
         Enqueue &q = *qp;
         constexpr uint32_t STEP = 256 / LPT * NG;            // tiles
         const uint32_t nb = (T + STEP - 1) / STEP;
         static ResidentCache cache;
-        const uint32_t res = resident_blocks(reinterpret_cast<const void *>(k_entropy<G, BF16, LPT, NG, HIST>), 256, cache);
+        const uint32_t res = resident_blocks(reinterpret_cast<const void *>(k_entropy<G, BF16, LPT, NG, HIST, APPROX>), 256, cache);
         // Every workgroup adds its histogram to the unit's, and what that costs are the additions that meet on one bin: four
         // steps per workgroup where that still leaves a workgroup per compute unit (three units of 77700 tiles of 16
         // channels: 14.1 -> 8.4 us)
         const uint32_t few = nb / 4 > 256u ? nb / 4 : 256u;
         const uint32_t most = HIST && few < res ? few : res;
         const uint32_t grid = nb < most ? nb : most;
-        q(k_entropy<G, BF16, LPT, NG, HIST>, dim3(grid), dim3(256), d_in, d_H, T, grid, eps_l1, eps_log, hist, (uint32_t)n_per_unit,
-          bins, bin_scale, prologue_blocks(pro, 256, grid), pro);
+        q(k_entropy<G, BF16, LPT, NG, HIST, APPROX>, dim3(grid), dim3(256), d_in, d_H, pivot, T, (nb + grid - 1) / grid, p.eps_l1, p.eps_log,
+          p.tau, p.eps_ratio, prologue_blocks(pro, 256, grid), hist, (uint32_t)n_per_unit, bins, bin_scale, pro);
     }
     template <int LPT, int NG>
-    static void with(const void *d_in, float *d_H, uint32_t T, float eps_l1, float eps_log, uint32_t *hist,
+    static void with(const void *d_in, float *d_H, uint8_t *pivot, uint32_t T, const EntropyParams &p, uint32_t *hist,
                      uint32_t bins, float bin_scale, uint64_t n_per_unit, const Prologue &pro, Enqueue *qp)
     {
-        if (hist) go<LPT, NG, true>(d_in, d_H, T, eps_l1, eps_log, hist, bins, bin_scale, n_per_unit, pro, qp);
-        else go<LPT, NG, false>(d_in, d_H, T, eps_l1, eps_log, hist, bins, bin_scale, n_per_unit, pro, qp);
+        if constexpr (BF16 && LPT == Lanes<G, 2>::usual) {
+            if (hist && p.approx) { go<LPT, NG, true, true>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp); return; }
+        }
+        if (hist) go<LPT, NG, true, false>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp);
+        else go<LPT, NG, false, false>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp);
     }
     // hist != nullptr: also build the selection's first histogram, `bins` bins per ranking unit (of at least one step): the keys'
     // first radix digit if bin_scale == 0, the entropies' linear bins otherwise
-    static void run(const void *d_in, float *d_H, uint32_t T, float eps_l1, float eps_log, uint32_t *hist,
+    static void run(const void *d_in, float *d_H, uint8_t *pivot, uint32_t T, const EntropyParams &p, uint32_t *hist,
                     uint32_t bins, float bin_scale, uint64_t n_per_unit, Prologue pro, Enqueue *qp)
     {
         using N = Lanes<G, BF16 ? 2 : 4>;
         constexpr int NG = kRowGroups<G, BF16 ? 2 : 4, N::usual>;
-        if (few_tiles<N>(T, 4)) with<N::few, 1>(d_in, d_H, T, eps_l1, eps_log, hist, bins, bin_scale, n_per_unit, pro, qp);
-        else if (NG == 1 || T < 1024u * 256u * NG) with<N::usual, 1>(d_in, d_H, T, eps_l1, eps_log, hist, bins, bin_scale, n_per_unit, pro, qp);
-        else with<N::usual, NG>(d_in, d_H, T, eps_l1, eps_log, hist, bins, bin_scale, n_per_unit, pro, qp);
+        if (few_tiles<N>(T, 4)) with<N::few, 1>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp);
+        else if (NG == 1 || T < 1024u * 256u * NG) with<N::usual, 1>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp);
+        else with<N::usual, NG>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp);
     }
     // units are whole steps, whatever those are
     static bool can_fuse_histogram(uint64_t n_per_unit)
@@ -173,33 +199,33 @@ template <int G, bool BF16>
 struct LaunchQuantPack {
     template <int LOW, int LPT>
     static void with(const void *d_in, uint8_t *packed, uint32_t T, float tau, float eps_ratio, bool ranked,
-                   bool all_wide, const Prologue &pro, Enqueue *qp)
+                   uint32_t how, const Prologue &pro, Enqueue *qp)
     {
         Enqueue &q = *qp;
         using B = Batch<G, BF16 ? 2 : 4, LPT>;
         const dim3 grid((T + B::TILES - 1) / B::TILES), block(B::TILES * LPT);
-        if (ranked) q(k_quant_pack<G, BF16, LOW, true, LPT>, grid, block, d_in, packed, T, tau, eps_ratio, 0u, pro);
-        else q(k_quant_pack<G, BF16, LOW, false, LPT>, grid, block, d_in, packed, T, tau, eps_ratio, all_wide ? 1u : 0u, pro);
+        if (ranked) q(k_quant_pack<G, BF16, LOW, true, LPT>, grid, block, d_in, packed, T, tau, eps_ratio, how, pro);
+        else q(k_quant_pack<G, BF16, LOW, false, LPT>, grid, block, d_in, packed, T, tau, eps_ratio, how, pro);
     }
     template <int LOW>
     static void go(const void *d_in, uint8_t *packed, uint32_t T, float tau, float eps_ratio, bool ranked,
-                   bool all_wide, const Prologue &pro, Enqueue *qp)
+                   uint32_t how, const Prologue &pro, Enqueue *qp)
     {
         using N = Lanes<G, BF16 ? 2 : 4>;
-        if (few_tiles<N>(T, 2)) with<LOW, N::few>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp);
-        else with<LOW, N::usual>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp);
+        if (few_tiles<N>(T, 2)) with<LOW, N::few>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp);
+        else with<LOW, N::usual>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp);
     }
     static void run(uint32_t low, const void *d_in, uint8_t *packed, uint32_t T, float tau, float eps_ratio,
-                    bool ranked, bool all_wide, Prologue pro, Enqueue *qp)
+                    bool ranked, uint32_t how, Prologue pro, Enqueue *qp)
     {
         switch (low) {
-        case 1: go<1>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
-        case 2: go<2>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
-        case 3: go<3>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
-        case 4: go<4>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
-        case 5: go<5>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
-        case 6: go<6>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
-        default: go<7>(d_in, packed, T, tau, eps_ratio, ranked, all_wide, pro, qp); break;
+        case 1: go<1>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp); break;
+        case 2: go<2>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp); break;
+        case 3: go<3>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp); break;
+        case 4: go<4>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp); break;
+        case 5: go<5>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp); break;
+        case 6: go<6>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp); break;
+        default: go<7>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp); break;
         }
     }
 };
@@ -240,58 +266,70 @@ template <int G, bool BF16>
 struct LaunchAllocEntropy {
     using N = Lanes<G, BF16 ? 2 : 4>;
     template <int LPT, bool WAVE_TEAM>
-    static void go(const void *d_in, float *d_H, uint32_t n_alloc, uint32_t m, float eps_l1, float eps_log, const Prologue &pro, Enqueue *qp)
+    static void go(const void *d_in, float *d_H, uint8_t *pivot, uint32_t n_alloc, uint32_t m, const EntropyParams &p, const Prologue &pro, Enqueue *qp)
     {
         Enqueue &q = *qp;
         constexpr uint32_t SLOTS = (WAVE_TEAM ? 64 : 256) / LPT, TEAMS = WAVE_TEAM ? 4 : 1;
         const uint32_t per = SLOTS / m, nb = (n_alloc + per * TEAMS - 1) / (per * TEAMS);
-        void (*kernel)(const void *, float *, uint32_t, uint32_t, uint32_t, uint32_t, float, float, uint32_t, Prologue);
+        void (*kernel)(const void *, float *, uint8_t *, uint32_t, uint32_t, uint32_t, uint32_t, float, float, uint32_t, float, float, Prologue);
         if constexpr (LPT == N::usual && WAVE_TEAM) kernel = k_alloc_entropy<G, BF16>;
         else kernel = k_alloc_entropy_by<G, BF16, LPT, WAVE_TEAM>;
         static ResidentCache cache;
         const uint32_t res = resident_blocks(reinterpret_cast<const void *>(kernel), 256, cache);
         const uint32_t grid = nb < res ? nb : res;
-        q(kernel, dim3(grid), dim3(256), d_in, d_H, n_alloc, grid, m, per, eps_l1, eps_log,
-          prologue_blocks(pro, 256, grid), pro);
+        q(kernel, dim3(grid), dim3(256), d_in, d_H, pivot, n_alloc, grid, m, per, p.eps_l1, p.eps_log,
+          prologue_blocks(pro, 256, grid), p.tau, p.eps_ratio, pro);
     }
     // A wavefront by itself where it wastes no more lanes than a workgroup would.
     template <int LPT>
-    static void one_pass(const void *d_in, float *d_H, uint32_t n_alloc, uint32_t m, float eps_l1, float eps_log, const Prologue &pro, Enqueue *qp)
+    static void one_pass(const void *d_in, float *d_H, uint8_t *pivot, uint32_t n_alloc, uint32_t m, const EntropyParams &p, const Prologue &pro, Enqueue *qp)
     {
         const uint32_t by_wave = 4 * (64 / LPT / m), by_group = 256 / LPT / m;       // allocation tiles per workgroup
-        if (by_wave >= by_group) go<LPT, true>(d_in, d_H, n_alloc, m, eps_l1, eps_log, pro, qp);
-        else go<LPT, false>(d_in, d_H, n_alloc, m, eps_l1, eps_log, pro, qp);
+        if (by_wave >= by_group) go<LPT, true>(d_in, d_H, pivot, n_alloc, m, p, pro, qp);
+        else go<LPT, false>(d_in, d_H, pivot, n_alloc, m, p, pro, qp);
     }
     // Entropies of allocation tiles of m > 1 quantization tiles: one pass if a workgroup's lanes hold whole
     // allocation tiles, otherwise two streaming passes over the tensor.
-    static void run(const void *d_in, float *d_H, float *part, float *inv_norm, uint32_t T, uint32_t m, float eps_l1,
-                    float eps_log, Prologue pro, Enqueue *qp)
+    static void run(const void *d_in, float *d_H, float *part, float *inv_norm, uint8_t *pivot, uint32_t T, uint32_t m, EntropyParams p,
+                    Prologue pro, Enqueue *qp)
     {
         Enqueue &q = *qp;
         const uint32_t n_alloc = T / m;
-        if (few_tiles<N>(T, 4) && m <= 256 / N::few) { one_pass<N::few>(d_in, d_H, n_alloc, m, eps_l1, eps_log, pro, qp); return; }
-        if (m <= 256 / N::usual) { one_pass<N::usual>(d_in, d_H, n_alloc, m, eps_l1, eps_log, pro, qp); return; }
+        if (few_tiles<N>(T, 4) && m <= 256 / N::few) { one_pass<N::few>(d_in, d_H, pivot, n_alloc, m, p, pro, qp); return; }
+        if (m <= 256 / N::usual) { one_pass<N::usual>(d_in, d_H, pivot, n_alloc, m, p, pro, qp); return; }
         using B = Batch<G, BF16 ? 2 : 4>;
         const uint32_t nb = (T + B::TILES - 1) / B::TILES;
         q(k_tile_partial<G, BF16, false>, dim3(nb), dim3(B::TILES), d_in,
-                           (const float *)nullptr, part, T, m, eps_log, prologue_blocks(pro, B::TILES, nb), pro);
+                           (const float *)nullptr, part, pivot, T, m, p.eps_log, p.tau, p.eps_ratio, prologue_blocks(pro, B::TILES, nb), pro);
         q(k_alloc_reduce<false>, dim3(blocks_for(n_alloc)), dim3(256), (const float *)part, (const float *)nullptr,
-                           inv_norm, n_alloc, m, eps_l1);
+                           inv_norm, n_alloc, m, p.eps_l1);
         q(k_tile_partial<G, BF16, true>, dim3(nb), dim3(B::TILES), d_in,
-                           (const float *)inv_norm, part, T, m, eps_log, 0u, Prologue{});
+                           (const float *)inv_norm, part, (uint8_t *)nullptr, T, m, p.eps_log, p.tau, p.eps_ratio, 0u, Prologue{});
         q(k_alloc_reduce<true>, dim3(blocks_for(n_alloc)), dim3(256), (const float *)part, (const float *)inv_norm,
-                           d_H, n_alloc, m, eps_l1);
+                           d_H, n_alloc, m, p.eps_l1);
     }
 };
 
-// Entropy of every quantization tile; with `hist`, also the selection's first histogram (the caller has checked
-// that the ranking units are whole batches).
-void launch_entropy(const Shape &s, const tahq_config *cfg, const void *d_in, float *d_H, uint32_t *hist, uint32_t bins,
-                    float bin_scale, const Prologue &pro, Enqueue *qp)
+// Entropy of every quantization tile; with `pivot`, also Eq. 3; with `hist`, also the selection's first histogram (the caller has
+// checked that the ranking units are whole steps).
+void launch_entropy(const Shape &s, const tahq_config *cfg, const void *d_in, float *d_H, uint8_t *pivot, bool approx, uint32_t *hist,
+                    uint32_t bins, float bin_scale, const Prologue &pro, Enqueue *qp)
 {
-    dispatch<LaunchEntropy>(s.G, s.dtype == TAHQ_BF16, d_in, d_H, (uint32_t)s.T, cfg->eps_l1, cfg->eps_log, hist, bins,
-                            bin_scale, s.n, pro, qp);
+    EntropyParams p = entropy_params(cfg);
+    p.approx = approx;
+    dispatch<LaunchEntropy>(s.G, s.dtype == TAHQ_BF16, d_in, d_H, pivot, (uint32_t)s.T, p, hist, bins, bin_scale, s.n, pro, qp);
 }
+
+// The first launch of the two-launch selection, with approximate entropies (bf16).
+template <int G, bool BF16>
+struct LaunchClassify {
+    static void run(dim3 grid, float *H, const Shape &s, uint32_t u0, float bin_scale, const uint32_t *lin_hist, uint32_t *fused,
+                    uint2 *cand, uint2 *block_counts, uint32_t *crowd_hist, uint64_t *bitmap, const void *d_in, EntropyParams p, Enqueue *qp)
+    {
+        (*qp)(k_select_classify<G, true, true>, grid, dim3(kFusedThreads), H, (uint32_t)s.n, (uint32_t)s.k, u0, bin_scale, lin_hist, fused,
+              cand, block_counts, crowd_hist, bitmap, d_in, p.eps_l1, p.eps_log, kEntropySlack);
+    }
+};
 
 template <uint32_t PLACES, uint32_t BINS, int SHIFT>
 void launch_select_small(dim3 grid, const float *H, uint32_t n, uint32_t k, const Shape &s, uint64_t *bitmap, uint32_t *ranks,
@@ -406,7 +444,7 @@ tahq_status tahq_tile_entropy(const tahq_config *cfg, const void *d_in, float *d
     if (!d_in || !d_entropy) return TAHQ_ERR_NULL;
     if (misaligned(d_in) || misaligned(d_entropy)) return TAHQ_ERR_MISALIGNED;
     Enqueue q{(hipStream_t)stream};
-    launch_entropy(s, cfg, d_in, d_entropy, nullptr, 0u, 0.0f, Prologue{}, &q);
+    launch_entropy(s, cfg, d_in, d_entropy, nullptr, false, nullptr, 0u, 0.0f, Prologue{}, &q);
     return q.result();
 }
 
@@ -420,7 +458,7 @@ tahq_status tahq_alloc_tile_entropy(const tahq_config *cfg, const void *d_in, fl
     if (misaligned(d_in) || misaligned(d_entropy)) return TAHQ_ERR_MISALIGNED;
     Enqueue q{(hipStream_t)stream};
     if (s.m == 1) {
-        launch_entropy(s, cfg, d_in, d_entropy, nullptr, 0u, 0.0f, Prologue{}, &q);
+        launch_entropy(s, cfg, d_in, d_entropy, nullptr, false, nullptr, 0u, 0.0f, Prologue{}, &q);
     } else {
         if (!d_workspace) return TAHQ_ERR_NULL;
         Workspace ws;
@@ -430,8 +468,8 @@ tahq_status tahq_alloc_tile_entropy(const tahq_config *cfg, const void *d_in, fl
         uint8_t *wsb = static_cast<uint8_t *>(d_workspace);
         dispatch<LaunchAllocEntropy>(s.G, s.dtype == TAHQ_BF16, d_in, d_entropy,
                                      reinterpret_cast<float *>(wsb + ws.part),
-                                     reinterpret_cast<float *>(wsb + ws.inv_norm), (uint32_t)s.T, s.m, cfg->eps_l1,
-                                     cfg->eps_log, Prologue{}, &q);
+                                     reinterpret_cast<float *>(wsb + ws.inv_norm), (uint8_t *)nullptr, (uint32_t)s.T, s.m,
+                                     entropy_params(cfg), Prologue{}, &q);
     }
     return q.result();
 }
@@ -519,6 +557,7 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
         // tiles, and every unit when the caller forces it, by the multi-launch radix select, whose first digit the entropy
         // kernel counts where units are whole batches.
         const bool fused_select = !wide && !small_units && !multi_launch;
+        const bool approx = fused_select && approximate_entropies(s, cfg);
         bool fused = false;
         if (!wide && multi_launch) dispatch<CanFuse>(s.G, s.dtype == TAHQ_BF16, s.n, &fused);
         uint32_t *lin_hist = reinterpret_cast<uint32_t *>(wsb + ws.lin_hist);
@@ -527,27 +566,30 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
         if (phases & TAHQ_PHASE_ENTROPY) {
             if (wide)
                 dispatch<LaunchAllocEntropy>(s.G, s.dtype == TAHQ_BF16, d_in, H, reinterpret_cast<float *>(wsb + ws.part),
-                                             reinterpret_cast<float *>(wsb + ws.inv_norm), (uint32_t)s.T, s.m,
-                                             cfg->eps_l1, cfg->eps_log, pro, &q);
+                                             reinterpret_cast<float *>(wsb + ws.inv_norm), packed + lay.pivot, (uint32_t)s.T,
+                                             s.m, entropy_params(cfg), pro, &q);
             else if (fused_select)
-                launch_entropy(s, cfg, d_in, H, lin_hist, kLinBins, bin_scale, pro, &q);
+                launch_entropy(s, cfg, d_in, H, packed + lay.pivot, approx, lin_hist, kLinBins, bin_scale, pro, &q);
             else
-                launch_entropy(s, cfg, d_in, H, fused ? hist0 : (uint32_t *)nullptr, kDigit0Bins, 0.0f, pro, &q);
+                launch_entropy(s, cfg, d_in, H, packed + lay.pivot, false, fused ? hist0 : (uint32_t *)nullptr, kDigit0Bins, 0.0f, pro, &q);
         }
         if ((phases & TAHQ_PHASE_SELECT) && fused_select) {
             uint32_t *fused_state = reinterpret_cast<uint32_t *>(wsb + ws.fused);
             uint2 *cand = reinterpret_cast<uint2 *>(wsb + ws.cand);
-            uint32_t *block_above = seg;             // fewer entries than the segments it was made for
+            uint2 *block_counts = reinterpret_cast<uint2 *>(seg);          // fewer entries than the segments it was made for
             for (uint32_t u0 = 0; u0 < s.U; u0 += kMaxGridY) {
                 const dim3 grid((uint32_t)((places + kFusedKeysPerBlock - 1) / kFusedKeysPerBlock),
                                 s.U - u0 < kMaxGridY ? s.U - u0 : kMaxGridY);
-                q(k_select_classify, grid, dim3(kFusedThreads), (const float *)H, (uint32_t)s.n,
-                                   (uint32_t)s.k, u0, bin_scale, (const uint32_t *)lin_hist, fused_state, cand, block_above,
-                                   hist0, bitmap);
+                if (approx)
+                    dispatch<LaunchClassify>(s.G, true, grid, H, s, u0, bin_scale, (const uint32_t *)lin_hist, fused_state, cand,
+                                             block_counts, hist0, bitmap, d_in, entropy_params(cfg), &q);
+                else
+                    q(k_select_classify<64, true, false>, grid, dim3(kFusedThreads), H, (uint32_t)s.n, (uint32_t)s.k, u0, bin_scale,
+                      (const uint32_t *)lin_hist, fused_state, cand, block_counts, hist0, bitmap, d_in, 0.0f, 0.0f, 0.0f);
                 q(k_select_resolve, grid, dim3(kFusedThreads), (const float *)H, (uint32_t)s.n,
-                                   (uint32_t)s.k, u0, bin_scale, (const uint32_t *)lin_hist, fused_state, cand,
-                                   (const uint32_t *)block_above, (const uint32_t *)hist0, reinterpret_cast<uint64_t *>(sel),
-                                   bitmap, ranks);
+                                   (uint32_t)s.k, u0, bin_scale, approx ? 2.0f * kEntropySlack : 0.0f, (const uint32_t *)lin_hist,
+                                   fused_state, cand, (const uint2 *)block_counts, (const uint32_t *)hist0,
+                                   reinterpret_cast<uint64_t *>(sel), bitmap, ranks);
             }
         } else
         if ((phases & TAHQ_PHASE_SELECT) && small_units) {
@@ -590,7 +632,8 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
 
     if (phases & TAHQ_PHASE_QUANT) {
         dispatch<LaunchQuantPack>(s.G, s.dtype == TAHQ_BF16, s.low, d_in, packed, (uint32_t)s.T, cfg->tau,
-                                  cfg->eps_ratio, !all_in_quant, s.kA == s.nA, pro, &q);
+                                  cfg->eps_ratio, select, (s.kA == s.nA ? QUANT_ALL_WIDE : 0u) | (stream_bytes(s) >= kStreamingFrom ? QUANT_STREAMING : 0u),
+                                  pro, &q);
     }
     return q.result();
 }

@@ -854,30 +854,55 @@ __device__ __forceinline__ void put_word(uint64_t *word, uint64_t mask, uint64_t
     else atomicOr(reinterpret_cast<unsigned long long *>(word), (unsigned long long)bits);
 }
 
+// The edges of the threshold bin as bit patterns, first and last, as signed integers (negative values and NaN with the sign bit set
+// lowest), `margin` further apart: tiles between them are the candidates.
+struct BinEdges {
+    int first, last;
+    __device__ __forceinline__ BinEdges(uint32_t bin, float scale, float margin)
+    {
+        // (a bin is wider than the margin, so the second bin's edge is above it)
+        first = bin == 0 ? INT32_MIN + 1 : (int)__float_as_uint(__uint_as_float((uint32_t)linear_bin_edge(bin, scale)) - margin);
+        last = bin == kLinBins - 1 ? INT32_MAX
+                                   : (int)__float_as_uint(__uint_as_float((uint32_t)linear_bin_edge(bin + 1, scale) - 1u) + margin);
+    }
+};
+
 // A workgroup takes 16384 places, its wavefront w the blocks w, w + 16, .. of 256, four consecutive places per lane.  The
 // threshold bin's edges turn into bit patterns once, so that an entropy costs two comparisons and its two bits; lanes collect
 // them in nibbles (a ballot per 64 entropies, and the bin of every entropy, took 2.5 us longer).
-__global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *__restrict__ H, uint32_t n, uint32_t k,
+//
+// APPROX: the entropies in H are within `slack` of the exact ones, and so is the k-th largest of them of the exact threshold.  The
+// candidates are then the tiles of the threshold bin and of a margin of 2 slack on either side: whoever is above that has an exact
+// entropy above the exact threshold, whoever is below one below it.  The workgroup computes its candidates' exact entropies from
+// the tensor (1.3 % of the tiles of [8,4096,8192], G = 64) and lists those.  How many candidates the margins add is not in the
+// histogram; where the two bins beside the threshold's could fill the list, the entropies go back into H, for candidates held
+// to the margins' ends (who is beyond them is decided), and are counted by sub-bin as for a crowd, in case it came to that.
+template <int G, bool BF16, bool APPROX>
+__global__ __launch_bounds__(kFusedThreads) void k_select_classify(float *__restrict__ H, uint32_t n, uint32_t k,
                                                                    uint32_t unit0, float bin_scale,
                                                                    const uint32_t *__restrict__ lin_hist,
                                                                    uint32_t *__restrict__ fused,
                                                                    uint2 *__restrict__ cand,
-                                                                   uint32_t *__restrict__ block_above,
+                                                                   uint2 *__restrict__ block_counts,
                                                                    uint32_t *__restrict__ crowd_hist,
-                                                                   uint64_t *__restrict__ bitmap)
+                                                                   uint64_t *__restrict__ bitmap, const void *__restrict__ in,
+                                                                   float eps_l1, float eps_log, float slack)
 {
     constexpr uint32_t WAVES = kFusedThreads / 64, BLOCKS = kFusedKeysPerBlock / 256 / WAVES;
     static_assert(kSubBins == kFusedThreads, "one sub-bin per thread");
     __shared__ uint32_t sub_hist[kSubBins];
     __shared__ uint32_t chosen[4];               // threshold bin, wanted inside it, its tiles; the workgroup's place in the list
     __shared__ uint32_t wave_cand[WAVES], wave_above[WAVES];
+    __shared__ uint16_t picked[APPROX ? kFusedKeysPerBlock : 1];         // the candidates, as places of the block
+    static_assert(kFusedKeysPerBlock <= 65536, "places of a block in 16 bits");
     const uint32_t u = unit0 + blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
     const UnitPlaces at(u, n);
-    const float *uH = H + ((uint64_t)u * n - at.phase);      // by place
+    float *uH = H + ((uint64_t)u * n - at.phase);            // by place
     uint2 *ucand = cand + (uint64_t)u * kCandCap;
     uint32_t *ubits = reinterpret_cast<uint32_t *>(bitmap + at.word0);
+    const uint32_t *uhist = lin_hist + (uint64_t)u * kLinBins;
 
     // all loads first.  (Whole words of 64 places, which may reach into the neighbouring units or past the entropies to the end of
     // their padded array; beyond them from a clamped index.)
@@ -889,13 +914,17 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *
         q[r] = *reinterpret_cast<const int4 *>(uH + (p < top ? p : top));
     }
     if (tid == 0) { chosen[0] = 0; chosen[1] = 0; chosen[2] = 0; }           // (for a histogram that does not hold k)
-    block_pick_bin<kLinBins>(lin_hist + (uint64_t)u * kLinBins, k, wave_above, chosen);
+    sub_hist[tid] = 0;
+    block_pick_bin<kLinBins>(uhist, k, wave_above, chosen);
     const uint32_t bstar = (uint32_t)__builtin_amdgcn_readfirstlane((int)chosen[0]);
-    // the bit patterns of that bin, first and last, as signed integers (negative values and NaN with the sign bit set lowest)
-    const int first = bstar == 0 ? INT32_MIN + 1 : linear_bin_edge(bstar, bin_scale);
-    const int last = bstar == kLinBins - 1 ? INT32_MAX : linear_bin_edge(bstar + 1, bin_scale) - 1;
+    const uint32_t in_bin = (uint32_t)__builtin_amdgcn_readfirstlane((int)chosen[2]);
+    const bool crowd = in_bin > crowd_from(n);               // (the same for all of the unit's workgroups, like `doubt`)
+    bool doubt = false;
+    if constexpr (APPROX) doubt = !crowd && in_bin + (bstar != 0 ? uhist[bstar - 1] : 0u) + (bstar != kLinBins - 1 ? uhist[bstar + 1] : 0u) > kCandCap;
+    const BinEdges edge(bstar, bin_scale, APPROX ? 2.0f * slack : 0.0f);
+    const int first = edge.first, last = edge.last;
 
-    uint32_t inside = 0, n_above = 0;            // my tiles of the bin, four bits per block, the last block lowest
+    uint32_t inside = 0, n_above = 0;            // my candidates, four bits per block, the last block lowest
 #pragma unroll
     for (uint32_t r = 0; r < BLOCKS; ++r) {
         const uint32_t base = blockIdx.x * kFusedKeysPerBlock + (r * WAVES + wave) * 256u, p = base + 4u * lane;
@@ -915,9 +944,52 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *
             else atomicOr(&ubits[p >> 5], d);    // (a word that units share: cleared by an earlier kernel)
         }
     }
-    if (__builtin_expect(chosen[2] > crowd_from(n), 0)) {    // (the same for all of the unit's workgroups)
-        sub_hist[tid] = 0;
+    // one place in the list for the whole workgroup (a unit's workgroups all add to one counter: few, large additions)
+    const uint32_t count = (uint32_t)__popc(inside), incl = wave_incl_scan(count), incl_above = wave_incl_scan(n_above);
+    __syncthreads();                             // everybody has the threshold bin: `wave_above` is used again
+    if (lane == 63) { wave_cand[wave] = incl; wave_above[wave] = incl_above; }
+    __syncthreads();
+    const uint32_t before = sum_of_waves_before(wave_cand, wave, lane);
+    if (wave == WAVES - 1) {
+        const uint32_t above_before = sum_of_waves_before(wave_above, wave, lane);
+        if (lane == 63) {
+            chosen[2] = before + incl;
+            chosen[3] = before + incl != 0 && !crowd ? atomicAdd(&fused[(uint64_t)u * 4], before + incl) : 0u;
+            block_counts[(uint64_t)u * gridDim.x + blockIdx.x] = make_uint2(above_before + incl_above, before + incl);
+        }
+    }
+    if constexpr (APPROX) {
+        uint32_t pos = before + incl - count;
+        for (uint32_t left = inside; left != 0; left &= left - 1u) {
+            const uint32_t bit = (uint32_t)__ffs((int)left) - 1u;
+            picked[pos++] = (uint16_t)((BLOCKS - 1 - bit / 4) * (WAVES * 256u) + wave * 256u + 4u * lane + bit % 4);
+        }
         __syncthreads();
+        using L = Lanes<G, BF16 ? 2 : 4>;
+        using W = Wave<G, BF16 ? 2 : 4, L::few>;
+        const uint32_t total = chosen[2], list_at = chosen[3], part = (uint32_t)tid % L::few;
+        for (uint32_t i = (uint32_t)tid / L::few; i < total; i += kFusedThreads / L::few) {
+            const uint32_t place = blockIdx.x * kFusedKeysPerBlock + picked[i];
+            const uint64_t j = (uint64_t)u * n + (place - at.phase);
+            TensorRow<W, BF16> x(static_cast<const uint8_t *>(in) + (j * L::few + part) * W::LANE_BYTES);
+            float h = entropy_of<W::EPL, L::few>(x, eps_l1, eps_log);
+            if (part != 0) continue;
+            if (h != h) h = uH[place];           // (no number, and exact as it was)
+            const uint32_t pos_in_list = list_at + i;
+            if (!crowd && pos_in_list < kCandCap) ucand[pos_in_list] = make_uint2(order_key(h), place);
+            if (crowd || doubt) {
+                int v = (int)__float_as_uint(h);
+                v = v < first ? first : v > last ? last : v;
+                uH[place] = __uint_as_float((uint32_t)v);
+                // (tiles that are alike meet on one counter: one addition for the wavefront's)
+                const uint32_t bin = crowd_sub_bin(__uint_as_float((uint32_t)v), bin_scale, bstar);
+                const uint32_t lead = (uint32_t)__builtin_amdgcn_readfirstlane((int)bin);
+                const uint64_t here = __ballot(true), same = __ballot(bin == lead);
+                if (here != same) atomicAdd(&sub_hist[bin], 1u);
+                else if (bits_below_me(here) == 0) atomicAdd(&sub_hist[lead], (uint32_t)__popcll(here));
+            }
+        }
+    } else if (crowd) {
         if (inside != 0) {
 #pragma unroll
             for (uint32_t r = 0; r < BLOCKS; ++r) {
@@ -934,39 +1006,28 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(const float *
                 }
             }
         }
+    } else {
         __syncthreads();
-        if (sub_hist[tid] != 0) atomicAdd(&crowd_hist[(uint64_t)u * kSubBins + tid], sub_hist[tid]);
-        return;
-    }
-    // one place in the list for the whole workgroup (a unit's workgroups all add to one counter: few, large additions)
-    const uint32_t count = (uint32_t)__popc(inside), incl = wave_incl_scan(count), incl_above = wave_incl_scan(n_above);
-    __syncthreads();                             // everybody has the threshold bin: `wave_above` is used again
-    if (lane == 63) { wave_cand[wave] = incl; wave_above[wave] = incl_above; }
-    __syncthreads();
-    const uint32_t before = sum_of_waves_before(wave_cand, wave, lane);
-    if (wave == WAVES - 1) {
-        const uint32_t above_before = sum_of_waves_before(wave_above, wave, lane);
-        if (lane == 63) {
-            chosen[3] = before + incl ? atomicAdd(&fused[(uint64_t)u * 4], before + incl) : 0u;
-            block_above[(uint64_t)u * gridDim.x + blockIdx.x] = above_before + incl_above;
-        }
-    }
-    __syncthreads();
-    uint32_t pos = chosen[3] + before + incl - count;
-    if (__ballot(inside != 0) != 0) {
-        // (from registers: a lane may hold sixteen of them, where tiles are all zero)
+        uint32_t pos = chosen[3] + before + incl - count;
+        if (__ballot(inside != 0) != 0) {
+            // (from registers: a lane may hold sixteen of them, where tiles are all zero)
 #pragma unroll
-        for (uint32_t r = 0; r < BLOCKS; ++r) {
-            const int v[4] = {q[r].x, q[r].y, q[r].z, q[r].w};
+            for (uint32_t r = 0; r < BLOCKS; ++r) {
+                const int v[4] = {q[r].x, q[r].y, q[r].z, q[r].w};
 #pragma unroll
-            for (uint32_t c = 0; c < 4; ++c) {
-                if ((inside >> (4 * (BLOCKS - 1 - r) + c)) & 1u) {
-                    if (pos < kCandCap)
-                        ucand[pos] = make_uint2(order_key(__uint_as_float((uint32_t)v[c])), place0 + r * (WAVES * 256u) + c);
-                    ++pos;
+                for (uint32_t c = 0; c < 4; ++c) {
+                    if ((inside >> (4 * (BLOCKS - 1 - r) + c)) & 1u) {
+                        if (pos < kCandCap)
+                            ucand[pos] = make_uint2(order_key(__uint_as_float((uint32_t)v[c])), place0 + r * (WAVES * 256u) + c);
+                        ++pos;
+                    }
                 }
             }
         }
+    }
+    if (crowd || doubt) {
+        __syncthreads();
+        if (sub_hist[tid] != 0) atomicAdd(&crowd_hist[(uint64_t)u * kSubBins + tid], sub_hist[tid]);
     }
 }
 
@@ -976,6 +1037,7 @@ struct ResolveLds {
     uint64_t list[kFusedThreads];                // candidates that are placed directly: key << 32 | ~tile
     uint32_t chosen[6];                          // threshold bin, wanted inside it, its tiles; the same of the threshold sub-bin
     uint32_t listed, n_before;
+    uint32_t above, candidates;                  // of the unit, by k_select_classify's counts
     uint32_t wave_total[kFusedThreads / 64];
     uint32_t words[2 * (kFusedKeysPerBlock / 64)];           // the block's bit map words, as dwords
 };
@@ -1046,9 +1108,10 @@ __device__ __forceinline__ void rank_candidates(uint32_t rem, uint32_t count, ui
 // A unit whose threshold bin holds more tiles than the candidate list: workgroup `blk` of `blocks`, each of 16384 places.
 // Every workgroup first settles its own tiles: those above the threshold's sub-bin into the bit map, those in it (`crowd`, of which
 // `rem` are selected) into `equal`, words over places that only this unit has; it finds the range of their keys and, where they
-// fit, lists them.  The last of the unit's workgroups to finish then knows them all.
+// fit, lists them (in a list of their own: `listed_before` is what k_select_classify has listed).  The last of the unit's workgroups to finish then knows them all.
 __device__ __forceinline__ void resolve_crowd(const float *__restrict__ H, uint32_t n, uint32_t k, uint32_t u, uint32_t blk,
-                                              uint32_t blocks, float bin_scale, uint32_t bstar, uint32_t rem,
+                                              uint32_t blocks, float bin_scale, float margin, uint32_t bstar, uint32_t rem,
+                                              uint32_t listed_before,
                                               const uint32_t *crowd_hist, uint32_t *state, uint2 *ucand, uint64_t *equal,
                                               uint64_t *bitmap, uint32_t *ranks, ResolveLds &L)
 {
@@ -1075,8 +1138,8 @@ __device__ __forceinline__ void resolve_crowd(const float *__restrict__ H, uint3
     rem = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[4]);
     uint32_t crowd = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[5]);
     const bool list_them = crowd <= kCandCap;
-    const int first = bstar == 0 ? INT32_MIN + 1 : linear_bin_edge(bstar, bin_scale);
-    const int last = bstar == kLinBins - 1 ? INT32_MAX : linear_bin_edge(bstar + 1, bin_scale) - 1;
+    const BinEdges edge(bstar, bin_scale, margin);
+    const int first = edge.first, last = edge.last;
 
     uint32_t inside = 0, key_max = 0, not_key_min = 0;
 #pragma unroll
@@ -1112,7 +1175,7 @@ __device__ __forceinline__ void resolve_crowd(const float *__restrict__ H, uint3
     __syncthreads();
     const uint32_t before = sum_of_waves_before(L.wave_total, wave, lane);
     if (wave == WAVES - 1 && lane == 63 && before + incl != 0) {
-        L.chosen[0] = list_them ? atomicAdd(&state[0], before + incl) : 0u;
+        L.chosen[0] = list_them ? atomicAdd(&state[0], before + incl) - listed_before : 0u;
         atomicMax(&state[2], L.n_before);
         atomicMax(&state[3], L.listed);
     }
@@ -1283,11 +1346,11 @@ __device__ __forceinline__ void resolve_crowd(const float *__restrict__ H, uint3
 }
 
 __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *__restrict__ H, uint32_t n, uint32_t k,
-                                                                  uint32_t unit0, float bin_scale,
+                                                                  uint32_t unit0, float bin_scale, float margin,
                                                                   const uint32_t *__restrict__ lin_hist,
                                                                   uint32_t *__restrict__ fused,
                                                                   uint2 *__restrict__ cand,
-                                                                  const uint32_t *__restrict__ block_above,
+                                                                  const uint2 *__restrict__ block_counts,
                                                                   const uint32_t *__restrict__ crowd_hist,
                                                                   uint64_t *__restrict__ equal,
                                                                   uint64_t *__restrict__ bitmap,
@@ -1311,22 +1374,35 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
     uint2 c[CPT];
 #pragma unroll
     for (int r = 0; r < AHEAD; ++r) c[r] = ucand[(uint32_t)r * kFusedThreads + tid];
-    const uint32_t listed = fused[(uint64_t)u * 4];
     uint64_t my_word = 0;
     if ((uint32_t)tid < mygroups) my_word = ubitmap[group0 + tid] & at.mask(group0 + tid);
-    uint32_t above_before = 0;
-    for (uint32_t b = tid; b < blk; b += kFusedThreads) above_before += block_above[(uint64_t)u * gridDim.x + b];
+    uint32_t above_before = 0, above_all = 0, cand_all = 0;
+    for (uint32_t b = tid; b < gridDim.x; b += kFusedThreads) {
+        const uint2 counts = block_counts[(uint64_t)u * gridDim.x + b];
+        above_before += b < blk ? counts.x : 0u;
+        above_all += counts.x;
+        cand_all += counts.y;
+    }
     if (tid < 6) L.chosen[tid] = 0;              // (for histograms that do not hold as many as are wanted)
-    if (tid == 0) { L.n_before = 0; L.listed = 0; }
+    if (tid == 0) { L.n_before = 0; L.listed = 0; L.above = 0; L.candidates = 0; }
     static_assert(kSubBins == kFusedThreads, "one sub-bin per thread");
     uint32_t *sub_hist = L.hist;                 // the threshold bin's candidates by sub-bin
     sub_hist[tid] = 0;
     if ((uint32_t)tid < GROUPS) { L.words[2 * tid] = (uint32_t)my_word; L.words[2 * tid + 1] = (uint32_t)(my_word >> 32); }
     block_pick_bin<kLinBins>(lin_hist + (uint64_t)u * kLinBins, k, L.wave_total, L.chosen);
-    const uint32_t bstar = L.chosen[0], rem = L.chosen[1];
+    {
+        const uint32_t a = wave_incl_scan(above_all), c = wave_incl_scan(cand_all);
+        if (lane == 63 && a != 0) atomicAdd(&L.above, a);
+        if (lane == 63 && c != 0) atomicAdd(&L.candidates, c);
+    }
+    __syncthreads();
+    // wanted among the candidates (where the histogram does not hold k: none)
+    const uint32_t bstar = L.chosen[0], rem = L.chosen[1] != 0 ? k - L.above : 0u;
+    const bool not_listed = L.chosen[2] > crowd_from(n);
+    const uint32_t listed = not_listed ? 0u : L.candidates;
 
-    if (__builtin_expect(L.chosen[2] > crowd_from(n), 0)) {  // (the same for all of the unit's workgroups)
-        resolve_crowd(H, n, k, u, blk, gridDim.x, bin_scale, bstar, rem, crowd_hist, fused + (uint64_t)u * 4, ucand,
+    if (__builtin_expect(not_listed || (rem != 0 && listed > kCandCap), 0)) {          // (the same for all of the unit's workgroups)
+        resolve_crowd(H, n, k, u, blk, gridDim.x, bin_scale, margin, bstar, rem, listed, crowd_hist, fused + (uint64_t)u * 4, ucand,
                       equal + (uint64_t)u * (n / 64 + 2), bitmap, ranks, L);
         return;
     }

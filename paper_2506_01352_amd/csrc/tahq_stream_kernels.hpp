@@ -211,6 +211,164 @@ __device__ __forceinline__ void wave_lds_fence()
     __builtin_amdgcn_wave_barrier();
 }
 
+// ------------------------------------------------------------- outlier test
+
+// Median of three unsigned integers in one vector instruction.
+__device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c)
+{
+    uint32_t r;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// Eq. 3 on a tile of LPT parts, of which I have the part-th, G elements: the magnitudes of the largest and the second-largest element
+// (with multiplicity) and the lowest index of the largest.  Elements come in index order, by pairs, then `finish`.
+template <int G, bool BF16, int LPT> struct Top2;
+
+// A bf16 magnitude has 16 free low bits: key = |bits| << 16 | (G-1-k) orders by magnitude, then by
+// lower index, under unsigned integer max.  Even and odd elements run in separate chains.
+template <int G, int LPT>
+struct Top2<G, true, LPT> {
+    // (the even chain's keys are shifted left by one, which drops the sign bit for free, and hold (G - 2 - k) / 2 for the index: the
+    // constants of both chains fit the instructions)
+    uint32_t e1 = 0, e2 = 0, o1 = 0, o2 = 0;
+    // the pair of elements k, k + 1 as it lies in memory
+    __device__ __forceinline__ void add(uint32_t k, uint32_t pair)
+    {
+        add_even((pair << 17) | (G - 2 - k));
+        add_odd((pair & 0x7fff0000u) | (G - 2 - k));
+    }
+    __device__ __forceinline__ void finish(uint32_t part, float *a1_out, float *a2_out, uint32_t *d_out)
+    {
+        e1 = ((e1 >> 1) & 0x7fff0000u) | ((e1 & 0xffffu) + 1u);      // G - 1 - k
+        e2 = ((e2 >> 1) & 0x7fff0000u) | ((e2 & 0xffffu) + 1u);
+        uint32_t k1 = e1 > o1 ? e1 : o1;
+        const uint32_t lo = e1 > o1 ? o1 : e1;
+        const uint32_t hi2 = e2 > o2 ? e2 : o2;
+        uint32_t k2 = lo > hi2 ? lo : hi2;
+        // the other parts of the tile: two pairs become one
+        auto merge = [&](uint32_t p1, uint32_t p2) {
+            const uint32_t less = k1 < p1 ? k1 : p1, more2 = k2 > p2 ? k2 : p2;
+            k1 = k1 > p1 ? k1 : p1;
+            k2 = less > more2 ? less : more2;
+        };
+        if constexpr (LPT >= 2) {
+            k1 += (LPT - 1 - part) * G;          // the low bits count indices of the whole tile from its end
+            merge(lane_xor<1>(k1), lane_xor<1>(k2));
+        }
+        if constexpr (LPT >= 4) merge(lane_xor<2>(k1), lane_xor<2>(k2));
+        *a1_out = __uint_as_float(k1 & 0x7fff0000u);
+        *a2_out = __uint_as_float(k2 & 0x7fff0000u);
+        *d_out = (LPT * G - 1) - (k1 & 0x7fu);
+    }
+private:
+    __device__ __forceinline__ void add_even(uint32_t key)
+    {
+        e2 = umed3(e1, e2, key);                 // second largest of {e1 >= e2, key}
+        e1 = e1 > key ? e1 : key;
+    }
+    __device__ __forceinline__ void add_odd(uint32_t key)
+    {
+        o2 = umed3(o1, o2, key);
+        o1 = o1 > key ? o1 : key;
+    }
+};
+
+template <int G, int LPT>
+struct Top2<G, false, LPT> {
+    float a1 = -1.0f, a2 = 0.0f;                 // magnitudes are >= 0: the first element always replaces a1
+    uint32_t d = 0;
+    __device__ __forceinline__ void add(uint32_t k, float x0, float x1)
+    {
+        add_one(k, x0);
+        add_one(k + 1, x1);
+    }
+    __device__ __forceinline__ void finish(uint32_t part, float *a1_out, float *a2_out, uint32_t *d_out)
+    {
+        auto merge = [&](float p1, float p2, uint32_t pd) {
+            const bool other = p1 > a1 || (p1 == a1 && pd < d);
+            a2 = __builtin_fmaxf(__builtin_fminf(a1, p1), __builtin_fmaxf(a2, p2));
+            a1 = other ? p1 : a1;
+            d = other ? pd : d;
+        };
+        if constexpr (LPT >= 2) {
+            d += part * G;
+            merge(lane_xor<1>(a1), lane_xor<1>(a2), lane_xor<1>(d));
+        }
+        if constexpr (LPT >= 4) merge(lane_xor<2>(a1), lane_xor<2>(a2), lane_xor<2>(d));
+        *a1_out = a1;
+        *a2_out = __builtin_fmaxf(a2, 0.0f);
+        *d_out = d;
+    }
+private:
+    __device__ __forceinline__ void add_one(uint32_t k, float x)
+    {
+        const float a = __builtin_fabsf(x);
+        const bool gt = a > a1;
+        a2 = gt ? a1 : __builtin_fmaxf(a2, a);
+        d = gt ? k : d;
+        a1 = gt ? a : a1;
+    }
+};
+
+// Outlier flag and pivot index of the tile: the pivot byte (bit 7 = flag, bits 0..6 = d).
+template <class T2>
+__device__ __forceinline__ uint32_t pivot_byte(T2 &t, uint32_t part, float tau, float eps_ratio)
+{
+    float a1, a2;
+    uint32_t d;
+    t.finish(part, &a1, &a2, &d);
+    return a1 > tau * (a2 + eps_ratio) ? (0x80u | d) : 0u;
+}
+
+// ... from my part's words in registers
+template <int EPL, bool BF16, int LPT>
+__device__ __forceinline__ uint32_t pivot_of(const uint32_t *w, uint32_t part, float tau, float eps_ratio)
+{
+    Top2<EPL, BF16, LPT> t;
+#pragma unroll
+    for (int k = 0; k < EPL; k += 2) {
+        if constexpr (BF16) t.add(k, w[k / 2]);
+        else t.add(k, __uint_as_float(w[k]), __uint_as_float(w[k + 1]));
+    }
+    return pivot_byte(t, part, tau, eps_ratio);
+}
+
+// ... from my part in an LDS row
+template <int EPL, bool BF16, int LPT>
+__device__ __forceinline__ uint32_t pivot_of(const uint8_t *row, uint32_t part, float tau, float eps_ratio)
+{
+    Top2<EPL, BF16, LPT> t;
+#pragma unroll
+    for (int c = 0; c < EPL * (BF16 ? 2 : 4) / 16; ++c) {
+        const uint4 w = *reinterpret_cast<const uint4 *>(row + c * 16);
+        const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+        if constexpr (BF16) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) t.add(8 * c + 2 * i, ws[i]);
+        } else {
+            t.add(4 * c, __uint_as_float(ws[0]), __uint_as_float(ws[1]));
+            t.add(4 * c + 2, __uint_as_float(ws[2]), __uint_as_float(ws[3]));
+        }
+    }
+    return pivot_byte(t, part, tau, eps_ratio);
+}
+
+// The pivot swap P_d on a tile's LDS row.
+template <bool BF16>
+__device__ __forceinline__ void swap_pivot(uint8_t *row, uint32_t d)
+{
+    if constexpr (BF16) {
+        uint16_t *r16 = reinterpret_cast<uint16_t *>(row);
+        const uint16_t v0 = r16[0], vd = r16[d];
+        r16[0] = vd; r16[d] = v0;
+    } else {
+        float *r32 = reinterpret_cast<float *>(row);
+        const float v0 = r32[0], vd = r32[d];
+        r32[0] = vd; r32[d] = v0;
+    }
+}
+
 // ------------------------------------------------------------- prologue
 
 // What a stream holds besides the kernels' results: header and zeroed section padding.  And the bit map words that ranking
@@ -272,19 +430,27 @@ __device__ __forceinline__ void constant_width_word(uint64_t w, uint32_t T, int 
 // computes hides its own loads.  Lane r's 128 bytes or less lie as `Wave` says; as consecutive lanes fill consecutive 16 bytes of
 // LDS, the swizzle is in the addresses they load from.
 //   src: row 0; rows: how many exist (lanes past them load the last one); NG groups of 64 rows
-template <class W, int NG>
+template <class W, int NG, bool MOSTLY_FULL>
 __device__ __forceinline__ void request_rows(const uint8_t *__restrict__ src, uint32_t rows, uint8_t *lds, uint32_t lane)
 {
     constexpr uint32_t STEP = 64 / W::CHUNKS;                // rows per load: a multiple of the swizzle's period
     const uint32_t r = lane / W::CHUNKS, c = (lane % W::CHUNKS) ^ W::swizzle(r);
-    const bool full = rows >= 64u * NG;
-#pragma unroll
-    for (uint32_t i = 0; i < (uint32_t)(NG * W::CHUNKS); ++i) {
-        uint32_t row = r + i * STEP;
-        if (!full) row = row < rows ? row : rows - 1;
-        // (2: non-temporal.  The tensor is much larger than any cache, and keeping part of it for the second pass was slower.)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + row * W::LANE_BYTES + c * 16u),
+    // (2: non-temporal.  The tensor is much larger than any cache, and keeping part of it for the second pass was slower.)
+    auto load = [&](const uint8_t *from, uint32_t i) {
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)from,
                                          (__attribute__((address_space(3))) void *)(lds + i * 1024u), 16, 0, 2);
+    };
+    // (mostly whole groups: without the rows' comparisons on the way to the loads)
+    if (MOSTLY_FULL && rows >= 64u * NG) {
+        const uint32_t at = r * W::LANE_BYTES + c * 16u;
+#pragma unroll
+        for (uint32_t i = 0; i < (uint32_t)(NG * W::CHUNKS); ++i) load(src + i * 1024u + at, i);
+    } else {
+#pragma unroll
+        for (uint32_t i = 0; i < (uint32_t)(NG * W::CHUNKS); ++i) {
+            const uint32_t row = r + i * STEP;
+            load(src + ((row < rows ? row : rows - 1) * W::LANE_BYTES + c * 16u), i);
+        }
     }
 }
 // ... have arrived
@@ -295,28 +461,84 @@ __device__ __forceinline__ void rows_are_read()
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
 }
+// A result that a later kernel reads, written through to memory at once.  Left in the L2 until it is evicted or the kernel ends, the
+// entropies cost a pass over 512 MB 8 us, so 4.
+template <class V>
+__device__ __forceinline__ void store_through(V *p, V v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// My row of group `g`, widened to fp32.
-template <class W, bool BF16>
-__device__ __forceinline__ void read_row(const uint8_t *lds, uint32_t g, uint32_t lane, float *x)
+// LDS accesses beside rows that are on their way.  The compiler cannot tell them from the loads' destination and would have each
+// of them wait until the rows have arrived; it does not see these.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint32_t lds_address(const void *p)
 {
-    const uint8_t *row = lds + g * W::LDS_BYTES + lane * W::LANE_BYTES;
-    const uint32_t swz = W::swizzle(lane) << 4;
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
+}
+__device__ __forceinline__ void lds_add_one(uint32_t at) { asm volatile("ds_add_u32 %0, %1" ::"v"(at), "v"(1u) : "memory"); }
+__device__ __forceinline__ void lds_store(uint32_t at, float v) { asm volatile("ds_write_b32 %0, %1" ::"v"(at), "v"(v) : "memory"); }
+__device__ __forceinline__ float lds_load(uint32_t at)
+{
+    float v;
+    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v) : "v"(at) : "memory");
+    return v;
+}
+// sixteen consecutive values, 16-byte aligned
+__device__ __forceinline__ void lds_load(uint32_t at, f32x4 (&v)[4])
+{
+    asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:16\n\tds_read_b128 %2, %4 offset:32\n\t"
+                 "ds_read_b128 %3, %4 offset:48\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]) : "v"(at) : "memory");
+}
+// Barrier of the workgroup for accesses to LDS only: the next rows stay on their way.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// My row of group `g`, as it is in memory, and its k-th element, widened to fp32.  Tiles stay packed in registers, and every pass
+// over them widens them anew: three quarters of a vector slot per element against 32 registers.
+template <class W, bool BF16>
+struct Row {
+    static constexpr int WORDS = W::LANE_BYTES / 4;
+    uint32_t w[WORDS];
+    __device__ __forceinline__ void read(const uint8_t *lds, uint32_t g, uint32_t lane)
+    {
+        const uint8_t *row = lds + g * W::LDS_BYTES + lane * W::LANE_BYTES;
+        const uint32_t swz = W::swizzle(lane) << 4;
 #pragma unroll
-    for (uint32_t c = 0; c < (uint32_t)W::CHUNKS; ++c) {
-        const uint4 w = *reinterpret_cast<const uint4 *>(row + ((c << 4) ^ swz));
-        const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if constexpr (BF16) {
-                x[8 * c + 2 * i] = __uint_as_float(ws[i] << 16);
-                x[8 * c + 2 * i + 1] = __uint_as_float(ws[i] & 0xffff0000u);
-            } else {
-                x[4 * c + i] = __uint_as_float(ws[i]);
-            }
+        for (uint32_t c = 0; c < (uint32_t)W::CHUNKS; ++c) {
+            const uint4 q = *reinterpret_cast<const uint4 *>(row + ((c << 4) ^ swz));
+            w[4 * c] = q.x; w[4 * c + 1] = q.y; w[4 * c + 2] = q.z; w[4 * c + 3] = q.w;
         }
     }
-}
+    __device__ __forceinline__ float operator[](int k) const
+    {
+        if constexpr (BF16) return __uint_as_float(k & 1 ? w[k >> 1] & 0xffff0000u : w[k >> 1] << 16);
+        else return __uint_as_float(w[k]);
+    }
+    // Nothing derived from the words is kept across this point.
+    __device__ __forceinline__ void forget()
+    {
+        if constexpr (BF16) {
+#pragma unroll
+            for (int i = 0; i < WORDS; ++i) asm volatile("" : "+v"(w[i]));
+        }
+    }
+};
+
+// A tile's row, or my part of it, from the tensor.
+template <class W, bool BF16>
+struct TensorRow : Row<W, BF16> {
+    __device__ __forceinline__ explicit TensorRow(const uint8_t *p)
+    {
+#pragma unroll
+        for (int c = 0; c < W::CHUNKS; ++c) {
+            const uint4 q = reinterpret_cast<const uint4 *>(p)[c];
+            this->w[4 * c] = q.x; this->w[4 * c + 1] = q.y; this->w[4 * c + 2] = q.z; this->w[4 * c + 3] = q.w;
+        }
+    }
+};
 
 // The sum over a tile from its LPT parts' sums, which meet in pairs: the top of the tile's binary tree.
 template <int LPT>
@@ -328,16 +550,16 @@ __device__ __forceinline__ float whole_tile(float part)
 }
 
 // Sum over my elements of |v| (Eq. 1), and of |v| log(|v| r + varsigma) (Eq. 2 but for its common factor r = 1 / (L1 + eps)).
-template <int N>
-__device__ __forceinline__ float magnitude_sum(const float *x)
+template <int N, class R>
+__device__ __forceinline__ float magnitude_sum(const R &x)
 {
     float a[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) a[k] = __builtin_fabsf(x[k]);
     return tree_sum<N>(a);
 }
-template <int N>
-__device__ __forceinline__ float weighted_sum(const float *x, float invL, float eps_log)
+template <int N, class R>
+__device__ __forceinline__ float weighted_sum(const R &x, float invL, float eps_log)
 {
     float a[N];
 #pragma unroll
@@ -348,6 +570,53 @@ __device__ __forceinline__ float weighted_sum(const float *x, float invL, float 
     return tree_sum<N>(a);
 }
 
+// Eq. 1-2 for a tile of LPT parts, of which `x` holds mine.
+template <int EPL, int LPT, class R>
+__device__ __forceinline__ float entropy_of(R &x, float eps_l1, float eps_log)
+{
+    const float invL = 1.0f / (whole_tile<LPT>(magnitude_sum<EPL>(x)) + eps_l1);
+    x.forget();
+    return 0.0f - invL * whole_tile<LPT>(weighted_sum<EPL>(x, invL, eps_log));
+}
+
+// The same to within kEntropySlack, with the hardware's logarithm, two vector slots instead of nine, and in one pass:
+//     H ~ ln2 (-r S - r L1 log2 r),  S = sum of |v| log2 (|v| + 2^-126)
+// (what is added keeps a zero's logarithm finite, and is lost in the rounding beside anything that counts).
+// What separates it from the sum above, in the norms' range below (where |log2 L1| <= 24, so the terms' magnitudes add up to 31):
+// LOG's distance from the logarithm, 1.11e-5 at most over [1e-12, 2), passed on by weights that add up to 1; varsigma inside
+// the logarithm, at most 128 times itself, 7.7e-6 (the caller takes this way for varsigma up to 2^-24 only); the roundings here, of the
+// sums (11 deep), the products, v_log_f32 (1 ulp) and the last steps, together at most 16 of 2^-24 times ln2 31, 2.1e-5, and
+// there, 9 of 2^-24 times 4.9, 2.7e-6.  Makes 4.3e-5.  (Seen: 6.7e-6.)  A tile whose norm is neither zero nor in the range takes the
+// other way, with its wavefront.
+constexpr float kEntropySlack = 6e-5f, kApproxLogMax = 0x1p-24f, kApproxLogMin = 1e-12f, kApproxNormMin = 0x1p-24f, kApproxNormMax = 0x1p24f;
+
+// `exact` is that other way: it reads the row again, so that nothing has to wait for it in registers.
+template <int EPL, int LPT, class R, class Exact>
+__device__ __forceinline__ float entropy_approx(const R &x, float eps_l1, Exact exact)
+{
+    float L1 = 0.0f, S = 0.0f;
+    // (eight elements at a time: left to itself the compiler works on all of them at once and runs out of registers)
+#pragma unroll
+    for (int k0 = 0; k0 < EPL; k0 += 8) {
+        float a[8], b[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            a[k] = __builtin_fabsf(x[k0 + k]);
+            b[k] = a[k] * __builtin_amdgcn_logf(a[k] + 0x1p-126f);
+        }
+        L1 = L1 + tree_sum<8>(a);
+        S = S + tree_sum<8>(b);
+        asm volatile("" : "+v"(L1), "+v"(S));
+    }
+    L1 = whole_tile<LPT>(L1);
+    S = whole_tile<LPT>(S);
+    const float r = 1.0f / (L1 + eps_l1);
+    float h = kLn2 * (-(r * S) - (r * L1) * __builtin_amdgcn_logf(r));
+    if (L1 == 0.0f) h = 0.0f;
+    if (__ballot(!(L1 == 0.0f || (L1 > kApproxNormMin && L1 < kApproxNormMax))) != 0) h = exact();
+    return h;
+}
+
 constexpr int kDigit0Bits = 10;                  // first radix digit of the selection: key bits 31..22
 static_assert((1u << kDigit0Bits) == kDigit0Bins, "digit 0 width");
 
@@ -355,24 +624,29 @@ static_assert((1u << kDigit0Bits) == kDigit0Bins, "digit 0 width");
 template <int G, int ESIZE, int LPT>
 constexpr int kRowGroups = 128 / (G * ESIZE / LPT);
 
-// Bound by vector issue (twelve and a half slots per element, ten of them the logarithm) and behind it by HBM.  Without barriers,
-// and with the next rows on their way to LDS while the present ones are in registers, bf16 [8,4096,8192] G = 64 108.7 -> 106.1 us,
-// fp32 [4,512,2048] 5.1 -> 4.6.
+// With exact entropies bound by vector issue (twelve and a half slots per element, ten of them the logarithm) and behind it by HBM.
+// Without barriers, and with the next rows on their way to LDS while the present ones are in registers, bf16 [8,4096,8192]
+// G = 64 108.7 -> 106.1 us, fp32 [4,512,2048] 5.1 -> 4.6.  With approximate ones bound by HBM: 88.8 us against 82 for the loads alone, and
+// 98.7 with Eq. 3 and the histogram, where exact entropies and both take 115.
 //
 // Persistent workgroups of four wavefronts; a step is 4 NG groups of rows, NG for each wavefront, and workgroup w handles a
 // contiguous run of steps.  A step's results are stored one step late, just before the next loads, so that no wait for loads ever
 // has a younger store in front of it.  The wavefronts of a workgroup meet only where the histogram moves to another unit.
+//
+// If `pivot` is given, Eq. 3 is decided here as well: with the approximate entropies this kernel has vector slots to spare behind
+// HBM, and k_quant_pack has not.
+// APPROX: entropies to within kEntropySlack, for a selection that makes up for it.
 //
 // If HIST, the kernel also builds the first histogram of the selection (Sec. 3.2, top-p%): per
 // ranking unit of `unit_tiles` tiles, counts of the keys' top 10 bits (bin_scale == 0) or of the entropies'
 // linear bins (bin_scale > 0), `hist_stride` bins per unit, accumulated in LDS and flushed with global atomics
 // when the workgroup moves to another unit, in the middle of a step if need be, and at its end.  A step may touch two
 // units, not more: `unit_tiles` is at least a step's tiles (the caller checks; otherwise it passes no histogram).
-template <int G, bool BF16, int LPT, int NG, bool HIST>
+template <int G, bool BF16, int LPT, int NG, bool HIST, bool APPROX>
 __global__ __launch_bounds__(256, 4)
-void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, uint32_t grid, float eps_l1, float eps_log,
-               uint32_t *__restrict__ hist0, uint32_t unit_tiles, uint32_t hist_stride, float bin_scale, uint32_t pro_blocks,
-               Prologue pro)
+void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint8_t *__restrict__ pivot, uint32_t T, uint32_t per,
+               float eps_l1, float eps_log, float tau, float eps_ratio, uint32_t pro_blocks, uint32_t *__restrict__ hist0,
+               uint32_t unit_tiles, uint32_t hist_stride, float bin_scale, Prologue pro)
 {
     using W = Wave<G, BF16 ? 2 : 4, LPT>;
     constexpr uint32_t WAVE_TILES = W::TILES * NG, STEP_TILES = 4 * WAVE_TILES;
@@ -383,7 +657,7 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, u
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     uint8_t *lds = lds_all + wave * (NG * W::LDS_BYTES);
     const uint32_t part = lane % LPT, mine = wave * WAVE_TILES + lane / LPT;          // my tile of the step's first group
-    const uint32_t steps = (T + STEP_TILES - 1) / STEP_TILES, per = (steps + grid - 1) / grid;
+    const uint32_t steps = (T + STEP_TILES - 1) / STEP_TILES;
     const uint32_t first = blockIdx.x * per;
     const uint32_t last = first + per < steps ? first + per : steps;      // my steps: [first, last)
 
@@ -391,16 +665,16 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, u
         const uint64_t j0 = (uint64_t)step * STEP_TILES + wave * WAVE_TILES;
         if (j0 >= T) return;                     // (the last step's last wavefronts)
         const uint64_t left = T - j0;
-        request_rows<W, NG>(static_cast<const uint8_t *>(in) + j0 * (G * (BF16 ? 2 : 4)),
+        request_rows<W, NG, true>(static_cast<const uint8_t *>(in) + j0 * (G * (BF16 ? 2 : 4)),
                             left < WAVE_TILES ? (uint32_t)left * LPT : 64u * NG, lds, lane);
     };
     if (first < last) request(first);
     if constexpr (HIST) {
         for (uint32_t i = tid; i < hist_stride; i += 256) lh[i] = 0;
-        __syncthreads();
+        lds_barrier();
     }
     auto flush = [&](uint32_t unit) {
-        __syncthreads();
+        lds_barrier();
         for (uint32_t i = tid; i < hist_stride; i += 256) {
             const uint32_t c = lh[i];
             if (c) { atomicAdd(&hist0[(uint64_t)unit * hist_stride + i], c); lh[i] = 0; }
@@ -408,13 +682,19 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, u
         __syncthreads();
     };
     float h[NG];
+    uint32_t pv[NG] = {};
     uint64_t j_prev = 0;                         // the step before, and its tiles
     uint32_t n_prev = 0;
     auto store = [&]() {
 #pragma unroll
-        for (uint32_t g = 0; g < (uint32_t)NG; ++g)
-            if (part == 0 && mine + g * W::TILES < n_prev) H[j_prev + mine + g * W::TILES] = h[g];
+        for (uint32_t g = 0; g < (uint32_t)NG; ++g) {
+            if (part == 0 && mine + g * W::TILES < n_prev) {
+                store_through(H + j_prev + (mine + g * W::TILES), h[g]);
+                if (pivot) store_through(pivot + j_prev + (mine + g * W::TILES), (uint8_t)pv[g]);
+            }
+        }
     };
+    const uint32_t lh_at = lds_address(lh);
     uint32_t cur_unit = HIST && first < last ? (uint32_t)((uint64_t)first * STEP_TILES / unit_tiles) : 0u;
     uint64_t unit_end = (uint64_t)(cur_unit + 1) * unit_tiles;            // the first tile after it
     auto bin_of = [&](float v) {
@@ -425,17 +705,27 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, u
         const uint32_t n = T - j0 < STEP_TILES ? (uint32_t)(T - j0) : STEP_TILES;
         if (HIST && j0 >= unit_end) { flush(cur_unit); ++cur_unit; unit_end += unit_tiles; }
         wait_for_rows();
-        float x[NG][W::EPL];
+        Row<W, BF16> x[NG];
 #pragma unroll
-        for (uint32_t g = 0; g < (uint32_t)NG; ++g) read_row<W, BF16>(lds, g, lane, x[g]);
+        for (uint32_t g = 0; g < (uint32_t)NG; ++g) x[g].read(lds, g, lane);
         rows_are_read();
         store();
         if (step + 1 < last) request(step + 1);
 #pragma unroll
         for (uint32_t g = 0; g < (uint32_t)NG; ++g) {
-            const float L1 = whole_tile<LPT>(magnitude_sum<W::EPL>(x[g]));
-            const float invL = 1.0f / (L1 + eps_l1);
-            h[g] = 0.0f - invL * whole_tile<LPT>(weighted_sum<W::EPL>(x[g], invL, eps_log));
+            if (pivot) {
+                pv[g] = pivot_of<W::EPL, BF16, LPT>(x[g].w, part, tau, eps_ratio);
+                x[g].forget();
+            }
+            if constexpr (APPROX) {
+                h[g] = entropy_approx<W::EPL, LPT>(x[g], eps_l1, [&]() {
+                    const uint32_t at = mine + g * W::TILES;
+                    TensorRow<W, BF16> y(static_cast<const uint8_t *>(in) +
+                                         ((j0 + (at < n ? at : n - 1)) * LPT + part) * W::LANE_BYTES);
+                    return entropy_of<W::EPL, LPT>(y, eps_l1, eps_log);
+                });
+            }
+            else h[g] = entropy_of<W::EPL, LPT>(x[g], eps_l1, eps_log);
         }
         j_prev = j0;
         n_prev = n;
@@ -444,7 +734,7 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, u
 #pragma unroll
                 for (uint32_t g = 0; g < (uint32_t)NG; ++g) {
                     const uint32_t j = mine + g * W::TILES;
-                    if (part == 0 && j >= from && j < to) atomicAdd(&lh[bin_of(h[g])], 1u);
+                    if (part == 0 && j >= from && j < to) lds_add_one(lh_at + 4u * bin_of(h[g]));
                 }
             };
             if (unit_end - j0 >= n) {
@@ -473,11 +763,12 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t T, u
 //   WEIGHTED = false: part[j] = sum over tile j of |v|
 //   WEIGHTED = true:  part[j] = sum over tile j of |v| log(|v| * r + varsigma), r = inv_norm[j / m] (the common factor r
 //                     of Eq. 2's sum is applied once, by the reduction)
-// One workgroup per batch of tiles, one lane per tile.
+// One workgroup per batch of tiles, one lane per tile.  If `pivot` is given, the first pass decides Eq. 3 as well.
 template <int G, bool BF16, bool WEIGHTED>
 __global__ __launch_bounds__((Batch<G, BF16 ? 2 : 4>::TILES))
 void k_tile_partial(const void *__restrict__ in, const float *__restrict__ inv_norm, float *__restrict__ part,
-                    uint32_t T, uint32_t m, float eps_log, uint32_t pro_blocks, Prologue pro)
+                    uint8_t *__restrict__ pivot, uint32_t T, uint32_t m, float eps_log, float tau, float eps_ratio,
+                    uint32_t pro_blocks, Prologue pro)
 {
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<G, ES>;
@@ -508,6 +799,10 @@ void k_tile_partial(const void *__restrict__ in, const float *__restrict__ inv_n
         }
         part[j] = tree_sum<G>(a);
     }
+    if constexpr (!WEIGHTED) {
+        if (pivot && (uint32_t)tid < nvalid)
+            pivot[j0 + tid] = (uint8_t)pivot_of<G, BF16, 1>(lds + tid * B::STRIDE, 0u, tau, eps_ratio);
+    }
     if (blockIdx.x < pro_blocks) write_prologue(pro, blockIdx.x * B::TILES + threadIdx.x, pro_blocks * B::TILES);
 }
 
@@ -519,13 +814,15 @@ void k_tile_partial(const void *__restrict__ in, const float *__restrict__ inv_n
 // at once, now 16.6.)
 template <int G, bool BF16, int LPT, bool WAVE_TEAM>
 __device__ __forceinline__
-void alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t n_alloc, uint32_t grid, uint32_t m, uint32_t per,
-                   float eps_l1, float eps_log, uint32_t pro_blocks, const Prologue &pro)
+void alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint8_t *__restrict__ pivot, uint32_t n_alloc,
+                   uint32_t grid, uint32_t m, uint32_t per, float eps_l1, float eps_log, uint32_t pro_blocks, float tau,
+                   float eps_ratio, const Prologue &pro)
 {
     using W = Wave<G, BF16 ? 2 : 4, LPT>;
     constexpr uint32_t TEAMS = WAVE_TEAM ? 4 : 1, SLOTS = (WAVE_TEAM ? 64 : 256) / LPT;       // teams per workgroup, tiles per team
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * W::LDS_BYTES];
     __shared__ __attribute__((aligned(16))) float parts[2][TEAMS * SLOTS];
+    __shared__ float sums[2][4];             // (at most three allocation tiles of more than 64 tiles)
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     uint8_t *lds = lds_all + wave * W::LDS_BYTES;
@@ -538,73 +835,100 @@ void alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t 
         const uint32_t have = (n_alloc - a0 < per ? n_alloc - a0 : per) * m * LPT;            // rows
         // (a wavefront without rows of its own repeats the team's last one)
         const uint32_t row0 = wave_row < have ? wave_row : have - 1;
-        request_rows<W, 1>(static_cast<const uint8_t *>(in) + ((uint64_t)a0 * m * LPT + row0) * W::LANE_BYTES, have - row0, lds, lane);
+        request_rows<W, 1, false>(static_cast<const uint8_t *>(in) + ((uint64_t)a0 * m * LPT + row0) * W::LANE_BYTES, have - row0, lds, lane);
     };
-    auto meet = [&](float (&at)[TEAMS * SLOTS], float value) {
-        if (part == 0) at[(WAVE_TEAM ? wave * SLOTS : 0u) + slot] = value;
+    const uint32_t parts_at[2] = {lds_address(parts[0]), lds_address(parts[1])};
+    const uint32_t sums_of[2] = {lds_address(sums[0]), lds_address(sums[1])};
+    auto meet = [&](uint32_t at, float value) {
+        if (part == 0) lds_store(at + 4u * ((WAVE_TEAM ? wave * SLOTS : 0u) + slot), value);
         if constexpr (WAVE_TEAM) wave_lds_fence();
-        else {
-            // (LDS only: the next rows stay on their way)
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-        }
+        else lds_barrier();
     };
     // my allocation tile's m values from left to right (lanes left over stay inside the array)
-    auto left_to_right = [&](const float (&at)[TEAMS * SLOTS]) {
-        const float *p = &at[group < per ? q0 : 0u];
+    auto left_to_right = [&](uint32_t at) {
+        uint32_t p = at + 4u * (group < per ? q0 : 0u);
         float acc = 0.0f;
         uint32_t q = 0;
         if (m % 4 == 0) {
-            for (; q + 8 <= m; q += 8) {
-                const float4 u = *reinterpret_cast<const float4 *>(p + q), v = *reinterpret_cast<const float4 *>(p + q + 4);
-                acc = acc + u.x; acc = acc + u.y; acc = acc + u.z; acc = acc + u.w;
-                acc = acc + v.x; acc = acc + v.y; acc = acc + v.z; acc = acc + v.w;
+            for (; q + 16 <= m; q += 16, p += 64) {
+                f32x4 v[4];
+                lds_load(p, v);
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc = acc + v[i / 4][i % 4];
             }
         }
-#pragma unroll 4
-        for (; q < m; ++q) acc = acc + p[q];
+        for (; q < m; ++q, p += 4) acc = acc + lds_load(p);
         return acc;
+    };
+    // Long sums are the work of one wavefront, in which the allocation tile begins, for all of its lanes: m additions in all four took
+    // a third of the vector slots at m = 256 ([4,2048,8192] A = 8192, G = 32: encode 89.5 us, 76.9 so).  (64 elements per lane leave no
+    // registers for it, and at their m = 128 it takes as long.)
+    constexpr bool ONE_WAVE = !WAVE_TEAM && W::EPL <= 32;
+    auto sum_up = [&](uint32_t at, uint32_t sums_at) {
+        if constexpr (ONE_WAVE) {
+            if (m > 64) {
+                const bool begins = group < per && slot == group * m;
+                if (__ballot(begins) != 0) {
+                    const float acc = left_to_right(at);
+                    if (begins && part == 0) lds_store(sums_at + 4u * group, acc);
+                }
+                lds_barrier();
+                return lds_load(sums_at + 4u * (group < per ? group : 0u));
+            }
+        }
+        return left_to_right(at);
     };
     const uint32_t stride = teams * per;
     uint32_t a0 = team * per;
     if (a0 < n_alloc) request(a0);
     float h = 0.0f;
-    uint32_t a_prev = n_alloc;                   // my allocation tile of the round before
+    uint32_t pv = 0, a_prev = n_alloc;           // my allocation tile of the round before
     const bool first = group < per && slot == group * m && part == 0;
+    auto store = [&]() {
+        if (a_prev >= n_alloc) return;
+        if (first) store_through(H + a_prev, h);
+        if (pivot && group < per && part == 0) store_through(pivot + ((uint64_t)a_prev * m + (slot - group * m)), (uint8_t)pv);
+    };
     for (; a0 < n_alloc; a0 += stride) {
         wait_for_rows();
-        float x[W::EPL];
-        read_row<W, BF16>(lds, 0, lane, x);
+        Row<W, BF16> x;
+        x.read(lds, 0, lane);
         rows_are_read();
-        if (first && a_prev < n_alloc) H[a_prev] = h;
+        store();
         if (a0 + stride < n_alloc) request(a0 + stride);
-        meet(parts[0], whole_tile<LPT>(magnitude_sum<W::EPL>(x)));
-        const float invL = 1.0f / (left_to_right(parts[0]) + eps_l1);
-        meet(parts[1], whole_tile<LPT>(weighted_sum<W::EPL>(x, invL, eps_log)));
-        h = 0.0f - invL * left_to_right(parts[1]);
+        meet(parts_at[0], whole_tile<LPT>(magnitude_sum<W::EPL>(x)));
+        x.forget();
+        if (pivot) pv = pivot_of<W::EPL, BF16, LPT>(x.w, part, tau, eps_ratio);
+        x.forget();
+        const float invL = 1.0f / (sum_up(parts_at[0], sums_of[0]) + eps_l1);
+        meet(parts_at[1], whole_tile<LPT>(weighted_sum<W::EPL>(x, invL, eps_log)));
+        h = 0.0f - invL * sum_up(parts_at[1], sums_of[1]);
         a_prev = a0 + group;
     }
-    if (first && a_prev < n_alloc) H[a_prev] = h;
+    store();
     if (blockIdx.x < pro_blocks) write_prologue(pro, blockIdx.x * 256 + tid, pro_blocks * 256);
 }
 
 // The usual lanes, wavefronts by themselves.
 template <int G, bool BF16>
 __global__ __launch_bounds__(256, 4)
-void k_alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint32_t n_alloc, uint32_t grid, uint32_t m, uint32_t per,
-                     float eps_l1, float eps_log, uint32_t pro_blocks, Prologue pro)
+void k_alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint8_t *__restrict__ pivot, uint32_t n_alloc,
+                     uint32_t grid, uint32_t m, uint32_t per, float eps_l1, float eps_log, uint32_t pro_blocks, float tau,
+                     float eps_ratio, Prologue pro)
 {
-    alloc_entropy<G, BF16, Lanes<G, BF16 ? 2 : 4>::usual, true>(in, H, n_alloc, grid, m, per, eps_l1, eps_log, pro_blocks, pro);
+    alloc_entropy<G, BF16, Lanes<G, BF16 ? 2 : 4>::usual, true>(in, H, pivot, n_alloc, grid, m, per, eps_l1, eps_log, pro_blocks,
+                                                                    tau, eps_ratio, pro);
 }
 
 // Any others.
 template <int G, bool BF16, int LPT, bool WAVE_TEAM>
 __global__ __launch_bounds__(256, 4)
-void k_alloc_entropy_by(const void *__restrict__ in, float *__restrict__ H, uint32_t n_alloc, uint32_t grid, uint32_t m, uint32_t per,
-                        float eps_l1, float eps_log, uint32_t pro_blocks, Prologue pro)
+void k_alloc_entropy_by(const void *__restrict__ in, float *__restrict__ H, uint8_t *__restrict__ pivot, uint32_t n_alloc,
+                        uint32_t grid, uint32_t m, uint32_t per, float eps_l1, float eps_log, uint32_t pro_blocks, float tau,
+                        float eps_ratio, Prologue pro)
 {
-    alloc_entropy<G, BF16, LPT, WAVE_TEAM>(in, H, n_alloc, grid, m, per, eps_l1, eps_log, pro_blocks, pro);
+    alloc_entropy<G, BF16, LPT, WAVE_TEAM>(in, H, pivot, n_alloc, grid, m, per, eps_l1, eps_log, pro_blocks,
+                                                                    tau, eps_ratio, pro);
 }
 
 // Left-to-right sum of the m partial sums of every allocation tile.  FINAL = false: the reciprocal norm
@@ -631,91 +955,6 @@ template <> struct Unit<16>  { using type = uint16_t; };
 template <> struct Unit<32>  { using type = uint32_t; };
 template <> struct Unit<64>  { using type = uint2; };
 template <> struct Unit<128> { using type = uint4; };
-
-// Median of three unsigned integers in one vector instruction.
-__device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t c)
-{
-    uint32_t r;
-    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
-// Eq. 3 on my tile, of which `row` (LDS) is my part of G elements: magnitude of the largest and second-largest element
-// (with multiplicity) and the lowest index of the largest, in the whole tile of LPT parts.
-template <int G, bool BF16, int LPT>
-__device__ __forceinline__ void top2(const uint8_t *row, uint32_t part, float *a1_out, float *a2_out, uint32_t *d_out)
-{
-    if constexpr (BF16) {
-        // A bf16 magnitude has 16 free low bits: key = |bits| << 16 | (G-1-k) orders by magnitude, then by
-        // lower index, under unsigned integer max.  Even and odd elements run in separate chains (the
-        // even chain keeps its keys shifted left by one, which drops the sign bit for free).
-        uint32_t e1 = 0, e2 = 0, o1 = 0, o2 = 0;
-#pragma unroll
-        for (int c = 0; c < G / 8; ++c) {
-            const uint4 w = *reinterpret_cast<const uint4 *>(row + c * 16);
-            const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t k_even = 8 * c + 2 * i, k_odd = k_even + 1;
-                const uint32_t ke = (ws[i] << 17) | ((G - 1 - k_even) << 1);
-                const uint32_t ko = (ws[i] & 0x7fff0000u) | (G - 1 - k_odd);
-                e2 = umed3(e1, e2, ke);   // second largest of {e1 >= e2, ke}
-                e1 = e1 > ke ? e1 : ke;
-                o2 = umed3(o1, o2, ko);
-                o1 = o1 > ko ? o1 : ko;
-            }
-        }
-        e1 >>= 1; e2 >>= 1;
-        uint32_t k1 = e1 > o1 ? e1 : o1;
-        const uint32_t lo = e1 > o1 ? o1 : e1;
-        const uint32_t hi2 = e2 > o2 ? e2 : o2;
-        uint32_t k2 = lo > hi2 ? lo : hi2;
-        // the other parts of the tile: two pairs become one
-        auto merge = [&](uint32_t p1, uint32_t p2) {
-            const uint32_t less = k1 < p1 ? k1 : p1, more2 = k2 > p2 ? k2 : p2;
-            k1 = k1 > p1 ? k1 : p1;
-            k2 = less > more2 ? less : more2;
-        };
-        if constexpr (LPT >= 2) {
-            k1 += (LPT - 1 - part) * G;          // the low bits count indices of the whole tile from its end
-            merge(lane_xor<1>(k1), lane_xor<1>(k2));
-        }
-        if constexpr (LPT >= 4) merge(lane_xor<2>(k1), lane_xor<2>(k2));
-        *a1_out = __uint_as_float(k1 & 0x7fff0000u);
-        *a2_out = __uint_as_float(k2 & 0x7fff0000u);
-        *d_out = (LPT * G - 1) - (k1 & 0x7fu);
-    } else {
-        float a1 = -1.0f, a2 = 0.0f;     // magnitudes are >= 0: the first element always replaces a1
-        uint32_t d = 0;
-#pragma unroll
-        for (int c = 0; c < G / 4; ++c) {
-            const float4 w = *reinterpret_cast<const float4 *>(row + c * 16);
-            const float ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float a = __builtin_fabsf(ws[i]);
-                const bool gt = a > a1;
-                a2 = gt ? a1 : __builtin_fmaxf(a2, a);
-                d = gt ? (uint32_t)(4 * c + i) : d;
-                a1 = gt ? a : a1;
-            }
-        }
-        auto merge = [&](float p1, float p2, uint32_t pd) {
-            const bool other = p1 > a1 || (p1 == a1 && pd < d);
-            a2 = __builtin_fmaxf(__builtin_fminf(a1, p1), __builtin_fmaxf(a2, p2));
-            a1 = other ? p1 : a1;
-            d = other ? pd : d;
-        };
-        if constexpr (LPT >= 2) {
-            d += part * G;
-            merge(lane_xor<1>(a1), lane_xor<1>(a2), lane_xor<1>(d));
-        }
-        if constexpr (LPT >= 4) merge(lane_xor<2>(a1), lane_xor<2>(a2), lane_xor<2>(d));
-        *a1_out = a1;
-        *a2_out = __builtin_fmaxf(a2, 0.0f);
-        *d_out = d;
-    }
-}
 
 // What a workgroup must know about a batch before it can place payload: the bit map words of the
 // batch's 64-tile groups and the rank-table entry of the first one.
@@ -817,30 +1056,6 @@ __device__ __forceinline__ float fmax3(float a, float b, float c)
     float r;
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
     return r;
-}
-
-// Eq. 3 for the tile in `row`, my part of which is the part-th of LPT: outlier flag and pivot index; for an outlier tile
-// with d != 0 the pivot swap P_d is applied to the LDS row on the spot.  Returns the pivot byte (bit 7 = flag, bits 0..6 = d).
-template <int G, bool BF16, int LPT>
-__device__ __forceinline__ uint32_t analyse_row(uint8_t *row, uint32_t part, float tau, float eps_ratio)
-{
-    float a1, a2;
-    uint32_t d;
-    constexpr int EPL = G / LPT;
-    top2<EPL, BF16, LPT>(row + part * (EPL * (BF16 ? 2 : 4)), part, &a1, &a2, &d);
-    const bool flag = a1 > tau * (a2 + eps_ratio);
-    if (flag && d != 0 && part == 0) {           // (the tile's other lanes have read the row: they are in this wavefront)
-        if constexpr (BF16) {
-            uint16_t *r16 = reinterpret_cast<uint16_t *>(row);
-            const uint16_t v0 = r16[0], vd = r16[d];
-            r16[0] = vd; r16[d] = v0;
-        } else {
-            float *r32 = reinterpret_cast<float *>(row);
-            const float v0 = r32[0], vd = r32[d];
-            r32[0] = vd; r32[d] = v0;
-        }
-    }
-    return flag ? (0x80u | d) : 0u;
 }
 
 // The rest of the encoder for one tile, in two steps with a workgroup barrier between them (the payload
@@ -1000,8 +1215,21 @@ __device__ __forceinline__ uint32_t quantize_values(const float *x, uint32_t b, 
     return s16 | (z16 << 16);
 }
 
-// One workgroup per batch of TILES tiles, in two stages.  Stage one: lane i examines tile i (Eq. 3, pivot
-// swap in LDS).  The tiles are then regrouped by class -- (plain | transformed) x (narrow | wide) -- so that in
+// Store of a payload unit that passes the caches by.
+template <class U>
+__device__ __forceinline__ void store_streaming(U *p, const U &v)
+{
+    if constexpr (sizeof(U) == 16) __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), reinterpret_cast<u32x4 *>(p));
+    else if constexpr (sizeof(U) == 8) __builtin_nontemporal_store(__builtin_bit_cast(uint64_t, v), reinterpret_cast<uint64_t *>(p));
+    else __builtin_nontemporal_store(v, p);
+}
+
+// How k_quant_pack goes about it.
+enum : uint32_t { QUANT_ALL_WIDE = 1, QUANT_STREAMING = 2 };
+
+// One workgroup per batch of TILES tiles, in two stages.  Stage one: lane i takes tile i's pivot byte, from the entropy pass where
+// tiles were ranked, from Eq. 3 on the spot otherwise, and swaps its pivot in LDS.  The tiles are regrouped by
+// class -- (plain | transformed) x (narrow | wide) -- so that in
 // stage two, where lane p takes the p-th tile in class order, most wavefronts hold a single class: the
 // Hadamard butterfly runs only in the wavefronts that hold transformed tiles, and the two packing
 // paths rarely both run.  The payload buffer reuses the rows' LDS once every lane holds its tile in
@@ -1014,7 +1242,7 @@ __device__ __forceinline__ uint32_t quantize_values(const float *x, uint32_t b, 
 template <int G, bool BF16, int LOW, bool RANKED, int LPT, bool FULL>
 __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, uint8_t *__restrict__ packed, const Sections &lay,
                                                  uint32_t T, float tau, float eps_ratio, uint32_t batch, uint32_t nvalid,
-                                                 bool all_wide, uint8_t *lds, uint32_t *info, uint16_t *order, uint32_t *class_count)
+                                                 bool all_wide, bool streaming, uint8_t *lds, uint32_t *info, uint16_t *order, uint32_t *class_count)
 {
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<G, ES, LPT>;
@@ -1044,26 +1272,33 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
         for (int w = 0; w < BatchMeta<B::TILES>::WORDS; ++w) meta.word[w] = w0 + w < words ? constant_word(w0 + w, T, all_wide) : 0ull;
         meta.rank0 = all_wide ? (uint32_t)j0 : 0u;
     }
-    store_batch<B, FULL>(v, nvalid, lds, tid);
+    const bool valid = FULL || slot < nvalid;
+    uint32_t pv = 0;                             // pivot byte of the tile of my slot, in storage order
+    if constexpr (RANKED) {
+        pv = packed[lay.pivot + j0 + (valid ? slot : 0u)];
+    }
     uint32_t b, rel, total4;
     tile_pos<B::TILES, LOW, LPT>(meta, tid, &b, &rel, &total4);
-    __syncthreads();
-
-    // stage one: the tile of my slot in storage order
-    const bool valid = FULL || slot < nvalid;
+    if constexpr (!RANKED) {
+        store_batch<B, FULL>(v, nvalid, lds, tid);
+        __syncthreads();
+        if (valid) pv = pivot_of<EPL, BF16, LPT>(lds + slot * B::STRIDE + part * (EPL * ES), part, tau, eps_ratio);
+    }
+    // stage one: my tile's class
     uint32_t cls = 4;                            // tiles past the end, and all lanes of a tile but its first, sort nowhere
-    if (valid) {
-        const uint32_t pv = analyse_row<G, BF16, LPT>(lds + slot * B::STRIDE, part, tau, eps_ratio);
-        if (part == 0) {
-            info[slot] = pv | ((b == WIDE) ? 0x100u : 0u) | (rel << 9);
-            cls = ((pv >> 7) << 1) | (b == WIDE ? 1u : 0u);
-        }
+    if (valid && part == 0) {
+        info[slot] = pv | ((b == WIDE) ? 0x100u : 0u) | (rel << 9);
+        cls = ((pv >> 7) << 1) | (b == WIDE ? 1u : 0u);
     }
     const uint32_t rank_in_wave = class_rank_in_wave<WAVES>(cls, (uint32_t)wave, (uint32_t)lane, class_count);
+    if constexpr (RANKED) store_batch<B, FULL>(v, nvalid, lds, tid);
     __syncthreads();
     {
         const uint32_t pos = rank_in_wave + class_group_base<WAVES>(cls, (uint32_t)wave, (uint32_t)lane, class_count);
-        if (cls < 4) order[pos] = (uint16_t)slot;
+        if (cls < 4) {
+            order[pos] = (uint16_t)slot;
+            if (pv > 0x80u) swap_pivot<BF16>(lds + slot * B::STRIDE, pv & 0x7fu);        // an outlier tile with d != 0
+        }
     }
     __syncthreads();
 
@@ -1085,7 +1320,7 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
         if (part == 0) {
             reinterpret_cast<uint16_t *>(packed + lay.scale)[j] = (uint16_t)meta16;
             reinterpret_cast<uint16_t *>(packed + lay.zero)[j] = (uint16_t)(meta16 >> 16);
-            packed[lay.pivot + j] = (uint8_t)inf;
+            if constexpr (!RANKED) packed[lay.pivot + j] = (uint8_t)inf;
         }
     }
     __syncthreads();
@@ -1096,7 +1331,10 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
 #pragma unroll
     for (int i = 0; i < ((int)WIDE + LPT - 1) / LPT; ++i) {
         const uint32_t q = (uint32_t)i * THREADS + tid;
-        if (q < span) gdst[q] = pay[q];
+        if (q < span) {
+            if (streaming) store_streaming(gdst + q, pay[q]);
+            else gdst[q] = pay[q];
+        }
     }
     if constexpr (!RANKED) {
         const uint64_t w = (j0 >> 6) + tid;
@@ -1112,7 +1350,7 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
 template <int G, bool BF16, int LOW, bool RANKED, int LPT>
 __global__ __launch_bounds__(256, 4)
 void k_quant_pack(const void *__restrict__ in, uint8_t *__restrict__ packed, uint32_t T, float tau, float eps_ratio,
-                  uint32_t all_wide, Prologue pro)
+                  uint32_t how, Prologue pro)
 {
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<G, ES, LPT>;
@@ -1124,10 +1362,10 @@ void k_quant_pack(const void *__restrict__ in, uint8_t *__restrict__ packed, uin
     const Sections lay(T);
     const uint32_t nfull = T / B::TILES;        // a workgroup per batch; the last one may be ragged
     if (blockIdx.x < nfull)
-        quant_pack_batch<G, BF16, LOW, RANKED, LPT, true>(in, packed, lay, T, tau, eps_ratio, blockIdx.x, B::TILES, all_wide != 0, lds, info,
+        quant_pack_batch<G, BF16, LOW, RANKED, LPT, true>(in, packed, lay, T, tau, eps_ratio, blockIdx.x, B::TILES, (how & QUANT_ALL_WIDE) != 0, (how & QUANT_STREAMING) != 0, lds, info,
                                              order, class_count);
     else
-        quant_pack_batch<G, BF16, LOW, RANKED, LPT, false>(in, packed, lay, T, tau, eps_ratio, nfull, T % B::TILES, all_wide != 0, lds, info,
+        quant_pack_batch<G, BF16, LOW, RANKED, LPT, false>(in, packed, lay, T, tau, eps_ratio, nfull, T % B::TILES, (how & QUANT_ALL_WIDE) != 0, (how & QUANT_STREAMING) != 0, lds, info,
                                               order, class_count);
     if constexpr (!RANKED) {
         if (blockIdx.x == 0) write_prologue(pro, threadIdx.x, THREADS);      // (nothing but header and padding)

@@ -1,0 +1,100 @@
+"""Large bf16 tensors are ranked from approximate entropies, and the tiles near the threshold from exact ones: the stream must be the one
+that the multi-launch selection writes, which ranks all tiles by their exact entropies."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2506_01352_amd as tahq
+
+pytestmark = pytest.mark.gpu
+
+ELEMENTS = 1 << 25                                       # from here on entropies are approximate
+
+
+def _both_ways(cfg, x):
+    codec = tahq.Codec(cfg, device="cuda")
+    codec.workspace.fill_(0xFF)
+    codec.packed.fill_(0xFF)
+    tahq.tahq_encode(cfg, x, codec.packed, codec.workspace)
+    fused = codec.packed.clone()
+    codec.workspace.fill_(0xFF)
+    tahq.tahq_encode_phases(cfg, x, codec.packed, codec.workspace, tahq.PHASE_ALL | tahq.SELECT_MULTI_LAUNCH)
+    torch.cuda.synchronize()
+    assert torch.equal(fused, codec.packed), "the two selections differ"
+
+
+def _normal(shape, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return torch.randn(shape, device="cuda", generator=g), g
+
+
+@pytest.mark.parametrize("G", (8, 16, 32, 64, 128))
+@pytest.mark.parametrize("shape,scope", (((2, 2048, 8192), 0), ((1, 4096, 8192), 1), ((3, 2731, 4128), 0)))
+def test_ordinary_values(G, shape, scope):
+    # whole tensors and samples as ranking units; the last shape's units are no multiple of 64 tiles
+    B, S, C = shape
+    C = C // G * G
+    S = max(S, -(-ELEMENTS // (B * C)))
+    x, g = _normal((B, S, C), G)
+    x = (x * torch.exp(0.5 * torch.randn(B, S, 1, device="cuda", generator=g))).to(torch.bfloat16)
+    for budget in (3.2, 3.77):
+        print(f"[case] ordinary [{B},{S},{C}] G={G} scope={scope} budget {budget}", flush=True)
+        _both_ways(tahq.make_config(B, S, C, G, tahq.BF16, budget, scope=scope), x)
+
+
+@pytest.mark.parametrize("G", (8, 64, 128))
+@pytest.mark.parametrize("share", (0.028, 0.3))
+def test_thresholds_in_and_beside_a_crowd_of_nearly_alike_tiles(G, share):
+    # tiles that are one tile's elements in another order, with other signs and another power of two: their entropies differ in the last
+    # bits only, far less than the approximation is off.  Thresholds from two bins below them to two above, where the bins
+    # beside the threshold's may or may not hold more candidates than are listed.
+    S, C = ELEMENTS // 8192, 8192
+    n = S * C // G
+    x, g = _normal((n, G), 7)
+    crowd = torch.randperm(n, device="cuda", generator=g)[:int(share * n)]
+    one = x[0].sort().values
+    order = torch.rand(crowd.numel(), G, device="cuda", generator=g).argsort(1)
+    sign = torch.randint(0, 2, (crowd.numel(), G), device="cuda", generator=g) * 2.0 - 1.0
+    power = torch.exp2(torch.randint(-6, 7, (crowd.numel(), 1), device="cuda", generator=g).float())
+    x[crowd] = one[order] * sign * power
+    x = x.to(torch.bfloat16).reshape(1, S, C)
+    H = torch.empty(n, device="cuda")
+    tahq.tahq_tile_entropy(tahq.make_config(1, S, C, G, tahq.BF16, 3.5), x, H)
+    at, width = H[crowd].median().item(), math.log(G) / 2048
+    for bins in (-2.1, -1.02, -0.98, -0.5, -0.02, 0.0, 0.02, 0.5, 0.98, 1.02, 2.1):
+        k = int((H > at + bins * width).sum()) + 3
+        print(f"[case] G={G} {share} alike, threshold {bins} bins from them", flush=True)
+        _both_ways(tahq.make_config(1, S, C, G, tahq.BF16, float(np.float32(3.0 + k / n))), x)
+
+
+@pytest.mark.parametrize("G", (16, 64))
+def test_values_outside_the_approximation(G):
+    # zero tiles, tokens so small or large that products would leave fp32, elements below the normal numbers, one-hot tiles, and
+    # numbers that are none
+    B, S, C = 1, ELEMENTS // 8192, 8192
+    x, g = _normal((B, S, C), 3)
+    x[:, ::7] = 0.0
+    x[:, 1::11] *= 1e-12
+    x[:, 2::13] *= 1e30
+    x[:, 3::17] *= 1e-39
+    x[:, 4::19, 5:] = 0.0
+    x[:, 5::23, ::2] *= 1e-38
+    x = x.to(torch.bfloat16)
+    for budget in (3.1, 3.6, 3.95):
+        print(f"[case] outside, G={G} budget {budget}", flush=True)
+        _both_ways(tahq.make_config(B, S, C, G, tahq.BF16, budget), x)
+    x[0, 9, 3], x[0, 100, 70], x[0, 101, 130] = float("nan"), float("inf"), float("-inf")
+    x[0, 200:240, :G] = float("nan")
+    print(f"[case] outside, not finite, G={G}", flush=True)
+    _both_ways(tahq.make_config(B, S, C, G, tahq.BF16, 3.6), x)
+
+
+def test_other_constants_take_the_exact_way():
+    x, _ = _normal((1, ELEMENTS // 8192, 8192), 5)
+    x = x.to(torch.bfloat16)
+    for eps_l1, eps_log in ((0.0, 1e-8), (1e-8, 0.0), (1e-8, 0.5), (1.0, 1e-8), (1e-3, 2.0 ** -24)):
+        print(f"[case] eps_l1 {eps_l1} eps_log {eps_log}", flush=True)
+        _both_ways(tahq.make_config(1, x.shape[1], 8192, 64, tahq.BF16, 3.5, eps_l1=eps_l1, eps_log=eps_log), x)
