@@ -178,7 +178,7 @@ struct LaunchEntropy {
         using N = Lanes<G, BF16 ? 2 : 4>;
         constexpr int NG = kRowGroups<G, BF16 ? 2 : 4, N::usual>;
         if (few_tiles<N>(T, 4)) with<N::few, 1>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp);
-        else if (NG == 1 || T < 1024u * 256u * NG) with<N::usual, 1>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp);
+        else if (NG == 1 || T < (hist ? 128u : 1024u) * 256u * NG) with<N::usual, 1>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp);
         else with<N::usual, NG>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp);
     }
     // units are whole steps, whatever those are
@@ -331,16 +331,21 @@ struct LaunchClassify {
     }
 };
 
+// k_select_small's and k_select_mid's lowest bin: the topmost bin but one holds ln A, the largest an entropy can be
+template <uint32_t BINS, int SHIFT>
+int lowest_bin(const Shape &s)
+{
+    const float ln_a = (float)__builtin_log((double)s.A);
+    int bits;
+    memcpy(&bits, &ln_a, 4);
+    return (bits >> SHIFT) - (int)(BINS - 2);
+}
+
 template <uint32_t PLACES, uint32_t BINS, int SHIFT>
 void launch_select_small(dim3 grid, const float *H, uint32_t n, uint32_t k, const Shape &s, uint64_t *bitmap, uint32_t *ranks,
                          Enqueue *qp)
 {
-    // the topmost bin but one holds ln A, the largest an entropy can be
-    const float ln_a = (float)__builtin_log((double)s.A);
-    int bits;
-    memcpy(&bits, &ln_a, 4);
-    (*qp)(k_select_small<PLACES, BINS, SHIFT>, grid, dim3(kSmallUnitThreads), H, n, k, s.m, (bits >> SHIFT) - (int)(BINS - 2),
-          bitmap, ranks);
+    (*qp)(k_select_small<PLACES, BINS, SHIFT>, grid, dim3(kSmallUnitThreads), H, n, k, s.m, lowest_bin<BINS, SHIFT>(s), bitmap, ranks);
 }
 
 // ---- backward-pass fixed-point compressor
@@ -500,7 +505,11 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
     const bool wide = s.m > 1;     // allocation tiles of several quantization tiles
     // ranking units that one workgroup can hold are ranked in a single launch
     const uint64_t places = s.nA + (!wide && s.n % 64 != 0 ? 63u : 0u);       // counted from a 64-tile boundary
-    const bool small_units = select && places <= kSmallUnitMaxKeys && !multi_launch;
+    // ... from LDS or from registers.  (Not where the two-launch selection's approximate entropies save more: [16,1024,4096] 77.8 us
+    // so, 80.5 with exact ones; and as long as every unit has a compute unit.)
+    const bool mid_units = select && !wide && !multi_launch && places > kSmallUnitMaxKeys && places <= kMidPlaces && s.U <= 256 &&
+                           !approximate_entropies(s, cfg);
+    const bool small_units = (select && places <= kSmallUnitMaxKeys && !multi_launch) || mid_units;
 
     // The multi-launch selection puts the unit into the grid's second dimension.  (The two-launch selection does so too, in
     // slices: 65536 units and more of 32706 to 32767 tiles each are a tensor of fewer than 2^31.)
@@ -598,7 +607,9 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
             const uint64_t unit_words = s.n / 64 + 2;
             const dim3 grid(s.U, wide ? (uint32_t)((unit_words + kExpandWords - 1) / kExpandWords) : 1u);
             // as little LDS as will do; the largest units leave room for half as many bins
-            if (places <= 4096) launch_select_small<4096, 8192, 12>(grid, H, n32, k32, s, bitmap, ranks, &q);
+            if (mid_units)
+                q(k_select_mid, grid, dim3(kSmallUnitThreads), (const float *)H, n32, k32, lowest_bin<kMidBins, kMidShift>(s), bitmap, ranks);
+            else if (places <= 4096) launch_select_small<4096, 8192, 12>(grid, H, n32, k32, s, bitmap, ranks, &q);
             else if (places <= 16384) launch_select_small<16384, 8192, 12>(grid, H, n32, k32, s, bitmap, ranks, &q);
             else if (places <= 28672) launch_select_small<28672, 8192, 12>(grid, H, n32, k32, s, bitmap, ranks, &q);
             else launch_select_small<kSmallUnitMaxKeys, 4096, 13>(grid, H, n32, k32, s, bitmap, ranks, &q);

@@ -1,11 +1,12 @@
 // Top-p% tile selection (Sec. 3.2): inside every ranking unit the k (allocation) tiles of highest entropy get
 // the wider code (4 bits by default), ties going to the lower tile index.  Exact, deterministic, no sort.
-// Entropies map to order-preserving 32-bit keys; three ways to find the k-th largest key K*, how many tiles equal to
+// Entropies map to order-preserving 32-bit keys; four ways to find the k-th largest key K*, how many tiles equal to
 // K* are still wanted (`take`), and from them the bit map and the rank table:
 //
 //   * ranking units of at most 32768 tiles (32705 where units start off the 64-tile boundaries): k_select_small, one workgroup per
 //     unit in one launch (entropies and a histogram in LDS, the threshold's bin ranked directly), because at that size several
 //     launches cost more than the work;
+//   * units of up to 65536 places in tensors whose entropies are exact: k_select_mid, the same from registers;
 //   * larger units: the entropy kernel also counts the entropies over 2048 linear bins per unit; k_select_classify
 //     settles every tile outside the bin that holds K* and lists the tiles inside it, k_select_resolve ranks that list
 //     (further down in this file);
@@ -18,7 +19,7 @@
 // small reductions a later kernel needs (which bin holds the k-th key, prefix over segments) are
 // recomputed by every block from a few KB of global data.
 //
-// In the third way the histograms of digits 1 and 2 are kept in two levels so that no address takes more than a handful
+// In the last way the histograms of digits 1 and 2 are kept in two levels so that no address takes more than a handful
 // of global atomics: every workgroup stores its own 2048-bin histogram with plain stores and adds only the
 // totals of its 64 super-bins (32 bins each) atomically.  The reader picks the super-bin from the 64
 // totals, then sums the workgroups' counts for the 32 bins inside it.
@@ -852,6 +853,226 @@ __device__ __forceinline__ void put_word(uint64_t *word, uint64_t mask, uint64_t
 {
     if (mask == ~0ull) *word = bits;
     else atomicOr(reinterpret_cast<unsigned long long *>(word), (unsigned long long)bits);
+}
+
+// ---- ranking units of up to 65536 tiles: one launch, from registers
+//
+// What k_select_small does for units whose entropies LDS holds, for units whose entropies the registers of 1024 threads hold: 16 blocks of
+// 256 places per wavefront, four places per lane and block.  The bins of the first cut are 1024 floats wide, so that the threshold's
+// seldom holds more of 65536 ordinary tiles than are placed directly (with bins of 4096 a second cut took 5 us).  Against
+// the two-launch selection it saves the launch that clears scratch, one of the selection's two, and the entropy pass its
+// histogram, whose additions meet on the bins of a few units.  Encode of bf16: 34816 tiles of 64 channels 30.7 -> 21.6 us, 40980 31.7 ->
+// 23.3, 65536 32.2 -> 27.6, four units of those 40.7 -> 38.1, 2 x 40960 of 16 channels 25.9 -> 20.7.  81920 tiles took as long as in two launches
+// (33.7 and 33.5), and 77700 of 16 channels longer.
+constexpr uint32_t kMidPlaces = 65536, kMidBins = 32768;
+constexpr int kMidShift = 10, kMidBlocks = (int)(kMidPlaces / 256 / (kSmallUnitThreads / 64));
+
+struct MidSelectLds {
+    uint32_t hist[kMidBins];
+    uint64_t list[kSmallListCap];
+    uint64_t words[kMidPlaces / 64], equal[kMidPlaces / 64];
+    uint32_t wave_total[kSmallUnitThreads / 64];
+    uint32_t chosen[3], listed, above_zero, zero;
+};
+
+__global__ __launch_bounds__(kSmallUnitThreads) void k_select_mid(const float *__restrict__ H, uint32_t n, uint32_t k, int bin0,
+                                                                  uint64_t *__restrict__ bitmap, uint32_t *__restrict__ ranks)
+{
+    __shared__ __attribute__((aligned(16))) MidSelectLds L;
+    constexpr uint32_t WAVES = kSmallUnitThreads / 64, WPT = kMidPlaces / 64 / kSmallUnitThreads;          // bit map words per thread
+    static_assert(kMidPlaces / 64 == WPT * kSmallUnitThreads && sizeof(L) <= 163840, "a thread's words, the LDS of a compute unit");
+    const uint32_t u = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    const UnitPlaces at(u, n);
+    const float *uH = H + ((uint64_t)u * n - at.phase);      // by place
+    const uint32_t top = at.nwords * 64u - 4u;
+
+    // All loads at once (whole words of 64 places, as k_select_classify reads them).
+    int4 q[kMidBlocks];
+#pragma unroll
+    for (int r = 0; r < kMidBlocks; ++r) {
+        const uint32_t p = ((uint32_t)r * WAVES + wave) * 256u + 4u * lane;
+        q[r] = *reinterpret_cast<const int4 *>(uH + (p < top ? p : top));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kMidBins / 4 / kSmallUnitThreads; ++i)
+        reinterpret_cast<uint4 *>(L.hist)[i * kSmallUnitThreads + tid] = make_uint4(0, 0, 0, 0);
+    if (tid == 0) { L.listed = 0; L.above_zero = 0; L.zero = 0; }
+    __syncthreads();
+    // f(block, its four bit patterns) for my blocks that hold places of the unit
+    auto each_block = [&](auto f) {
+#pragma unroll
+        for (int r = 0; r < kMidBlocks; ++r) {
+            const uint32_t b = (uint32_t)r * WAVES + wave;
+            if (b * 256u < at.end) f(b, q[r]);
+            __builtin_amdgcn_sched_barrier(0);   // (one block after the other: the registers are full)
+        }
+    };
+    // Bit patterns in the order of their keys from here on: signed integers, negative ones' other bits turned over.  Places outside the
+    // unit take the lowest of all, which is no entropy's.
+    const uint32_t outside = (at.end + 255u) / 256u * 256u - n;          // so many, in the unit's blocks
+#pragma unroll
+    for (int r = 0; r < kMidBlocks; ++r) {
+        auto ordered = [](int v) { return v ^ ((v >> 31) & INT32_MAX); };
+        q[r].x = ordered(q[r].x); q[r].y = ordered(q[r].y); q[r].z = ordered(q[r].z); q[r].w = ordered(q[r].w);
+        const uint32_t base = ((uint32_t)r * WAVES + wave) * 256u, i = base + 4u * lane - at.phase;
+        if (base < at.end && (base < at.phase || base + 256u > at.end)) {
+            q[r].x = i < n ? q[r].x : INT32_MIN; q[r].y = i + 1u < n ? q[r].y : INT32_MIN;
+            q[r].z = i + 2u < n ? q[r].z : INT32_MIN; q[r].w = i + 3u < n ? q[r].w : INT32_MIN;
+        }
+    }
+    each_block([&](uint32_t, const int4 &v4) {
+        const int v[4] = {v4.x, v4.y, v4.z, v4.w};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int bin = (v[c] >> kMidShift) - bin0;
+            atomicAdd(&L.hist[bin < 0 ? 0 : bin > (int)kMidBins - 1 ? (int)kMidBins - 1 : bin], 1u);
+        }
+    });
+    __syncthreads();
+    block_pick_bin<(int)kMidBins>(L.hist, k, L.wave_total, L.chosen);
+    const uint32_t bstar = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[0]);
+    uint32_t rem = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[1]);
+    uint32_t crowd = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[2]);
+    if (bstar == 0) crowd -= outside;            // bin 0 has counted them as well
+    // the bin's patterns, first and last
+    int lo = bstar == 0 ? INT32_MIN + 1 : (int)((bstar + (uint32_t)bin0) << kMidShift);
+    int hi = bstar == kMidBins - 1 ? INT32_MAX : (int)(((bstar + (uint32_t)bin0 + 1u) << kMidShift) - 1u);
+    auto four_bits = [](const int4 &v, auto test) {
+        return (test(v.x) ? 1u : 0u) | (test(v.y) ? 2u : 0u) | (test(v.z) ? 4u : 0u) | (test(v.w) ? 8u : 0u);
+    };
+    auto put_bits = [&](uint64_t *out, uint32_t b, uint32_t four) {
+        const uint32_t d = nibbles_to_dword(four, lane);
+        if ((lane & 7) == 0) reinterpret_cast<uint32_t *>(out)[b * 8u + (lane >> 3)] = d;
+    };
+    if (crowd > kSmallListCap && bstar == 0) {
+        // the lowest bin's usual crowd are the entropies of all-zero tiles, +0.0f, which counting tells from those above and below
+        uint32_t above = 0, zero = 0;
+        each_block([&](uint32_t, const int4 &v) {
+            above += (uint32_t)__popc(four_bits(v, [&](int x) { return x > 0 && x <= hi; }));
+            zero += (uint32_t)__popc(four_bits(v, [](int x) { return x == 0; }));
+        });
+        above = wave_incl_scan(above);
+        zero = wave_incl_scan(zero);
+        if (lane == 63) { atomicAdd(&L.above_zero, above); atomicAdd(&L.zero, zero); }
+        __syncthreads();
+        above = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.above_zero);
+        zero = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.zero);
+        if (rem <= above) { lo = 1; crowd = above; }
+        else if (rem <= above + zero) { lo = hi = 0; rem -= above; crowd = zero; }
+        else { hi = -1; rem -= above + zero; crowd -= above + zero; }
+    }
+    // more tiles than the list takes: cut again, 4096 parts at a time, until they fit or all share one entropy (three times at most)
+#pragma unroll 1
+    while (crowd > kSmallListCap && lo != hi) {
+        // (nothing about the entropies is kept from one round to the next: there are no registers for it)
+#pragma unroll
+        for (int r = 0; r < kMidBlocks; ++r) asm volatile("" : "+v"(q[r].x), "+v"(q[r].y), "+v"(q[r].z), "+v"(q[r].w));
+        const uint32_t span = (uint32_t)hi - (uint32_t)lo;
+        const int bits = 32 - __builtin_clz(span), shift = bits > 12 ? bits - 12 : 0;
+        reinterpret_cast<uint4 *>(L.hist)[tid] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+        each_block([&](uint32_t, const int4 &v4) {
+            const int v[4] = {v4.x, v4.y, v4.z, v4.w};
+            const uint32_t from_lo0 = (uint32_t)v[0] - (uint32_t)lo;
+            // (tokens that are alike make a crowd of neighbours: one addition for the four)
+            if (v[0] == v[1] && v[1] == v[2] && v[2] == v[3]) {
+                if (from_lo0 <= span) atomicAdd(&L.hist[from_lo0 >> shift], 4u);
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const uint32_t from_lo = (uint32_t)v[c] - (uint32_t)lo;
+                    if (from_lo <= span) atomicAdd(&L.hist[from_lo >> shift], 1u);
+                }
+            }
+        });
+        __syncthreads();
+        block_pick_bin<4096>(L.hist, rem, L.wave_total, L.chosen);
+        lo = (int)((uint32_t)lo + ((uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[0]) << shift));
+        rem = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[1]);
+        crowd = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[2]);
+        const uint32_t room = (uint32_t)hi - (uint32_t)lo, part = (1u << shift) - 1u;
+        hi = (int)((uint32_t)lo + (room < part ? room : part));
+    }
+    const bool by_list = crowd <= kSmallListCap;
+    each_block([&](uint32_t b, const int4 &v) {
+        const uint32_t above = four_bits(v, [&](int x) { return x > hi; });
+        const uint32_t reach = four_bits(v, [&](int x) { return x >= lo; });
+        const uint32_t inside = reach & ~above;
+        put_bits(L.words, b, above);
+        if (!by_list) {
+            put_bits(L.equal, b, inside);
+        } else if (inside != 0) {
+            const int x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if ((inside >> c) & 1u)
+                    L.list[atomicAdd(&L.listed, 1u) & (kSmallListCap - 1u)] =
+                        ((uint64_t)((uint32_t)x[c] ^ 0x80000000u) << 32) | (uint32_t)~(b * 256u + 4u * lane + c);
+            }
+        }
+    });
+    __syncthreads();
+    uint64_t word[WPT];
+    const uint32_t g0 = WPT * (uint32_t)tid;
+    if (by_list) {
+        // four threads per listed tile count the tiles ahead of it
+        if ((uint32_t)tid < 4 * crowd) {
+            const uint64_t mine = L.list[tid >> 2];
+            uint32_t ahead = 0;
+#pragma unroll 4
+            for (uint32_t i = (uint32_t)tid & 3u; i < crowd; i += 4) ahead += L.list[i] > mine ? 1u : 0u;
+            ahead += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ahead, 0xB1, 0xF, 0xF, true);      // lane ^ 1
+            ahead += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ahead, 0x4E, 0xF, 0xF, true);      // lane ^ 2
+            const uint32_t place = ~(uint32_t)mine;
+            if (((uint32_t)tid & 3u) == 0 && ahead < rem)
+                atomicOr(reinterpret_cast<uint32_t *>(L.words) + (place >> 5), 1u << (place & 31u));
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t i = 0; i < WPT; ++i) word[i] = g0 + i < at.nwords ? L.words[g0 + i] : 0ull;
+    } else {
+        // `crowd` tiles of one entropy: taken in index order until `rem` are used up
+        uint64_t eq[WPT];
+        uint32_t count = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < WPT; ++i) {
+            eq[i] = g0 + i < at.nwords ? L.equal[g0 + i] : 0ull;
+            count += (uint32_t)__popcll(eq[i]);
+        }
+        const uint32_t incl = wave_incl_scan(count);
+        if (lane == 63) L.wave_total[wave] = incl;
+        __syncthreads();
+        uint32_t eq_before = sum_of_waves_before(L.wave_total, wave, lane) + incl - count;
+        __syncthreads();
+#pragma unroll
+        for (uint32_t i = 0; i < WPT; ++i) {
+            const uint32_t here = (uint32_t)__popcll(eq[i]);
+            uint64_t taken = eq_before < rem ? eq[i] : 0ull;
+            for (uint32_t over = eq_before + here; taken != 0 && over > rem; --over) taken &= ~(1ull << (63 - __builtin_clzll(taken)));
+            word[i] = g0 + i < at.nwords ? L.words[g0 + i] | taken : 0ull;
+            eq_before += here;
+        }
+    }
+    // selected places before every word
+    uint32_t count = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < WPT; ++i) count += (uint32_t)__popcll(word[i]);
+    const uint32_t incl = wave_incl_scan(count);
+    if (lane == 63) L.wave_total[wave] = incl;
+    __syncthreads();
+    uint32_t rank = u * k + sum_of_waves_before(L.wave_total, wave, lane) + incl - count;    // (every earlier unit holds exactly k)
+#pragma unroll
+    for (uint32_t i = 0; i < WPT; ++i) {
+        const uint32_t g = g0 + i;
+        if (g < at.nwords) {
+            put_word(&bitmap[at.word0 + g], at.mask(g), word[i]);
+            if (g != 0 || at.phase == 0) ranks[at.word0 + g] = rank;
+        }
+        rank += (uint32_t)__popcll(word[i]);
+    }
 }
 
 // The edges of the threshold bin as bit patterns, first and last, as signed integers (negative values and NaN with the sign bit set

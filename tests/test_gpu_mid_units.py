@@ -1,0 +1,57 @@
+"""Ranking units of 32769 to 65536 tiles, ranked by one workgroup from its registers, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from oracle import o32
+import paper_2506_01352_amd as tahq
+
+pytestmark = pytest.mark.gpu
+
+G = 8
+
+
+def _check(x, B, S, C, budget, scope=0):
+    cfg = tahq.make_config(B, S, C, G, tahq.BF16, budget, scope=scope)
+    codec = tahq.Codec(cfg, device="cuda")
+    codec.workspace.fill_(0xFF)
+    codec.packed.fill_(0xFF)
+    codec.encode(torch.from_numpy(x.view(np.int16)).cuda())
+    torch.cuda.synchronize()
+    want = o32.encode(o32.make_cfg(B, S, C, G, o32.BF16, budget, scope=scope), x)
+    assert np.array_equal(codec.packed.cpu().numpy(), want), "stream differs from the oracle"
+
+
+@pytest.mark.parametrize("tiles", (32769, 32832, 40001, 49152, 65473, 65474, 65535, 65536, 65537))
+def test_units_of_all_lengths(tiles):
+    # three samples, off the 64-tile boundaries where the length is; the last lengths that fit, by where the unit starts, and the
+    # first that does not
+    rng = np.random.default_rng(tiles)
+    x = workloads.f32_to_bf16_bits(rng.standard_normal((3, tiles, G)).astype(np.float32)).reshape(3, tiles, G)
+    for budget in (3.0 + 1.0 / tiles, 3.37, 3.9):
+        print(f"[case] 3 units of {tiles} tiles, budget {budget}", flush=True)
+        _check(np.ascontiguousarray(x), 3, tiles, G, float(np.float32(budget)))
+
+
+@pytest.mark.parametrize("share,how", ((0.02, "zero"), (0.4, "zero"), (0.4, "constant"), (1.0, "constant"), (0.3, "one-hot"), (0.01, "nan")))
+@pytest.mark.parametrize("tiles,scope", ((40000, 0), (27001, 1)))
+def test_crowds_at_the_threshold(tiles, scope, share, how):
+    # tiles of one entropy, more and fewer than are placed directly, with the threshold above, among and below them
+    rng = np.random.default_rng(int(100 * share) + tiles)
+    x = rng.standard_normal((3, tiles, G)).astype(np.float32)
+    at = rng.random((3, tiles)) < share
+    x[at] = {"zero": np.zeros(G), "constant": np.full(G, 1.5), "one-hot": np.eye(G)[2], "nan": np.full(G, np.nan)}[how]
+    x = np.ascontiguousarray(workloads.f32_to_bf16_bits(x).reshape(3, tiles, G))
+    if how == "nan":                                     # (outside the contract; the two selections agree)
+        d = torch.from_numpy(x.view(np.int16)).cuda()
+        cfg = tahq.make_config(3, tiles, G, G, tahq.BF16, 3.5, scope=scope)
+        a, b = tahq.Codec(cfg, device="cuda"), tahq.Codec(cfg, device="cuda")
+        a.encode(d)
+        tahq.tahq_encode_phases(cfg, d, b.packed, b.workspace, tahq.PHASE_ALL | tahq.SELECT_MULTI_LAUNCH)
+        torch.cuda.synchronize()
+        assert torch.equal(a.packed, b.packed)
+        return
+    for budget in (3.005, 3.3, 3.62, 3.85, 3.995):
+        print(f"[case] {tiles} tiles, scope {scope}, {share} {how}, budget {budget}", flush=True)
+        _check(x, 3, tiles, G, budget, scope)
