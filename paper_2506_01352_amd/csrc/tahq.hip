@@ -152,9 +152,10 @@ struct LaunchEntropy {
         static ResidentCache cache;
         const uint32_t res = resident_blocks(reinterpret_cast<const void *>(k_entropy<G, BF16, LPT, NG, HIST, APPROX>), 256, cache);
         // Every workgroup adds its histogram to the unit's, and what that costs are the additions that meet on one bin: four
-        // steps per workgroup where that still leaves a workgroup per compute unit (three units of 77700 tiles of 16
+        // rounds of its lanes per workgroup where that still leaves a workgroup per compute unit (three units of 77700 tiles of 16
         // channels: 14.1 -> 8.4 us)
-        const uint32_t few = nb / 4 > 256u ? nb / 4 : 256u;
+        const uint32_t rounds = nb * NG;
+        const uint32_t few = rounds / 4 > 256u ? rounds / 4 : 256u;
         const uint32_t most = HIST && few < res ? few : res;
         const uint32_t grid = nb < most ? nb : most;
         q(k_entropy<G, BF16, LPT, NG, HIST, APPROX>, dim3(grid), dim3(256), d_in, d_H, pivot, T, (nb + grid - 1) / grid, p.eps_l1, p.eps_log,

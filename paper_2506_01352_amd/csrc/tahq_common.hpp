@@ -44,7 +44,7 @@ struct Workspace {
     uint64_t keys;       // float[T] entropies
     uint64_t cand;       // uint2[U][kCandCap]: (key, tile) of the tiles in the threshold bin
     uint64_t seg;        // uint32[U][nseg][2]: keys equal to / above the threshold, per segment; the two-launch
-                         // selection: tiles above the threshold bin, per block of 16384 places
+                         // selection: tiles above the candidates, and candidates, per block of 16384 places
     uint64_t sel;        // uint8[T] (multi-launch selection, only when n % 64 != 0, or A > G); two-launch selection:
                          // uint64[U][n / 64 + 2], the words of the tiles that share a crowded threshold's sub-bin
     uint64_t part;       // float[T]: per-quantization-tile partial sums            (only when A > G)

@@ -274,84 +274,83 @@ private:
     }
 };
 
+// (fp32 magnitudes leave no room for the index: the two largest first, and where that makes an outlier tile in the wavefront, a second
+// look at the elements for the lowest index.  2 or 4 vector slots per element; carrying the index along took 5.5.)
 template <int G, int LPT>
 struct Top2<G, false, LPT> {
-    float a1 = -1.0f, a2 = 0.0f;                 // magnitudes are >= 0: the first element always replaces a1
-    uint32_t d = 0;
-    __device__ __forceinline__ void add(uint32_t k, float x0, float x1)
-    {
-        add_one(k, x0);
-        add_one(k + 1, x1);
-    }
-    __device__ __forceinline__ void finish(uint32_t part, float *a1_out, float *a2_out, uint32_t *d_out)
-    {
-        auto merge = [&](float p1, float p2, uint32_t pd) {
-            const bool other = p1 > a1 || (p1 == a1 && pd < d);
-            a2 = __builtin_fmaxf(__builtin_fminf(a1, p1), __builtin_fmaxf(a2, p2));
-            a1 = other ? p1 : a1;
-            d = other ? pd : d;
-        };
-        if constexpr (LPT >= 2) {
-            d += part * G;
-            merge(lane_xor<1>(a1), lane_xor<1>(a2), lane_xor<1>(d));
-        }
-        if constexpr (LPT >= 4) merge(lane_xor<2>(a1), lane_xor<2>(a2), lane_xor<2>(d));
-        *a1_out = a1;
-        *a2_out = __builtin_fmaxf(a2, 0.0f);
-        *d_out = d;
-    }
-private:
-    __device__ __forceinline__ void add_one(uint32_t k, float x)
+    float a1 = -1.0f, a2 = -1.0f;                // magnitudes are >= 0: the first element always replaces a1
+    __device__ __forceinline__ void add(float x)
     {
         const float a = __builtin_fabsf(x);
-        const bool gt = a > a1;
-        a2 = gt ? a1 : __builtin_fmaxf(a2, a);
-        d = gt ? k : d;
-        a1 = gt ? a : a1;
+        a2 = __builtin_amdgcn_fmed3f(a1, a2, a); // second largest of {a1 >= a2, a}; a NaN counts as the smallest
+        a1 = __builtin_fmaxf(a1, a);
+    }
+    // of the whole tile
+    __device__ __forceinline__ void merge()
+    {
+        auto with = [&](float p1, float p2) {
+            a2 = __builtin_fmaxf(__builtin_fminf(a1, p1), __builtin_fmaxf(a2, p2));
+            a1 = __builtin_fmaxf(a1, p1);
+        };
+        if constexpr (LPT >= 2) with(lane_xor<1>(a1), lane_xor<1>(a2));
+        if constexpr (LPT >= 4) with(lane_xor<2>(a1), lane_xor<2>(a2));
+        a2 = __builtin_fmaxf(a2, 0.0f);
+    }
+    // the lowest index of an element of magnitude a1; element(k): the k-th of mine
+    template <class Element>
+    __device__ __forceinline__ uint32_t index(uint32_t part, Element element) const
+    {
+        uint32_t d = 0x7fu;
+#pragma unroll
+        for (int k = G; k-- > 0;) d = __builtin_fabsf(element(k)) == a1 ? part * G + k : d;
+        if constexpr (LPT >= 2) { const uint32_t p = lane_xor<1>(d); d = p < d ? p : d; }
+        if constexpr (LPT >= 4) { const uint32_t p = lane_xor<2>(d); d = p < d ? p : d; }
+        return d;
     }
 };
 
-// Outlier flag and pivot index of the tile: the pivot byte (bit 7 = flag, bits 0..6 = d).
-template <class T2>
-__device__ __forceinline__ uint32_t pivot_byte(T2 &t, uint32_t part, float tau, float eps_ratio)
+// Outlier flag and pivot index of the tile: the pivot byte (bit 7 = flag, bits 0..6 = d).  word(i): the i-th dword of my part.
+template <int EPL, bool BF16, int LPT, class Word>
+__device__ __forceinline__ uint32_t pivot_from(Word word, uint32_t part, float tau, float eps_ratio)
 {
-    float a1, a2;
-    uint32_t d;
-    t.finish(part, &a1, &a2, &d);
-    return a1 > tau * (a2 + eps_ratio) ? (0x80u | d) : 0u;
+    Top2<EPL, BF16, LPT> t;
+    if constexpr (BF16) {
+#pragma unroll
+        for (int k = 0; k < EPL; k += 2) t.add(k, word(k / 2));
+        float a1, a2;
+        uint32_t d;
+        t.finish(part, &a1, &a2, &d);
+        return a1 > tau * (a2 + eps_ratio) ? (0x80u | d) : 0u;
+    } else {
+#pragma unroll
+        for (int k = 0; k < EPL; ++k) t.add(__uint_as_float(word(k)));
+        t.merge();
+        const bool flag = t.a1 > tau * (t.a2 + eps_ratio);
+        if (__ballot(flag) == 0) return 0u;
+        const uint32_t d = t.index(part, [&](int k) { return __uint_as_float(word(k)); });
+        return flag ? (0x80u | d) : 0u;
+    }
 }
 
-// ... from my part's words in registers
+// ... in registers
 template <int EPL, bool BF16, int LPT>
 __device__ __forceinline__ uint32_t pivot_of(const uint32_t *w, uint32_t part, float tau, float eps_ratio)
 {
-    Top2<EPL, BF16, LPT> t;
-#pragma unroll
-    for (int k = 0; k < EPL; k += 2) {
-        if constexpr (BF16) t.add(k, w[k / 2]);
-        else t.add(k, __uint_as_float(w[k]), __uint_as_float(w[k + 1]));
-    }
-    return pivot_byte(t, part, tau, eps_ratio);
+    return pivot_from<EPL, BF16, LPT>([&](int i) { return w[i]; }, part, tau, eps_ratio);
 }
 
-// ... from my part in an LDS row
+// ... in an LDS row
 template <int EPL, bool BF16, int LPT>
 __device__ __forceinline__ uint32_t pivot_of(const uint8_t *row, uint32_t part, float tau, float eps_ratio)
 {
-    Top2<EPL, BF16, LPT> t;
+    constexpr int WORDS = EPL * (BF16 ? 2 : 4) / 4;
+    uint32_t w[WORDS];
 #pragma unroll
-    for (int c = 0; c < EPL * (BF16 ? 2 : 4) / 16; ++c) {
-        const uint4 w = *reinterpret_cast<const uint4 *>(row + c * 16);
-        const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-        if constexpr (BF16) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) t.add(8 * c + 2 * i, ws[i]);
-        } else {
-            t.add(4 * c, __uint_as_float(ws[0]), __uint_as_float(ws[1]));
-            t.add(4 * c + 2, __uint_as_float(ws[2]), __uint_as_float(ws[3]));
-        }
+    for (int c = 0; c < WORDS / 4; ++c) {
+        const uint4 q = *reinterpret_cast<const uint4 *>(row + c * 16);
+        w[4 * c] = q.x; w[4 * c + 1] = q.y; w[4 * c + 2] = q.z; w[4 * c + 3] = q.w;
     }
-    return pivot_byte(t, part, tau, eps_ratio);
+    return pivot_from<EPL, BF16, LPT>([&](int i) { return w[i]; }, part, tau, eps_ratio);
 }
 
 // The pivot swap P_d on a tile's LDS row.
