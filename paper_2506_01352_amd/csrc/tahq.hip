@@ -120,7 +120,7 @@ inline bool few_tiles(uint64_t T, uint32_t deep) { return T * N::usual < 65536u 
 // Streams from here on pass the caches by.  Written through them, a large stream is not there any more when the decoder reads it and
 // comes out as dirty lines in the middle of the reads of the next kernels.  bf16 [8,S,8192] on three sets of buffers in turn, encode
 // and decode in us, through the caches and past them: G = 64 at 3.25 bits: 62 MiB 180 and 183, 125 MiB 363 and 341 (encode
-// alone 261 and 234); at 4 bits: 74 MiB 117 and 120, 149 MiB 238 and 231; G = 128 at 3 bits: 106 MiB 233 and 244; G = 32 at 4 bits: 85 MiB
+// alone 261 and 234; on one set of buffers, decoded at once on the same card, 338 and 347); at 4 bits: 74 MiB 117 and 120, 149 MiB 238 and 231; G = 128 at 3 bits: 106 MiB 233 and 244; G = 32 at 4 bits: 85 MiB
 // 118 and 123, 170 MiB 242 and 238.
 constexpr uint64_t kStreamingFrom = 112ull << 20;
 
