@@ -579,7 +579,7 @@ __device__ __forceinline__ float entropy_of(R &x, float eps_l1, float eps_log)
 }
 
 // The same to within kEntropySlack, with the hardware's logarithm, two vector slots instead of nine, and in one pass:
-//     H ~ ln2 (-r S - r L1 log2 r),  S = sum of |v| log2 (|v| + 2^-126)
+//     H ~ 0 - ln2 (r S + r L1 log2 r),  S = sum of |v| log2 (|v| + 2^-126)
 // (what is added keeps a zero's logarithm finite, and is lost in the rounding beside anything that counts).
 // What separates it from the sum above, in the norms' range below (where |log2 L1| <= 24, so the terms' magnitudes add up to 31):
 // LOG's distance from the logarithm, 1.11e-5 at most over [1e-12, 2), passed on by weights that add up to 1; varsigma inside
@@ -610,7 +610,9 @@ __device__ __forceinline__ float entropy_approx(const R &x, float eps_l1, Exact 
     L1 = whole_tile<LPT>(L1);
     S = whole_tile<LPT>(S);
     const float r = 1.0f / (L1 + eps_l1);
-    float h = kLn2 * (-(r * S) - (r * L1) * __builtin_amdgcn_logf(r));
+    // (a difference from +0.0f, as above: never -0.0f, which the selection takes for a place outside the ranking unit.  A single
+    // element of magnitude 1 makes both products +0.0f.)
+    float h = 0.0f - kLn2 * (r * S + (r * L1) * __builtin_amdgcn_logf(r));
     if (L1 == 0.0f) h = 0.0f;
     if (__ballot(!(L1 == 0.0f || (L1 > kApproxNormMin && L1 < kApproxNormMax))) != 0) h = exact();
     return h;

@@ -23,6 +23,30 @@ def _both_ways(cfg, x):
     tahq.tahq_encode_phases(cfg, x, codec.packed, codec.workspace, tahq.PHASE_ALL | tahq.SELECT_MULTI_LAUNCH)
     torch.cuda.synchronize()
     assert torch.equal(fused, codec.packed), "the two selections differ"
+    return fused
+
+
+def _approximate(cfg, x):
+    """The entropies that the selection starts from: the scratch behind its counters, histograms and candidate lists."""
+    codec = tahq.Codec(cfg, device="cuda")
+    for phase in (tahq.PHASE_PROLOGUE, tahq.PHASE_ENTROPY):
+        tahq.tahq_encode_phases(cfg, x, codec.packed, codec.workspace, phase)
+    tiles = cfg.batch * cfg.seq * cfg.hidden // cfg.tile
+    units = 1 if cfg.scope else cfg.batch
+
+    def pad256(v):
+        return (v + 255) // 256 * 256
+    at = pad256(units * (512 + 32 + 4096 + 8192 + 16))
+    at = pad256(at + units * 2 * min(-(-tiles // units // 8192), 64) * 2048 * 4)
+    at = pad256(at + units * 16384 * 8)
+    torch.cuda.synchronize()
+    return codec.workspace[at:at + 4 * tiles].view(torch.float32).clone()
+
+
+def _exact(cfg, x):
+    H = torch.empty(cfg.batch * cfg.seq * cfg.hidden // cfg.tile, device="cuda")
+    tahq.tahq_tile_entropy(cfg, x, H)
+    return H
 
 
 def _normal(shape, seed):
@@ -90,6 +114,33 @@ def test_values_outside_the_approximation(G):
     x[0, 200:240, :G] = float("nan")
     print(f"[case] outside, not finite, G={G}", flush=True)
     _both_ways(tahq.make_config(B, S, C, G, tahq.BF16, 3.6), x)
+
+
+@pytest.mark.parametrize("B,S,C,G,scope", ((1, 4096, 8192, 64, 0), (2, 2048, 8192, 8, 0), (2, 2048, 8192, 128, 1), (3, 2731, 4128, 32, 0)))
+@pytest.mark.parametrize("share", (0.4, 0.9, 1.0))
+def test_one_hot_tiles(B, S, C, G, scope, share):
+    # tiles with a single element of 1 or of another power of two among zeros, whose entropies the approximation takes for zeros of
+    # either sign: all tie, a little below the all-zero tiles.  Thresholds above, among and below them.
+    x, g = _normal((B * S * C // G, G), 11)
+    one_hot = torch.rand(x.shape[0], device="cuda", generator=g) < share
+    x[one_hot] = 0.0
+    sign = torch.randint(0, 2, (x.shape[0],), device="cuda", generator=g) * 2.0 - 1.0
+    x[:, G // 3] = torch.where(one_hot, sign, x[:, G // 3])
+    x[1::4, G // 3] *= 2.0
+    x[2::4, G // 3] *= 0.125
+    x[3::16] = 0.0
+    x = x.to(torch.bfloat16)
+    cfg = tahq.make_config(B, S, C, G, tahq.BF16, 3.5, scope=scope)
+    H, exact = _approximate(cfg, x), _exact(cfg, x)
+    assert float((H - exact).abs().max()) < 1e-3, "these are the entropies"
+    assert not bool((H.view(torch.int32) == -2 ** 31).any()), "an entropy of -0.0f, the selection's mark of places outside a unit"
+    words = -(-B * S * C // G // 64)
+    for budget in (3.002, 3.0625, 3.3, 3.6, 3.93, 3.999):
+        print(f"[case] one-hot [{B},{S},{C}] G={G} scope={scope} share {share} budget {budget}", flush=True)
+        cfg = tahq.make_config(B, S, C, G, tahq.BF16, budget, scope=scope)
+        packed = _both_ways(cfg, x)
+        chosen = np.unpackbits(packed[64:64 + 8 * words].cpu().numpy(), bitorder="little").sum()
+        assert int(chosen) == tahq.tahq_k_per_unit(cfg) * (1 if scope else B), "so many tiles are wide"
 
 
 def test_other_constants_take_the_exact_way():
