@@ -296,7 +296,7 @@ struct Top2<G, false, LPT> {
         if constexpr (LPT >= 4) with(lane_xor<2>(a1), lane_xor<2>(a2));
         a2 = __builtin_fmaxf(a2, 0.0f);
     }
-    // the lowest index of an element of magnitude a1; element(k): the k-th of mine
+    // the lowest index of an element of magnitude a1, 0 in a tile of NaN only; element(k): the k-th of mine
     template <class Element>
     __device__ __forceinline__ uint32_t index(uint32_t part, Element element) const
     {
@@ -305,7 +305,7 @@ struct Top2<G, false, LPT> {
         for (int k = G; k-- > 0;) d = __builtin_fabsf(element(k)) == a1 ? part * G + k : d;
         if constexpr (LPT >= 2) { const uint32_t p = lane_xor<1>(d); d = p < d ? p : d; }
         if constexpr (LPT >= 4) { const uint32_t p = lane_xor<2>(d); d = p < d ? p : d; }
-        return d;
+        return a1 < 0.0f ? 0u : d;               // (no element has replaced a1, and none equals it)
     }
 };
 
@@ -1298,7 +1298,8 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
         const uint32_t pos = rank_in_wave + class_group_base<WAVES>(cls, (uint32_t)wave, (uint32_t)lane, class_count);
         if (cls < 4) {
             order[pos] = (uint16_t)slot;
-            if (pv > 0x80u) swap_pivot<BF16>(lds + slot * B::STRIDE, pv & 0x7fu);        // an outlier tile with d != 0
+            // an outlier tile with d != 0 (inside the row whatever the stream holds, as in the decoder)
+            if (pv > 0x80u) swap_pivot<BF16>(lds + slot * B::STRIDE, pv & (G - 1u));
         }
     }
     __syncthreads();
