@@ -911,7 +911,8 @@ __global__ __launch_bounds__(kSmallUnitThreads) void k_select_mid(const float *_
         }
     };
     // Bit patterns in the order of their keys from here on: signed integers, negative ones' other bits turned over.  Places outside the
-    // unit take the lowest of all, which is no entropy's.
+    // unit take the lowest of all, which is also that of a NaN with all bits set: where a range reaches down to it they are told
+    // apart by their place.
     const uint32_t outside = (at.end + 255u) / 256u * 256u - n;          // so many, in the unit's blocks
 #pragma unroll
     for (int r = 0; r < kMidBlocks; ++r) {
@@ -938,7 +939,7 @@ __global__ __launch_bounds__(kSmallUnitThreads) void k_select_mid(const float *_
     uint32_t crowd = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[2]);
     if (bstar == 0) crowd -= outside;            // bin 0 has counted them as well
     // the bin's patterns, first and last
-    int lo = bstar == 0 ? INT32_MIN + 1 : (int)((bstar + (uint32_t)bin0) << kMidShift);
+    int lo = bstar == 0 ? INT32_MIN : (int)((bstar + (uint32_t)bin0) << kMidShift);
     int hi = bstar == kMidBins - 1 ? INT32_MAX : (int)(((bstar + (uint32_t)bin0 + 1u) << kMidShift) - 1u);
     auto four_bits = [](const int4 &v, auto test) {
         return (test(v.x) ? 1u : 0u) | (test(v.y) ? 2u : 0u) | (test(v.z) ? 4u : 0u) | (test(v.w) ? 8u : 0u);
@@ -989,6 +990,10 @@ __global__ __launch_bounds__(kSmallUnitThreads) void k_select_mid(const float *_
             }
         });
         __syncthreads();
+        if (lo == INT32_MIN) {                   // (the first part has counted the places outside the unit as well)
+            if (tid == 0) L.hist[0] -= outside;
+            __syncthreads();
+        }
         block_pick_bin<4096>(L.hist, rem, L.wave_total, L.chosen);
         lo = (int)((uint32_t)lo + ((uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[0]) << shift));
         rem = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[1]);
@@ -999,8 +1004,11 @@ __global__ __launch_bounds__(kSmallUnitThreads) void k_select_mid(const float *_
     const bool by_list = crowd <= kSmallListCap;
     each_block([&](uint32_t b, const int4 &v) {
         const uint32_t above = four_bits(v, [&](int x) { return x > hi; });
-        const uint32_t reach = four_bits(v, [&](int x) { return x >= lo; });
-        const uint32_t inside = reach & ~above;
+        uint32_t inside = four_bits(v, [&](int x) { return x >= lo; }) & ~above;
+        if (lo == INT32_MIN) {
+            const uint32_t i = b * 256u + 4u * lane - at.phase;
+            inside &= (i < n ? 1u : 0u) | (i + 1u < n ? 2u : 0u) | (i + 2u < n ? 4u : 0u) | (i + 3u < n ? 8u : 0u);
+        }
         put_bits(L.words, b, above);
         if (!by_list) {
             put_bits(L.equal, b, inside);

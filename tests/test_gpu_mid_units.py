@@ -55,3 +55,38 @@ def test_crowds_at_the_threshold(tiles, scope, share, how):
     for budget in (3.005, 3.3, 3.62, 3.85, 3.995):
         print(f"[case] {tiles} tiles, scope {scope}, {share} {how}, budget {budget}", flush=True)
         _check(x, 3, tiles, G, budget, scope)
+
+
+@pytest.mark.parametrize("share", (0.0001, 0.3, 0.9, 1.0))
+@pytest.mark.parametrize("tiles,scope", ((40001, 0), (27001, 1), (33000, 1)))
+def test_entropies_of_all_bits_set(tiles, scope, share):
+    # fp32 values of all bits set, as memory that is filled with 0xff holds, give NaN entropies of that pattern: the lowest key there is.
+    # Few and many of them beside other NaN of either sign, with thresholds above, among and below them; the multi-launch selection
+    # ranks by the keys' digits.
+    rng = np.random.default_rng(int(100 * share) + tiles)
+    B = 3 if scope == 0 else 2 if tiles == 27001 else 1
+    x = rng.standard_normal((B, tiles, G)).astype(np.float32)
+    bits = x.view(np.uint32)
+    bits[rng.random((B, tiles)) < share] = 0xffffffff
+    for pattern in (0x7fc00000, 0xfffffffe, 0xffc00001, 0x7f800000):
+        bits[rng.random((B, tiles)) < 0.002, 3] = pattern
+    d = torch.from_numpy(x).cuda()
+    units = 1 if scope else B
+    H = torch.empty(B * tiles, device="cuda")
+    tahq.tahq_tile_entropy(tahq.make_config(B, tiles, G, G, tahq.F32, 3.5), d, H)
+    assert bool((H.view(torch.int32) == -1).any()), "such entropies occur"
+    n = B * tiles // units
+    for k in (1, n // 100, n // 2, int(0.69 * n), int(0.71 * n), int(0.95 * n), n - 2, n - 1):
+        cfg = tahq.make_config(B, tiles, G, G, tahq.F32, float(np.float32(3.0 + k / n)), scope=scope)
+        print(f"[case] {units} units of {n} tiles, {share} with all bits set, k = {tahq.tahq_k_per_unit(cfg)}", flush=True)
+        a, b = tahq.Codec(cfg, device="cuda"), tahq.Codec(cfg, device="cuda")
+        for c in (a, b):
+            c.workspace.fill_(0xFF)
+            c.packed.fill_(0xFF)
+        a.encode(d)
+        tahq.tahq_encode_phases(cfg, d, b.packed, b.workspace, tahq.PHASE_ALL | tahq.SELECT_MULTI_LAUNCH)
+        torch.cuda.synchronize()
+        assert torch.equal(a.packed, b.packed), "the two selections differ"
+        T = B * tiles
+        chosen = np.unpackbits(a.packed[64:64 + -(-T // 64) * 8].cpu().numpy(), bitorder="little").sum()
+        assert int(chosen) == units * tahq.tahq_k_per_unit(cfg)
