@@ -281,7 +281,8 @@ struct Top2<G, false, LPT> {
     float a1 = -1.0f, a2 = -1.0f;                // magnitudes are >= 0: the first element always replaces a1
     __device__ __forceinline__ void add(float x)
     {
-        const float a = __builtin_fabsf(x);
+        // (a signalling NaN made quiet: the median would make a NaN of a2 from it.  The maximum asks for the same instruction.)
+        const float a = __builtin_canonicalizef(__builtin_fabsf(x));
         a2 = __builtin_amdgcn_fmed3f(a1, a2, a); // second largest of {a1 >= a2, a}; a NaN counts as the smallest
         a1 = __builtin_fmaxf(a1, a);
     }

@@ -58,3 +58,26 @@ def test_tiles_of_nan_only_are_transformed_from_their_first_element(G, tiles, ta
         if budget == 3.0:
             a, b = (s[4].reshape(tiles, -1)[~nan] for s in (got, want))
             assert np.array_equal(a, b), "payload of the other tiles"
+
+
+@pytest.mark.parametrize("tiles", (211, 66003))
+@pytest.mark.parametrize("G", (8, 16, 32, 64, 128))
+def test_nan_of_every_kind_is_no_magnitude(G, tiles):
+    # quiet and signalling NaN at every place but a tile's first (the oracle's search starts from that), beside two large elements:
+    # the second largest stays what it is, and the tile is none of the outliers that a lost one makes it
+    rng = np.random.default_rng(3 * G + tiles)
+    x = rng.uniform(0.5, 1.5, size=(1, tiles, G)).astype(np.float32)
+    at = rng.permuted(np.tile(np.arange(1, G), (tiles, 1)), axis=1)[:, :4]
+    rows = np.arange(tiles)
+    x[0, rows, at[:, 0]], x[0, rows, at[:, 1]] = 5.0, -4.0
+    x[0, ::5, at[0, 0]] = 50.0
+    bits = x.view(np.uint32)[0]
+    kinds = np.array([0x7fa00000, 0xff800001, 0x7fbfffff, 0x7fc00000, 0xffffffff], np.uint32)
+    bits[rows, at[:, 2]] = kinds[rng.integers(0, kinds.size, tiles)]
+    some = rng.random(tiles) < 0.5
+    bits[rows[some], at[some, 3]] = kinds[rng.integers(0, kinds.size, int(some.sum()))]
+    for budget in (3.0, 3.5):
+        print(f"[case] G={G} {tiles} tiles, budget {budget}", flush=True)
+        got, want = (f(x, G, budget) for f in (_encode, _oracle))
+        wrong = np.nonzero(got[0] != want[0])[0]
+        assert wrong.size == 0, f"{wrong.size} pivot bytes differ, first in tile {wrong[0]}"
