@@ -619,6 +619,24 @@ __device__ __forceinline__ float entropy_approx(const R &x, float eps_l1, Exact 
     return h;
 }
 
+// The entropy of a tile with NaN among its elements: that with the largest payload, made quiet, with the sign turned over.  Which
+// payload came through the sums above would be the choice of whoever ordered the instructions' operands, and differ between the
+// kernels that compute the same entropies.  (With one kind of NaN in the tile this is what the sums give.)
+template <class W, bool BF16, int LPT>
+__device__ __forceinline__ float nan_entropy(const Row<W, BF16> &x, float h)
+{
+    uint32_t most = 0;
+#pragma unroll
+    for (int i = 0; i < Row<W, BF16>::WORDS; ++i) {
+        const uint32_t a = BF16 ? (x.w[i] << 16) & 0x7fff0000u : 0u, b = x.w[i] & (BF16 ? 0x7fff0000u : 0x7fffffffu);
+        most = most > a ? most : a;
+        most = most > b ? most : b;
+    }
+    if constexpr (LPT >= 2) { const uint32_t p = lane_xor<1>(most); most = most > p ? most : p; }
+    if constexpr (LPT >= 4) { const uint32_t p = lane_xor<2>(most); most = most > p ? most : p; }
+    return h != h && most > 0x7f800000u ? __uint_as_float(most | 0x80400000u) : h;
+}
+
 constexpr int kDigit0Bits = 10;                  // first radix digit of the selection: key bits 31..22
 static_assert((1u << kDigit0Bits) == kDigit0Bins, "digit 0 width");
 
@@ -719,15 +737,19 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint8_t *__re
                 pv[g] = pivot_of<W::EPL, BF16, LPT>(x[g].w, part, tau, eps_ratio);
                 x[g].forget();
             }
+            auto again = [&]() {                 // my row, from memory
+                const uint32_t at = mine + g * W::TILES;
+                return TensorRow<W, BF16>(static_cast<const uint8_t *>(in) +
+                                          ((j0 + (at < n ? at : n - 1)) * LPT + part) * W::LANE_BYTES);
+            };
             if constexpr (APPROX) {
                 h[g] = entropy_approx<W::EPL, LPT>(x[g], eps_l1, [&]() {
-                    const uint32_t at = mine + g * W::TILES;
-                    TensorRow<W, BF16> y(static_cast<const uint8_t *>(in) +
-                                         ((j0 + (at < n ? at : n - 1)) * LPT + part) * W::LANE_BYTES);
+                    TensorRow<W, BF16> y = again();
                     return entropy_of<W::EPL, LPT>(y, eps_l1, eps_log);
                 });
             }
             else h[g] = entropy_of<W::EPL, LPT>(x[g], eps_l1, eps_log);
+            if (__ballot(h[g] != h[g]) != 0) h[g] = nan_entropy<W, BF16, LPT>(again(), h[g]);
         }
         j_prev = j0;
         n_prev = n;
