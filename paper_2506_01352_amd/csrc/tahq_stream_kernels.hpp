@@ -582,13 +582,23 @@ __device__ __forceinline__ float entropy_of(R &x, float eps_l1, float eps_log)
 // The same to within kEntropySlack, with the hardware's logarithm, two vector slots instead of nine, and in one pass:
 //     H ~ 0 - ln2 (r S + r L1 log2 r),  S = sum of |v| log2 (|v| + 2^-126)
 // (what is added keeps a zero's logarithm finite, and is lost in the rounding beside anything that counts).
-// What separates it from the sum above, in the norms' range below (where |log2 L1| <= 24, so the terms' magnitudes add up to 31):
-// LOG's distance from the logarithm, 1.11e-5 at most over [1e-12, 2), passed on by weights that add up to 1; varsigma inside
-// the logarithm, at most 128 times itself, 7.7e-6 (the caller takes this way for varsigma up to 2^-24 only); the roundings here, of the
-// sums (11 deep), the products, v_log_f32 (1 ulp) and the last steps, together at most 16 of 2^-24 times ln2 31, 2.1e-5, and
-// there, 9 of 2^-24 times 4.9, 2.7e-6.  Makes 4.3e-5.  (Seen: 6.7e-6.)  A tile whose norm is neither zero nor in the range takes the
-// other way, with its wavefront.
-constexpr float kEntropySlack = 6e-5f, kApproxLogMax = 0x1p-24f, kApproxLogMin = 1e-12f, kApproxNormMin = 0x1p-24f, kApproxNormMax = 0x1p24f;
+// How far it is from the sum above, for norms in the range below; r is what either side computed, p = |v| r, u = 2^-24.
+//   - The terms here.  In bits, p |log2 |v|| adds up to at most 31, as |log2 L1| <= 24 and p's own entropy is at most 7, and r L1
+//     |log2 r| to 24.6 (24 and, for an eps beside which the norm vanishes, x |log2 x| of their ratio x).  Each of the two
+//     passes 11 additions, two products and the hardware's logarithm: v_log_f32 is within 2 u of its result, relatively, for
+//     every float from 2^-25 to 2^25 (all of them compared with the double logarithm).  Then a sum and two steps by ln2, of at most 7.
+//   - r: sums of 11 and 7 levels, the addition of eps and the division, 22 u between the two.  The sum over p log p moves by
+//     that times at most ln 128 - 1.
+//   - LOG's distance from the logarithm, 1.11e-5 at most over [1e-12, 2), passed on by weights p that add up to 1.
+//   - varsigma inside the logarithm, at most 128 times itself (the caller takes this way for varsigma up to 2^-24 only).
+//   - The roundings of the sum above: LOG's argument, a product, 7 additions and the factor r, of at most ln 128.
+// (Seen: 2.2e-5.)  A tile whose norm is neither zero nor in the range takes the other way, with its wavefront.
+constexpr float kApproxLogMax = 0x1p-24f, kApproxLogMin = 1e-12f, kApproxNormMin = 0x1p-24f, kApproxNormMax = 0x1p24f;
+constexpr double kApproxError = 0x1p-24 * ((15 * 31 + 15 * 24.6 + 3 * 7) * 0.69315 + 22 * 3.86 + 10 * 4.86) + 1.11e-5 + 128.0 * kApproxLogMax;
+constexpr float kEntropySlack = 7e-5f;           // (more by far than the rounding of a bin's edge that it is added to twice)
+static_assert(kApproxError + 1e-6 < kEntropySlack, "the selection's candidates rest on it");
+// k_select_classify looks for candidates no further than the two bins beside the threshold's: the narrowest are ln 8 / kLinBins wide.
+static_assert(2.0f * kEntropySlack * kLinBins < 2.07f, "the margin is narrower than a bin");
 
 // `exact` is that other way: it reads the row again, so that nothing has to wait for it in registers.
 template <int EPL, int LPT, class R, class Exact>

@@ -49,6 +49,9 @@ def _exact(cfg, x):
     return H
 
 
+SLACK = 7e-5                                             # derived beside the kernel's constant of that value
+
+
 def _normal(shape, seed):
     g = torch.Generator(device="cuda")
     g.manual_seed(seed)
@@ -114,6 +117,30 @@ def test_values_outside_the_approximation(G):
     x[0, 200:240, :G] = float("nan")
     print(f"[case] outside, not finite, G={G}", flush=True)
     _both_ways(tahq.make_config(B, S, C, G, tahq.BF16, 3.6), x)
+
+
+@pytest.mark.parametrize("eps_l1,eps_log", ((1e-8, 1e-8), (1e-30, 1e-12), (1e-8, 2.0 ** -24), (1e3, 1e-8)))
+@pytest.mark.parametrize("G", (8, 16, 32, 64, 128))
+def test_distance_from_the_exact_entropies(G, eps_l1, eps_log):
+    # Elements of one magnitude, of many, few that are not zero, all alike but one; norms all over the approximation's range, and
+    # among the last tiles below and above it (where a wavefront's tiles all take the exact way).
+    S, C = ELEMENTS // 8192, 8192
+    x, g = _normal((S * C // G, G), G)
+    x[0::5] = torch.exp(3.0 * x[0::5])
+    x[1::5] = torch.sign(x[1::5])
+    x[2::5] *= (torch.rand(x[2::5].shape, device="cuda", generator=g) < 3.0 / G)
+    x[3::5] = 1.0 + 0.01 * x[3::5]
+    x[3::5, 0] *= 200.0
+    norm = x.abs().sum(1, keepdim=True).clamp_min(1e-20)
+    power = torch.empty_like(norm).uniform_(-23.9, 23.9, generator=g)
+    power[-x.shape[0] // 8:] *= 1.25
+    x *= torch.exp2(power) / norm
+    x = x.to(torch.bfloat16)
+    cfg = tahq.make_config(1, S, C, G, tahq.BF16, 3.5, eps_l1=eps_l1, eps_log=eps_log)
+    off = (_approximate(cfg, x) - _exact(cfg, x)).abs()
+    print(f"[case] G={G} eps_l1 {eps_l1} eps_log {eps_log}: {float(off.max()):.3g}, of {float((off > 0).float().mean()):.2f} of the tiles", flush=True)
+    assert float((off > 0).float().mean()) > 0.5, "these entropies are approximate"
+    assert float(off.max()) <= SLACK
 
 
 @pytest.mark.parametrize("B,S,C,G,scope", ((1, 4096, 8192, 64, 0), (2, 2048, 8192, 8, 0), (2, 2048, 8192, 128, 1), (3, 2731, 4128, 32, 0)))
