@@ -152,10 +152,13 @@ struct LaunchEntropy {
         static ResidentCache cache;
         const uint32_t res = resident_blocks(reinterpret_cast<const void *>(k_entropy<G, BF16, LPT, NG, HIST, APPROX>), 256, cache);
         // Every workgroup adds its histogram to the unit's, and what that costs are the additions that meet on one bin: four
-        // rounds of its lanes per workgroup where that still leaves a workgroup per compute unit (three units of 77700 tiles of 16
-        // channels: 14.1 -> 8.4 us)
-        const uint32_t rounds = nb * NG;
-        const uint32_t few = rounds / 4 > 256u ? rounds / 4 : 256u;
+        // steps per workgroup, or four rounds of its lanes where those make no more than two workgroups per compute unit.  Encode of
+        // bf16 with four rounds for all, and so: [1,4096,8192] G = 16 106 -> 72 us, G = 8 115 -> 84, [3,4672,2560] G = 16
+        // 89.2 -> 63.8, [4,4096,4096] G = 32 83.7 -> 79.8, fp32 [1,5760,5120] G = 8 152 -> 92.  (With four steps for all bf16
+        // [8,360,5120] G = 16 40.2 -> 42.8, [4,3028,2048] G = 32 47.9 -> 51; three units of 77700 tiles of 16 channels: 14.1 us with a
+        // workgroup per round, 8.4 so.)
+        const uint32_t rounds = nb * NG / 4 < 512u ? nb * NG / 4 : 512u;
+        const uint32_t some = nb / 4 > rounds ? nb / 4 : rounds, few = some > 256u ? some : 256u;
         const uint32_t most = HIST && few < res ? few : res;
         const uint32_t grid = nb < most ? nb : most;
         q(k_entropy<G, BF16, LPT, NG, HIST, APPROX>, dim3(grid), dim3(256), d_in, d_H, pivot, T, (nb + grid - 1) / grid, p.eps_l1, p.eps_log,

@@ -78,3 +78,10 @@ def test_a_million_ordinary_tiles_do_not_overwhelm_the_two_launch_selection(tahq
     base = _encode_us(tahq, _normal(1, 4097, 8256)[0], 64, 3.5)
     twice = _encode_us(tahq, _normal(1, 8193, 8256)[0], 64, 3.5)
     assert twice < 3.0 * base
+
+
+def test_one_units_histogram_does_not_hold_up_its_tensor(tahq):
+    # two million tiles of 16 channels, ranked as one unit, whose workgroups all add to one histogram, and as 64 without any
+    x = _normal(64, 64, 8192)[0]
+    base = _encode_us(tahq, x, 16, 3.5)
+    assert _encode_us(tahq, x.reshape(1, 4096, 8192), 16, 3.5) < 1.75 * base         # 1.4 as measured; 2.0 with four times the workgroups
