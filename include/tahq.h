@@ -155,12 +155,12 @@ tahq_status tahq_encode_noalloc(const tahq_config *cfg, const void *d_in,
 /* The encoder's phases, in the order they run.  tahq_encode runs all of them. */
 enum {
     TAHQ_PHASE_PROLOGUE = 1,   /* header, section padding, cleared selection scratch          */
-    TAHQ_PHASE_ENTROPY = 2,    /* Eq. 1-2 and the outlier test, Eq. 3, for every tile (skipped when every
-                                  tile gets one width: the test is part of the quantizer then);
+    TAHQ_PHASE_ENTROPY = 2,    /* Eq. 1-2 for every tile, and for some bf16 tensors the outlier test, Eq. 3, which
+                                  is part of the quantizer otherwise (skipped when every tile gets one width);
                                   clears the bit map words of d_packed that two ranking units share */
     TAHQ_PHASE_SELECT = 4,     /* top-p% selection: bit map and rank table     [Sec. 3.2]; adds to the
                                   words that the entropy phase has cleared                    */
-    TAHQ_PHASE_QUANT = 8,      /* Eq. 4, quantize, pack                        [Sec. 3.3-3.4] */
+    TAHQ_PHASE_QUANT = 8,      /* Eq. 3 (or the entropy phase's), Eq. 4, quantize, pack  [Sec. 3.3-3.4] */
     TAHQ_PHASE_ALL = 15,
     /* Not a phase but an option, OR-ed into `phases`: rank every ranking unit with the general
      * multi-launch selection.  By default one workgroup ranks a unit of up to 32768 tiles (32705 where

@@ -185,6 +185,8 @@ struct LaunchEntropy {
         else if (NG == 1 || T < (hist ? 128u : 1024u) * 256u * NG) with<N::usual, 1>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp);
         else with<N::usual, NG>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp);
     }
+    // Whether exact entropies of T tiles are computed by lanes with whole tiles each, and those with Eq. 3.
+    static bool pivots(uint32_t T) { return kWholeTiles<G, BF16> && !few_tiles<Lanes<G, 2>>(T, 4); }
     // units are whole steps, whatever those are
     static bool can_fuse_histogram(uint64_t n_per_unit)
     {
@@ -198,38 +200,48 @@ struct CanFuse {
     static void run(uint64_t n_per_unit, bool *out) { *out = LaunchEntropy<G, BF16>::can_fuse_histogram(n_per_unit); }
 };
 
+// Where a call's tiles get their widths from: one for all of them, or the stream's bit map, and with that maybe their pivot bytes
+// (bf16 at the usual lanes only: the entropies of fewer tiles come without Eq. 3).
+enum class Widths { one, ranked, ranked_with_pivots };
+
 // `low`: the narrower of the two code widths, 1..7 (3: INT3/INT4).
 template <int G, bool BF16>
 struct LaunchQuantPack {
     template <int LOW, int LPT>
-    static void with(const void *d_in, uint8_t *packed, uint32_t T, float tau, float eps_ratio, bool ranked,
+    static void with(const void *d_in, uint8_t *packed, uint32_t T, float tau, float eps_ratio, Widths widths,
                    uint32_t how, const Prologue &pro, Enqueue *qp)
     {
         Enqueue &q = *qp;
         using B = Batch<G, BF16 ? 2 : 4, LPT>;
         const dim3 grid((T + B::TILES - 1) / B::TILES), block(B::TILES * LPT);
-        if (ranked) q(k_quant_pack<G, BF16, LOW, true, LPT>, grid, block, d_in, packed, T, tau, eps_ratio, how, pro);
-        else q(k_quant_pack<G, BF16, LOW, false, LPT>, grid, block, d_in, packed, T, tau, eps_ratio, how, pro);
+        if constexpr (BF16 && LPT == Lanes<G, 2>::usual) {
+            if (widths == Widths::ranked_with_pivots) {
+                q(k_quant_pack<G, BF16, LOW, true, true, LPT>, grid, block, d_in, packed, T, tau, eps_ratio, how, pro);
+                return;
+            }
+        }
+        if (widths == Widths::one) q(k_quant_pack<G, BF16, LOW, false, false, LPT>, grid, block, d_in, packed, T, tau, eps_ratio, how, pro);
+        else q(k_quant_pack<G, BF16, LOW, true, false, LPT>, grid, block, d_in, packed, T, tau, eps_ratio, how, pro);
     }
     template <int LOW>
-    static void go(const void *d_in, uint8_t *packed, uint32_t T, float tau, float eps_ratio, bool ranked,
+    static void go(const void *d_in, uint8_t *packed, uint32_t T, float tau, float eps_ratio, Widths widths,
                    uint32_t how, const Prologue &pro, Enqueue *qp)
     {
         using N = Lanes<G, BF16 ? 2 : 4>;
-        if (few_tiles<N>(T, 2)) with<LOW, N::few>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp);
-        else with<LOW, N::usual>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp);
+        if (few_tiles<N>(T, 2)) with<LOW, N::few>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp);
+        else with<LOW, N::usual>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp);
     }
     static void run(uint32_t low, const void *d_in, uint8_t *packed, uint32_t T, float tau, float eps_ratio,
-                    bool ranked, uint32_t how, Prologue pro, Enqueue *qp)
+                    Widths widths, uint32_t how, Prologue pro, Enqueue *qp)
     {
         switch (low) {
-        case 1: go<1>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp); break;
-        case 2: go<2>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp); break;
-        case 3: go<3>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp); break;
-        case 4: go<4>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp); break;
-        case 5: go<5>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp); break;
-        case 6: go<6>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp); break;
-        default: go<7>(d_in, packed, T, tau, eps_ratio, ranked, how, pro, qp); break;
+        case 1: go<1>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp); break;
+        case 2: go<2>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp); break;
+        case 3: go<3>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp); break;
+        case 4: go<4>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp); break;
+        case 5: go<5>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp); break;
+        case 6: go<6>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp); break;
+        default: go<7>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp); break;
         }
     }
 };
@@ -275,22 +287,31 @@ struct LaunchAllocEntropy {
         Enqueue &q = *qp;
         constexpr uint32_t SLOTS = (WAVE_TEAM ? 64 : 256) / LPT, TEAMS = WAVE_TEAM ? 4 : 1;
         const uint32_t per = SLOTS / m, nb = (n_alloc + per * TEAMS - 1) / (per * TEAMS);
-        void (*kernel)(const void *, float *, uint8_t *, uint32_t, uint32_t, uint32_t, uint32_t, float, float, uint32_t, float, float, Prologue);
-        if constexpr (LPT == N::usual && WAVE_TEAM) kernel = k_alloc_entropy<G, BF16>;
-        else kernel = k_alloc_entropy_by<G, BF16, LPT, WAVE_TEAM>;
         static ResidentCache cache;
-        const uint32_t res = resident_blocks(reinterpret_cast<const void *>(kernel), 256, cache);
-        const uint32_t grid = nb < res ? nb : res;
-        q(kernel, dim3(grid), dim3(256), d_in, d_H, pivot, n_alloc, grid, m, per, p.eps_l1, p.eps_log,
-          prologue_blocks(pro, 256, grid), p.tau, p.eps_ratio, pro);
+        auto launch = [&](auto kernel, auto... params) {
+            const uint32_t res = resident_blocks(reinterpret_cast<const void *>(kernel), 256, cache);
+            const uint32_t grid = nb < res ? nb : res, pro_blocks = prologue_blocks(pro, 256, grid);
+            if constexpr (sizeof...(params) != 0)
+                q(kernel, dim3(grid), dim3(256), d_in, d_H, pivot, n_alloc, grid, m, per, p.eps_l1, p.eps_log, pro_blocks, params..., pro);
+            else q(kernel, dim3(grid), dim3(256), d_in, d_H, n_alloc, grid, m, per, p.eps_l1, p.eps_log, pro_blocks, pro);
+        };
+        if constexpr (LPT == N::usual && WAVE_TEAM) launch(k_alloc_entropy<G, BF16>, p.tau, p.eps_ratio);
+        else launch(k_alloc_entropy_by<G, BF16, LPT, WAVE_TEAM>);
     }
-    // A wavefront by itself where it wastes no more lanes than a workgroup would.
+    // A wavefront by itself where it wastes no more lanes than a workgroup would: as many allocation tiles per workgroup.
+    template <int LPT>
+    static bool by_wave(uint32_t m) { return 4 * (64 / LPT / m) >= 256 / LPT / m; }
     template <int LPT>
     static void one_pass(const void *d_in, float *d_H, uint8_t *pivot, uint32_t n_alloc, uint32_t m, const EntropyParams &p, const Prologue &pro, Enqueue *qp)
     {
-        const uint32_t by_wave = 4 * (64 / LPT / m), by_group = 256 / LPT / m;       // allocation tiles per workgroup
-        if (by_wave >= by_group) go<LPT, true>(d_in, d_H, pivot, n_alloc, m, p, pro, qp);
+        if (by_wave<LPT>(m)) go<LPT, true>(d_in, d_H, pivot, n_alloc, m, p, pro, qp);
         else go<LPT, false>(d_in, d_H, pivot, n_alloc, m, p, pro, qp);
+    }
+    // Whether it is k_alloc_entropy that a call of T tiles takes, and that with Eq. 3.
+    static bool pivots(uint32_t T, uint32_t m)
+    {
+        const bool few = few_tiles<N>(T, 4) && m <= 256 / N::few;
+        return kWholeTiles<G, BF16> && !few && m <= 256 / N::usual && by_wave<N::usual>(m);
     }
     // Entropies of allocation tiles of m > 1 quantization tiles: one pass if a workgroup's lanes hold whole
     // allocation tiles, otherwise two streaming passes over the tensor.
@@ -304,13 +325,22 @@ struct LaunchAllocEntropy {
         using B = Batch<G, BF16 ? 2 : 4>;
         const uint32_t nb = (T + B::TILES - 1) / B::TILES;
         q(k_tile_partial<G, BF16, false>, dim3(nb), dim3(B::TILES), d_in,
-                           (const float *)nullptr, part, pivot, T, m, p.eps_log, p.tau, p.eps_ratio, prologue_blocks(pro, B::TILES, nb), pro);
+                           (const float *)nullptr, part, T, m, p.eps_log, prologue_blocks(pro, B::TILES, nb), pro);
         q(k_alloc_reduce<false>, dim3(blocks_for(n_alloc)), dim3(256), (const float *)part, (const float *)nullptr,
                            inv_norm, n_alloc, m, p.eps_l1);
         q(k_tile_partial<G, BF16, true>, dim3(nb), dim3(B::TILES), d_in,
-                           (const float *)inv_norm, part, (uint8_t *)nullptr, T, m, p.eps_log, p.tau, p.eps_ratio, 0u, Prologue{});
+                           (const float *)inv_norm, part, T, m, p.eps_log, 0u, Prologue{});
         q(k_alloc_reduce<true>, dim3(blocks_for(n_alloc)), dim3(256), (const float *)part, (const float *)inv_norm,
                            d_H, n_alloc, m, p.eps_l1);
+    }
+};
+
+// Whether the entropies of a call come with Eq. 3.
+template <int G, bool BF16>
+struct EntropyPivots {
+    static void run(uint32_t T, uint32_t m, bool *pivots)
+    {
+        *pivots = m == 1 ? LaunchEntropy<G, BF16>::pivots(T) : LaunchAllocEntropy<G, BF16>::pivots(T, m);
     }
 };
 
@@ -514,6 +544,14 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
     const bool mid_units = select && !wide && !multi_launch && places > kSmallUnitMaxKeys && places <= kMidPlaces && s.U <= 256 &&
                            !approximate_entropies(s, cfg);
     const bool small_units = (select && places <= kSmallUnitMaxKeys && !multi_launch) || mid_units;
+    // Large units are ranked in two launches from a histogram of linear bins that the entropy kernel builds; allocation
+    // tiles, and every unit when the caller forces it, by the multi-launch radix select, whose first digit the entropy
+    // kernel counts where units are whole batches.
+    const bool fused_select = select && !wide && !small_units && !multi_launch;
+    const bool approx = fused_select && approximate_entropies(s, cfg);
+    // Eq. 3 rides in the entropy pass with approximate entropies, and where it is the better place for it with exact ones.
+    bool pivots = approx;
+    if (select && !approx) dispatch<EntropyPivots>(s.G, s.dtype == TAHQ_BF16, (uint32_t)s.T, s.m, &pivots);
 
     // The multi-launch selection puts the unit into the grid's second dimension.  (The two-launch selection does so too, in
     // slices: 65536 units and more of 32706 to 32767 tiles each are a tensor of fewer than 2^31.)
@@ -566,25 +604,21 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
         uint32_t *state = reinterpret_cast<uint32_t *>(wsb + ws.state);
         uint32_t *seg = reinterpret_cast<uint32_t *>(wsb + ws.seg);
         uint8_t *sel = wsb + ws.sel;
-        // Large units are ranked in two launches from a histogram of linear bins that the entropy kernel builds; allocation
-        // tiles, and every unit when the caller forces it, by the multi-launch radix select, whose first digit the entropy
-        // kernel counts where units are whole batches.
-        const bool fused_select = !wide && !small_units && !multi_launch;
-        const bool approx = fused_select && approximate_entropies(s, cfg);
         bool fused = false;
         if (!wide && multi_launch) dispatch<CanFuse>(s.G, s.dtype == TAHQ_BF16, s.n, &fused);
         uint32_t *lin_hist = reinterpret_cast<uint32_t *>(wsb + ws.lin_hist);
         // bins of width ln(A) / kLinBins: the entropy of A channels lies in [0, ln A]
         const float bin_scale = (float)((double)kLinBins / __builtin_log((double)s.A));
+        uint8_t *pivot = pivots ? packed + lay.pivot : nullptr;
         if (phases & TAHQ_PHASE_ENTROPY) {
             if (wide)
                 dispatch<LaunchAllocEntropy>(s.G, s.dtype == TAHQ_BF16, d_in, H, reinterpret_cast<float *>(wsb + ws.part),
-                                             reinterpret_cast<float *>(wsb + ws.inv_norm), packed + lay.pivot, (uint32_t)s.T,
+                                             reinterpret_cast<float *>(wsb + ws.inv_norm), pivot, (uint32_t)s.T,
                                              s.m, entropy_params(cfg), pro, &q);
             else if (fused_select)
-                launch_entropy(s, cfg, d_in, H, packed + lay.pivot, approx, lin_hist, kLinBins, bin_scale, pro, &q);
+                launch_entropy(s, cfg, d_in, H, pivot, approx, lin_hist, kLinBins, bin_scale, pro, &q);
             else
-                launch_entropy(s, cfg, d_in, H, packed + lay.pivot, false, fused ? hist0 : (uint32_t *)nullptr, kDigit0Bins, 0.0f, pro, &q);
+                launch_entropy(s, cfg, d_in, H, pivot, false, fused ? hist0 : (uint32_t *)nullptr, kDigit0Bins, 0.0f, pro, &q);
         }
         if ((phases & TAHQ_PHASE_SELECT) && fused_select) {
             uint32_t *fused_state = reinterpret_cast<uint32_t *>(wsb + ws.fused);
@@ -647,7 +681,8 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
 
     if (phases & TAHQ_PHASE_QUANT) {
         dispatch<LaunchQuantPack>(s.G, s.dtype == TAHQ_BF16, s.low, d_in, packed, (uint32_t)s.T, cfg->tau,
-                                  cfg->eps_ratio, select, (s.kA == s.nA ? QUANT_ALL_WIDE : 0u) | (stream_bytes(s) >= kStreamingFrom ? QUANT_STREAMING : 0u),
+                                  cfg->eps_ratio, !select ? Widths::one : pivots ? Widths::ranked_with_pivots : Widths::ranked,
+                                  (s.kA == s.nA ? QUANT_ALL_WIDE : 0u) | (stream_bytes(s) >= kStreamingFrom ? QUANT_STREAMING : 0u),
                                   pro, &q);
     }
     return q.result();

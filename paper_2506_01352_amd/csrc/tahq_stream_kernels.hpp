@@ -654,6 +654,14 @@ static_assert((1u << kDigit0Bits) == kDigit0Bins, "digit 0 width");
 template <int G, int ESIZE, int LPT>
 constexpr int kRowGroups = 128 / (G * ESIZE / LPT);
 
+// A lane usually holds a whole bf16 tile, in which Eq. 3 is two vector slots per element.  Where it does, the entropy kernels can decide
+// Eq. 3, into the stream's pivot bytes, which takes a barrier out of the quantizer.  With exact entropies both passes are bound by
+// vector issue, and this is what tells them apart: encode of bf16 with Eq. 3 in the entropies, and in the quantizer: [64,64,8192]
+// G = 16 54.5 us and 56.8, G = 32 42.3 and 43.4, [16,1024,1600] G = 64 38.3 and 39.0; of tiles that lanes share: [16,512,8192]
+// G = 128 73.0 and 68.9, [8,1024,4096] 48.6 and 47.4; and of fp32, where it is three or four slots: [8,2048,4096] G = 64 116.5 and 115.5,
+// [6,3000,2048] G = 16 79.9 and 78.3.
+template <int G, bool BF16> constexpr bool kWholeTiles = BF16 && Lanes<G, 2>::usual == 1;
+
 // With exact entropies bound by vector issue (twelve and a half slots per element, ten of them the logarithm) and behind it by HBM.
 // Without barriers, and with the next rows on their way to LDS while the present ones are in registers, bf16 [8,4096,8192]
 // G = 64 108.7 -> 106.1 us, fp32 [4,512,2048] 5.1 -> 4.6.  With approximate ones bound by HBM: 88.8 us against 82 for the loads alone, and
@@ -663,9 +671,9 @@ constexpr int kRowGroups = 128 / (G * ESIZE / LPT);
 // contiguous run of steps.  A step's results are stored one step late, just before the next loads, so that no wait for loads ever
 // has a younger store in front of it.  The wavefronts of a workgroup meet only where the histogram moves to another unit.
 //
-// If `pivot` is given, Eq. 3 is decided here as well: with the approximate entropies this kernel has vector slots to spare behind
-// HBM, and k_quant_pack has not.
 // APPROX: entropies to within kEntropySlack, for a selection that makes up for it.
+// PIVOTS (below): Eq. 3 is decided here as well, if `pivot` is given: of whole tiles, and with approximate entropies of all, since
+// this kernel has vector slots to spare behind HBM then, and k_quant_pack has not.
 //
 // If HIST, the kernel also builds the first histogram of the selection (Sec. 3.2, top-p%): per
 // ranking unit of `unit_tiles` tiles, counts of the keys' top 10 bits (bin_scale == 0) or of the entropies'
@@ -679,6 +687,7 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint8_t *__re
                uint32_t unit_tiles, uint32_t hist_stride, float bin_scale, Prologue pro)
 {
     using W = Wave<G, BF16 ? 2 : 4, LPT>;
+    constexpr bool PIVOTS = APPROX || (kWholeTiles<G, BF16> && LPT == 1);
     constexpr uint32_t WAVE_TILES = W::TILES * NG, STEP_TILES = 4 * WAVE_TILES;
     __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * NG * W::LDS_BYTES];
     static_assert(kLinBins >= kDigit0Bins, "one LDS histogram serves both kinds of bins");
@@ -720,7 +729,9 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint8_t *__re
         for (uint32_t g = 0; g < (uint32_t)NG; ++g) {
             if (part == 0 && mine + g * W::TILES < n_prev) {
                 store_through(H + j_prev + (mine + g * W::TILES), h[g]);
-                if (pivot) store_through(pivot + j_prev + (mine + g * W::TILES), (uint8_t)pv[g]);
+                if constexpr (PIVOTS) {
+                    if (pivot) store_through(pivot + j_prev + (mine + g * W::TILES), (uint8_t)pv[g]);
+                }
             }
         }
     };
@@ -743,8 +754,8 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint8_t *__re
         if (step + 1 < last) request(step + 1);
 #pragma unroll
         for (uint32_t g = 0; g < (uint32_t)NG; ++g) {
-            if (pivot) {
-                pv[g] = pivot_of<W::EPL, BF16, LPT>(x[g].w, part, tau, eps_ratio);
+            if constexpr (PIVOTS) {
+                if (pivot) pv[g] = pivot_of<W::EPL, BF16, LPT>(x[g].w, part, tau, eps_ratio);
                 x[g].forget();
             }
             auto again = [&]() {                 // my row, from memory
@@ -797,12 +808,11 @@ void k_entropy(const void *__restrict__ in, float *__restrict__ H, uint8_t *__re
 //   WEIGHTED = false: part[j] = sum over tile j of |v|
 //   WEIGHTED = true:  part[j] = sum over tile j of |v| log(|v| * r + varsigma), r = inv_norm[j / m] (the common factor r
 //                     of Eq. 2's sum is applied once, by the reduction)
-// One workgroup per batch of tiles, one lane per tile.  If `pivot` is given, the first pass decides Eq. 3 as well.
+// One workgroup per batch of tiles, one lane per tile.
 template <int G, bool BF16, bool WEIGHTED>
 __global__ __launch_bounds__((Batch<G, BF16 ? 2 : 4>::TILES))
 void k_tile_partial(const void *__restrict__ in, const float *__restrict__ inv_norm, float *__restrict__ part,
-                    uint8_t *__restrict__ pivot, uint32_t T, uint32_t m, float eps_log, float tau, float eps_ratio,
-                    uint32_t pro_blocks, Prologue pro)
+                    uint32_t T, uint32_t m, float eps_log, uint32_t pro_blocks, Prologue pro)
 {
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<G, ES>;
@@ -833,10 +843,6 @@ void k_tile_partial(const void *__restrict__ in, const float *__restrict__ inv_n
         }
         part[j] = tree_sum<G>(a);
     }
-    if constexpr (!WEIGHTED) {
-        if (pivot && (uint32_t)tid < nvalid)
-            pivot[j0 + tid] = (uint8_t)pivot_of<G, BF16, 1>(lds + tid * B::STRIDE, 0u, tau, eps_ratio);
-    }
     if (blockIdx.x < pro_blocks) write_prologue(pro, blockIdx.x * B::TILES + threadIdx.x, pro_blocks * B::TILES);
 }
 
@@ -846,11 +852,16 @@ void k_tile_partial(const void *__restrict__ in, const float *__restrict__ inv_n
 // registers and the next rows are on their way.  A wavefront by itself needs no barriers.  (Where a workgroup's first lanes added
 // up for all and the others waited at barriers, [4,2048,4096] A = 4096, G = 64 took 18.7 us, or 20.7 when its workgroups started
 // at once, now 16.6.)
-template <int G, bool BF16, int LPT, bool WAVE_TEAM>
+//
+// PIVOTS: Eq. 3 is decided here as well, if `pivot` is given: by wavefronts by themselves whose lanes hold whole tiles (encode of
+// [4,2048,4096] A = 4096, G = 64: 41.7 us, and 42.5 with Eq. 3 in the quantizer).  Where workgroups meet at barriers or lanes share
+// tiles the quantizer has it: [8,2048,5120] A = 5120, G = 32 106.2 us here, 101.0 there; [4,2048,8192] A = 8192, G = 64
+// 74.8 and 73.5, G = 128 71.1 and 67.5; fp32 [4,2048,4096] A = 4096, G = 64 57.2 and 56.7.
+template <int G, bool BF16, int LPT, bool WAVE_TEAM, bool PIVOTS>
 __device__ __forceinline__
-void alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint8_t *__restrict__ pivot, uint32_t n_alloc,
-                   uint32_t grid, uint32_t m, uint32_t per, float eps_l1, float eps_log, uint32_t pro_blocks, float tau,
-                   float eps_ratio, const Prologue &pro)
+void alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint8_t *__restrict__ pivot, uint32_t n_alloc, uint32_t grid,
+                   uint32_t m, uint32_t per, float eps_l1, float eps_log, float tau, float eps_ratio, uint32_t pro_blocks,
+                   const Prologue &pro)
 {
     using W = Wave<G, BF16 ? 2 : 4, LPT>;
     constexpr uint32_t TEAMS = WAVE_TEAM ? 4 : 1, SLOTS = (WAVE_TEAM ? 64 : 256) / LPT;       // teams per workgroup, tiles per team
@@ -895,9 +906,8 @@ void alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint8_t *
         return acc;
     };
     // Long sums are the work of one wavefront, in which the allocation tile begins, for all of its lanes: m additions in all four took
-    // a third of the vector slots at m = 256 ([4,2048,8192] A = 8192, G = 32: encode 89.5 us, 76.9 so).  (64 elements per lane leave no
-    // registers for it, and at their m = 128 it takes as long.)
-    constexpr bool ONE_WAVE = !WAVE_TEAM && W::EPL <= 32;
+    // a third of the vector slots at m = 256 ([4,2048,8192] A = 8192, G = 32: encode 89.5 us, 76.9 so; G = 64, m = 128: 74.8 and 73.9).
+    constexpr bool ONE_WAVE = !WAVE_TEAM;
     auto sum_up = [&](uint32_t at, uint32_t sums_at) {
         if constexpr (ONE_WAVE) {
             if (m > 64) {
@@ -921,7 +931,10 @@ void alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint8_t *
     auto store = [&]() {
         if (a_prev >= n_alloc) return;
         if (first) store_through(H + a_prev, h);
-        if (pivot && group < per && part == 0) store_through(pivot + ((uint64_t)a_prev * m + (slot - group * m)), (uint8_t)pv);
+        if constexpr (PIVOTS) {
+            if (pivot && group < per && part == 0)
+                store_through(pivot + ((uint64_t)a_prev * m + (slot - group * m)), (uint8_t)pv);
+        }
     };
     for (; a0 < n_alloc; a0 += stride) {
         wait_for_rows();
@@ -932,8 +945,10 @@ void alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint8_t *
         if (a0 + stride < n_alloc) request(a0 + stride);
         meet(parts_at[0], whole_tile<LPT>(magnitude_sum<W::EPL>(x)));
         x.forget();
-        if (pivot) pv = pivot_of<W::EPL, BF16, LPT>(x.w, part, tau, eps_ratio);
-        x.forget();
+        if constexpr (PIVOTS) {
+            if (pivot) pv = pivot_of<W::EPL, BF16, LPT>(x.w, part, tau, eps_ratio);
+            x.forget();
+        }
         const float invL = 1.0f / (sum_up(parts_at[0], sums_of[0]) + eps_l1);
         meet(parts_at[1], whole_tile<LPT>(weighted_sum<W::EPL>(x, invL, eps_log)));
         h = 0.0f - invL * sum_up(parts_at[1], sums_of[1]);
@@ -950,19 +965,17 @@ void k_alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint8_t
                      uint32_t grid, uint32_t m, uint32_t per, float eps_l1, float eps_log, uint32_t pro_blocks, float tau,
                      float eps_ratio, Prologue pro)
 {
-    alloc_entropy<G, BF16, Lanes<G, BF16 ? 2 : 4>::usual, true>(in, H, pivot, n_alloc, grid, m, per, eps_l1, eps_log, pro_blocks,
-                                                                    tau, eps_ratio, pro);
+    alloc_entropy<G, BF16, Lanes<G, BF16 ? 2 : 4>::usual, true, kWholeTiles<G, BF16>>(in, H, pivot, n_alloc, grid, m, per, eps_l1,
+                                                                                       eps_log, tau, eps_ratio, pro_blocks, pro);
 }
 
 // Any others.
 template <int G, bool BF16, int LPT, bool WAVE_TEAM>
 __global__ __launch_bounds__(256, 4)
-void k_alloc_entropy_by(const void *__restrict__ in, float *__restrict__ H, uint8_t *__restrict__ pivot, uint32_t n_alloc,
-                        uint32_t grid, uint32_t m, uint32_t per, float eps_l1, float eps_log, uint32_t pro_blocks, float tau,
-                        float eps_ratio, Prologue pro)
+void k_alloc_entropy_by(const void *__restrict__ in, float *__restrict__ H, uint32_t n_alloc, uint32_t grid, uint32_t m, uint32_t per,
+                        float eps_l1, float eps_log, uint32_t pro_blocks, Prologue pro)
 {
-    alloc_entropy<G, BF16, LPT, WAVE_TEAM>(in, H, pivot, n_alloc, grid, m, per, eps_l1, eps_log, pro_blocks,
-                                                                    tau, eps_ratio, pro);
+    alloc_entropy<G, BF16, LPT, WAVE_TEAM, false>(in, H, nullptr, n_alloc, grid, m, per, eps_l1, eps_log, 0.0f, 0.0f, pro_blocks, pro);
 }
 
 // Left-to-right sum of the m partial sums of every allocation tile.  FINAL = false: the reciprocal norm
@@ -1261,8 +1274,8 @@ __device__ __forceinline__ void store_streaming(U *p, const U &v)
 // How k_quant_pack goes about it.
 enum : uint32_t { QUANT_ALL_WIDE = 1, QUANT_STREAMING = 2 };
 
-// One workgroup per batch of TILES tiles, in two stages.  Stage one: lane i takes tile i's pivot byte, from the entropy pass where
-// tiles were ranked, from Eq. 3 on the spot otherwise, and swaps its pivot in LDS.  The tiles are regrouped by
+// One workgroup per batch of TILES tiles, in two stages.  Stage one: lane i takes tile i's pivot byte, from the entropy pass if
+// PIVOTS, from Eq. 3 on the spot otherwise, and swaps its pivot in LDS.  The tiles are regrouped by
 // class -- (plain | transformed) x (narrow | wide) -- so that in
 // stage two, where lane p takes the p-th tile in class order, most wavefronts hold a single class: the
 // Hadamard butterfly runs only in the wavefronts that hold transformed tiles, and the two packing
@@ -1273,7 +1286,7 @@ enum : uint32_t { QUANT_ALL_WIDE = 1, QUANT_STREAMING = 2 };
 // every tile: with a lane per tile such workgroups had 64 or 128 threads of 200 registers, one or two wavefronts per
 // vector unit, where it takes four to issue at the full rate.  bf16 [8,1024,4096] G = 128 at 3 bits: 28.5 -> 24.2 us, fp32
 // [4,512,2048] G = 64: 8.3 -> 6.7.
-template <int G, bool BF16, int LOW, bool RANKED, int LPT, bool FULL>
+template <int G, bool BF16, int LOW, bool RANKED, bool PIVOTS, int LPT, bool FULL>
 __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, uint8_t *__restrict__ packed, const Sections &lay,
                                                  uint32_t T, float tau, float eps_ratio, uint32_t batch, uint32_t nvalid,
                                                  bool all_wide, bool streaming, uint8_t *lds, uint32_t *info, uint16_t *order, uint32_t *class_count)
@@ -1308,12 +1321,12 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
     }
     const bool valid = FULL || slot < nvalid;
     uint32_t pv = 0;                             // pivot byte of the tile of my slot, in storage order
-    if constexpr (RANKED) {
+    if constexpr (PIVOTS) {
         pv = packed[lay.pivot + j0 + (valid ? slot : 0u)];
     }
     uint32_t b, rel, total4;
     tile_pos<B::TILES, LOW, LPT>(meta, tid, &b, &rel, &total4);
-    if constexpr (!RANKED) {
+    if constexpr (!PIVOTS) {
         store_batch<B, FULL>(v, nvalid, lds, tid);
         __syncthreads();
         if (valid) pv = pivot_of<EPL, BF16, LPT>(lds + slot * B::STRIDE + part * (EPL * ES), part, tau, eps_ratio);
@@ -1325,7 +1338,7 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
         cls = ((pv >> 7) << 1) | (b == WIDE ? 1u : 0u);
     }
     const uint32_t rank_in_wave = class_rank_in_wave<WAVES>(cls, (uint32_t)wave, (uint32_t)lane, class_count);
-    if constexpr (RANKED) store_batch<B, FULL>(v, nvalid, lds, tid);
+    if constexpr (PIVOTS) store_batch<B, FULL>(v, nvalid, lds, tid);
     __syncthreads();
     {
         const uint32_t pos = rank_in_wave + class_group_base<WAVES>(cls, (uint32_t)wave, (uint32_t)lane, class_count);
@@ -1355,7 +1368,7 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
         if (part == 0) {
             reinterpret_cast<uint16_t *>(packed + lay.scale)[j] = (uint16_t)meta16;
             reinterpret_cast<uint16_t *>(packed + lay.zero)[j] = (uint16_t)(meta16 >> 16);
-            if constexpr (!RANKED) packed[lay.pivot + j] = (uint8_t)inf;
+            if constexpr (!PIVOTS) packed[lay.pivot + j] = (uint8_t)inf;
         }
     }
     __syncthreads();
@@ -1382,7 +1395,7 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
 // RANKED: the widths are in the stream's bit map.  Otherwise all tiles have one, and the kernel is the call's only one and
 // writes bit map, rank table and prologue as well.  (A variant of its own: the same as a run-time choice delayed the loads of
 // the ranked case, 126 -> 136 us on bf16 [8,4096,8192].)
-template <int G, bool BF16, int LOW, bool RANKED, int LPT>
+template <int G, bool BF16, int LOW, bool RANKED, bool PIVOTS, int LPT>
 __global__ __launch_bounds__(256, 4)
 void k_quant_pack(const void *__restrict__ in, uint8_t *__restrict__ packed, uint32_t T, float tau, float eps_ratio,
                   uint32_t how, Prologue pro)
@@ -1397,10 +1410,10 @@ void k_quant_pack(const void *__restrict__ in, uint8_t *__restrict__ packed, uin
     const Sections lay(T);
     const uint32_t nfull = T / B::TILES;        // a workgroup per batch; the last one may be ragged
     if (blockIdx.x < nfull)
-        quant_pack_batch<G, BF16, LOW, RANKED, LPT, true>(in, packed, lay, T, tau, eps_ratio, blockIdx.x, B::TILES, (how & QUANT_ALL_WIDE) != 0, (how & QUANT_STREAMING) != 0, lds, info,
+        quant_pack_batch<G, BF16, LOW, RANKED, PIVOTS, LPT, true>(in, packed, lay, T, tau, eps_ratio, blockIdx.x, B::TILES, (how & QUANT_ALL_WIDE) != 0, (how & QUANT_STREAMING) != 0, lds, info,
                                              order, class_count);
     else
-        quant_pack_batch<G, BF16, LOW, RANKED, LPT, false>(in, packed, lay, T, tau, eps_ratio, nfull, T % B::TILES, (how & QUANT_ALL_WIDE) != 0, (how & QUANT_STREAMING) != 0, lds, info,
+        quant_pack_batch<G, BF16, LOW, RANKED, PIVOTS, LPT, false>(in, packed, lay, T, tau, eps_ratio, nfull, T % B::TILES, (how & QUANT_ALL_WIDE) != 0, (how & QUANT_STREAMING) != 0, lds, info,
                                               order, class_count);
     if constexpr (!RANKED) {
         if (blockIdx.x == 0) write_prologue(pro, threadIdx.x, THREADS);      // (nothing but header and padding)

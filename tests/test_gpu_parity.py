@@ -252,6 +252,22 @@ def test_allocation_tiles_of_three_edge_tiles(tahq, G):
     check_case(tahq, workloads.f32_to_bf16_bits(tiles[:n]), n // 3, 1, 3 * G, G, tahq.BF16, 3.5, alloc_tile=3 * G)
 
 
+@pytest.mark.parametrize("G,dtype", ((16, 1), (64, 1), (128, 1), (64, 0)))
+@pytest.mark.parametrize("m", (1, 2, 3, 5, 32, 64, 65, 130))
+def test_outlier_test_in_either_pass(tahq, G, dtype, m):
+    # tile counts on both sides of where tiles get the usual lanes, and allocation tiles that wavefronts and workgroups take:
+    # Eq. 3 is decided with the entropies in some of these calls and in the quantizer in the others
+    rng = np.random.default_rng(G + m)
+    for tiles in (65536 - m, 65536 + 3 * m):
+        S = tiles // m
+        x = rng.standard_normal((1, S, m * G)).astype(np.float32)
+        x[:, :, ::7 * G // 2] *= 9.0
+        x[:, ::5] *= rng.standard_normal((1, -(-S // 5), 1)).astype(np.float32) ** 4
+        xin = workloads.f32_to_bf16_bits(x) if dtype else x
+        _say(f"[case] G={G} dtype {dtype} {S * m} tiles, {m} to an allocation tile")
+        check_case(tahq, xin, 1, S, m * G, G, dtype, 3.4, alloc_tile=m * G)
+
+
 def test_allocation_tile_ties_and_many_small_units(tahq):
     # all-zero tokens give allocation tiles of entropy exactly 0; 300 samples of 3 allocation tiles each
     w, x = workloads.generate(5, batch=2, seq=64)
