@@ -99,8 +99,8 @@ def test_thresholds_in_and_beside_a_crowd_of_nearly_alike_tiles(G, share):
 
 @pytest.mark.parametrize("G", (16, 64))
 def test_values_outside_the_approximation(G):
-    # zero tiles, tokens so small or large that products would leave fp32, elements below the normal numbers, one-hot tiles, and
-    # numbers that are none
+    # zero tiles, tokens so small or large that products would leave fp32, elements below the normal numbers, tokens of five
+    # elements, and numbers that are none
     B, S, C = 1, ELEMENTS // 8192, 8192
     x, g = _normal((B, S, C), 3)
     x[:, ::7] = 0.0

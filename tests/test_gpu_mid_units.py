@@ -90,3 +90,22 @@ def test_entropies_of_all_bits_set(tiles, scope, share):
         T = B * tiles
         chosen = np.unpackbits(a.packed[64:64 + -(-T // 64) * 8].cpu().numpy(), bitorder="little").sum()
         assert int(chosen) == units * tahq.tahq_k_per_unit(cfg)
+
+
+@pytest.mark.parametrize("units", (256, 257))
+def test_units_as_many_as_have_a_compute_unit_each_and_one_more(units):
+    # fp32 units of 33001 tiles: ranked from registers, and in two launches
+    tiles = 33001
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(units)
+    x = torch.randn(units, tiles, G, device="cuda", generator=gen)
+    x[:, ::7] = 0.0
+    cfg = tahq.make_config(units, tiles, G, G, tahq.F32, 3.6)
+    a, b = tahq.Codec(cfg, device="cuda"), tahq.Codec(cfg, device="cuda")
+    for c in (a, b):
+        c.workspace.fill_(0xFF)
+        c.packed.fill_(0xFF)
+    a.encode(x)
+    tahq.tahq_encode_phases(cfg, x, b.packed, b.workspace, tahq.PHASE_ALL | tahq.SELECT_MULTI_LAUNCH)
+    torch.cuda.synchronize()
+    assert torch.equal(a.packed, b.packed), "the two selections differ"

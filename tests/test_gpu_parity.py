@@ -193,15 +193,17 @@ def test_whole_tensor_ranking_scope(tahq):
     check_case(tahq, x, w.batch, w.seq, w.hidden, w.tile, w.dtype, 3.4, scope=1)
 
 
-def test_large_units_with_ties_at_the_threshold(tahq):
-    # Ranking units of 65536 and 49152 tiles take the two-launch selection of large units: a histogram of the
-    # entropies, then an exact ranking of the tiles in the threshold bin only.  (a) two kinds of token, all tiles of a
+@pytest.mark.parametrize("S,S_pool", ((512, 384), (640, 600)))
+def test_large_units_with_ties_at_the_threshold(tahq, S, S_pool):
+    # Ranking units of 65536 and 49152 tiles are ranked by one workgroup, from its registers; units of 81920 and 76800 take the
+    # two-launch selection of large units: a histogram of the entropies, then an exact ranking of the tiles in the threshold
+    # bin only.  (a) two kinds of token, all tiles of a
     # token alike: the threshold bin holds half a unit, more than the candidate list takes, and thousands of equal
     # entropies are split by tile index; (b) a fifth of the tiles share the highest entropy and the budget cuts that
     # group in two: the list holds them all, the tie is resolved by a second selection on the index; (c) random
     # tiles drawn from a pool of 3000, so that a few equal entropies meet at the threshold; (d) whole-tensor ranking.
     rng = np.random.default_rng(21)
-    S, Cc, G = 512, 8192, 64
+    Cc, G = 8192, 64
     pat = rng.standard_normal((2, G)).astype(np.float32)
     pat[1, 5] *= 30.0
     kind = rng.integers(0, 2, size=(2, S))
@@ -217,11 +219,11 @@ def test_large_units_with_ties_at_the_threshold(tahq):
     check_case(tahq, workloads.f32_to_bf16_bits(tiles), 2, S, Cc, G, tahq.BF16, 3.1)
 
     pool = rng.standard_normal((3000, G)).astype(np.float32)
-    xc = pool[rng.integers(0, 3000, size=3 * 384 * (Cc // G))]
+    xc = pool[rng.integers(0, 3000, size=3 * S_pool * (Cc // G))]
     _say("[case] large units, tiles from a pool")
-    check_case(tahq, xc, 3, 384, Cc, G, tahq.F32, 3.4)
+    check_case(tahq, xc, 3, S_pool, Cc, G, tahq.F32, 3.4)
     _say("[case] large units, whole-tensor ranking")
-    check_case(tahq, xc, 3, 384, Cc, G, tahq.F32, 3.6, scope=1)
+    check_case(tahq, xc, 3, S_pool, Cc, G, tahq.F32, 3.6, scope=1)
 
 
 # Sec. 3.2 with allocation tiles of several quantization tiles, up to the whole token (A = C)
@@ -707,10 +709,11 @@ def test_more_lanes_per_tile_up_to_the_tensor_sizes_that_take_fewer(tahq, G, dty
         check_case(tahq, x, 1, T, G, G, dtype, low + 0.4, low_bits=low, tau=2.0)
 
 
-@pytest.mark.parametrize("B,n", [(3, 32706), (2, 32769), (2, 49151), (3, 49153), (2, 65535), (5, 40001)])
+@pytest.mark.parametrize("B,n", [(3, 32706), (2, 32769), (2, 49151), (3, 49153), (2, 65535), (5, 40001),
+                                 (2, 65537), (2, 65599), (3, 81919), (2, 81921), (2, 98305), (5, 70001)])
 @pytest.mark.parametrize("ties", (False, True))
 def test_large_units_off_the_64_tile_boundaries(tahq, B, n, ties):
-    # two-launch selection of units that share bit map words: blocks of 16384 places that a unit fills, overhangs by a few
+    # units of up to 65473 tiles: one workgroup's registers; beyond, the two-launch selection of units that share bit map words: blocks of 16384 places that a unit fills, overhangs by a few
     # places or does not reach; batches of the entropy kernel that hold two units; `ties`: more tiles in the threshold's bin
     # than the candidate list takes
     G = 16
@@ -726,7 +729,7 @@ def test_large_units_off_the_64_tile_boundaries(tahq, B, n, ties):
     check_case(tahq, x16, B, n, G, 8, tahq.BF16, 2.6, low_bits=2)
 
 
-@pytest.mark.parametrize("B,n", [(2, 40001), (1, 131072), (2, 98305)])
+@pytest.mark.parametrize("B,n", [(2, 40001), (1, 131072), (2, 98305), (2, 70001)])
 @pytest.mark.parametrize("spread", (0.05, 0.01, 0.003, 1e-3))
 def test_large_units_of_nearly_equal_tiles(tahq, B, n, spread):
     # entropies within a few bins, a few sub-bins or one sub-bin below ln G: the crowd's way with a short list of candidates, with
@@ -739,7 +742,8 @@ def test_large_units_of_nearly_equal_tiles(tahq, B, n, spread):
         check_case(tahq, x, B, n, G, G, tahq.F32, budget)
 
 
-@pytest.mark.parametrize("n,alike", [(40001, 1024), (40001, 1025), (40001, 2400), (40001, 2600), (300001, 16000), (300001, 19000)])
+@pytest.mark.parametrize("n,alike", [(40001, 1024), (40001, 1025), (40001, 2400), (40001, 2600), (300001, 16000), (300001, 19000),
+                                     (70001, 1024), (70001, 1025), (70001, 2400), (70001, 2600)])
 def test_large_units_with_alike_tiles_at_the_threshold(tahq, n, alike):
     # tiles of one entropy in a bin of their own, or with a one-hot tile and one of a single dominant element beside them: placed
     # from the candidate list one by one or by runs of places, or as a crowd by index alone
@@ -870,13 +874,14 @@ def test_nan_inf_and_huge_inputs_are_lossy_but_never_a_fault(tahq):
         assert np.array_equal(out[n * G:].view(np.uint32), want_out.view(np.uint32))
 
 
-def test_non_finite_entropies_in_large_ranking_units_follow_key_order(tahq):
+@pytest.mark.parametrize("S", (1024, 1280))
+def test_non_finite_entropies_in_large_ranking_units_follow_key_order(tahq, S):
     # NaN and infinite inputs give NaN entropies; the selection orders tiles by their entropies' order-preserving keys,
-    # where a NaN with the sign bit clear sorts above +infinity.  The two-launch selection of large units (bins of
+    # where a NaN with the sign bit clear sorts above +infinity.  The selections of large units (bins of
     # the entropy) and the multi-launch radix select (digits of the key) must agree on such a tensor too; run_gpu
     # compares their streams.  The clean sample is checked against the oracle.
     rng = np.random.default_rng(19)
-    G, S, M = 32, 1024, 64                          # 65536 tiles per sample: above the single-launch limit
+    G, M = 32, 64                                    # 65536 tiles per sample, one workgroup's; 81920: two launches
     x = rng.standard_normal((2, S, M * G)).astype(np.float32)
     clean = x[1:2].copy()
     x[0, 0, 3] = np.nan
@@ -937,8 +942,8 @@ def test_decoding_a_damaged_stream_stays_inside_its_buffers(tahq, G, low):
 
 
 def _large_unit_cases(count, seed):
-    """Ranking units above the single-launch limit that start on 64-tile boundaries (the two-launch selection from the
-    entropy kernel's histogram), with data that crowds or overflows the threshold bin."""
+    """Ranking units of more than 32768 tiles that start on 64-tile boundaries (one workgroup's registers up to 65536, the
+    two-launch selection from the entropy kernel's histogram beyond), with data that crowds or overflows the threshold bin."""
     rng = np.random.default_rng(seed)
     out = []
     while len(out) < count:

@@ -27,10 +27,12 @@ def tahq():
 
 
 CASES = [
-    # (config, shape, budget, samples per run): small ranking units; units of 65536 tiles (two-launch selection);
+    # (config, shape, budget, samples per run): small ranking units; units of 65536 tiles (ranked from registers) and of
+    # 76800 (two-launch selection);
     # fp32 with a run length that does not divide the batch; single-pass encode (budget 4.0)
     (4, dict(batch=6, seq=96), 3.25, 1),
     (4, dict(batch=3, seq=512), 3.4, 1),
+    (4, dict(batch=4, seq=600), 3.4, 1),
     (2, dict(batch=5, seq=40), 3.5, 2),
     (5, dict(batch=4, seq=30), 4.0, 3),
 ]
