@@ -70,8 +70,12 @@ def test_stored_counter_readings_come_from_the_profile_summaries():
     w = workloads.CONFIGS[3]
     size = o32.packed_size(o32.make_cfg(w.batch, w.seq, w.hidden, w.tile, w.dtype, w.budget_bits))
     alg = bench.algorithmic_bytes(w, size, w.elements // w.tile, True)
+    # (beside its entropies k_entropy writes a pivot byte per tile, and adds the histograms of 4096 workgroups, of 2048 counts each at
+    # most, to the units': 4 MB and up to 34 MB of its 554)
+    beside = {"k_entropy": w.elements // w.tile + 4096 * 2048 * 4}
     for kernel in ("k_entropy", "k_quant_pack", "k_decode"):
-        assert abs(per[kernel] / alg[kernel] - 1.0) < 0.02, kernel
+        more = beside.get(kernel, 0) / alg[kernel]
+        assert -0.02 < per[kernel] / alg[kernel] - 1.0 < 0.02 + more, kernel
     assert {"k_select_classify", "k_select_resolve"} <= set(per), sorted(per)
     assert step == sum(per.values()) and step > sum(alg.values())
     naive, _, nsrc = bench.stored_traffic("hbm_traffic_naive_cfg5_bf16_16x2048x5120_b8")
