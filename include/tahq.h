@@ -165,7 +165,8 @@ enum {
     /* Not a phase but an option, OR-ed into `phases`: rank every ranking unit with the general
      * multi-launch selection.  By default one workgroup ranks a unit of up to 32768 tiles (32705 where
      * units are no multiple of 64 tiles) in a single launch, and so it does with up to 65536 tiles
-     * (65473) unless the tensor is bf16 with 2^25 elements or more, or has more than 256 units; larger
+     * (65473) unless the tensor is bf16 with 2^25 elements or more (and eps_l1 in [1e-30, 1e30],
+     * eps_log in [1e-12, 2^-24], as by default), or has more than 256 units; larger
      * units are ranked in two launches from a histogram the entropy phase builds
      * (allocation tiles of several quantization tiles excepted).  Same result; meant for tests and timing.  Pass it with
      * every phase of a call sequence, since the prologue and the entropy phase prepare different

@@ -119,9 +119,11 @@ inline bool few_tiles(uint64_t T, uint32_t deep) { return T * N::usual < 65536u 
 
 // Streams from here on pass the caches by.  Written through them, a large stream is not there any more when the decoder reads it and
 // comes out as dirty lines in the middle of the reads of the next kernels.  bf16 [8,S,8192] on three sets of buffers in turn, encode
-// and decode in us, through the caches and past them: G = 64 at 3.25 bits: 62 MiB 180 and 183, 125 MiB 363 and 341 (encode
-// alone 261 and 234; on one set of buffers, decoded at once on the same card, 338 and 347); at 4 bits: 74 MiB 117 and 120, 149 MiB 238 and 231; G = 128 at 3 bits: 106 MiB 233 and 244; G = 32 at 4 bits: 85 MiB
-// 118 and 123, 170 MiB 242 and 238.
+// and decode in us, through the caches and past them: G = 64 at 3.25 bits: 62 MiB 180 and 183, 125 MiB 363 and 341; at 4 bits:
+// 74 MiB 117 and 120, 149 MiB 238 and 231; G = 128 at 3 bits: 106 MiB 233 and 244; G = 32 at 4 bits: 85 MiB 118 and 123,
+// 170 MiB 242 and 238.  What it trades: the encode of 125 MiB alone takes 234 us instead of 261, and a decode on the same card
+// right after it 120 instead of 97, because the stream is no longer in the Infinity Cache: both on one set of buffers 347
+// instead of 338.  A stream that leaves for another card has the gain alone.
 constexpr uint64_t kStreamingFrom = 112ull << 20;
 
 // What the entropy pass computes by: Eq. 1-2, and Eq. 3 where it decides that as well.
@@ -161,8 +163,8 @@ struct LaunchEntropy {
         const uint32_t some = nb / 4 > rounds ? nb / 4 : rounds, few = some > 256u ? some : 256u;
         const uint32_t most = HIST && few < res ? few : res;
         const uint32_t grid = nb < most ? nb : most;
-        q(k_entropy<G, BF16, LPT, NG, HIST, APPROX>, dim3(grid), dim3(256), d_in, d_H, pivot, T, (nb + grid - 1) / grid, p.eps_l1, p.eps_log,
-          p.tau, p.eps_ratio, prologue_blocks(pro, 256, grid), hist, (uint32_t)n_per_unit, bins, bin_scale, pro);
+        q(k_entropy<G, BF16, LPT, NG, HIST, APPROX>, dim3(grid), dim3(256), d_in, d_H, pivot, T, (nb + grid - 1) / grid, p.eps_l1,
+          p.eps_log, p.tau, p.eps_ratio, prologue_blocks(pro, 256, grid), hist, (uint32_t)n_per_unit, bins, bin_scale, pro);
     }
     template <int LPT, int NG>
     static void with(const void *d_in, float *d_H, uint8_t *pivot, uint32_t T, const EntropyParams &p, uint32_t *hist,
@@ -182,7 +184,8 @@ struct LaunchEntropy {
         using N = Lanes<G, BF16 ? 2 : 4>;
         constexpr int NG = kRowGroups<G, BF16 ? 2 : 4, N::usual>;
         if (few_tiles<N>(T, 4)) with<N::few, 1>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp);
-        else if (NG == 1 || T < (hist ? 128u : 1024u) * 256u * NG) with<N::usual, 1>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp);
+        else if (NG == 1 || T < (hist ? 128u : 1024u) * 256u * NG)
+            with<N::usual, 1>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp);
         else with<N::usual, NG>(d_in, d_H, pivot, T, p, hist, bins, bin_scale, n_per_unit, pro, qp);
     }
     // Whether exact entropies of T tiles are computed by lanes with whole tiles each, and those with Eq. 3.
@@ -282,7 +285,8 @@ template <int G, bool BF16>
 struct LaunchAllocEntropy {
     using N = Lanes<G, BF16 ? 2 : 4>;
     template <int LPT, bool WAVE_TEAM>
-    static void go(const void *d_in, float *d_H, uint8_t *pivot, uint32_t n_alloc, uint32_t m, const EntropyParams &p, const Prologue &pro, Enqueue *qp)
+    static void go(const void *d_in, float *d_H, uint8_t *pivot, uint32_t n_alloc, uint32_t m, const EntropyParams &p,
+                   const Prologue &pro, Enqueue *qp)
     {
         Enqueue &q = *qp;
         constexpr uint32_t SLOTS = (WAVE_TEAM ? 64 : 256) / LPT, TEAMS = WAVE_TEAM ? 4 : 1;
@@ -302,7 +306,8 @@ struct LaunchAllocEntropy {
     template <int LPT>
     static bool by_wave(uint32_t m) { return 4 * (64 / LPT / m) >= 256 / LPT / m; }
     template <int LPT>
-    static void one_pass(const void *d_in, float *d_H, uint8_t *pivot, uint32_t n_alloc, uint32_t m, const EntropyParams &p, const Prologue &pro, Enqueue *qp)
+    static void one_pass(const void *d_in, float *d_H, uint8_t *pivot, uint32_t n_alloc, uint32_t m, const EntropyParams &p,
+                         const Prologue &pro, Enqueue *qp)
     {
         if (by_wave<LPT>(m)) go<LPT, true>(d_in, d_H, pivot, n_alloc, m, p, pro, qp);
         else go<LPT, false>(d_in, d_H, pivot, n_alloc, m, p, pro, qp);
@@ -358,7 +363,8 @@ void launch_entropy(const Shape &s, const tahq_config *cfg, const void *d_in, fl
 template <int G, bool BF16>
 struct LaunchClassify {
     static void run(dim3 grid, float *H, const Shape &s, uint32_t u0, float bin_scale, const uint32_t *lin_hist, uint32_t *fused,
-                    uint2 *cand, uint2 *block_counts, uint32_t *crowd_hist, uint64_t *bitmap, const void *d_in, EntropyParams p, Enqueue *qp)
+                    uint2 *cand, uint2 *block_counts, uint32_t *crowd_hist, uint64_t *bitmap, const void *d_in, EntropyParams p,
+                    Enqueue *qp)
     {
         (*qp)(k_select_classify<G, true, true>, grid, dim3(kFusedThreads), H, (uint32_t)s.n, (uint32_t)s.k, u0, bin_scale, lin_hist, fused,
               cand, block_counts, crowd_hist, bitmap, d_in, p.eps_l1, p.eps_log, kEntropySlack);
@@ -646,7 +652,8 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
             const dim3 grid(s.U, wide ? (uint32_t)((unit_words + kExpandWords - 1) / kExpandWords) : 1u);
             // as little LDS as will do; the largest units leave room for half as many bins
             if (mid_units)
-                q(k_select_mid, grid, dim3(kSmallUnitThreads), (const float *)H, n32, k32, lowest_bin<kMidBins, kMidShift>(s), bitmap, ranks);
+                q(k_select_mid, grid, dim3(kSmallUnitThreads), (const float *)H, n32, k32, lowest_bin<kMidBins, kMidShift>(s), bitmap,
+                  ranks);
             else if (places <= 4096) launch_select_small<4096, 8192, 12>(grid, H, n32, k32, s, bitmap, ranks, &q);
             else if (places <= 16384) launch_select_small<16384, 8192, 12>(grid, H, n32, k32, s, bitmap, ranks, &q);
             else if (places <= 28672) launch_select_small<28672, 8192, 12>(grid, H, n32, k32, s, bitmap, ranks, &q);

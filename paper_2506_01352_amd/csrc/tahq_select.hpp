@@ -10,8 +10,8 @@
 //   * larger units: the entropy kernel also counts the entropies over 2048 linear bins per unit; k_select_classify
 //     settles every tile outside the bin that holds K* and lists the tiles inside it, k_select_resolve ranks that list
 //     (further down in this file);
-//   * larger units of allocation tiles (A > G), and every unit when the caller forces it: three histogram passes (10 + 11 + 11 bits, from the
-//     top; the first one folded into the entropy kernel where units are whole batches) find K* and `take`; then, per
+//   * larger units of allocation tiles (A > G), and every unit when the caller forces it: three histogram passes (10 + 11 + 11
+//     bits, from the top; the first one folded into the entropy kernel where units are whole steps) find K* and `take`; then, per
 //     segment of tiles, counts of keys == K* and > K*, whose prefix sums give every tile its place among the equal keys
 //     (index order) and every 64-tile group its rank-table entry: k_radix_pass x 2, k_seg_count, k_assign.
 //
@@ -861,9 +861,9 @@ __device__ __forceinline__ void put_word(uint64_t *word, uint64_t mask, uint64_t
 // 256 places per wavefront, four places per lane and block.  The bins of the first cut are 1024 floats wide, so that the threshold's
 // seldom holds more of 65536 ordinary tiles than are placed directly (with bins of 4096 a second cut took 5 us).  Against
 // the two-launch selection it saves the launch that clears scratch, one of the selection's two, and the entropy pass its
-// histogram, whose additions meet on the bins of a few units.  Encode of bf16: 34816 tiles of 64 channels 30.7 -> 21.6 us, 40980 31.7 ->
-// 23.3, 65536 32.2 -> 27.6, four units of those 40.7 -> 38.1, 2 x 40960 of 16 channels 25.9 -> 20.7.  81920 tiles took as long as in two launches
-// (33.7 and 33.5), and 77700 of 16 channels longer.
+// histogram, whose additions meet on the bins of a few units.  Encode of bf16: 34816 tiles of 64 channels 30.7 -> 21.6 us, 40980
+// 31.7 -> 23.3, 65536 32.2 -> 27.6, four units of those 40.7 -> 38.1, 2 x 40960 of 16 channels 25.9 -> 20.7.  81920 tiles took
+// as long as in two launches (33.7 and 33.5), and 77700 of 16 channels longer.
 constexpr uint32_t kMidPlaces = 65536, kMidBins = 32768;
 constexpr int kMidShift = 10, kMidBlocks = (int)(kMidPlaces / 256 / (kSmallUnitThreads / 64));
 
@@ -1149,7 +1149,9 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(float *__rest
     const uint32_t in_bin = (uint32_t)__builtin_amdgcn_readfirstlane((int)chosen[2]);
     const bool crowd = in_bin > crowd_from(n);               // (the same for all of the unit's workgroups, like `doubt`)
     bool doubt = false;
-    if constexpr (APPROX) doubt = !crowd && in_bin + (bstar != 0 ? uhist[bstar - 1] : 0u) + (bstar != kLinBins - 1 ? uhist[bstar + 1] : 0u) > kCandCap;
+    if constexpr (APPROX)
+        doubt = !crowd &&
+                in_bin + (bstar != 0 ? uhist[bstar - 1] : 0u) + (bstar != kLinBins - 1 ? uhist[bstar + 1] : 0u) > kCandCap;
     const BinEdges edge(bstar, bin_scale, APPROX ? 2.0f * slack : 0.0f);
     const int first = edge.first, last = edge.last;
 
@@ -1158,12 +1160,14 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_classify(float *__rest
     for (uint32_t r = 0; r < BLOCKS; ++r) {
         const uint32_t base = blockIdx.x * kFusedKeysPerBlock + (r * WAVES + wave) * 256u, p = base + 4u * lane;
         if (base < at.phase || base + 256u > at.end) {
-            // places outside the unit: the bit pattern of -0.0f, the lowest of all and no entropy's
+            // places outside the unit: the bit pattern of -0.0f, the lowest of all and no entropy's, approximate ones included
             q[r].x = p - at.phase < n ? q[r].x : INT32_MIN; q[r].y = p + 1u - at.phase < n ? q[r].y : INT32_MIN;
             q[r].z = p + 2u - at.phase < n ? q[r].z : INT32_MIN; q[r].w = p + 3u - at.phase < n ? q[r].w : INT32_MIN;
         }
-        const uint32_t above = (q[r].x > last ? 1u : 0u) | (q[r].y > last ? 2u : 0u) | (q[r].z > last ? 4u : 0u) | (q[r].w > last ? 8u : 0u);
-        const uint32_t reach = (q[r].x >= first ? 1u : 0u) | (q[r].y >= first ? 2u : 0u) | (q[r].z >= first ? 4u : 0u) | (q[r].w >= first ? 8u : 0u);
+        const uint32_t above =
+            (q[r].x > last ? 1u : 0u) | (q[r].y > last ? 2u : 0u) | (q[r].z > last ? 4u : 0u) | (q[r].w > last ? 8u : 0u);
+        const uint32_t reach =
+            (q[r].x >= first ? 1u : 0u) | (q[r].y >= first ? 2u : 0u) | (q[r].z >= first ? 4u : 0u) | (q[r].w >= first ? 8u : 0u);
         inside = (inside << 4) | (reach & ~above);
         n_above += (uint32_t)__popc(above);
         // eight neighbouring lanes fill a dword of the bit map
@@ -1337,7 +1341,8 @@ __device__ __forceinline__ void rank_candidates(uint32_t rem, uint32_t count, ui
 // A unit whose threshold bin holds more tiles than the candidate list: workgroup `blk` of `blocks`, each of 16384 places.
 // Every workgroup first settles its own tiles: those above the threshold's sub-bin into the bit map, those in it (`crowd`, of which
 // `rem` are selected) into `equal`, words over places that only this unit has; it finds the range of their keys and, where they
-// fit, lists them (in a list of their own: `listed_before` is what k_select_classify has listed).  The last of the unit's workgroups to finish then knows them all.
+// fit, lists them (in a list of their own: `listed_before` is what k_select_classify has listed).  The last of the unit's
+// workgroups to finish then knows them all.
 __device__ __forceinline__ void resolve_crowd(const float *__restrict__ H, uint32_t n, uint32_t k, uint32_t u, uint32_t blk,
                                               uint32_t blocks, float bin_scale, float margin, uint32_t bstar, uint32_t rem,
                                               uint32_t listed_before,

@@ -594,7 +594,8 @@ __device__ __forceinline__ float entropy_of(R &x, float eps_l1, float eps_log)
 //   - The roundings of the sum above: LOG's argument, a product, 7 additions and the factor r, of at most ln 128.
 // (Seen: 2.2e-5.)  A tile whose norm is neither zero nor in the range takes the other way, with its wavefront.
 constexpr float kApproxLogMax = 0x1p-24f, kApproxLogMin = 1e-12f, kApproxNormMin = 0x1p-24f, kApproxNormMax = 0x1p24f;
-constexpr double kApproxError = 0x1p-24 * ((15 * 31 + 15 * 24.6 + 3 * 7) * 0.69315 + 22 * 3.86 + 10 * 4.86) + 1.11e-5 + 128.0 * kApproxLogMax;
+constexpr double kApproxError = 0x1p-24 * ((15 * 31 + 15 * 24.6 + 3 * 7) * 0.69315 + 22 * 3.86 + 10 * 4.86) + 1.11e-5 +
+                                128.0 * kApproxLogMax;
 constexpr float kEntropySlack = 7e-5f;           // (more by far than the rounding of a bin's edge that it is added to twice)
 static_assert(kApproxError + 1e-6 < kEntropySlack, "the selection's candidates rest on it");
 // k_select_classify looks for candidates no further than the two bins beside the threshold's: the narrowest are ln 8 / kLinBins wide.
@@ -880,7 +881,8 @@ void alloc_entropy(const void *__restrict__ in, float *__restrict__ H, uint8_t *
         const uint32_t have = (n_alloc - a0 < per ? n_alloc - a0 : per) * m * LPT;            // rows
         // (a wavefront without rows of its own repeats the team's last one)
         const uint32_t row0 = wave_row < have ? wave_row : have - 1;
-        request_rows<W, 1, false>(static_cast<const uint8_t *>(in) + ((uint64_t)a0 * m * LPT + row0) * W::LANE_BYTES, have - row0, lds, lane);
+        request_rows<W, 1, false>(static_cast<const uint8_t *>(in) + ((uint64_t)a0 * m * LPT + row0) * W::LANE_BYTES, have - row0,
+                                  lds, lane);
     };
     const uint32_t parts_at[2] = {lds_address(parts[0]), lds_address(parts[1])};
     const uint32_t sums_of[2] = {lds_address(sums[0]), lds_address(sums[1])};
@@ -1289,7 +1291,8 @@ enum : uint32_t { QUANT_ALL_WIDE = 1, QUANT_STREAMING = 2 };
 template <int G, bool BF16, int LOW, bool RANKED, bool PIVOTS, int LPT, bool FULL>
 __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, uint8_t *__restrict__ packed, const Sections &lay,
                                                  uint32_t T, float tau, float eps_ratio, uint32_t batch, uint32_t nvalid,
-                                                 bool all_wide, bool streaming, uint8_t *lds, uint32_t *info, uint16_t *order, uint32_t *class_count)
+                                                 bool all_wide, bool streaming, uint8_t *lds, uint32_t *info, uint16_t *order,
+                                                 uint32_t *class_count)
 {
     constexpr int ES = BF16 ? 2 : 4;
     using B = Batch<G, ES, LPT>;
@@ -1410,11 +1413,13 @@ void k_quant_pack(const void *__restrict__ in, uint8_t *__restrict__ packed, uin
     const Sections lay(T);
     const uint32_t nfull = T / B::TILES;        // a workgroup per batch; the last one may be ragged
     if (blockIdx.x < nfull)
-        quant_pack_batch<G, BF16, LOW, RANKED, PIVOTS, LPT, true>(in, packed, lay, T, tau, eps_ratio, blockIdx.x, B::TILES, (how & QUANT_ALL_WIDE) != 0, (how & QUANT_STREAMING) != 0, lds, info,
-                                             order, class_count);
+        quant_pack_batch<G, BF16, LOW, RANKED, PIVOTS, LPT, true>(in, packed, lay, T, tau, eps_ratio, blockIdx.x, B::TILES,
+                                                                  (how & QUANT_ALL_WIDE) != 0, (how & QUANT_STREAMING) != 0, lds,
+                                                                  info, order, class_count);
     else
-        quant_pack_batch<G, BF16, LOW, RANKED, PIVOTS, LPT, false>(in, packed, lay, T, tau, eps_ratio, nfull, T % B::TILES, (how & QUANT_ALL_WIDE) != 0, (how & QUANT_STREAMING) != 0, lds, info,
-                                              order, class_count);
+        quant_pack_batch<G, BF16, LOW, RANKED, PIVOTS, LPT, false>(in, packed, lay, T, tau, eps_ratio, nfull, T % B::TILES,
+                                                                   (how & QUANT_ALL_WIDE) != 0, (how & QUANT_STREAMING) != 0, lds,
+                                                                   info, order, class_count);
     if constexpr (!RANKED) {
         if (blockIdx.x == 0) write_prologue(pro, threadIdx.x, THREADS);      // (nothing but header and padding)
     }
