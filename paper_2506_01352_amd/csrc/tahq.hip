@@ -18,6 +18,7 @@
 #include "tahq_common.hpp"
 #include "tahq_select.hpp"
 #include "tahq_stream_kernels.hpp"
+#include "tahq_rank_quant.hpp"
 #include "tahq_naive_kernels.hpp"
 #include "tahq_naive.h"
 
@@ -247,6 +248,45 @@ struct LaunchQuantPack {
         default: go<7>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp); break;
         }
     }
+};
+
+// Places per workgroup of k_rank_quant for U units of up to `places` places: as few as keep its workgroups, each of which fills a
+// compute unit, to one round of the 256, so that as many of them work as can; 0 if that takes more than a workgroup holds.  (In a
+// second round everything would be ranked once more: 7 us, for the 3 that a launch less gives.)
+template <int G, bool BF16>
+struct LaunchRankQuant {
+    static constexpr uint32_t most = kCrewThreads / Lanes<G, BF16 ? 2 : 4>::few;
+    static void batch_for(uint64_t places, uint32_t U, uint32_t *batch)
+    {
+        *batch = 0;
+        for (uint32_t b = 64; b <= most; b += 64)
+            if ((uint64_t)U * ((places + b - 1) / b) <= 256) { *batch = b; return; }
+    }
+    template <int LOW>
+    static void go(const float *H, const void *d_in, uint8_t *packed, const Shape &s, uint64_t places, uint32_t batch, int bin0,
+                   float tau, float eps_ratio, Enqueue *qp)
+    {
+        (*qp)(k_rank_quant<G, BF16, LOW>, dim3((uint32_t)((places + batch - 1) / batch), s.U), dim3(kCrewThreads), H, d_in, packed,
+              (uint32_t)s.T, (uint32_t)s.n, (uint32_t)s.k, batch, bin0, tau, eps_ratio);
+    }
+    static void run(const float *H, const void *d_in, uint8_t *packed, const Shape &s, uint64_t places, uint32_t batch, int bin0,
+                    float tau, float eps_ratio, Enqueue *qp)
+    {
+        switch (s.low) {
+        case 1: go<1>(H, d_in, packed, s, places, batch, bin0, tau, eps_ratio, qp); break;
+        case 2: go<2>(H, d_in, packed, s, places, batch, bin0, tau, eps_ratio, qp); break;
+        case 3: go<3>(H, d_in, packed, s, places, batch, bin0, tau, eps_ratio, qp); break;
+        case 4: go<4>(H, d_in, packed, s, places, batch, bin0, tau, eps_ratio, qp); break;
+        case 5: go<5>(H, d_in, packed, s, places, batch, bin0, tau, eps_ratio, qp); break;
+        case 6: go<6>(H, d_in, packed, s, places, batch, bin0, tau, eps_ratio, qp); break;
+        default: go<7>(H, d_in, packed, s, places, batch, bin0, tau, eps_ratio, qp); break;
+        }
+    }
+};
+
+template <int G, bool BF16>
+struct RankQuantBatch {
+    static void run(uint64_t places, uint32_t U, uint32_t *batch) { LaunchRankQuant<G, BF16>::batch_for(places, U, batch); }
 };
 
 template <int G, bool BF16>
@@ -555,9 +595,14 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
     // kernel counts where units are whole batches.
     const bool fused_select = select && !wide && !small_units && !multi_launch;
     const bool approx = fused_select && approximate_entropies(s, cfg);
+    // Tensors of one round of workgroups are ranked where they are quantized, unless the caller has the phases apart.
+    uint32_t batch = 0;
+    if (small_units && !wide && places <= kCrewPlaces && (phases & (uint32_t)TAHQ_PHASE_SELECT) && (phases & (uint32_t)TAHQ_PHASE_QUANT))
+        dispatch<RankQuantBatch>(s.G, s.dtype == TAHQ_BF16, places, s.U, &batch);
+    const bool ranked_in_quant = batch != 0;
     // Eq. 3 rides in the entropy pass with approximate entropies, and where it is the better place for it with exact ones.
     bool pivots = approx;
-    if (select && !approx) dispatch<EntropyPivots>(s.G, s.dtype == TAHQ_BF16, (uint32_t)s.T, s.m, &pivots);
+    if (select && !approx && !ranked_in_quant) dispatch<EntropyPivots>(s.G, s.dtype == TAHQ_BF16, (uint32_t)s.T, s.m, &pivots);
 
     // The multi-launch selection puts the unit into the grid's second dimension.  (The two-launch selection does so too, in
     // slices: 65536 units and more of 32706 to 32767 tiles each are a tensor of fewer than 2^31.)
@@ -644,8 +689,10 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
                                    fused_state, cand, (const uint2 *)block_counts, (const uint32_t *)hist0,
                                    reinterpret_cast<uint64_t *>(sel), bitmap, ranks);
             }
-        } else
-        if ((phases & TAHQ_PHASE_SELECT) && small_units) {
+        } else if (ranked_in_quant) {
+            dispatch<LaunchRankQuant>(s.G, s.dtype == TAHQ_BF16, (const float *)H, d_in, packed, s, places, batch,
+                                      lowest_bin<kCrewBins, kCrewShift>(s), cfg->tau, cfg->eps_ratio, &q);
+        } else if ((phases & TAHQ_PHASE_SELECT) && small_units) {
             const uint32_t n32 = (uint32_t)s.nA, k32 = (uint32_t)s.kA;
             // with A > G every workgroup expands a part of the unit's bit map (a unit may start inside a word)
             const uint64_t unit_words = s.n / 64 + 2;
@@ -686,7 +733,7 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
                            s.kA == s.nA ? 1 : 0, bitmap, ranks);
     }
 
-    if (phases & TAHQ_PHASE_QUANT) {
+    if ((phases & TAHQ_PHASE_QUANT) && !ranked_in_quant) {
         dispatch<LaunchQuantPack>(s.G, s.dtype == TAHQ_BF16, s.low, d_in, packed, (uint32_t)s.T, cfg->tau,
                                   cfg->eps_ratio, !select ? Widths::one : pivots ? Widths::ranked_with_pivots : Widths::ranked,
                                   (s.kA == s.nA ? QUANT_ALL_WIDE : 0u) | (stream_bytes(s) >= kStreamingFrom ? QUANT_STREAMING : 0u),

@@ -1180,12 +1180,11 @@ __device__ __forceinline__ void place_codes(const uint32_t *q, uint32_t *dw)
     }
 }
 
-// Step 2: range and quantizer parameters of the tile, codes of my G elements of it, and their LSB-first bit string written
-// as b units at `dst` (LDS); b is LOW or LOW + 1.  Returns scale | zero << 16.
-template <int G, int LOW, int LPT>
-__device__ __forceinline__ uint32_t quantize_values(const float *x, uint32_t b, typename Unit<G>::type *dst)
+// The range of a tile of LPT parts, of which I have G elements.
+struct TileRange { float mn, mx; };
+template <int G, int LPT>
+__device__ __forceinline__ TileRange tile_range(const float *x)
 {
-    constexpr uint32_t WIDE = LOW + 1;
     float mn = fmin3(x[0], x[1], x[2]), mx = fmax3(x[0], x[1], x[2]);
 #pragma unroll
     for (int k = 3; k + 1 < G; k += 2) { mn = fmin3(mn, x[k], x[k + 1]); mx = fmax3(mx, x[k], x[k + 1]); }
@@ -1193,8 +1192,16 @@ __device__ __forceinline__ uint32_t quantize_values(const float *x, uint32_t b, 
     mx = __builtin_fmaxf(mx, x[G - 1]);
     if constexpr (LPT >= 2) { mn = __builtin_fminf(mn, lane_xor<1>(mn)); mx = __builtin_fmaxf(mx, lane_xor<1>(mx)); }
     if constexpr (LPT >= 4) { mn = __builtin_fminf(mn, lane_xor<2>(mn)); mx = __builtin_fmaxf(mx, lane_xor<2>(mx)); }
-    mn = mn + 0.0f;
-    mx = mx + 0.0f;
+    return {mn + 0.0f, mx + 0.0f};
+}
+
+// Step 2: quantizer parameters of the tile from its range, codes of my G elements of it, and their LSB-first bit string written
+// as b units at `dst` (LDS); b is LOW or LOW + 1.  Returns scale | zero << 16.
+template <int G, int LOW>
+__device__ __forceinline__ uint32_t quantize_values(const float *x, const TileRange &range, uint32_t b, typename Unit<G>::type *dst)
+{
+    constexpr uint32_t WIDE = LOW + 1;
+    const float mn = range.mn, mx = range.mx;
 
     // asymmetric quantizer, binary16 metadata rounded outwards
     const float Lv = (b == WIDE) ? (float)((1u << WIDE) - 1u) : (float)((1u << LOW) - 1u);
@@ -1365,8 +1372,8 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
     if (valid) {
         // (a part's share of the payload is b units of EPL/8 bytes)
         const uint32_t width = (inf & 0x100u) ? WIDE : (uint32_t)LOW;
-        const uint32_t meta16 = quantize_values<EPL, LOW, LPT>(
-            x, width, reinterpret_cast<typename Unit<EPL>::type *>(pay + (inf >> 9)) + part * width);
+        const uint32_t meta16 = quantize_values<EPL, LOW>(
+            x, tile_range<EPL, LPT>(x), width, reinterpret_cast<typename Unit<EPL>::type *>(pay + (inf >> 9)) + part * width);
         const uint64_t j = j0 + t;
         if (part == 0) {
             reinterpret_cast<uint16_t *>(packed + lay.scale)[j] = (uint16_t)meta16;
