@@ -1,10 +1,11 @@
-"""Compile csrc/tahq.hip into libtahq.so (gfx950) next to this file."""
+"""Compile csrc/*.hip into libtahq.so (gfx950) next to this file."""
 import os
 import subprocess
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SRC = os.path.join(HERE, "csrc", "tahq.hip")
+SOURCES = [os.path.join(HERE, "csrc", name) for name in ("tahq.hip", "tahq_rank_quant.hip")]
 LIB = os.path.join(HERE, "libtahq.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -13,7 +14,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # packed-fp32-ops is switched off for the device pass (the host pass warns that it does not know the feature).
 # amdgpu-kernarg-preload-count: the first words of a kernel's arguments are in scalar registers when its wavefronts start.
 FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-ffp-contract=off", "-fno-fast-math",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-mllvm", "-amdgpu-kernarg-preload-count=16",
@@ -23,9 +24,16 @@ FLAGS = [
 
 
 def build(force=True):
-    if not force and os.path.exists(LIB) and os.path.getmtime(LIB) >= os.path.getmtime(SRC):
+    if not force and os.path.exists(LIB) and os.path.getmtime(LIB) >= max(os.path.getmtime(src) for src in SOURCES):
         return LIB
-    subprocess.run([HIPCC] + FLAGS + [SRC, "-o", LIB], check=True)
+    # a compiler for each source, side by side
+    with tempfile.TemporaryDirectory() as tmp:
+        objects = [os.path.join(tmp, os.path.basename(src) + ".o") for src in SOURCES]
+        running = [subprocess.Popen([HIPCC] + FLAGS + ["-c", src, "-o", obj]) for src, obj in zip(SOURCES, objects)]
+        codes = [p.wait() for p in running]
+        if any(codes):
+            raise subprocess.CalledProcessError(max(codes), HIPCC)
+        subprocess.run([HIPCC, "--offload-arch=gfx950", "-fPIC", "-shared"] + objects + ["-o", LIB], check=True)
     return LIB
 
 

@@ -18,14 +18,12 @@
 #include "tahq_common.hpp"
 #include "tahq_select.hpp"
 #include "tahq_stream_kernels.hpp"
-#include "tahq_rank_quant.hpp"
+#include "tahq_launch.hpp"
 #include "tahq_naive_kernels.hpp"
 #include "tahq_naive.h"
 
 #include <atomic>
 #include <mutex>
-#include <tuple>
-#include <utility>
 
 using namespace tahq;
 
@@ -48,42 +46,6 @@ inline bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) &
 constexpr uint32_t kMaxGridY = 65535;
 
 inline uint32_t blocks_for(uint64_t threads) { return (uint32_t)((threads + 255) / 256); }
-
-// Dispatch on the tile width G and on a dtype flag (bf16 or not) to a functor template.
-template <template <int, bool> class F, typename... Args>
-inline void dispatch(uint32_t G, bool bf16, Args... args)
-{
-    if (G == 8) { if (bf16) F<8, true>::run(args...); else F<8, false>::run(args...); }
-    else if (G == 16) { if (bf16) F<16, true>::run(args...); else F<16, false>::run(args...); }
-    else if (G == 32) { if (bf16) F<32, true>::run(args...); else F<32, false>::run(args...); }
-    else if (G == 64) { if (bf16) F<64, true>::run(args...); else F<64, false>::run(args...); }
-    else { if (bf16) F<128, true>::run(args...); else F<128, false>::run(args...); }
-}
-
-// Kernel launches of one call: each launch returns its own status (the thread's sticky "last error", which may
-// belong to the caller's earlier work, is neither read nor cleared), and after a failure nothing more is enqueued.
-struct Enqueue {
-    hipStream_t stream;
-    hipError_t status = hipSuccess;
-
-    template <typename... P, typename... A>
-    void operator()(void (*kernel)(P...), dim3 grid, dim3 block, A... args)
-    {
-        static_assert(sizeof...(P) == sizeof...(A), "one argument per kernel parameter");
-        if (status != hipSuccess) return;
-        std::tuple<P...> values(static_cast<P>(args)...);
-        status = launch(kernel, grid, block, values, std::index_sequence_for<P...>{});
-    }
-    tahq_status result() const { return status == hipSuccess ? TAHQ_OK : TAHQ_ERR_HIP; }
-
-private:
-    template <typename... P, size_t... I>
-    hipError_t launch(void (*kernel)(P...), dim3 grid, dim3 block, std::tuple<P...> &values, std::index_sequence<I...>)
-    {
-        void *ptrs[] = {static_cast<void *>(&std::get<I>(values))...};
-        return hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, ptrs, 0, stream);
-    }
-};
 
 // Grid of a persistent kernel: four times the workgroups that fit on the device at once (or fewer, if there
 // are fewer batches).  Every workgroup still pipelines a few batches, and the hardware dispatcher evens
@@ -109,14 +71,6 @@ inline uint32_t resident_blocks(const void *kernel, int threads, ResidentCache &
     if (cached) cache.per_device[dev].store(res, std::memory_order_relaxed);
     return res;
 }
-
-// Fewer wavefronts than the chip has vector units (256 compute units of four), at the usual number of lanes per tile: the launch
-// takes as long as one lane does, and tiles are spread over more lanes, as long as those make no more wavefronts per vector
-// unit than `deep`: 4, all that run at once, or 2 in the quantizer, which has more to do once per lane.  Above that the usual
-// lanes have less to issue.  bf16, G = 64, usual -> few: 25600 tiles: entropies 4.2 -> 3.1 us, quantizer 5.6 -> 4.4, decoder
-// 4.5 -> 3.6; 51200: 4.3 -> 3.9, 5.7 -> 5.8, 4.7 -> 4.2; 64512: 4.4 -> 4.0, 5.8 -> 6.0, 4.8 -> 4.4.
-template <class N>
-inline bool few_tiles(uint64_t T, uint32_t deep) { return T * N::usual < 65536u && T * N::few < deep * 65536u; }
 
 // Streams from here on pass the caches by.  Written through them, a large stream is not there any more when the decoder reads it and
 // comes out as dirty lines in the middle of the reads of the next kernels.  bf16 [8,S,8192] on three sets of buffers in turn, encode
@@ -229,64 +183,27 @@ struct LaunchQuantPack {
     }
     template <int LOW>
     static void go(const void *d_in, uint8_t *packed, uint32_t T, float tau, float eps_ratio, Widths widths,
-                   uint32_t how, const Prologue &pro, Enqueue *qp)
+                   uint32_t how, const CrewPlan &crew, const Prologue &pro, Enqueue *qp)
     {
         using N = Lanes<G, BF16 ? 2 : 4>;
-        if (few_tiles<N>(T, 2)) with<LOW, N::few>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp);
+        // (the tensors that k_rank_quant takes are quantized by as many lanes per tile when the phases are apart)
+        if (crew.batch != 0 ? crew.few : few_tiles<N>(T, 2)) with<LOW, N::few>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp);
+        else if (crew.batch != 0) with<LOW, kCrewHalf<G, BF16>>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp);
         else with<LOW, N::usual>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp);
     }
     static void run(uint32_t low, const void *d_in, uint8_t *packed, uint32_t T, float tau, float eps_ratio,
-                    Widths widths, uint32_t how, Prologue pro, Enqueue *qp)
+                    Widths widths, uint32_t how, CrewPlan crew, Prologue pro, Enqueue *qp)
     {
         switch (low) {
-        case 1: go<1>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp); break;
-        case 2: go<2>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp); break;
-        case 3: go<3>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp); break;
-        case 4: go<4>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp); break;
-        case 5: go<5>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp); break;
-        case 6: go<6>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp); break;
-        default: go<7>(d_in, packed, T, tau, eps_ratio, widths, how, pro, qp); break;
+        case 1: go<1>(d_in, packed, T, tau, eps_ratio, widths, how, crew, pro, qp); break;
+        case 2: go<2>(d_in, packed, T, tau, eps_ratio, widths, how, crew, pro, qp); break;
+        case 3: go<3>(d_in, packed, T, tau, eps_ratio, widths, how, crew, pro, qp); break;
+        case 4: go<4>(d_in, packed, T, tau, eps_ratio, widths, how, crew, pro, qp); break;
+        case 5: go<5>(d_in, packed, T, tau, eps_ratio, widths, how, crew, pro, qp); break;
+        case 6: go<6>(d_in, packed, T, tau, eps_ratio, widths, how, crew, pro, qp); break;
+        default: go<7>(d_in, packed, T, tau, eps_ratio, widths, how, crew, pro, qp); break;
         }
     }
-};
-
-// Places per workgroup of k_rank_quant for U units of up to `places` places: as few as keep its workgroups, each of which fills a
-// compute unit, to one round of the 256, so that as many of them work as can; 0 if that takes more than a workgroup holds.  (In a
-// second round everything would be ranked once more: 7 us, for the 3 that a launch less gives.)
-template <int G, bool BF16>
-struct LaunchRankQuant {
-    static constexpr uint32_t most = kCrewThreads / Lanes<G, BF16 ? 2 : 4>::few;
-    static void batch_for(uint64_t places, uint32_t U, uint32_t *batch)
-    {
-        *batch = 0;
-        for (uint32_t b = 64; b <= most; b += 64)
-            if ((uint64_t)U * ((places + b - 1) / b) <= 256) { *batch = b; return; }
-    }
-    template <int LOW>
-    static void go(const float *H, const void *d_in, uint8_t *packed, const Shape &s, uint64_t places, uint32_t batch, int bin0,
-                   float tau, float eps_ratio, Enqueue *qp)
-    {
-        (*qp)(k_rank_quant<G, BF16, LOW>, dim3((uint32_t)((places + batch - 1) / batch), s.U), dim3(kCrewThreads), H, d_in, packed,
-              (uint32_t)s.T, (uint32_t)s.n, (uint32_t)s.k, batch, bin0, tau, eps_ratio);
-    }
-    static void run(const float *H, const void *d_in, uint8_t *packed, const Shape &s, uint64_t places, uint32_t batch, int bin0,
-                    float tau, float eps_ratio, Enqueue *qp)
-    {
-        switch (s.low) {
-        case 1: go<1>(H, d_in, packed, s, places, batch, bin0, tau, eps_ratio, qp); break;
-        case 2: go<2>(H, d_in, packed, s, places, batch, bin0, tau, eps_ratio, qp); break;
-        case 3: go<3>(H, d_in, packed, s, places, batch, bin0, tau, eps_ratio, qp); break;
-        case 4: go<4>(H, d_in, packed, s, places, batch, bin0, tau, eps_ratio, qp); break;
-        case 5: go<5>(H, d_in, packed, s, places, batch, bin0, tau, eps_ratio, qp); break;
-        case 6: go<6>(H, d_in, packed, s, places, batch, bin0, tau, eps_ratio, qp); break;
-        default: go<7>(H, d_in, packed, s, places, batch, bin0, tau, eps_ratio, qp); break;
-        }
-    }
-};
-
-template <int G, bool BF16>
-struct RankQuantBatch {
-    static void run(uint64_t places, uint32_t U, uint32_t *batch) { LaunchRankQuant<G, BF16>::batch_for(places, U, batch); }
 };
 
 template <int G, bool BF16>
@@ -410,16 +327,6 @@ struct LaunchClassify {
               cand, block_counts, crowd_hist, bitmap, d_in, p.eps_l1, p.eps_log, kEntropySlack);
     }
 };
-
-// k_select_small's and k_select_mid's lowest bin: the topmost bin but one holds ln A, the largest an entropy can be
-template <uint32_t BINS, int SHIFT>
-int lowest_bin(const Shape &s)
-{
-    const float ln_a = (float)__builtin_log((double)s.A);
-    int bits;
-    memcpy(&bits, &ln_a, 4);
-    return (bits >> SHIFT) - (int)(BINS - 2);
-}
 
 template <uint32_t PLACES, uint32_t BINS, int SHIFT>
 void launch_select_small(dim3 grid, const float *H, uint32_t n, uint32_t k, const Shape &s, uint64_t *bitmap, uint32_t *ranks,
@@ -583,26 +490,26 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
     uint32_t *ranks = reinterpret_cast<uint32_t *>(packed + lay.ranks);
     const bool select = s.kA != 0 && s.kA != s.nA;
     const bool wide = s.m > 1;     // allocation tiles of several quantization tiles
-    // ranking units that one workgroup can hold are ranked in a single launch
+    // Tensors of one round of workgroups are ranked where they are quantized, unless the caller has the phases apart.
     const uint64_t places = s.nA + (!wide && s.n % 64 != 0 ? 63u : 0u);       // counted from a 64-tile boundary
-    // ... from LDS or from registers.  (Not where the two-launch selection's approximate entropies save more: [16,1024,4096] 77.8 us
+    CrewPlan crew = {0, false, false};
+    if (select && !wide && !approximate_entropies(s, cfg))
+        crew = plan_rank_quant(s, places);
+    constexpr uint32_t together = TAHQ_PHASE_ENTROPY | TAHQ_PHASE_SELECT | TAHQ_PHASE_QUANT;
+    const bool ranked_in_quant = crew.batch != 0 && !multi_launch && (phases & together) == together;
+    // Otherwise ranking units that one workgroup can hold are ranked in a single launch, from LDS or from registers.  (Not where the two-launch selection's approximate entropies save more: [16,1024,4096] 77.8 us
     // so, 80.5 with exact ones; and as long as every unit has a compute unit.)
     const bool mid_units = select && !wide && !multi_launch && places > kSmallUnitMaxKeys && places <= kMidPlaces && s.U <= 256 &&
                            !approximate_entropies(s, cfg);
-    const bool small_units = (select && places <= kSmallUnitMaxKeys && !multi_launch) || mid_units;
+    const bool small_units = (select && places <= kSmallUnitMaxKeys && !multi_launch) || mid_units || ranked_in_quant;
     // Large units are ranked in two launches from a histogram of linear bins that the entropy kernel builds; allocation
     // tiles, and every unit when the caller forces it, by the multi-launch radix select, whose first digit the entropy
     // kernel counts where units are whole batches.
     const bool fused_select = select && !wide && !small_units && !multi_launch;
     const bool approx = fused_select && approximate_entropies(s, cfg);
-    // Tensors of one round of workgroups are ranked where they are quantized, unless the caller has the phases apart.
-    uint32_t batch = 0;
-    if (small_units && !wide && places <= kCrewPlaces && (phases & (uint32_t)TAHQ_PHASE_SELECT) && (phases & (uint32_t)TAHQ_PHASE_QUANT))
-        dispatch<RankQuantBatch>(s.G, s.dtype == TAHQ_BF16, places, s.U, &batch);
-    const bool ranked_in_quant = batch != 0;
     // Eq. 3 rides in the entropy pass with approximate entropies, and where it is the better place for it with exact ones.
     bool pivots = approx;
-    if (select && !approx && !ranked_in_quant) dispatch<EntropyPivots>(s.G, s.dtype == TAHQ_BF16, (uint32_t)s.T, s.m, &pivots);
+    if (select && !approx && crew.batch == 0) dispatch<EntropyPivots>(s.G, s.dtype == TAHQ_BF16, (uint32_t)s.T, s.m, &pivots);
 
     // The multi-launch selection puts the unit into the grid's second dimension.  (The two-launch selection does so too, in
     // slices: 65536 units and more of 32706 to 32767 tiles each are a tensor of fewer than 2^31.)
@@ -690,8 +597,7 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
                                    reinterpret_cast<uint64_t *>(sel), bitmap, ranks);
             }
         } else if (ranked_in_quant) {
-            dispatch<LaunchRankQuant>(s.G, s.dtype == TAHQ_BF16, (const float *)H, d_in, packed, s, places, batch,
-                                      lowest_bin<kCrewBins, kCrewShift>(s), cfg->tau, cfg->eps_ratio, &q);
+            launch_rank_quant(H, d_in, packed, s, places, crew, cfg->tau, cfg->eps_ratio, &q);
         } else if ((phases & TAHQ_PHASE_SELECT) && small_units) {
             const uint32_t n32 = (uint32_t)s.nA, k32 = (uint32_t)s.kA;
             // with A > G every workgroup expands a part of the unit's bit map (a unit may start inside a word)
@@ -737,7 +643,7 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
         dispatch<LaunchQuantPack>(s.G, s.dtype == TAHQ_BF16, s.low, d_in, packed, (uint32_t)s.T, cfg->tau,
                                   cfg->eps_ratio, !select ? Widths::one : pivots ? Widths::ranked_with_pivots : Widths::ranked,
                                   (s.kA == s.nA ? QUANT_ALL_WIDE : 0u) | (stream_bytes(s) >= kStreamingFrom ? QUANT_STREAMING : 0u),
-                                  pro, &q);
+                                  crew, pro, &q);
     }
     return q.result();
 }

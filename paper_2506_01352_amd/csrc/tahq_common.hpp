@@ -81,7 +81,7 @@ struct Sections {
     }
 };
 
-tahq_status make_shape(const tahq_config *c, Shape *s)
+inline tahq_status make_shape(const tahq_config *c, Shape *s)
 {
     if (!c) return TAHQ_ERR_NULL;
     // shorter structs are the layouts from before alloc_tile (48 bytes) and low_bits (52 bytes) were added
@@ -117,9 +117,9 @@ tahq_status make_shape(const tahq_config *c, Shape *s)
     return TAHQ_OK;
 }
 
-uint64_t stream_bytes(const Shape &s) { return Sections((uint32_t)s.T).end(s.G, s.low, (uint32_t)s.T, (uint64_t)s.U * s.k); }
+inline uint64_t stream_bytes(const Shape &s) { return Sections((uint32_t)s.T).end(s.G, s.low, (uint32_t)s.T, (uint64_t)s.U * s.k); }
 
-void make_workspace(const Shape &s, Workspace *w)
+inline void make_workspace(const Shape &s, Workspace *w)
 {
     w->nseg = (uint32_t)((s.nA + kSegTiles - 1) / kSegTiles);
     uint64_t hb = (s.nA + kRadixKeysPerBlock - 1) / kRadixKeysPerBlock;

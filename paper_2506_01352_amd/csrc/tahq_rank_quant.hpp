@@ -6,11 +6,18 @@
 namespace tahq {
 
 constexpr int kCrewThreads = 1024, kCrewWaves = kCrewThreads / 64;
-constexpr uint32_t kCrewPlaces = 28672;          // places of a unit whose entropies LDS holds beside the histogram
+// Places of a unit whose entropies stay in LDS beside the histogram, and of a unit at all.  Larger units are read from memory for
+// every pass, two or three, out of the L2: encode of bf16, against a selection of its own (one launch up to 65536 tiles, two and a
+// histogram in the entropy pass above), at 3.8 bits: one unit of 32768 tiles G = 16 14.9 -> 11.2 us, 49152 20.3 -> 13.5,
+// 65536 22.6 -> 15.7, 77700 28.5 -> 17.7, 98304 29.3 -> 20.1, 131072 29.1 -> 24.8, 163840 30.4 -> 29.0; G = 64 49152 23.7 -> 16.0, 98304
+// 34.2 -> 26.0, 114688 35.5 -> 30.2; [3,777,1600] G = 16 at 2.25 bits 29.0 -> 23.7.  Ends where a threshold among tiles that are alike,
+// which takes four passes, would cost more than the other way (128000 tiles G = 32, a fifth of them all zero: 41.3 and 40.7).
+constexpr uint32_t kCrewPlaces = 28672, kCrewMost = 98304;
 // Bins of 2048 neighbouring floats, two octaves below ln A: half as wide as k_select_small's, so that half as many tiles have to be
 // placed directly.
 constexpr uint32_t kCrewBins = 8192;
 constexpr int kCrewShift = 11;
+constexpr uint32_t kCrewMany = 2048;             // tiles of the threshold's bin that are listed at all
 
 struct CrewLds {
     uint64_t list[kSmallListCap];                // tiles of the threshold bin: key << 32 | ~place
@@ -33,49 +40,132 @@ __device__ __forceinline__ uint32_t before_in_sixteen(uint32_t own)
     return v - own;
 }
 
-// The unit's entropies' bit patterns in LDS, by place, counted in bins of 2^kCrewShift neighbouring floats by the whole workgroup.
-__device__ __forceinline__ void count_places(int *key, uint32_t *hist, const UnitPlaces &at, uint32_t n, int bin0)
-{
-    const int lane = threadIdx.x & 63;
-    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t nblocks = (at.end + 255u) / 256u;
+// The bit patterns of a unit's entropies, four consecutive places per lane and block of 256, places outside the unit as that of -0.0f,
+// the lowest of all as a signed integer and no entropy's: from LDS, where they lie by place, or from memory each time.
+template <bool RESIDENT>
+struct UnitKeys {
+    static constexpr bool resident = RESIDENT;
+    int *key;                                    // in LDS
+    const float *uH;                             // in memory, by place
+    uint32_t n, phase, end, top;
+    uint32_t lane, wave;
+    __device__ __forceinline__ UnitKeys(int *lds, const float *H, const UnitPlaces &at, uint32_t unit)
+        : key(lds), uH(H), n(unit), phase(at.phase), end(at.end), top(at.nwords * 64u - 4u), lane(threadIdx.x & 63u),
+          wave((uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) {}
+    __device__ __forceinline__ uint32_t blocks() const { return (end + 255u) / 256u; }
+    // The unit's entropies straight to LDS.  (Whole words of 64 places are read, which may reach into the neighbouring units or up
+    // to 63 floats past the entropies, where the workspace goes on; beyond them from a clamped index.)
+    __device__ __forceinline__ void request() const
+    {
+        static_assert(RESIDENT, "in LDS");
 #pragma unroll 1
-    for (uint32_t b = wave; b < nblocks; b += kCrewWaves) {
-        int4 *own = reinterpret_cast<int4 *>(&key[b * 256u + 4u * lane]);
-        int4 q = *own;
-        if ((b == 0 && at.phase != 0) || (b == nblocks - 1 && (at.end & 255u) != 0)) {
-            // places outside the unit take the bit pattern of -0.0f, the lowest of all as a signed integer and no entropy's
-            const uint32_t i = b * 256u + 4u * lane - at.phase;
-            q.x = i < n ? q.x : INT32_MIN; q.y = i + 1u < n ? q.y : INT32_MIN;
-            q.z = i + 2u < n ? q.z : INT32_MIN; q.w = i + 3u < n ? q.w : INT32_MIN;
-            *own = q;
-        }
-        const int v[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int bin = (v[c] >> kCrewShift) - bin0;     // as signed integers: negative values and NaN with the sign bit set lowest
-            atomicAdd(&hist[bin < 0 ? 0 : bin > (int)kCrewBins - 1 ? (int)kCrewBins - 1 : bin], 1u);
+        for (uint32_t b = wave; b * 256u < end; b += kCrewWaves) {
+            const uint32_t place = b * 256u + 4u * lane;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(uH + (place < top ? place : top)),
+                                             (__attribute__((address_space(3))) void *)&key[b * 256u], 16, 0, 0);
         }
     }
+    __device__ __forceinline__ bool edge(uint32_t b) const
+    {
+        return (b == 0 && phase != 0) || (b == blocks() - 1 && (end & 255u) != 0);
+    }
+    __device__ __forceinline__ int4 inside(uint32_t b, int4 q) const
+    {
+        const uint32_t i = b * 256u + 4u * lane - phase;
+        q.x = i < n ? q.x : INT32_MIN; q.y = i + 1u < n ? q.y : INT32_MIN;
+        q.z = i + 2u < n ? q.z : INT32_MIN; q.w = i + 3u < n ? q.w : INT32_MIN;
+        return q;
+    }
+    // f(block, its four bit patterns) for my wavefront's blocks below `last`; FIRST: the first time
+    template <bool FIRST, class F>
+    __device__ __forceinline__ void each(uint32_t last, F f) const
+    {
+        if constexpr (RESIDENT) {
+            if (wave >= last) return;
+            int4 next = *reinterpret_cast<const int4 *>(&key[wave * 256u + 4u * lane]);
+#pragma unroll 1
+            for (uint32_t b = wave; b < last; b += kCrewWaves) {
+                int4 q = next;
+                if (b + kCrewWaves < last) next = *reinterpret_cast<const int4 *>(&key[(b + kCrewWaves) * 256u + 4u * lane]);
+                if (FIRST && edge(b)) {
+                    q = inside(b, q);
+                    *reinterpret_cast<int4 *>(&key[b * 256u + 4u * lane]) = q;
+                }
+                f(b, q);
+            }
+        } else {
+            constexpr uint32_t AHEAD = 2;        // blocks on their way (4 as fast, 8 slower by 1 us: more code to fetch)
+            auto load = [&](uint32_t b) {
+                const uint32_t place = b * 256u + 4u * lane;
+                return *reinterpret_cast<const int4 *>(uH + (place < top ? place : top));
+            };
+            int4 q[AHEAD];
+#pragma unroll
+            for (uint32_t i = 0; i < AHEAD; ++i) q[i] = load(wave + i * kCrewWaves);
+#pragma unroll 1
+            for (uint32_t b0 = wave; b0 < last; b0 += AHEAD * kCrewWaves) {
+#pragma unroll
+                for (uint32_t i = 0; i < AHEAD; ++i) {
+                    const uint32_t b = b0 + i * kCrewWaves;
+                    if (b < last) f(b, edge(b) ? inside(b, q[i]) : q[i]);
+                    q[i] = load(b + AHEAD * kCrewWaves);
+                }
+            }
+        }
+    }
+};
+
+// Median of three integers in one vector instruction.
+__device__ __forceinline__ int imed3(int a, int b, int c)
+{
+    int r;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// A unit's entropies counted in bins of 2^kCrewShift neighbouring floats by the whole workgroup, all but the lowest bin's, which the
+// caller has filled.  Its usual ones are all-zero tiles, whose additions, a wavefront's at a time, would meet on one counter; they
+// go to 64 words in front of the histogram instead, a lane's each.  (Encode of [1,1000,4096] G = 32, a fifth of the tokens all zero,
+// 49 us with a counter, 29 so; with those lanes switched off 30, and every other tensor 0.3 us longer.  [3,777,1600] G = 16 with a fifth
+// constant 43 us at one addition per tile, 35 as below.)
+template <class Keys>
+__device__ __forceinline__ void count_places(const Keys &keys, uint32_t *hist, int bin0)
+{
+    const int mine = -1 - (int)keys.lane;
+    keys.template each<true>(keys.blocks(), [&](uint32_t, const int4 &q) {
+        const int v[4] = {q.x, q.y, q.z, q.w};
+        auto add = [&](int value, uint32_t times) {
+            const int bin = (value >> kCrewShift) - bin0;    // as signed integers: negative values and NaN with the sign bit set lowest
+            atomicAdd(hist + imed3(bin, mine, (int)kCrewBins - 1), times);
+        };
+        if (!Keys::resident && __builtin_expect(__ballot(v[0] == v[3]) != 0, 0)) {
+            // (tokens that are alike make a crowd of neighbours: one addition for the four.  In small units it takes longer than that)
+            if (v[0] == v[1] && v[1] == v[2] && v[2] == v[3]) {
+                add(v[0], 4);
+                return;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) add(v[c], 1);
+    });
 }
 
 // Which of the places [p0, p0 + batch) of a unit are selected, and how many before them, found by the whole workgroup from the unit's
-// entropies' bit patterns in LDS, by place (`key`).  p0 and batch are multiples of 64.  The result is in L.words and L.before behind
-// the last barrier.
-__device__ __forceinline__ void rank_batch(int *key, uint32_t *hist, const UnitPlaces &at, uint32_t n, uint32_t k, int bin0, uint32_t p0,
-                                           uint32_t batch, CrewLds &L)
+// entropies and their counts.  p0 and batch are multiples of 64.  The result is in L.words and L.before behind the last barrier.
+template <class Keys>
+__device__ __forceinline__ void rank_batch(const Keys &keys, uint32_t *hist, uint32_t n, uint32_t k, int bin0, uint32_t p0, uint32_t batch,
+                                           CrewLds &L)
 {
     const int tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t nblocks = (at.end + 255u) / 256u;
-  
+    const uint32_t nblocks = keys.blocks();
+    const uint32_t upto = (p0 + batch + 255u) / 256u < nblocks ? (p0 + batch + 255u) / 256u : nblocks;        // blocks up to the batch's end
     lds_barrier();
-  
     block_pick_bin<(int)kCrewBins>(hist, k, L.wave_total, L.chosen);
     const uint32_t bstar = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[0]);
     uint32_t rem = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[1]);
     uint32_t crowd = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[2]);
-    if (bstar == 0) crowd -= nblocks * 256u - n;             // bin 0 has counted the places outside the unit as well
+    if (bstar == 0) crowd = n - (k - rem);       // (it was filled with as many as there could be)
     // the bit patterns of that bin, first and last
     int lo = bstar == 0 ? INT32_MIN + 1 : (int)((bstar + (uint32_t)bin0) << kCrewShift);
     int hi = bstar == kCrewBins - 1 ? INT32_MAX : (int)(((bstar + (uint32_t)bin0 + 1u) << kCrewShift) - 1u);
@@ -88,20 +178,15 @@ __device__ __forceinline__ void rank_batch(int *key, uint32_t *hist, const UnitP
         if ((lane & 7) == 0 && place >= p0 && place < p0 + batch) reinterpret_cast<uint32_t *>(out)[(place - p0) >> 5] = d;
     };
     uint32_t before = 0;
-    // Every place that is_above is selected, and of the `crowd` others that are not below, the `rem` first by (key descending,
-    // tile ascending), placed directly among each other.
-    auto place_directly = [&](auto is_above, auto is_not_below, auto any_between) {
-        int4 next = *reinterpret_cast<const int4 *>(&key[wave * 256u + 4u * lane]);
-#pragma unroll 1
-        for (uint32_t b = wave; b < nblocks; b += kCrewWaves) {
-            const int4 q = next;
-            if (b + kCrewWaves < nblocks) next = *reinterpret_cast<const int4 *>(&key[(b + kCrewWaves) * 256u + 4u * lane]);
+    // Every place that is_above is selected; those others that are not below are listed.
+    auto classify = [&](uint64_t *list, uint32_t mask, auto is_above, auto is_not_below, auto any_between) {
+        keys.template each<false>(nblocks, [&](uint32_t b, const int4 &q) {
             if (__ballot(any_between(q)) != 0) {
                 const int v[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     if (is_not_below(v[c]) && !is_above(v[c]))
-                        L.list[atomicAdd(&L.listed, 1u) & (kSmallListCap - 1u)] =
+                        list[atomicAdd(&L.listed, 1u) & mask] =
                             ((uint64_t)order_key(__uint_as_float((uint32_t)v[c])) << 32) | (uint32_t)~(b * 256u + 4u * lane + c);
                 }
             }
@@ -113,13 +198,19 @@ __device__ __forceinline__ void rank_batch(int *key, uint32_t *hist, const UnitP
                 put_bits(L.words, b, above);
                 if (b * 256u + 4u * lane < p0) before += (uint32_t)__popc(above);
             }
-        }
-      
+        });
+        lds_barrier();
+    };
+    auto select = [&](bool selected, uint32_t place) {
+        const uint64_t earlier = __ballot(selected && place < p0);
+        if (lane == 0 && earlier != 0) atomicAdd(&L.before, (uint32_t)__popcll(earlier));
+        if (selected && place >= p0 && place < p0 + batch)
+            atomicOr(reinterpret_cast<uint32_t *>(L.words) + ((place - p0) >> 5), 1u << (place & 31u));
+    };
+    // Of the `crowd` listed tiles the `rem` first by (key descending, tile ascending): four threads per tile count those ahead of it.
+    auto place_listed = [&]() {
         before = wave_incl_scan(before);
         if (lane == 63 && before != 0) atomicAdd(&L.before, before);
-        lds_barrier();
-      
-        // four threads per listed tile count the tiles ahead of it
         if ((uint32_t)tid < 4 * crowd) {
             const uint64_t mine = L.list[tid >> 2];
             uint32_t ahead = 0;
@@ -127,23 +218,51 @@ __device__ __forceinline__ void rank_batch(int *key, uint32_t *hist, const UnitP
             for (uint32_t i = (uint32_t)tid & 3u; i < crowd; i += 4) ahead += L.list[i] > mine ? 1u : 0u;
             ahead += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ahead, 0xB1, 0xF, 0xF, true);      // lane ^ 1
             ahead += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ahead, 0x4E, 0xF, 0xF, true);      // lane ^ 2
-            const uint32_t place = ~(uint32_t)mine;
-            const bool selected = ((uint32_t)tid & 3u) == 0 && ahead < rem;
-            const uint64_t earlier = __ballot(selected && place < p0);
-            if (lane == 0 && earlier != 0) atomicAdd(&L.before, (uint32_t)__popcll(earlier));
-            if (selected && place >= p0 && place < p0 + batch)
-                atomicOr(reinterpret_cast<uint32_t *>(L.words) + ((place - p0) >> 5), 1u << (place & 31u));
+            select(((uint32_t)tid & 3u) == 0 && ahead < rem, ~(uint32_t)mine);
         }
         lds_barrier();
     };
-  
-    if (__builtin_expect(crowd <= kSmallListCap, 1)) {
-        place_directly([&](int v) { return v > hi; }, [&](int v) { return v >= lo; }, [&](const int4 &q) {
+    const bool few = crowd <= kSmallListCap;
+    if (__builtin_expect(few || (bstar != 0 && crowd <= kCrewMany), 1)) {
+        // the histogram's first half takes the list of many, its second half the counts of their parts
+        uint64_t *many = reinterpret_cast<uint64_t *>(hist);
+        uint32_t *parts = hist + kCrewBins / 2;
+        static_assert(kCrewMany * 2 <= kCrewBins / 2 && kCrewBins / 2 >= 4096, "they fit");
+        if (!few) reinterpret_cast<uint4 *>(parts)[tid] = make_uint4(0, 0, 0, 0);
+        classify(few ? L.list : many, few ? kSmallListCap - 1u : kCrewMany - 1u, [&](int v) { return v > hi; },
+                 [&](int v) { return v >= lo; }, [&](const int4 &q) {
             const uint32_t a = (uint32_t)q.x - (uint32_t)lo, b = (uint32_t)q.y - (uint32_t)lo, c = (uint32_t)q.z - (uint32_t)lo,
                            d = (uint32_t)q.w - (uint32_t)lo, ab = a < b ? a : b, cd = c < d ? c : d;
             return (ab < cd ? ab : cd) <= (uint32_t)hi - (uint32_t)lo;
         });
-        return;
+        if (few) { place_listed(); return; }
+        // Many: the list is cut into 4096 parts, of one float each as a rule, and what is in the threshold's placed directly.  (Units of
+        // 65536 tiles and more have hundreds of ordinary tiles in a bin, and a second pass over 128000 entropies took 15 us.)
+        const uint32_t key0 = order_key(__uint_as_float((uint32_t)lo)), span = (uint32_t)hi - (uint32_t)lo;
+        const int bits = 32 - __builtin_clz(span | 1u), shift = bits > 12 ? bits - 12 : 0;
+        for (uint32_t i = (uint32_t)tid; i < crowd; i += kCrewThreads) atomicAdd(&parts[((uint32_t)(many[i] >> 32) - key0) >> shift], 1u);
+        if (tid == 0) L.listed = 0;
+        lds_barrier();
+        block_pick_bin<4096>(parts, rem, L.wave_total, L.chosen);
+        const uint32_t part = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[0]), most = crowd;
+        rem = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[1]);
+        crowd = (uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[2]);
+        if (crowd <= kSmallListCap) {
+            for (uint32_t i = (uint32_t)tid; i < (most + 63u) / 64u * 64u; i += kCrewThreads) {      // (whole wavefronts)
+                const uint64_t entry = i < most ? many[i] : 0ull;
+                const uint32_t in = i < most ? ((uint32_t)(entry >> 32) - key0) >> shift : 0u;
+                if (i < most && in == part) L.list[atomicAdd(&L.listed, 1u) & (kSmallListCap - 1u)] = entry;
+                select(i < most && in > part, ~(uint32_t)entry);
+            }
+            lds_barrier();
+            place_listed();
+            return;
+        }
+        // (too many that are nearly alike: the general way, inside that part)
+        lo = (int)((uint32_t)lo + (part << shift));
+        const uint32_t room = (uint32_t)hi - (uint32_t)lo, whole = (1u << shift) - 1u;
+        hi = (int)((uint32_t)lo + (room < whole ? room : whole));
+        before = 0;
     }
     // More tiles in the bin than the list takes: it is cut again, 4096 parts at a time, until they fit or all share one
     // entropy.  Bit patterns count in the order of their keys here, as signed integers, in which -0.0f (the places outside
@@ -153,12 +272,10 @@ __device__ __forceinline__ void rank_batch(int *key, uint32_t *hist, const UnitP
         // The lowest bin's usual crowd are the entropies of all-zero tiles, +0.0f, which counting tells from those above
         // and below.
         uint32_t above = 0, zero = 0;
-#pragma unroll 1
-        for (uint32_t b = wave; b < nblocks; b += kCrewWaves) {
-            const int4 q = *reinterpret_cast<const int4 *>(&key[b * 256u + 4u * lane]);
+        keys.template each<false>(nblocks, [&](uint32_t, const int4 &q) {
             above += (uint32_t)__popc(four_bits(q, [&](int v) { return v > 0 && v <= hi; }));
             zero += (uint32_t)__popc(four_bits(q, [](int v) { return v == 0; }));
-        }
+        });
         above = wave_incl_scan(above);
         zero = wave_incl_scan(zero);
         if (lane == 63) { atomicAdd(&L.above_zero, above); atomicAdd(&L.zero, zero); }
@@ -176,9 +293,7 @@ __device__ __forceinline__ void rank_batch(int *key, uint32_t *hist, const UnitP
         static_assert(kCrewBins >= 4096, "the parts' counts");
         reinterpret_cast<uint4 *>(hist)[tid] = make_uint4(0, 0, 0, 0);
         lds_barrier();
-#pragma unroll 1
-        for (uint32_t b = wave; b < nblocks; b += kCrewWaves) {
-            const int4 q = *reinterpret_cast<const int4 *>(&key[b * 256u + 4u * lane]);
+        keys.template each<false>(nblocks, [&](uint32_t, const int4 &q) {
             const uint32_t from_lo[4] = {(uint32_t)ordered(q.x) - (uint32_t)lo, (uint32_t)ordered(q.y) - (uint32_t)lo,
                                          (uint32_t)ordered(q.z) - (uint32_t)lo, (uint32_t)ordered(q.w) - (uint32_t)lo};
             // (where a crowd shares one entropy all additions meet on one counter, one after the other; tokens that are
@@ -190,7 +305,7 @@ __device__ __forceinline__ void rank_batch(int *key, uint32_t *hist, const UnitP
                 for (int c = 0; c < 4; ++c)
                     if (from_lo[c] <= span) atomicAdd(&hist[from_lo[c] >> shift], 1u);
             }
-        }
+        });
         lds_barrier();
         block_pick_bin<4096>(hist, rem, L.wave_total, L.chosen);
         lo = (int)((uint32_t)lo + ((uint32_t)__builtin_amdgcn_readfirstlane((int)L.chosen[0]) << shift));
@@ -201,19 +316,18 @@ __device__ __forceinline__ void rank_batch(int *key, uint32_t *hist, const UnitP
     }
     auto is_above = [&](int v) { return ordered(v) > hi && v != INT32_MIN; };
     if (crowd <= kSmallListCap) {
-        place_directly(is_above, [&](int v) { return ordered(v) >= lo && v != INT32_MIN; }, [](const int4 &) { return true; });
+        classify(L.list, kSmallListCap - 1u, is_above, [&](int v) { return ordered(v) >= lo && v != INT32_MIN; }, [](const int4 &) { return true; });
+        place_listed();
         return;
     }
     // `crowd` tiles of one entropy: taken in index order until `rem` are used up
     uint32_t equal_before = 0;
-#pragma unroll 1
-    for (uint32_t b = wave; b < nblocks && b * 256u < p0 + batch; b += kCrewWaves) {
-        const int4 q = *reinterpret_cast<const int4 *>(&key[b * 256u + 4u * lane]);
+    keys.template each<false>(upto, [&](uint32_t b, const int4 &q) {
         const uint32_t above = four_bits(q, is_above), same = four_bits(q, [&](int v) { return ordered(v) == lo; });
         put_bits(L.words, b, above);
         put_bits(L.equal, b, same);
         if (b * 256u + 4u * lane < p0) { before += (uint32_t)__popc(above); equal_before += (uint32_t)__popc(same); }
-    }
+    });
     before = wave_incl_scan(before);
     equal_before = wave_incl_scan(equal_before);
     if (lane == 63) { atomicAdd(&L.before, before); atomicAdd(&L.equal_before, equal_before); }
@@ -265,67 +379,59 @@ __device__ __forceinline__ void swap_across(float *x, uint32_t part, uint32_t d)
 // 8 to 64 channels 12.4 -> 9.0; [1,1600,2048] G = 128 16.5 -> 14.7; [10,1638,128] G = 8, 256 workgroups, 16.7 -> 16.3.
 // (With the entropies in registers and loops unrolled over them: [1,1024,1600] 13.1.  Rows requested before the entropies have
 // arrived: the fp32 tensor 22.5, as those wait behind all workgroups' rows.  Two histograms, by the lanes' parity: no faster.)
-template <int G, bool BF16, int LOW>
+template <int G, bool BF16, int LOW, int LPT, bool RESIDENT>
 __global__ __launch_bounds__(kCrewThreads)
 void k_rank_quant(const float *__restrict__ H, const void *__restrict__ in, uint8_t *__restrict__ packed, uint32_t T, uint32_t n,
                   uint32_t k, uint32_t batch, int bin0, float tau, float eps_ratio)
 {
-    constexpr int ES = BF16 ? 2 : 4, LPT = Lanes<G, ES>::few;
+    constexpr int ES = BF16 ? 2 : 4;
     using W = Wave<G, ES, LPT>;
     using U = typename Unit<G>::type;
     constexpr int EPL = W::EPL, WORDS = W::LANE_BYTES / 4;
-    constexpr uint32_t WIDE = LOW + 1, ROWS = kCrewWaves * W::LDS_BYTES, RANK = (kCrewPlaces + kCrewBins) * 4;
+    constexpr uint32_t WIDE = LOW + 1, PLACES = RESIDENT ? kCrewPlaces : 0u;
+    constexpr uint32_t ROWS = kCrewWaves * W::LDS_BYTES, RANK = (PLACES + 64u + kCrewBins) * 4;
     // the unit's entropies and their histogram; later the rows, and the payload
     __shared__ __attribute__((aligned(16))) uint8_t lds[ROWS > RANK ? ROWS : RANK];
     __shared__ CrewLds L;
     static_assert(sizeof(lds) + sizeof(L) <= 163840, "the LDS of a compute unit");
-    int *key = reinterpret_cast<int *>(lds);
-    uint32_t *hist = reinterpret_cast<uint32_t *>(lds) + kCrewPlaces;
+    uint32_t *hist = reinterpret_cast<uint32_t *>(lds) + PLACES + 64;
     const int tid = threadIdx.x;
     const uint32_t lane = (uint32_t)tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t u = blockIdx.y, p0 = blockIdx.x * batch;
     const UnitPlaces at(u, n);
     if (p0 >= at.end) return;                    // (units that start off a boundary reach one batch further)
-  
     const uint64_t first = (uint64_t)u * n - at.phase;       // the tile of place 0
-    const float *uH = H + first;
-    const uint32_t top = at.nwords * 64u - 4u;
-
+    const UnitKeys<RESIDENT> keys(reinterpret_cast<int *>(lds), H + first, at, n);
     // (cleared first: the compiler has LDS accesses wait for what is on its way to LDS)
 #pragma unroll
     for (uint32_t i = 0; i < kCrewBins / 4 / kCrewThreads; ++i)
         reinterpret_cast<uint4 *>(hist)[i * kCrewThreads + tid] = make_uint4(0, 0, 0, 0);
     if (tid < kCrewWaves) { L.words[tid] = 0; L.equal[tid] = 0; }
     if (tid == 0) { L.listed = 0; L.above_zero = 0; L.zero = 0; L.before = 0; L.equal_before = 0; }
-    // The unit's entropies, straight to LDS.  (Whole words of 64 places are read, which may reach into the neighbouring units or up
-    // to 63 floats past the entropies, where the workspace goes on; beyond them from a clamped index.)
-#pragma unroll 1
-    for (uint32_t b = wave; b * 256u < at.end; b += kCrewWaves) {
-        const uint32_t place = b * 256u + 4u * lane;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(uH + (place < top ? place : top)),
-                                         (__attribute__((address_space(3))) void *)&key[b * 256u], 16, 0, 0);
-    }
+    if (tid == 0) hist[0] = n;                   // the lowest bin takes whatever the others leave
+    if constexpr (RESIDENT) keys.request();
     // my wavefront's places of the batch, [w0, w1), and of those the unit's, [v0, v1)
     const uint32_t w0 = p0 + wave * W::TILES;
     const uint32_t v0 = w0 > at.phase ? w0 : at.phase, w1 = w0 + W::TILES, v1 = w1 < at.end ? w1 : at.end;
     const bool works = wave * W::TILES < batch && v0 < v1;
     const uint32_t place = w0 + lane / LPT, part = lane % LPT;
     const bool valid = place >= v0 && place < v1;
-    const uint64_t j = first + (valid ? place : v0);
-    __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0): my wavefront's entropies are in LDS
+    // (a wavefront without places takes the unit's first tile, so that the loads are under no condition, behind which the compiler would
+    // wait for them)
+    const uint64_t j = first + (valid ? place : works ? v0 : at.phase);
+    if constexpr (RESIDENT) __builtin_amdgcn_s_waitcnt(0x0f70);            // vmcnt(0): my wavefront's entropies are in LDS
     lds_barrier();
-  
     // (requested only now: the entropies would wait behind all workgroups' rows)
     uint32_t w[WORDS];
-    if (works) {
+    {
         const uint4 *src = reinterpret_cast<const uint4 *>(static_cast<const uint8_t *>(in) + (j * LPT + part) * W::LANE_BYTES);
 #pragma unroll
-        for (int c = 0; c < WORDS / 4; ++c) {
-            const uint4 v = src[c];
-            w[4 * c] = v.x; w[4 * c + 1] = v.y; w[4 * c + 2] = v.z; w[4 * c + 3] = v.w;
+        for (int i = 0; i < WORDS / 4; ++i) {
+            const uint4 v = src[i];
+            w[4 * i] = v.x; w[4 * i + 1] = v.y; w[4 * i + 2] = v.z; w[4 * i + 3] = v.w;
         }
     }
-    count_places(key, hist, at, n, bin0);
+    count_places(keys, hist, bin0);
     // Eq. 3 and 4, and the tile's range, which do not depend on its width, before the barrier behind the counts.
     float x[EPL];
     uint32_t pv = 0;
@@ -344,7 +450,7 @@ void k_rank_quant(const float *__restrict__ H, const void *__restrict__ in, uint
         }
         range = tile_range<EPL, LPT>(x);
     }
-    rank_batch(key, hist, at, n, k, bin0, p0, batch, L);
+    rank_batch(keys, hist, n, k, bin0, p0, batch, L);
 
     const Sections lay(T);
     // selected places of the batch before each of its words: lane i of the first 16 has word i's
@@ -380,14 +486,12 @@ void k_rank_quant(const float *__restrict__ H, const void *__restrict__ in, uint
     wave_lds_fence();
     const uint64_t upto = (v1 & 63u) != 0 ? word & ((1ull << (v1 & 63u)) - 1ull) : word;
     const uint32_t units = LOW * (v1 - v0) + (uint32_t)__popcll(upto) - below0;
-  
     U *dst = reinterpret_cast<U *>(packed + lay.payload) + ((uint64_t)LOW * (first + v0) + rank0 + before_word + below0);
 #pragma unroll
     for (int i = 0; i < ((int)WIDE + LPT - 1) / LPT; ++i) {
         const uint32_t s = (uint32_t)i * 64 + lane;
         if (s < units) dst[s] = pay[s];
     }
-  
 }
 
 }  // namespace tahq

@@ -317,7 +317,7 @@ __global__ __launch_bounds__(256) void k_radix_pass(const float *__restrict__ H,
 
 // Per segment of kSegTiles tiles (one wavefront each): how many keys equal K* and how many exceed it.
 // K* and `take` come from the pass-2 histogram; every block derives them, block 0 records them.
-__global__ __launch_bounds__(256) void k_seg_count(const float *__restrict__ H, uint32_t n, uint32_t nseg,
+[[maybe_unused]] static __global__ __launch_bounds__(256) void k_seg_count(const float *__restrict__ H, uint32_t n, uint32_t nseg,
                                                    const uint32_t *__restrict__ coarse,
                                                    const uint32_t *__restrict__ partial, uint32_t hb,
                                                    uint32_t *__restrict__ state, uint32_t *__restrict__ seg)
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(256) void k_seg_count(const float *__restrict__ H, 
 // A block owns 4 consecutive segments.  Its first wavefront sums the segment counts that precede
 // the block: equal keys before it (they are taken in index order until `take` are used up) and
 // wide tiles before it (every earlier ranking unit contributes exactly k).
-__global__ __launch_bounds__(256) void k_assign(const float *__restrict__ H, uint32_t n, uint32_t k, uint32_t nseg,
+[[maybe_unused]] static __global__ __launch_bounds__(256) void k_assign(const float *__restrict__ H, uint32_t n, uint32_t k, uint32_t nseg,
                                                 const uint32_t *__restrict__ state,
                                                 const uint32_t *__restrict__ seg,
                                                 uint64_t *__restrict__ bitmap, uint32_t *__restrict__ ranks,
@@ -467,7 +467,7 @@ __global__ __launch_bounds__(256) void k_assign(const float *__restrict__ H, uin
     }
 }
 
-__global__ __launch_bounds__(256) void k_bitmap_pack(const uint8_t *__restrict__ sel_bytes, uint32_t T,
+[[maybe_unused]] static __global__ __launch_bounds__(256) void k_bitmap_pack(const uint8_t *__restrict__ sel_bytes, uint32_t T,
                                                      uint64_t *__restrict__ bitmap)
 {
     const uint64_t j = (uint64_t)blockIdx.x * 256 + threadIdx.x;
@@ -481,7 +481,7 @@ __global__ __launch_bounds__(256) void k_bitmap_pack(const uint8_t *__restrict__
 // width of allocation tile j / m, and the wide quantization tiles before j are m times the wide
 // allocation tiles before j / m, plus j % m if its own allocation tile is wide.  One wavefront per
 // 64 quantization tiles.
-__global__ __launch_bounds__(256) void k_expand_alloc(const uint8_t *__restrict__ sel_a,
+[[maybe_unused]] static __global__ __launch_bounds__(256) void k_expand_alloc(const uint8_t *__restrict__ sel_a,
                                                       const uint32_t *__restrict__ ranks_a, uint32_t T, uint32_t m,
                                                       uint64_t *__restrict__ bitmap, uint32_t *__restrict__ ranks)
 {
@@ -875,7 +875,7 @@ struct MidSelectLds {
     uint32_t chosen[3], listed, above_zero, zero;
 };
 
-__global__ __launch_bounds__(kSmallUnitThreads) void k_select_mid(const float *__restrict__ H, uint32_t n, uint32_t k, int bin0,
+[[maybe_unused]] static __global__ __launch_bounds__(kSmallUnitThreads) void k_select_mid(const float *__restrict__ H, uint32_t n, uint32_t k, int bin0,
                                                                   uint64_t *__restrict__ bitmap, uint32_t *__restrict__ ranks)
 {
     __shared__ __attribute__((aligned(16))) MidSelectLds L;
@@ -1579,7 +1579,7 @@ __device__ __forceinline__ void resolve_crowd(const float *__restrict__ H, uint3
     }
 }
 
-__global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *__restrict__ H, uint32_t n, uint32_t k,
+[[maybe_unused]] static __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *__restrict__ H, uint32_t n, uint32_t k,
                                                                   uint32_t unit0, float bin_scale, float margin,
                                                                   const uint32_t *__restrict__ lin_hist,
                                                                   uint32_t *__restrict__ fused,
@@ -1728,7 +1728,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_select_resolve(const float *_
     }
 }
 
-__global__ __launch_bounds__(256) void k_bitmap_const(uint32_t T, int all_wide, uint64_t *__restrict__ bitmap,
+[[maybe_unused]] static __global__ __launch_bounds__(256) void k_bitmap_const(uint32_t T, int all_wide, uint64_t *__restrict__ bitmap,
                                                       uint32_t *__restrict__ ranks)
 {
     const uint64_t w = (uint64_t)blockIdx.x * 256 + threadIdx.x;
@@ -1736,7 +1736,7 @@ __global__ __launch_bounds__(256) void k_bitmap_const(uint32_t T, int all_wide, 
 }
 
 // The prologue in a launch of its own, with the scratch of the large units' selections cleared.
-__global__ __launch_bounds__(256) void k_prologue(Prologue pro, uint32_t *__restrict__ zero_base, uint32_t zero_words)
+[[maybe_unused]] static __global__ __launch_bounds__(256) void k_prologue(Prologue pro, uint32_t *__restrict__ zero_base, uint32_t zero_words)
 {
     const uint32_t gid = blockIdx.x * 256 + threadIdx.x;
     write_prologue(pro, gid, gridDim.x * 256);

@@ -50,13 +50,36 @@ def test_batches_and_units_of_all_lengths(G, f32):
             _check(x, B, n, G, G, float(np.float32(budget)))
 
 
-@pytest.mark.parametrize("n,B", ((28672, 1), (28673, 1), (28609, 2), (28610, 2), (16383, 4), (16384, 4)))
+@pytest.mark.parametrize("n,B", ((28672, 1), (28673, 1), (28609, 2), (28610, 2), (16383, 4), (16384, 4), (65537, 2), (98304, 1), (98305, 1), (98241, 2), (98242, 2)))
 def test_the_largest_units(n, B):
     rng = np.random.default_rng(n)
     x = np.ascontiguousarray(_values(rng, (B, n, 8), False))
     for budget in (3.0 + 1.0 / n, 3.5, 4.0 - 1.0 / n):
         print(f"[case] {B} units of {n} tiles, budget {budget}", flush=True)
         _check(x, B, n, 8, 8, float(np.float32(budget)))
+
+
+@pytest.mark.parametrize("G,n,B,f32", ((64, 17500, 4, False), (64, 17500, 4, True), (64, 16384, 8, True), (32, 25600, 5, True), (32, 40001, 2, False),
+                                       (16, 33333, 4, True), (16, 77700, 3, False), (64, 50001, 1, True), (128, 30000, 1, False)))
+def test_as_many_tiles_as_fit_one_round(G, n, B, f32):
+    # lanes of more elements, entropies in LDS and from memory; the smaller thresholds' bins hold hundreds of tiles
+    x = np.ascontiguousarray(_values(np.random.default_rng(n), (B, n, G), f32))
+    for budget in (3.07, 3.5, 3.8):
+        print(f"[case] {B} units of {n} tiles of {G}, fp32 {f32}, budget {budget}", flush=True)
+        _check(x, B, n, G, G, budget)
+
+
+@pytest.mark.parametrize("n,values", ((30000, 3), (90000, 40), (20000, 300)))
+def test_tiles_of_a_few_entropies(n, values):
+    # a bin of more tiles than are listed, or than are placed directly, of a few entropies each; the threshold among, above and
+    # below every one of them
+    rng = np.random.default_rng(values)
+    kinds = rng.standard_normal((values, 8)).astype(np.float32)
+    kinds[1:] = kinds[0] + 1e-3 * kinds[1:]              # nearly alike
+    x = kinds[rng.integers(0, values, (1, n))]
+    for share in (1 / n, 0.11, 0.33, 0.34, 0.5, 0.75, 0.97):
+        print(f"[case] {n} tiles of {values} kinds, share {share}", flush=True)
+        _check(np.ascontiguousarray(x), 1, n, 8, 8, float(np.float32(3.0 + share)))
 
 
 @pytest.mark.parametrize("low", (1, 2, 4, 5, 6, 7))
@@ -68,7 +91,7 @@ def test_other_widths(low):
 
 
 @pytest.mark.parametrize("share,how", ((0.02, "zero"), (0.4, "zero"), (0.4, "constant"), (1.0, "constant"), (0.3, "one-hot"), (0.01, "nan")))
-@pytest.mark.parametrize("n,scope", ((5001, 0), (8000, 1)))
+@pytest.mark.parametrize("n,scope", ((5001, 0), (8000, 1), (32001, 0)))
 def test_crowds_at_the_threshold(n, scope, share, how):
     # tiles of one entropy, more and fewer than are placed directly, with the threshold above, among and below them, in units
     # of many batches
