@@ -24,6 +24,7 @@
 
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 using namespace tahq;
 
@@ -170,16 +171,21 @@ struct LaunchQuantPack {
                    uint32_t how, const Prologue &pro, Enqueue *qp)
     {
         Enqueue &q = *qp;
-        using B = Batch<G, BF16 ? 2 : 4, LPT>;
-        const dim3 grid((T + B::TILES - 1) / B::TILES), block(B::TILES * LPT);
+        // by workgroups where a lane has a bf16 tile of 32 channels or more, by wavefronts otherwise (the figures are at the kernels)
+        constexpr bool by_wave = LPT > 1 || !BF16 || G < 32;
+        constexpr uint32_t tiles = by_wave ? 4 * (64 / LPT) : Batch<G, 2>::TILES;
+        const dim3 grid((T + tiles - 1) / tiles), block(256);
+        auto launch = [&](auto ranked, auto pivots) {
+            if constexpr (by_wave)
+                q(k_quant_by_wave<G, BF16, LOW, ranked.value, pivots.value, LPT>, grid, block, d_in, packed, T, tau, eps_ratio, how, pro);
+            else
+                q(k_quant_pack<G, LOW, ranked.value, pivots.value>, grid, block, d_in, packed, T, tau, eps_ratio, how, pro);
+        };
         if constexpr (BF16 && LPT == Lanes<G, 2>::usual) {
-            if (widths == Widths::ranked_with_pivots) {
-                q(k_quant_pack<G, BF16, LOW, true, true, LPT>, grid, block, d_in, packed, T, tau, eps_ratio, how, pro);
-                return;
-            }
+            if (widths == Widths::ranked_with_pivots) { launch(std::true_type{}, std::true_type{}); return; }
         }
-        if (widths == Widths::one) q(k_quant_pack<G, BF16, LOW, false, false, LPT>, grid, block, d_in, packed, T, tau, eps_ratio, how, pro);
-        else q(k_quant_pack<G, BF16, LOW, true, false, LPT>, grid, block, d_in, packed, T, tau, eps_ratio, how, pro);
+        if (widths == Widths::one) launch(std::false_type{}, std::false_type{});
+        else launch(std::true_type{}, std::false_type{});
     }
     template <int LOW>
     static void go(const void *d_in, uint8_t *packed, uint32_t T, float tau, float eps_ratio, Widths widths,

@@ -354,19 +354,12 @@ __device__ __forceinline__ uint32_t pivot_of(const uint8_t *row, uint32_t part, 
     return pivot_from<EPL, BF16, LPT>([&](int i) { return w[i]; }, part, tau, eps_ratio);
 }
 
-// The pivot swap P_d on a tile's LDS row.
-template <bool BF16>
+// The pivot swap P_d on a bf16 tile's LDS row.
 __device__ __forceinline__ void swap_pivot(uint8_t *row, uint32_t d)
 {
-    if constexpr (BF16) {
-        uint16_t *r16 = reinterpret_cast<uint16_t *>(row);
-        const uint16_t v0 = r16[0], vd = r16[d];
-        r16[0] = vd; r16[d] = v0;
-    } else {
-        float *r32 = reinterpret_cast<float *>(row);
-        const float v0 = r32[0], vd = r32[d];
-        r32[0] = vd; r32[d] = v0;
-    }
+    uint16_t *r16 = reinterpret_cast<uint16_t *>(row);
+    const uint16_t v0 = r16[0], vd = r16[d];
+    r16[0] = vd; r16[d] = v0;
 }
 
 // ------------------------------------------------------------- prologue
@@ -1037,12 +1030,12 @@ __device__ __forceinline__ uint32_t bits_below_me(uint64_t mask)
 }
 
 // Width of my tile (LOW or LOW + 1 bits), its payload position inside the batch (in units of G/8 bytes), and
-// the number of wide tiles in the batch.  My tile is tid / LPT: a wavefront's tiles lie in one bit map word.
-template <int TILES, int LOW, int LPT>
+// the number of wide tiles in the batch.  A wavefront's tiles are one bit map word.
+template <int TILES, int LOW>
 __device__ __forceinline__ void tile_pos(const BatchMeta<TILES> &m, int tid, uint32_t *b, uint32_t *rel, uint32_t *total4)
 {
-    const uint32_t mine_word = (uint32_t)__builtin_amdgcn_readfirstlane(tid / (64 * LPT));      // the same in every lane
-    const uint32_t tile = (uint32_t)tid / LPT, at = tile & 63u;
+    const uint32_t mine_word = (uint32_t)__builtin_amdgcn_readfirstlane(tid / 64);      // the same in every lane
+    const uint32_t tile = (uint32_t)tid, at = tile & 63u;
     uint64_t mine = 0;
     uint32_t before = 0, tot = 0;
 #pragma unroll
@@ -1052,10 +1045,7 @@ __device__ __forceinline__ void tile_pos(const BatchMeta<TILES> &m, int tid, uin
     }
     const uint32_t half = at < 32u ? (uint32_t)mine : (uint32_t)(mine >> 32);
     *b = (uint32_t)LOW + ((half >> (at & 31u)) & 1u);
-    uint32_t below;
-    if constexpr (LPT == 1) below = bits_below_me(mine);
-    else below = (uint32_t)__popc(half & ((1u << (at & 31u)) - 1u)) + (at < 32u ? 0u : (uint32_t)__popc((uint32_t)mine));
-    *rel = (uint32_t)LOW * tile + before + below;
+    *rel = (uint32_t)LOW * tile + before + bits_below_me(mine);
     *total4 = tot;
 }
 
@@ -1109,17 +1099,15 @@ __device__ __forceinline__ float fmax3(float a, float b, float c)
 
 // The rest of the encoder for one tile, in two steps with a workgroup barrier between them (the payload
 // buffer that step 2 writes shares LDS with the rows that step 1 reads).
-// Step 1: my part of the row (which already carries P_d) into registers; Eq. 4 on outlier tiles.
-template <int G, bool BF16, int LPT>
-__device__ __forceinline__ void transform_row(const uint8_t *row, uint32_t part, bool flag, float *x)
+// Step 1: the row (which already carries P_d) into registers; Eq. 4 on outlier tiles.
+template <int G>
+__device__ __forceinline__ void transform_row(const uint8_t *row, bool flag, float *x)
 {
-    constexpr int EPL = G / LPT;
-    read_tile<EPL, BF16>(row + part * (EPL * (BF16 ? 2 : 4)), x);
-    if (flag) {                                  // the lanes of a tile agree
-        butterfly<EPL>(x);
-        butterfly_across<EPL, LPT>(x, part);
+    read_tile<G, true>(row, x);
+    if (flag) {
+        butterfly<G>(x);
 #pragma unroll
-        for (int k = 0; k < EPL; ++k) x[k] = x[k] * TileConst<G>::c;
+        for (int k = 0; k < G; ++k) x[k] = x[k] * TileConst<G>::c;
     }
 }
 
@@ -1291,20 +1279,16 @@ enum : uint32_t { QUANT_ALL_WIDE = 1, QUANT_STREAMING = 2 };
 // paths rarely both run.  The payload buffer reuses the rows' LDS once every lane holds its tile in
 // registers, which keeps the workgroup small enough for four to share a compute unit: this kernel
 // lives on the loads of its neighbours being in flight while it computes.
-// Tiles of more than 128 bytes take LPT lanes each, so that a workgroup has 256 threads and a lane at most 64 elements for
-// every tile: with a lane per tile such workgroups had 64 or 128 threads of 200 registers, one or two wavefronts per
-// vector unit, where it takes four to issue at the full rate.  bf16 [8,1024,4096] G = 128 at 3 bits: 28.5 -> 24.2 us, fp32
-// [4,512,2048] G = 64: 8.3 -> 6.7.
-template <int G, bool BF16, int LOW, bool RANKED, bool PIVOTS, int LPT, bool FULL>
+// For bf16 tiles of 32 and 64 channels in tensors of many; all others are quantized by wavefronts, below.
+template <int G, int LOW, bool RANKED, bool PIVOTS, bool FULL>
 __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, uint8_t *__restrict__ packed, const Sections &lay,
                                                  uint32_t T, float tau, float eps_ratio, uint32_t batch, uint32_t nvalid,
                                                  bool all_wide, bool streaming, uint8_t *lds, uint32_t *info, uint16_t *order,
                                                  uint32_t *class_count)
 {
-    constexpr int ES = BF16 ? 2 : 4;
-    using B = Batch<G, ES, LPT>;
+    using B = Batch<G, 2>;
     using U = typename Unit<G>::type;
-    constexpr int EPL = G / LPT, THREADS = B::TILES * LPT;
+    constexpr int THREADS = B::TILES;
     constexpr int WAVES = THREADS / 64;
     constexpr uint32_t WIDE = LOW + 1;           // the two code widths are LOW and WIDE bits
     static_assert(sizeof(U) * WIDE * B::TILES <= (size_t)B::LDS_BYTES, "payload buffer must fit in the rows");
@@ -1314,10 +1298,10 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t slot = (uint32_t)tid / LPT, part = (uint32_t)tid % LPT;
+    const uint32_t slot = (uint32_t)tid;
     const uint64_t j0 = (uint64_t)batch * B::TILES;
 
-    uint4 v[B::CHUNKS / LPT];
+    uint4 v[B::CHUNKS];
     load_batch<B, FULL, true>(in, j0, nvalid, v, tid);           // second and last read of the tensor
     BatchMeta<B::TILES> meta;
     if constexpr (RANKED) {
@@ -1335,15 +1319,15 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
         pv = packed[lay.pivot + j0 + (valid ? slot : 0u)];
     }
     uint32_t b, rel, total4;
-    tile_pos<B::TILES, LOW, LPT>(meta, tid, &b, &rel, &total4);
+    tile_pos<B::TILES, LOW>(meta, tid, &b, &rel, &total4);
     if constexpr (!PIVOTS) {
         store_batch<B, FULL>(v, nvalid, lds, tid);
         __syncthreads();
-        if (valid) pv = pivot_of<EPL, BF16, LPT>(lds + slot * B::STRIDE + part * (EPL * ES), part, tau, eps_ratio);
+        if (valid) pv = pivot_of<G, true, 1>(lds + slot * B::STRIDE, 0, tau, eps_ratio);
     }
     // stage one: my tile's class
-    uint32_t cls = 4;                            // tiles past the end, and all lanes of a tile but its first, sort nowhere
-    if (valid && part == 0) {
+    uint32_t cls = 4;                            // tiles past the end sort nowhere
+    if (valid) {
         info[slot] = pv | ((b == WIDE) ? 0x100u : 0u) | (rel << 9);
         cls = ((pv >> 7) << 1) | (b == WIDE ? 1u : 0u);
     }
@@ -1355,31 +1339,26 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
         if (cls < 4) {
             order[pos] = (uint16_t)slot;
             // an outlier tile with d != 0 (inside the row whatever the stream holds, as in the decoder)
-            if (pv > 0x80u) swap_pivot<BF16>(lds + slot * B::STRIDE, pv & (G - 1u));
+            if (pv > 0x80u) swap_pivot(lds + slot * B::STRIDE, pv & (G - 1u));
         }
     }
     __syncthreads();
 
     // stage two: the tile of my slot in class order
-    float x[EPL];
+    float x[G];
     uint32_t t = 0, inf = 0;
     if (valid) {
         t = order[slot];
         inf = info[t];
-        transform_row<G, BF16, LPT>(lds + t * B::STRIDE, part, (inf & 0x80u) != 0, x);
+        transform_row<G>(lds + t * B::STRIDE, (inf & 0x80u) != 0, x);
     }
     __syncthreads();                             // the rows are dead: their LDS becomes the payload buffer
     if (valid) {
-        // (a part's share of the payload is b units of EPL/8 bytes)
-        const uint32_t width = (inf & 0x100u) ? WIDE : (uint32_t)LOW;
-        const uint32_t meta16 = quantize_values<EPL, LOW>(
-            x, tile_range<EPL, LPT>(x), width, reinterpret_cast<typename Unit<EPL>::type *>(pay + (inf >> 9)) + part * width);
+        const uint32_t meta16 = quantize_values<G, LOW>(x, tile_range<G, 1>(x), (inf & 0x100u) ? WIDE : (uint32_t)LOW, pay + (inf >> 9));
         const uint64_t j = j0 + t;
-        if (part == 0) {
-            reinterpret_cast<uint16_t *>(packed + lay.scale)[j] = (uint16_t)meta16;
-            reinterpret_cast<uint16_t *>(packed + lay.zero)[j] = (uint16_t)(meta16 >> 16);
-            if constexpr (!PIVOTS) packed[lay.pivot + j] = (uint8_t)inf;
-        }
+        reinterpret_cast<uint16_t *>(packed + lay.scale)[j] = (uint16_t)meta16;
+        reinterpret_cast<uint16_t *>(packed + lay.zero)[j] = (uint16_t)(meta16 >> 16);
+        if constexpr (!PIVOTS) packed[lay.pivot + j] = (uint8_t)inf;
     }
     __syncthreads();
 
@@ -1387,7 +1366,7 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
     const uint32_t span = (uint32_t)LOW * nvalid + total4;
     U *gdst = reinterpret_cast<U *>(packed + lay.payload) + ((uint64_t)LOW * j0 + meta.rank0);
 #pragma unroll
-    for (int i = 0; i < ((int)WIDE + LPT - 1) / LPT; ++i) {
+    for (int i = 0; i < (int)WIDE; ++i) {
         const uint32_t q = (uint32_t)i * THREADS + tid;
         if (q < span) {
             if (streaming) store_streaming(gdst + q, pay[q]);
@@ -1405,14 +1384,13 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
 // RANKED: the widths are in the stream's bit map.  Otherwise all tiles have one, and the kernel is the call's only one and
 // writes bit map, rank table and prologue as well.  (A variant of its own: the same as a run-time choice delayed the loads of
 // the ranked case, 126 -> 136 us on bf16 [8,4096,8192].)
-template <int G, bool BF16, int LOW, bool RANKED, bool PIVOTS, int LPT>
+template <int G, int LOW, bool RANKED, bool PIVOTS>
 __global__ __launch_bounds__(256, 4)
 void k_quant_pack(const void *__restrict__ in, uint8_t *__restrict__ packed, uint32_t T, float tau, float eps_ratio,
                   uint32_t how, Prologue pro)
 {
-    constexpr int ES = BF16 ? 2 : 4;
-    using B = Batch<G, ES, LPT>;
-    constexpr int THREADS = B::TILES * LPT, WAVES = THREADS / 64;
+    using B = Batch<G, 2>;
+    constexpr int THREADS = B::TILES, WAVES = THREADS / 64;
     __shared__ __attribute__((aligned(16))) uint8_t lds[B::LDS_BYTES];
     __shared__ uint32_t info[B::TILES];          // per tile: pivot byte | (b == WIDE) << 8 | rel << 9
     __shared__ uint16_t order[B::TILES];         // tiles in class order
@@ -1420,15 +1398,123 @@ void k_quant_pack(const void *__restrict__ in, uint8_t *__restrict__ packed, uin
     const Sections lay(T);
     const uint32_t nfull = T / B::TILES;        // a workgroup per batch; the last one may be ragged
     if (blockIdx.x < nfull)
-        quant_pack_batch<G, BF16, LOW, RANKED, PIVOTS, LPT, true>(in, packed, lay, T, tau, eps_ratio, blockIdx.x, B::TILES,
+        quant_pack_batch<G, LOW, RANKED, PIVOTS, true>(in, packed, lay, T, tau, eps_ratio, blockIdx.x, B::TILES,
                                                                   (how & QUANT_ALL_WIDE) != 0, (how & QUANT_STREAMING) != 0, lds,
                                                                   info, order, class_count);
     else
-        quant_pack_batch<G, BF16, LOW, RANKED, PIVOTS, LPT, false>(in, packed, lay, T, tau, eps_ratio, nfull, T % B::TILES,
+        quant_pack_batch<G, LOW, RANKED, PIVOTS, false>(in, packed, lay, T, tau, eps_ratio, nfull, T % B::TILES,
                                                                    (how & QUANT_ALL_WIDE) != 0, (how & QUANT_STREAMING) != 0, lds,
                                                                    info, order, class_count);
     if constexpr (!RANKED) {
         if (blockIdx.x == 0) write_prologue(pro, threadIdx.x, THREADS);      // (nothing but header and padding)
+    }
+}
+
+// The quantizer of a wavefront by itself, for the tiles of its lanes, without barriers, as the decoder is.  The butterfly then runs in every
+// wavefront that meets an outlier tile, instead of in those that hold the outlier tiles of a workgroup.  That costs vector slots,
+// which are there where tiles have few channels, many bytes or several lanes; what it saves are the barriers, at which most
+// of a workgroup waited for its loads and then for the wavefront with the outlier tiles.  RANKED and PIVOTS as in k_quant_pack.
+// Encode against k_quant_pack, at 3 bits: bf16 G = 128 [4,1024,4096] 13.3 -> 11.8 us, [8,4096,8192] 131.6 -> 126.2, G = 8 [4,2048,8192]
+// 58.5 -> 54.3, G = 16 44.2 -> 42.2; fp32 G = 64 [8,2048,8192] 106.5 -> 102.2, G = 32 [4,2048,8192] 55.0 -> 53.8, G = 8 69.4 -> 65.2; at
+// 3.5 bits bf16 G = 128 [8,2048,8192] 133.3 -> 129.6, G = 8 [4,2048,8192] 132.2 -> 124.5, fp32 G = 64 [8,1024,2048] 41.0 -> 39.4.
+// bf16 G = 32, a lane per tile: [8,1024,2048] 12.4 -> 11.9, but [4,2048,8192] at 3.5 bits 81.2 -> 82.1 and [16,2048,5120] alike; with
+// 64 elements in a lane vector issue is what bounds the quantizer.  Those two stay with k_quant_pack.
+template <int G, bool BF16, int LOW, bool RANKED, bool PIVOTS, int LPT>
+__global__ __launch_bounds__(256, 4)
+void k_quant_by_wave(const void *__restrict__ in, uint8_t *__restrict__ packed, uint32_t T, float tau, float eps_ratio, uint32_t how,
+                     Prologue pro)
+{
+    using W = Wave<G, BF16 ? 2 : 4, LPT>;
+    using U = typename Unit<G>::type;
+    constexpr int EPL = W::EPL;
+    constexpr uint32_t WIDE = LOW + 1;
+    static_assert(WIDE * W::TILES * sizeof(U) <= (size_t)W::LDS_BYTES, "the payload lies where the rows were");
+    __shared__ __attribute__((aligned(16))) uint8_t lds_all[4 * W::LDS_BYTES];
+    const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint64_t j0 = ((uint64_t)blockIdx.x * 4 + wave) * W::TILES;
+    if (j0 < T) {
+        uint8_t *lds = lds_all + wave * W::LDS_BYTES;
+        const uint32_t left = (uint32_t)(T - j0), tiles = left < (uint32_t)W::TILES ? left : (uint32_t)W::TILES;
+        request_rows<W, 1, true>(static_cast<const uint8_t *>(in) + j0 * W::EPL * LPT * (BF16 ? 2 : 4), tiles * LPT, lds, lane);
+        const Sections lay(T);
+        const uint32_t t = lane / LPT, part = lane % LPT, mine = t < tiles ? t : tiles - 1;      // (lanes past the end: the last tile)
+        // my tile's width and, in units of G/8 bytes, its place in the wavefront's payload, which starts at unit `first` and has `units`
+        uint32_t b, at;
+        uint64_t first;
+        uint32_t units;
+        if constexpr (RANKED) {
+            const uint64_t word = reinterpret_cast<const uint64_t *>(packed + lay.bitmap)[j0 >> 6] >> (j0 & 63u);
+            const uint64_t before = reinterpret_cast<const uint64_t *>(packed + lay.bitmap)[j0 >> 6] & ((1ull << (j0 & 63u)) - 1ull);
+            const uint32_t rank0 = reinterpret_cast<const uint32_t *>(packed + lay.ranks)[j0 >> 6];
+            b = (uint32_t)LOW + ((uint32_t)(word >> mine) & 1u);
+            at = (uint32_t)LOW * t + (uint32_t)__popcll(word & ((1ull << mine) - 1ull));
+            first = (uint64_t)LOW * j0 + rank0 + (uint32_t)__popcll(before);
+            units = (uint32_t)LOW * tiles + (uint32_t)__popcll(tiles < 64 ? word & ((1ull << tiles) - 1ull) : word);
+        } else {
+            const bool all_wide = (how & QUANT_ALL_WIDE) != 0;
+            b = all_wide ? WIDE : (uint32_t)LOW;
+            at = b * t;
+            first = b * j0;
+            units = b * tiles;
+            if ((j0 & 63u) == 0 && lane == 0)
+                constant_width_word(j0 >> 6, T, all_wide, reinterpret_cast<uint64_t *>(packed + lay.bitmap),
+                                    reinterpret_cast<uint32_t *>(packed + lay.ranks));
+        }
+        uint32_t pv = 0;
+        if constexpr (PIVOTS) pv = packed[lay.pivot + j0 + mine];
+        wait_for_rows();
+        Row<W, BF16> row;
+        row.read(lds, 0, lane);
+        if constexpr (!PIVOTS) pv = pivot_of<EPL, BF16, LPT>(row.w, part, tau, eps_ratio);
+        if (__ballot(pv > 0x80u) != 0) {
+            // P_d, on the rows in LDS
+            if (pv > 0x80u && part == 0) {
+                uint8_t *e0 = lds + W::element_at(lane, 0), *ed = lds + W::element_at(lane, pv & (G - 1u));
+                if constexpr (BF16) {
+                    const uint16_t v0 = *reinterpret_cast<uint16_t *>(e0), vd = *reinterpret_cast<uint16_t *>(ed);
+                    *reinterpret_cast<uint16_t *>(e0) = vd; *reinterpret_cast<uint16_t *>(ed) = v0;
+                } else {
+                    const float v0 = *reinterpret_cast<float *>(e0), vd = *reinterpret_cast<float *>(ed);
+                    *reinterpret_cast<float *>(e0) = vd; *reinterpret_cast<float *>(ed) = v0;
+                }
+            }
+            wave_lds_fence();
+            row.read(lds, 0, lane);
+        }
+        float x[EPL];
+#pragma unroll
+        for (int k = 0; k < EPL; ++k) x[k] = row[k];
+        if ((pv & 0x80u) != 0) {                 // the lanes of a tile agree
+            butterfly<EPL>(x);
+            butterfly_across<EPL, LPT>(x, part);
+#pragma unroll
+            for (int k = 0; k < EPL; ++k) x[k] = x[k] * TileConst<G>::c;
+        }
+        wave_lds_fence();                        // the rows are dead: their LDS becomes the payload buffer
+        U *pay = reinterpret_cast<U *>(lds);
+        if (t < tiles) {
+            const uint32_t meta16 = quantize_values<EPL, LOW>(x, tile_range<EPL, LPT>(x), b,
+                                                              reinterpret_cast<typename Unit<EPL>::type *>(pay + at) + part * b);
+            if (part == 0) {
+                const uint64_t j = j0 + t;
+                reinterpret_cast<uint16_t *>(packed + lay.scale)[j] = (uint16_t)meta16;
+                reinterpret_cast<uint16_t *>(packed + lay.zero)[j] = (uint16_t)(meta16 >> 16);
+                if constexpr (!PIVOTS) packed[lay.pivot + j] = (uint8_t)pv;
+            }
+        }
+        wave_lds_fence();
+        U *dst = reinterpret_cast<U *>(packed + lay.payload) + first;
+#pragma unroll
+        for (int i = 0; i < ((int)WIDE + LPT - 1) / LPT; ++i) {
+            const uint32_t q = (uint32_t)i * 64 + lane;
+            if (q < units) {
+                if (how & QUANT_STREAMING) store_streaming(dst + q, pay[q]);
+                else dst[q] = pay[q];
+            }
+        }
+    }
+    if constexpr (!RANKED) {
+        if (blockIdx.x == 0) write_prologue(pro, threadIdx.x, 256);    // (nothing but header and padding)
     }
 }
 
