@@ -1,9 +1,10 @@
 // Top-p% tile selection (Sec. 3.2): inside every ranking unit the k (allocation) tiles of highest entropy get
 // the wider code (4 bits by default), ties going to the lower tile index.  Exact, deterministic, no sort.
-// Entropies map to order-preserving 32-bit keys; four ways to find the k-th largest key K*, how many tiles equal to
+// Entropies map to order-preserving 32-bit keys; five ways to find the k-th largest key K*, how many tiles equal to
 // K* are still wanted (`take`), and from them the bit map and the rank table:
 //
-//   * ranking units of at most 32768 tiles (32705 where units start off the 64-tile boundaries): k_select_small, one workgroup per
+//   * ranking units of at most 98304 tiles in tensors of one round of workgroups: in the quantizer's launch (tahq_rank_quant.hpp);
+//   * other ranking units of at most 32768 tiles (32705 where units start off the 64-tile boundaries): k_select_small, one workgroup per
 //     unit in one launch (entropies and a histogram in LDS, the threshold's bin ranked directly), because at that size several
 //     launches cost more than the work;
 //   * units of up to 65536 places in tensors whose entropies are exact: k_select_mid, the same from registers;

@@ -3,10 +3,10 @@
 //
 // Mapping: A LANE OWNS A TILE, or, of a tile of more than 128 bytes or in a tensor of few tiles, one part of two or four.  The
 // codec is bound by vector-ALU issue as much as by HBM, so the per-tile work (reductions, butterflies, quantizer
-// parameters) crosses lanes in its last one or two levels only, inside a quad.  In the quantizer a workgroup stages TILES
-// consecutive tiles through LDS with coalesced 128-bit global accesses, then every lane pulls its part into registers; LDS rows
-// are padded by 16 bytes so that the lane-per-row 128-bit reads are bank-conflict free.  In the entropy kernels and the decoder
-// every wavefront works by itself on LDS of its own.
+// parameters) crosses lanes in its last one or two levels only, inside a quad.  In the quantizer of bf16 tiles of 32 and 64 channels a
+// workgroup stages TILES consecutive tiles through LDS with coalesced 128-bit global accesses, then every lane pulls its tile into
+// registers; LDS rows are padded by 16 bytes so that the lane-per-row 128-bit reads are bank-conflict free.  In the other quantizer,
+// the entropy kernels and the decoder every wavefront works by itself on LDS of its own.
 #pragma once
 #include "tahq_common.hpp"
 
