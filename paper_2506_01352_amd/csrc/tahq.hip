@@ -503,8 +503,9 @@ tahq_status tahq_encode_phases(const tahq_config *cfg, const void *d_in, void *d
         crew = plan_rank_quant(s, places);
     constexpr uint32_t together = TAHQ_PHASE_ENTROPY | TAHQ_PHASE_SELECT | TAHQ_PHASE_QUANT;
     const bool ranked_in_quant = crew.batch != 0 && !multi_launch && (phases & together) == together;
-    // Otherwise ranking units that one workgroup can hold are ranked in a single launch, from LDS or from registers.  (Not where the two-launch selection's approximate entropies save more: [16,1024,4096] 77.8 us
-    // so, 80.5 with exact ones; and as long as every unit has a compute unit.)
+    // Otherwise ranking units that one workgroup can hold are ranked in a single launch, from LDS or from registers.  (Not where the
+    // two-launch selection's approximate entropies save more: [16,1024,4096] 77.8 us so, 80.5 with exact ones; and as long as every
+    // unit has a compute unit.)
     const bool mid_units = select && !wide && !multi_launch && places > kSmallUnitMaxKeys && places <= kMidPlaces && s.U <= 256 &&
                            !approximate_entropies(s, cfg);
     const bool small_units = (select && places <= kSmallUnitMaxKeys && !multi_launch) || mid_units || ranked_in_quant;

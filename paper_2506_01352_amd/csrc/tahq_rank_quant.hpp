@@ -316,7 +316,8 @@ __device__ __forceinline__ void rank_batch(const Keys &keys, uint32_t *hist, uin
     }
     auto is_above = [&](int v) { return ordered(v) > hi && v != INT32_MIN; };
     if (crowd <= kSmallListCap) {
-        classify(L.list, kSmallListCap - 1u, is_above, [&](int v) { return ordered(v) >= lo && v != INT32_MIN; }, [](const int4 &) { return true; });
+        classify(L.list, kSmallListCap - 1u, is_above, [&](int v) { return ordered(v) >= lo && v != INT32_MIN; },
+                 [](const int4 &) { return true; });
         place_listed();
         return;
     }

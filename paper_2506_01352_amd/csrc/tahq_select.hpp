@@ -876,8 +876,9 @@ struct MidSelectLds {
     uint32_t chosen[3], listed, above_zero, zero;
 };
 
-[[maybe_unused]] static __global__ __launch_bounds__(kSmallUnitThreads) void k_select_mid(const float *__restrict__ H, uint32_t n, uint32_t k, int bin0,
-                                                                  uint64_t *__restrict__ bitmap, uint32_t *__restrict__ ranks)
+[[maybe_unused]] static __global__ __launch_bounds__(kSmallUnitThreads)
+void k_select_mid(const float *__restrict__ H, uint32_t n, uint32_t k, int bin0, uint64_t *__restrict__ bitmap,
+                  uint32_t *__restrict__ ranks)
 {
     __shared__ __attribute__((aligned(16))) MidSelectLds L;
     constexpr uint32_t WAVES = kSmallUnitThreads / 64, WPT = kMidPlaces / 64 / kSmallUnitThreads;          // bit map words per thread
