@@ -1045,7 +1045,8 @@ __device__ __forceinline__ void tile_pos(const BatchMeta<TILES> &m, int tid, uin
     }
     const uint32_t half = at < 32u ? (uint32_t)mine : (uint32_t)(mine >> 32);
     *b = (uint32_t)LOW + ((half >> (at & 31u)) & 1u);
-    *rel = (uint32_t)LOW * tile + before + bits_below_me(mine);
+    const uint32_t below = bits_below_me(mine);
+    *rel = (uint32_t)LOW * tile + before + below;
     *total4 = tot;
 }
 
@@ -1180,7 +1181,9 @@ __device__ __forceinline__ TileRange tile_range(const float *x)
     mx = __builtin_fmaxf(mx, x[G - 1]);
     if constexpr (LPT >= 2) { mn = __builtin_fminf(mn, lane_xor<1>(mn)); mx = __builtin_fmaxf(mx, lane_xor<1>(mx)); }
     if constexpr (LPT >= 4) { mn = __builtin_fminf(mn, lane_xor<2>(mn)); mx = __builtin_fmaxf(mx, lane_xor<2>(mx)); }
-    return {mn + 0.0f, mx + 0.0f};
+    mn = mn + 0.0f;
+    mx = mx + 0.0f;
+    return {mn, mx};
 }
 
 // Step 2: quantizer parameters of the tile from its range, codes of my G elements of it, and their LSB-first bit string written
@@ -1354,7 +1357,8 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
     }
     __syncthreads();                             // the rows are dead: their LDS becomes the payload buffer
     if (valid) {
-        const uint32_t meta16 = quantize_values<G, LOW>(x, tile_range<G, 1>(x), (inf & 0x100u) ? WIDE : (uint32_t)LOW, pay + (inf >> 9));
+        const uint32_t width = (inf & 0x100u) ? WIDE : (uint32_t)LOW;
+        const uint32_t meta16 = quantize_values<G, LOW>(x, tile_range<G, 1>(x), width, pay + (inf >> 9));
         const uint64_t j = j0 + t;
         reinterpret_cast<uint16_t *>(packed + lay.scale)[j] = (uint16_t)meta16;
         reinterpret_cast<uint16_t *>(packed + lay.zero)[j] = (uint16_t)(meta16 >> 16);
