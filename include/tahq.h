@@ -163,11 +163,10 @@ enum {
     TAHQ_PHASE_QUANT = 8,      /* Eq. 3 (or the entropy phase's), Eq. 4, quantize, pack  [Sec. 3.3-3.4] */
     TAHQ_PHASE_ALL = 15,
     /* Not a phase but an option, OR-ed into `phases`: rank every ranking unit with the general
-     * multi-launch selection.  By default units of up to 98304 tiles (98241 where units are no multiple of 64
-     * tiles) of a small tensor are ranked by the quantizer's launch if the call has the entropy, selection
-     * and quantizer phases; otherwise one workgroup ranks a unit of up to 32768 tiles (32705) in a single
-     * launch, and so it does with up to 65536 tiles
-     * (65473) unless the tensor is bf16 with 2^25 elements or more (and eps_l1 in [1e-30, 1e30],
+     * multi-launch selection.  By default the unit of a small tensor, of up to 98304 tiles, or its units of up
+     * to 86016 each (85953 where they are no multiple of 64 tiles), are ranked by the quantizer's launch if the
+     * call has the entropy, selection and quantizer phases; otherwise one workgroup ranks a unit of up to 32768
+     * tiles (32705) in a single launch, and so it does with up to 65536 tiles (65473) unless the tensor is bf16 with 2^25 elements or more (and eps_l1 in [1e-30, 1e30],
      * eps_log in [1e-12, 2^-24], as by default), or has more than 256 units; larger
      * units are ranked in two launches from a histogram the entropy phase builds
      * (allocation tiles of several quantization tiles excepted).  Same result; meant for tests and timing.  Pass it with

@@ -11,8 +11,10 @@ constexpr int kCrewThreads = 1024, kCrewWaves = kCrewThreads / 64;
 // histogram in the entropy pass above), at 3.8 bits: one unit of 32768 tiles G = 16 14.9 -> 11.2 us, 49152 20.3 -> 13.5,
 // 65536 22.6 -> 15.7, 77700 28.5 -> 17.7, 98304 29.3 -> 20.1, 131072 29.1 -> 24.8, 163840 30.4 -> 29.0; G = 64 49152 23.7 -> 16.0, 98304
 // 34.2 -> 26.0, 114688 35.5 -> 30.2; [3,777,1600] G = 16 at 2.25 bits 29.0 -> 23.7.  Ends where a threshold among tiles that are alike,
-// which takes four passes, would cost more than the other way (128000 tiles G = 32, a fifth of them all zero: 41.3 and 40.7).
-constexpr uint32_t kCrewPlaces = 28672, kCrewMost = 98304;
+// which takes four passes, costs clearly more than the other way: a fifth of the tokens constant, G = 8, one unit of 90112 tiles 35.3 ->
+// 35.7, 98304 36.7 -> 38.2 (ordinary ones 25.7 -> 20.8), two of 86016 37.4 -> 35.3, 90112 34.5 -> 36.2, 98304 35.4 -> 38.6; fp32 G = 16
+// two of 98304 ordinary tiles 26.4 -> 27.9.
+constexpr uint32_t kCrewPlaces = 28672, kCrewMost = 98304, kCrewMostOfSeveral = 86016;
 // Bins of 2048 neighbouring floats, two octaves below ln A: half as wide as k_select_small's, so that half as many tiles have to be
 // placed directly.
 constexpr uint32_t kCrewBins = 8192;

@@ -3,7 +3,8 @@
 // Entropies map to order-preserving 32-bit keys; five ways to find the k-th largest key K*, how many tiles equal to
 // K* are still wanted (`take`), and from them the bit map and the rank table:
 //
-//   * ranking units of at most 98304 tiles in tensors of one round of workgroups: in the quantizer's launch (tahq_rank_quant.hpp);
+//   * ranking units of at most 86016 tiles (98304 where there is one) in tensors of one round of workgroups: in the quantizer's launch
+//     (tahq_rank_quant.hpp);
 //   * other ranking units of at most 32768 tiles (32705 where units start off the 64-tile boundaries): k_select_small, one workgroup per
 //     unit in one launch (entropies and a histogram in LDS, the threshold's bin ranked directly), because at that size several
 //     launches cost more than the work;

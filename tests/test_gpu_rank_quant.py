@@ -50,7 +50,8 @@ def test_batches_and_units_of_all_lengths(G, f32):
             _check(x, B, n, G, G, float(np.float32(budget)))
 
 
-@pytest.mark.parametrize("n,B", ((28672, 1), (28673, 1), (28609, 2), (28610, 2), (16383, 4), (16384, 4), (65537, 2), (98304, 1), (98305, 1), (98241, 2), (98242, 2)))
+@pytest.mark.parametrize("n,B", ((28672, 1), (28673, 1), (28609, 2), (28610, 2), (16383, 4), (16384, 4), (65537, 2), (86016, 2), (86017, 2), (85953, 2), (85954, 2), (98304, 1),
+                                 (98305, 1), (98241, 2), (98242, 2)))
 def test_the_largest_units(n, B):
     rng = np.random.default_rng(n)
     x = np.ascontiguousarray(_values(rng, (B, n, 8), False))
@@ -60,9 +61,12 @@ def test_the_largest_units(n, B):
 
 
 @pytest.mark.parametrize("G,n,B,f32", ((64, 17500, 4, False), (64, 17500, 4, True), (64, 16384, 8, True), (32, 25600, 5, True), (32, 40001, 2, False),
-                                       (16, 33333, 4, True), (16, 77700, 3, False), (64, 50001, 1, True), (128, 30000, 1, False)))
+                                       (16, 33333, 4, True), (16, 77700, 3, False), (64, 50001, 1, True), (128, 30000, 1, False), (128, 12287, 1, True),
+                                       (128, 12288, 1, True), (128, 20480, 2, True), (128, 20481, 2, True), (128, 32769, 1, True), (128, 40960, 1, True),
+                                       (128, 40961, 1, True), (64, 23001, 3, True), (64, 40960, 2, True)))
 def test_as_many_tiles_as_fit_one_round(G, n, B, f32):
-    # lanes of more elements, entropies in LDS and from memory; the smaller thresholds' bins hold hundreds of tiles
+    # lanes of more elements, entropies in LDS and from memory; the smaller thresholds' bins hold hundreds of tiles; fp32 lanes of 128
+    # bytes on both sides of the lines between which they are taken
     x = np.ascontiguousarray(_values(np.random.default_rng(n), (B, n, G), f32))
     for budget in (3.07, 3.5, 3.8):
         print(f"[case] {B} units of {n} tiles of {G}, fp32 {f32}, budget {budget}", flush=True)
