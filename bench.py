@@ -3,7 +3,7 @@
 One step = tahq_encode + tahq_decode of one micro-batch of synthetic activations that is already resident in HBM.
 Prints ONE JSON line: encode+decode GB/s of input activations (and the share of the HBM peak, on the bytes the method must
 move and on the bytes the counters saw), encode and decode times from events, the roofline of the dominant kernel
-(measured live with events on the launch stream), a plain-copy ceiling measured in the same run, the decode time with
+(measured live with events on the launch stream, behind the timed region), a plain-copy ceiling measured in the same run, the decode time with
 fp32 output, and the CPU oracle's throughput on a bounded sample of the same workload.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--config 4] [--alloc-tile A] [--no-cpu-baseline]
@@ -332,41 +332,43 @@ def main():
     torch.cuda.synchronize()
     warm_ms = {nm: float(np.median([e[i].elapsed_time(e[i + 1]) for e in wev])) for i, nm in enumerate(names)}
     alg = algorithmic_bytes(w, packed_size, T, select)
-    # with A > G the entropy phase is several kernels (two passes over the tensor): not a roofline candidate
-    streaming = {nm: warm_ms[nm] for nm in alg if (nm != "k_entropy" or (select and not wide))}
+    # with A > G the entropy phase is several kernels (two passes over the tensor): not a roofline candidate.  A tensor of up to
+    # 262144 tiles may be ranked in the quantizer's launch when encoded in one call: its phases one by one are other kernels.
+    one_call_differs = select and not wide and T <= 262144
+    streaming = {nm: warm_ms[nm] for nm in alg
+                 if nm == "k_decode" or not one_call_differs and (nm != "k_entropy" or (select and not wide))}
     dominant = max(streaming, key=streaming.get)
 
-    def plain_step():
+    def plain_step(mid=None):
         tahq.tahq_encode(cfg, d_in, codec.packed, codec.workspace, stream)
+        if mid:
+            mid.record(stream)
         tahq.tahq_decode(cfg, codec.packed, codec.out, codec.out_dtype, stream)
 
-    # the timed step: tahq_encode and tahq_decode.  One event per step boundary (per-step times, their median);
-    # every EVENT_EVERY-th step also carries an event between encode and decode, and tahq_encode is split there where
-    # the dominant kernel needs its two events.
+    # the timed step: tahq_encode and tahq_decode, each one call.  One event per step boundary (per-step times, their median);
+    # every EVENT_EVERY-th step also carries an event between encode and decode.  Behind the timed region follow as many steps in
+    # which tahq_encode is split where the dominant kernel needs its two events.
     before = {"k_entropy": P.PHASE_PROLOGUE, "k_quant_pack": P.PHASE_PROLOGUE | P.PHASE_ENTROPY | P.PHASE_SELECT,
               "k_decode": P.PHASE_ALL}[dominant]
     own = {"k_entropy": P.PHASE_ENTROPY, "k_quant_pack": P.PHASE_QUANT, "k_decode": 0}[dominant]
     after = P.PHASE_ALL & ~(before | own)
 
-    def split_step(e0, e1, mid):
+    def split_step(e0, e1):
         tahq.tahq_encode_phases(cfg, d_in, codec.packed, codec.workspace, before, stream)
+        e0.record(stream)
         if own:
-            e0.record(stream)
             tahq.tahq_encode_phases(cfg, d_in, codec.packed, codec.workspace, own, stream)
             e1.record(stream)
             if after:
                 tahq.tahq_encode_phases(cfg, d_in, codec.packed, codec.workspace, after, stream)
-            mid.record(stream)
-            tahq.tahq_decode(cfg, codec.packed, codec.out, codec.out_dtype, stream)
-        else:
-            mid.record(stream)
-            e0.record(stream)
-            tahq.tahq_decode(cfg, codec.packed, codec.out, codec.out_dtype, stream)
+        tahq.tahq_decode(cfg, codec.packed, codec.out, codec.out_dtype, stream)
+        if not own:
             e1.record(stream)
 
     EVENT_EVERY = 4
     n_split = (args.steps + EVENT_EVERY - 1) // EVENT_EVERY
-    evs = [(new_event(), new_event(), new_event()) for _ in range(n_split)]
+    mids = [new_event() for _ in range(n_split)]
+    evs = [(new_event(), new_event()) for _ in range(n_split)]
     bounds = [new_event() for _ in range(args.steps + 1)]
 
     n_settle = settle_steps(args, sum(warm_ms.values()))
@@ -376,22 +378,26 @@ def main():
     t0 = time.perf_counter()
     for i in range(args.steps):
         bounds[i].record(stream)
-        if i % EVENT_EVERY == 0:
-            split_step(*evs[i // EVENT_EVERY])
-        else:
-            plain_step()
+        plain_step(mids[i // EVENT_EVERY] if i % EVENT_EVERY == 0 else None)
     bounds[args.steps].record(stream)
     torch.cuda.synchronize()
     t1 = time.perf_counter()
+    for _ in range(10):                              # (the queue is empty behind the synchronization)
+        plain_step()
+    for e0, e1 in evs:
+        split_step(e0, e1)
+        for _ in range(EVENT_EVERY - 1):
+            plain_step()
+    torch.cuda.synchronize()
 
     wall_ms = (t1 - t0) * 1e3 / args.steps
     step_ms = [bounds[i].elapsed_time(bounds[i + 1]) for i in range(args.steps)]
     median_ms = float(np.median(step_ms))
     ms_per_step = median_ms if args.steps >= 50 else wall_ms
     value = nbytes / (ms_per_step * 1e-3) / 1e9
-    encode_ms = float(np.median([bounds[EVENT_EVERY * j].elapsed_time(evs[j][2]) for j in range(n_split)]))
-    decode_ms = float(np.median([evs[j][2].elapsed_time(bounds[EVENT_EVERY * j + 1]) for j in range(n_split)]))
-    dom_ms = float(np.mean([e0.elapsed_time(e1) for e0, e1, _ in evs]))
+    encode_ms = float(np.median([bounds[EVENT_EVERY * j].elapsed_time(mids[j]) for j in range(n_split)]))
+    decode_ms = float(np.median([mids[j].elapsed_time(bounds[EVENT_EVERY * j + 1]) for j in range(n_split)]))
+    dom_ms = float(np.mean([e0.elapsed_time(e1) for e0, e1 in evs]))
     achieved = alg[dominant] / (dom_ms * 1e-3) / 1e9
 
     # a plain device copy of the input tensor and a plain fill of as many bytes, right after the timed region (the GPU

@@ -63,3 +63,26 @@ def test_backward_bench_line():
     rf = d["roofline"]
     assert rf["kernel"] in ("k_naive_encode", "k_naive_decode") and 0.05 < rf["frac"] < 1.0
     assert rf["algorithmic_bytes_per_launch"] == 335544320 + 167772224
+
+
+@pytest.mark.parametrize("shape", ("2x1024x1600", "4x1024x4096"))
+def test_timed_steps_encode_in_one_call(shape):
+    # ten settling steps and the four timed ones in a row, none of them by phases, which small tensors take another way
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"[case] bench.py, calls of the encoder at {shape}", file=sys.stderr, flush=True)
+    code = ("import sys\n"
+            "import bench, paper_2506_01352_amd as t\n"
+            "calls, one, by_phases = [], t.tahq_encode, t.tahq_encode_phases\n"
+            "t.tahq_encode = lambda *a, **k: (calls.append('E'), one(*a, **k))[1]\n"
+            "t.tahq_encode_phases = lambda *a, **k: (calls.append('A' if a[4] == t.PHASE_ALL else 'p'), by_phases(*a, **k))[1]\n"
+            f"sys.argv = ['bench.py', '--steps', '4', '--warmup', '2', '--settle', '10', '--settle-ms', '0', '--no-cpu-baseline',\n"
+            f"            '--no-extras', '--shape', '{shape}', '--budget', '3.8']\n"
+            "bench.main()\n"
+            "print(''.join(calls))\n")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=280, cwd=ROOT)
+    assert r.returncode == 0, r.stderr[-2000:]
+    line, calls = r.stdout.strip().splitlines()
+    assert calls.startswith("p" * 8 + "E" * 14)                 # two warm-up steps phase by phase
+    if shape == "2x1024x1600":
+        assert json.loads(line)["roofline"]["kernel"] == "k_decode" and "p" not in calls[8:]
