@@ -83,6 +83,12 @@ def stored_valu(stem):
     return (per_kernel, "profiles/" + name) if per_kernel else (None, None)
 
 
+def quantizer_kernel(bf16, tile, T):
+    """Name of the quantizer of a tensor of T tiles when it is a launch of its own: by workgroups where a lane has a bf16 tile of 32 or
+    64 channels, which tensors of few tiles spread over four lanes, by wavefronts otherwise."""
+    return "k_quant_pack" if bf16 and tile in (32, 64) and T >= 32768 else "k_quant_by_wave"
+
+
 def algorithmic_bytes(w, packed_size, T, select):
     """Bytes each kernel must move per launch (per-element figures x elements of one launch)."""
     del select
@@ -91,7 +97,7 @@ def algorithmic_bytes(w, packed_size, T, select):
         # entropy kernel: reads the tensor once, writes one float per tile
         "k_entropy": n * e + 4 * T,
         # quantize+pack kernel: reads the tensor once, reads bit map + ranks, writes the stream
-        "k_quant_pack": n * e + packed_size,
+        quantizer_kernel(w.dtype == 1, w.tile, T): n * e + packed_size,
         # decode kernel: reads the stream once, writes the tensor once
         "k_decode": packed_size + n * e,
     }
@@ -311,8 +317,11 @@ def main():
         return torch.cuda.Event(enable_timing=True)
 
     P = tahq
-    PHASES = [("prologue", P.PHASE_PROLOGUE), ("k_entropy", P.PHASE_ENTROPY), ("select", P.PHASE_SELECT),
-              ("k_quant_pack", P.PHASE_QUANT)]
+    # A tensor of up to 262144 tiles may be ranked in the quantizer's launch when encoded in one call: its phases one by one are other
+    # kernels.
+    one_call_differs = select and not wide and T <= 262144
+    quantizer = "quantizer" if one_call_differs else quantizer_kernel(w.dtype == P.BF16, w.tile, T)
+    PHASES = [("prologue", P.PHASE_PROLOGUE), ("k_entropy", P.PHASE_ENTROPY), ("select", P.PHASE_SELECT), (quantizer, P.PHASE_QUANT)]
 
     def instrumented_step(events):
         """Every phase of tahq_encode as a call of its own, and tahq_decode, with an event between each."""
@@ -332,9 +341,7 @@ def main():
     torch.cuda.synchronize()
     warm_ms = {nm: float(np.median([e[i].elapsed_time(e[i + 1]) for e in wev])) for i, nm in enumerate(names)}
     alg = algorithmic_bytes(w, packed_size, T, select)
-    # with A > G the entropy phase is several kernels (two passes over the tensor): not a roofline candidate.  A tensor of up to
-    # 262144 tiles may be ranked in the quantizer's launch when encoded in one call: its phases one by one are other kernels.
-    one_call_differs = select and not wide and T <= 262144
+    # with A > G the entropy phase is several kernels (two passes over the tensor): not a roofline candidate
     streaming = {nm: warm_ms[nm] for nm in alg
                  if nm == "k_decode" or not one_call_differs and (nm != "k_entropy" or (select and not wide))}
     dominant = max(streaming, key=streaming.get)
@@ -348,9 +355,9 @@ def main():
     # the timed step: tahq_encode and tahq_decode, each one call.  One event per step boundary (per-step times, their median);
     # every EVENT_EVERY-th step also carries an event between encode and decode.  Behind the timed region follow as many steps in
     # which tahq_encode is split where the dominant kernel needs its two events.
-    before = {"k_entropy": P.PHASE_PROLOGUE, "k_quant_pack": P.PHASE_PROLOGUE | P.PHASE_ENTROPY | P.PHASE_SELECT,
+    before = {"k_entropy": P.PHASE_PROLOGUE, quantizer: P.PHASE_PROLOGUE | P.PHASE_ENTROPY | P.PHASE_SELECT,
               "k_decode": P.PHASE_ALL}[dominant]
-    own = {"k_entropy": P.PHASE_ENTROPY, "k_quant_pack": P.PHASE_QUANT, "k_decode": 0}[dominant]
+    own = {"k_entropy": P.PHASE_ENTROPY, quantizer: P.PHASE_QUANT, "k_decode": 0}[dominant]
     after = P.PHASE_ALL & ~(before | own)
 
     def split_step(e0, e1):

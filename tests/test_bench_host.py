@@ -101,3 +101,23 @@ def test_settling_steps_follow_the_requested_time():
     assert bench.settle_steps(NS(settle=500, settle_ms=150.0), 0.37) == 500
     assert bench.settle_steps(NS(settle=10, settle_ms=150.0), 0.001) == 20000
     assert bench.settle_steps(NS(settle=10, settle_ms=150.0), 0.0) == 10
+
+
+def test_counters_are_those_of_the_quantizer_that_runs():
+    # bf16 tiles of 128 channels are quantized by wavefronts, configurations 4 and 5 by workgroups; a line joins a kernel's time with
+    # its own counters only
+    sys.path.insert(0, ROOT)
+    import bench
+    import workloads
+    names = {}
+    for index in (3, 4, 5):
+        w = workloads.CONFIGS[index - 1]
+        names[index] = bench.quantizer_kernel(w.dtype == 1, w.tile, w.elements // w.tile)
+        per, _, _ = bench.stored_traffic(f"hbm_traffic_cfg{index}_bf16_{w.batch}x{w.seq}x{w.hidden}_g{w.tile}")
+        assert {n for n in per if "quant" in n} == {names[index]}
+        assert names[index] in bench.algorithmic_bytes(w, 0, w.elements // w.tile, True)
+    assert names == {3: "k_quant_by_wave", 4: "k_quant_pack", 5: "k_quant_pack"}
+    valu, _ = bench.stored_valu("valu_counters_cfg3_bf16_8x1024x4096_g128")
+    assert set(valu) == {"k_quant_by_wave", "k_decode"}
+    assert bench.quantizer_kernel(False, 64, 1 << 20) == bench.quantizer_kernel(True, 16, 1 << 20) == "k_quant_by_wave"
+    assert bench.quantizer_kernel(True, 64, 32768) == "k_quant_pack" and bench.quantizer_kernel(True, 64, 32767) == "k_quant_by_wave"
