@@ -1,4 +1,5 @@
-"""Ranking units of 32769 to 65536 tiles, ranked by one workgroup from its registers, against the oracle."""
+"""Ranking units of 32769 to 65536 tiles against the oracle: by phases, where one workgroup ranks each from its registers, as it does in
+one call of larger tensors, and in one call, which ranks those of small tensors in the quantizer's launch."""
 import numpy as np
 import pytest
 import torch
@@ -12,15 +13,26 @@ pytestmark = pytest.mark.gpu
 G = 8
 
 
+def _encode_by_phases(cfg, d, codec):
+    codec.workspace.fill_(0xFF)
+    codec.packed.fill_(0xFF)
+    for phase in (tahq.PHASE_PROLOGUE, tahq.PHASE_ENTROPY, tahq.PHASE_SELECT, tahq.PHASE_QUANT):
+        tahq.tahq_encode_phases(cfg, d, codec.packed, codec.workspace, phase)
+
+
 def _check(x, B, S, C, budget, scope=0):
     cfg = tahq.make_config(B, S, C, G, tahq.BF16, budget, scope=scope)
     codec = tahq.Codec(cfg, device="cuda")
     codec.workspace.fill_(0xFF)
     codec.packed.fill_(0xFF)
-    codec.encode(torch.from_numpy(x.view(np.int16)).cuda())
+    d = torch.from_numpy(x.view(np.int16)).cuda()
+    codec.encode(d)
+    apart = tahq.Codec(cfg, device="cuda")
+    _encode_by_phases(cfg, d, apart)
     torch.cuda.synchronize()
     want = o32.encode(o32.make_cfg(B, S, C, G, o32.BF16, budget, scope=scope), x)
     assert np.array_equal(codec.packed.cpu().numpy(), want), "stream differs from the oracle"
+    assert np.array_equal(apart.packed.cpu().numpy(), want), "stream of the phases one by one differs from the oracle"
 
 
 @pytest.mark.parametrize("tiles", (32769, 32832, 40001, 49152, 65473, 65474, 65535, 65536, 65537))
@@ -37,7 +49,8 @@ def test_units_of_all_lengths(tiles):
 @pytest.mark.parametrize("share,how", ((0.02, "zero"), (0.4, "zero"), (0.4, "constant"), (1.0, "constant"), (0.3, "one-hot"), (0.01, "nan")))
 @pytest.mark.parametrize("tiles,scope", ((40000, 0), (27001, 1)))
 def test_crowds_at_the_threshold(tiles, scope, share, how):
-    # tiles of one entropy, more and fewer than are placed directly, with the threshold above, among and below them
+    # tiles of one entropy, more and fewer than are placed directly, with the threshold above, among and below them (3 x 27001
+    # tiles as one unit, by phases: in two launches)
     rng = np.random.default_rng(int(100 * share) + tiles)
     x = rng.standard_normal((3, tiles, G)).astype(np.float32)
     at = rng.random((3, tiles)) < share
@@ -46,11 +59,12 @@ def test_crowds_at_the_threshold(tiles, scope, share, how):
     if how == "nan":                                     # (outside the contract; the two selections agree)
         d = torch.from_numpy(x.view(np.int16)).cuda()
         cfg = tahq.make_config(3, tiles, G, G, tahq.BF16, 3.5, scope=scope)
-        a, b = tahq.Codec(cfg, device="cuda"), tahq.Codec(cfg, device="cuda")
+        a, b, c = (tahq.Codec(cfg, device="cuda") for _ in range(3))
         a.encode(d)
         tahq.tahq_encode_phases(cfg, d, b.packed, b.workspace, tahq.PHASE_ALL | tahq.SELECT_MULTI_LAUNCH)
+        _encode_by_phases(cfg, d, c)
         torch.cuda.synchronize()
-        assert torch.equal(a.packed, b.packed)
+        assert torch.equal(a.packed, b.packed) and torch.equal(c.packed, b.packed)
         return
     for budget in (3.005, 3.3, 3.62, 3.85, 3.995):
         print(f"[case] {tiles} tiles, scope {scope}, {share} {how}, budget {budget}", flush=True)
@@ -85,8 +99,11 @@ def test_entropies_of_all_bits_set(tiles, scope, share):
             c.packed.fill_(0xFF)
         a.encode(d)
         tahq.tahq_encode_phases(cfg, d, b.packed, b.workspace, tahq.PHASE_ALL | tahq.SELECT_MULTI_LAUNCH)
+        apart = tahq.Codec(cfg, device="cuda")
+        _encode_by_phases(cfg, d, apart)
         torch.cuda.synchronize()
         assert torch.equal(a.packed, b.packed), "the two selections differ"
+        assert torch.equal(apart.packed, b.packed), "the selection of the phases one by one differs"
         T = B * tiles
         chosen = np.unpackbits(a.packed[64:64 + -(-T // 64) * 8].cpu().numpy(), bitorder="little").sum()
         assert int(chosen) == units * tahq.tahq_k_per_unit(cfg)

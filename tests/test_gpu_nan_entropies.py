@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype", (tahq.F32, tahq.BF16))
 @pytest.mark.parametrize("G", (8, 16, 32, 64, 128))
-# units of one workgroup, of its registers, of two launches, and (bf16) of approximate entropies
+# units that the phases one by one rank by one workgroup, from its registers, in two launches (the one call ranks most of them in the
+# quantizer's launch), and (bf16) of approximate entropies
 @pytest.mark.parametrize("B,tiles,scope", ((3, 1024, 0), (2, 40960, 1), (3, 77700, 0), (1, 98304, 0), (1, 0, 0)))
 def test_tiles_of_any_bits(B, tiles, scope, G, dtype):
     if tiles == 0:
@@ -39,3 +40,9 @@ def test_tiles_of_any_bits(B, tiles, scope, G, dtype):
         tahq.tahq_encode_phases(cfg, d, b.packed, b.workspace, tahq.PHASE_ALL | tahq.SELECT_MULTI_LAUNCH)
         torch.cuda.synchronize()
         assert torch.equal(a.packed, b.packed), "the two selections differ"
+        a.packed.fill_(0xFF)
+        a.workspace.fill_(0xFF)
+        for phase in (tahq.PHASE_PROLOGUE, tahq.PHASE_ENTROPY, tahq.PHASE_SELECT, tahq.PHASE_QUANT):
+            tahq.tahq_encode_phases(cfg, d, a.packed, a.workspace, phase)
+        torch.cuda.synchronize()
+        assert torch.equal(a.packed, b.packed), "the selection of the phases one by one differs"

@@ -71,15 +71,22 @@ def run_gpu(tahq, cfg, x, out_dtype, want_alloc_entropy=False):
     ws.view.fill_(0x3C)         # the encoder must not rely on what the call above left behind
     tahq.tahq_encode(cfg, d_in, packed.view, ws.view)
     tahq.tahq_decode(cfg, packed.view, out.view, out_dtype)
-    # the same encode with the general multi-launch selection (small ranking units take a single-launch path
-    # by default): byte-identical stream
+    # the same encode with the general multi-launch selection (small ranking units take single launches by default):
+    # byte-identical stream
     packed2 = Guarded(tahq.tahq_packed_size(cfg))
     ws.view.fill_(0xC3)
     tahq.tahq_encode_phases(cfg, d_in, packed2.view, ws.view, tahq.PHASE_ALL | tahq.SELECT_MULTI_LAUNCH)
+    # and phase by phase, which ranks the units of small tensors in the selections that larger tensors take (the one call ranks
+    # them in the quantizer's launch)
+    packed3 = Guarded(tahq.tahq_packed_size(cfg))
+    ws.view.fill_(0x69)
+    for phase in (tahq.PHASE_PROLOGUE, tahq.PHASE_ENTROPY, tahq.PHASE_SELECT, tahq.PHASE_QUANT):
+        tahq.tahq_encode_phases(cfg, d_in, packed3.view, ws.view, phase)
     torch.cuda.synchronize()
-    for g in (packed, packed2, ws, ent, ent_a, out):
+    for g in (packed, packed2, packed3, ws, ent, ent_a, out):
         g.check()
     assert torch.equal(packed.view, packed2.view), "single-launch and multi-launch selection disagree"
+    assert torch.equal(packed.view, packed3.view), "the one call and its phases disagree"
     H = ent.view.cpu().numpy().view(np.float32)
     o = out.view.cpu().numpy().view(np.float32 if out_dtype == tahq.F32 else np.uint16)
     if want_alloc_entropy:
@@ -603,8 +610,8 @@ def test_hidden_size_1600_and_small_tiles_on_a_workload(tahq, G):
 @pytest.mark.parametrize("B,S,Cc,G", [(1, 1000, 1600, 64), (2, 1024, 1024, 32), (1, 700, 4096, 64), (1, 513, 2048, 32),
                                        (3, 1024, 1024, 64), (2, 260, 8064, 64)])
 def test_ranking_units_of_every_single_launch_size(tahq, B, S, Cc, G):
-    # units of 25000 / 32768 / 44800 / 32832 / 16384 / 32760 tiles: every keys-per-thread variant of the single-launch
-    # selection, aligned and not aligned to 64 tiles, with all-zero tokens (massive ties) and near-constant tokens
+    # units of 25000 / 32768 / 44800 / 32832 / 16384 / 32760 tiles: every variant of the single-launch selections (by phases) and
+    # of the quantizer's launch, aligned and not aligned to 64 tiles, with all-zero tokens (massive ties) and near-constant tokens
     rng = np.random.default_rng(B * S + Cc + G)
     x = rng.standard_normal((B, S, Cc)).astype(np.float32)
     x[:, :, 3::97] *= 20.0
@@ -633,7 +640,8 @@ def test_single_launch_selection_at_the_edges_of_its_sizes(tahq, B, S, Cc, G, A)
 
 @pytest.mark.parametrize("crowd", (1, 255, 256, 257, 1500))
 def test_single_launch_selection_with_a_crowded_threshold_bin(tahq, crowd):
-    # `crowd` tiles of equal entropy, in a bin of their own, hold the threshold: up to 256 are placed directly
+    # `crowd` tiles of equal entropy, in a bin of their own, hold the threshold: up to 256 are placed directly (by the selection of the
+    # phases one by one, and by the one call's)
     rng = np.random.default_rng(crowd)
     n, G = 2000, 16
     x = rng.standard_normal((2, n, G)).astype(np.float32)
@@ -667,7 +675,7 @@ def test_single_launch_selection_with_crowds_in_the_lowest_bin(tahq, n):
 
 @pytest.mark.parametrize("S,M", [(143, 7), (20, 1613), (317, 257)])
 def test_non_finite_entropies_off_the_64_tile_boundaries_follow_key_order(tahq, S, M):
-    # units for one launch and for two, that share bit map words; NaN entropies among the widest and, with the sign bit set,
+    # units for one launch and (by phases) for two, that share bit map words; NaN entropies among the widest and, with the sign bit set,
     # among the narrowest: run_gpu compares with the multi-launch selection, which ranks by the keys' digits
     G = 16
     rng = np.random.default_rng(S)
@@ -713,9 +721,10 @@ def test_more_lanes_per_tile_up_to_the_tensor_sizes_that_take_fewer(tahq, G, dty
                                  (2, 65537), (2, 65599), (3, 81919), (2, 81921), (2, 98305), (5, 70001)])
 @pytest.mark.parametrize("ties", (False, True))
 def test_large_units_off_the_64_tile_boundaries(tahq, B, n, ties):
-    # units of up to 65473 tiles: one workgroup's registers; beyond, the two-launch selection of units that share bit map words: blocks of 16384 places that a unit fills, overhangs by a few
-    # places or does not reach; batches of the entropy kernel that hold two units; `ties`: more tiles in the threshold's bin
-    # than the candidate list takes
+    # by phases, units of up to 65473 tiles: one workgroup's registers; beyond, the two-launch selection of units that share bit map
+    # words: blocks of 16384 places that a unit fills, overhangs by a few places or does not reach; batches of the entropy kernel
+    # that hold two units; `ties`: more tiles in the threshold's bin than the candidate list takes.  The one call ranks all but
+    # (2, 98305) and (5, 70001) in the quantizer's launch
     G = 16
     rng = np.random.default_rng(B * n + ties)
     x = rng.standard_normal((B, n, G)).astype(np.float32)
@@ -733,7 +742,7 @@ def test_large_units_off_the_64_tile_boundaries(tahq, B, n, ties):
 @pytest.mark.parametrize("spread", (0.05, 0.01, 0.003, 1e-3))
 def test_large_units_of_nearly_equal_tiles(tahq, B, n, spread):
     # entropies within a few bins, a few sub-bins or one sub-bin below ln G: the crowd's way with a short list of candidates, with
-    # a long one, and with too many for a list that are not all alike
+    # a long one, and with too many for a list that are not all alike (40001 tiles: by phases ranked from registers)
     G = 16
     rng = np.random.default_rng(n)
     x = (1.0 + spread * rng.standard_normal((B, n, G))).astype(np.float32)
@@ -746,7 +755,8 @@ def test_large_units_of_nearly_equal_tiles(tahq, B, n, spread):
                                      (70001, 1024), (70001, 1025), (70001, 2400), (70001, 2600)])
 def test_large_units_with_alike_tiles_at_the_threshold(tahq, n, alike):
     # tiles of one entropy in a bin of their own, or with a one-hot tile and one of a single dominant element beside them: placed
-    # from the candidate list one by one or by runs of places, or as a crowd by index alone
+    # from the candidate list one by one or by runs of places, or as a crowd by index alone (70001: by phases; 40001, by phases: from
+    # registers)
     G = 16
     rng = np.random.default_rng(alike)
     for value in (1.5, 0.0):
@@ -765,7 +775,8 @@ def test_large_units_with_alike_tiles_at_the_threshold(tahq, n, alike):
 @pytest.mark.parametrize("B,S,M,G,zeros", [(3, 777, 100, 16, 0.2), (1, 4097, 160, 32, 0.2), (2, 4097, 140, 8, 0.4), (1, 8193, 129, 64, 0.0)])
 def test_crowded_units_give_the_same_bytes_on_every_replay(tahq, B, S, M, G, zeros):
     # which workgroup settles a crowd is a matter of which one is last: replays of a captured encode over poisoned buffers, with
-    # eager work between them, against the multi-launch selection, which knows no crowds
+    # eager work between them, against the multi-launch selection, which knows no crowds.  In one call and in two by phases, which
+    # takes the first to the two-launch selection, too
     gen = torch.Generator(device="cuda")
     gen.manual_seed(S + M)
     x = torch.randn(B, S, M * G, device="cuda", generator=gen)
@@ -778,15 +789,19 @@ def test_crowded_units_give_the_same_bytes_on_every_replay(tahq, B, S, M, G, zer
     tahq.tahq_encode_phases(cfg, x, packed.view, ws.view, tahq.PHASE_ALL | tahq.SELECT_MULTI_LAUNCH)
     want = packed.view.clone()
     torch.cuda.synchronize()
-    graph = torch.cuda.CUDAGraph()
+    graph, apart = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         tahq.tahq_encode(cfg, x, packed.view, ws.view)
+    with torch.cuda.graph(apart):
+        tahq.tahq_encode_phases(cfg, x, packed.view, ws.view, tahq.PHASE_PROLOGUE | tahq.PHASE_ENTROPY)
+        tahq.tahq_encode_phases(cfg, x, packed.view, ws.view, tahq.PHASE_SELECT | tahq.PHASE_QUANT)
     for i in range(12):
-        packed.view.fill_(0xFF if i % 2 else 0)
-        ws.view.fill_((37 * i) & 0xFF)
-        graph.replay()
-        torch.cuda.synchronize()
-        assert torch.equal(packed.view, want), f"replay {i}"
+        for way in (graph, apart):
+            packed.view.fill_(0xFF if i % 2 else 0)
+            ws.view.fill_((37 * i) & 0xFF)
+            way.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(packed.view, want), f"replay {i}, {'one call' if way is graph else 'by phases'}"
     packed.check()
     ws.check()
 
@@ -881,7 +896,7 @@ def test_non_finite_entropies_in_large_ranking_units_follow_key_order(tahq, S):
     # the entropy) and the multi-launch radix select (digits of the key) must agree on such a tensor too; run_gpu
     # compares their streams.  The clean sample is checked against the oracle.
     rng = np.random.default_rng(19)
-    G, M = 32, 64                                    # 65536 tiles per sample, one workgroup's; 81920: two launches
+    G, M = 32, 64                                    # 65536 tiles per sample, by phases one workgroup's; 81920: two launches
     x = rng.standard_normal((2, S, M * G)).astype(np.float32)
     clean = x[1:2].copy()
     x[0, 0, 3] = np.nan
