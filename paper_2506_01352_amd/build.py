@@ -1,4 +1,5 @@
 """Compile csrc/*.hip into libtahq.so (gfx950) next to this file."""
+import glob
 import os
 import subprocess
 import tempfile
@@ -23,8 +24,14 @@ FLAGS = [
 ]
 
 
+def _newest_input():
+    """When the sources, or the headers that nearly all of the code is in, were last changed."""
+    headers = glob.glob(os.path.join(HERE, "csrc", "*.hpp")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
+    return max(os.path.getmtime(path) for path in SOURCES + headers)
+
+
 def build(force=True):
-    if not force and os.path.exists(LIB) and os.path.getmtime(LIB) >= max(os.path.getmtime(src) for src in SOURCES):
+    if not force and os.path.exists(LIB) and os.path.getmtime(LIB) >= _newest_input():
         return LIB
     # a compiler for each source, side by side
     with tempfile.TemporaryDirectory() as tmp:
@@ -32,7 +39,7 @@ def build(force=True):
         running = [subprocess.Popen([HIPCC] + FLAGS + ["-c", src, "-o", obj]) for src, obj in zip(SOURCES, objects)]
         codes = [p.wait() for p in running]
         if any(codes):
-            raise subprocess.CalledProcessError(max(codes), HIPCC)
+            raise subprocess.CalledProcessError(next(c for c in codes if c), HIPCC)
         subprocess.run([HIPCC, "--offload-arch=gfx950", "-fPIC", "-shared"] + objects + ["-o", LIB], check=True)
     return LIB
 
