@@ -1,7 +1,7 @@
 // Selection and quantizer in one launch (Sec. 3.2 top-p%, Sec. 3.3 Eq. 3-4, Sec. 3.4), for tensors that are one round of workgroups: every
 // workgroup ranks its tiles' whole unit for itself, while the rows it will quantize are on their way.
 #pragma once
-#include "tahq_select.hpp"
+#include "tahq_rank_common.hpp"
 
 namespace tahq {
 

@@ -8,9 +8,9 @@ import paper_2506_01352_amd as tahq
 
 
 def _kernels():
-    """name -> metadata of every kernel in the library's gfx950 code object (an ELF file inside the host library)."""
+    """(name, metadata) of every kernel in the library's gfx950 code objects (ELF files inside the host library)."""
     blob = open(tahq.library_path(), "rb").read()
-    found = {}
+    found = []
     at = blob.find(b"\x7fELF", 4)
     while at >= 0:
         e_machine, = struct.unpack_from("<H", blob, at + 18)
@@ -29,7 +29,7 @@ def _kernels():
                     desc = pos + 12 + (namesz + 3) // 4 * 4
                     if ntype == 32 and blob[pos + 12:pos + 18] == b"AMDGPU":
                         meta = msgpack.unpackb(blob[desc:desc + descsz], raw=False, strict_map_key=False)
-                        found.update((k[".name"], k) for k in meta["amdhsa.kernels"])
+                        found.extend((k[".name"], k) for k in meta["amdhsa.kernels"])
                     pos = desc + (descsz + 3) // 4 * 4
         at = blob.find(b"\x7fELF", at + 4)
     return found
@@ -37,7 +37,7 @@ def _kernels():
 
 @pytest.fixture(scope="module")
 def kernels():
-    k = _kernels()
+    k = dict(_kernels())
     assert len(k) > 300, "no code object found in the library"
     return k
 
@@ -51,3 +51,9 @@ def test_allocation_tile_entropies_keep_their_wavefronts(kernels):
     for G, wavefronts in ((8, 8), (16, 8), (32, 7), (64, 4), (128, 2)):
         name, = [n for n in kernels if f"k_alloc_entropyILi{G}ELb1E" in n]
         assert 512 // (-(-kernels[name][".vgpr_count"] // 8) * 8) >= wavefronts, name
+
+
+def test_every_kernel_is_in_the_library_once():
+    # the library is linked of several code objects; a kernel that a shared header defines would be in each
+    names = [name for name, _ in _kernels()]
+    assert len(names) > 300 and len(set(names)) == len(names)
