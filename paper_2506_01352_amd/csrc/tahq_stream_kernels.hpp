@@ -22,11 +22,12 @@ struct Lanes {
     static_assert(usual <= few && few <= 4, "quads");
 };
 
-// Geometry of one workgroup's batch of tiles for an element type of ESIZE bytes: 256 threads, LPT lanes per tile.
-template <int G, int ESIZE, int LPT = Lanes<G, ESIZE>::usual>
+// Geometry of one workgroup's batch of tiles for an element type of ESIZE bytes: as many as 256 threads hold at the usual number of
+// lanes per tile.
+template <int G, int ESIZE>
 struct Batch {
     static constexpr int BYTES = G * ESIZE;                                   // one tile
-    static constexpr int TILES = 256 / LPT;                                   // tiles per workgroup
+    static constexpr int TILES = 256 / Lanes<G, ESIZE>::usual;                // tiles per workgroup
     static constexpr int STRIDE = BYTES + 16;                                 // padded LDS row
     static constexpr int CHUNKS = BYTES / 16;                                 // 16-byte chunks per tile
     static constexpr int LDS_BYTES = TILES * STRIDE;
@@ -310,48 +311,40 @@ struct Top2<G, false, LPT> {
     }
 };
 
-// Outlier flag and pivot index of the tile: the pivot byte (bit 7 = flag, bits 0..6 = d).  word(i): the i-th dword of my part.
-template <int EPL, bool BF16, int LPT, class Word>
-__device__ __forceinline__ uint32_t pivot_from(Word word, uint32_t part, float tau, float eps_ratio)
+// Outlier flag and pivot index of the tile: the pivot byte (bit 7 = flag, bits 0..6 = d), from the dwords of my part.
+template <int EPL, bool BF16, int LPT>
+__device__ __forceinline__ uint32_t pivot_of(const uint32_t *w, uint32_t part, float tau, float eps_ratio)
 {
     Top2<EPL, BF16, LPT> t;
     if constexpr (BF16) {
 #pragma unroll
-        for (int k = 0; k < EPL; k += 2) t.add(k, word(k / 2));
+        for (int k = 0; k < EPL; k += 2) t.add(k, w[k / 2]);
         float a1, a2;
         uint32_t d;
         t.finish(part, &a1, &a2, &d);
         return a1 > tau * (a2 + eps_ratio) ? (0x80u | d) : 0u;
     } else {
 #pragma unroll
-        for (int k = 0; k < EPL; ++k) t.add(__uint_as_float(word(k)));
+        for (int k = 0; k < EPL; ++k) t.add(__uint_as_float(w[k]));
         t.merge();
         const bool flag = t.a1 > tau * (t.a2 + eps_ratio);
         if (__ballot(flag) == 0) return 0u;
-        const uint32_t d = t.index(part, [&](int k) { return __uint_as_float(word(k)); });
+        const uint32_t d = t.index(part, [&](int k) { return __uint_as_float(w[k]); });
         return flag ? (0x80u | d) : 0u;
     }
 }
 
-// ... in registers
-template <int EPL, bool BF16, int LPT>
-__device__ __forceinline__ uint32_t pivot_of(const uint32_t *w, uint32_t part, float tau, float eps_ratio)
+// ... of a bf16 tile that one lane has, in its LDS row
+template <int G>
+__device__ __forceinline__ uint32_t pivot_of_row(const uint8_t *row, float tau, float eps_ratio)
 {
-    return pivot_from<EPL, BF16, LPT>([&](int i) { return w[i]; }, part, tau, eps_ratio);
-}
-
-// ... in an LDS row
-template <int EPL, bool BF16, int LPT>
-__device__ __forceinline__ uint32_t pivot_of(const uint8_t *row, uint32_t part, float tau, float eps_ratio)
-{
-    constexpr int WORDS = EPL * (BF16 ? 2 : 4) / 4;
-    uint32_t w[WORDS];
+    uint32_t w[G / 2];
 #pragma unroll
-    for (int c = 0; c < WORDS / 4; ++c) {
+    for (int c = 0; c < G / 8; ++c) {
         const uint4 q = *reinterpret_cast<const uint4 *>(row + c * 16);
         w[4 * c] = q.x; w[4 * c + 1] = q.y; w[4 * c + 2] = q.z; w[4 * c + 3] = q.w;
     }
-    return pivot_from<EPL, BF16, LPT>([&](int i) { return w[i]; }, part, tau, eps_ratio);
+    return pivot_of<G, true, 1>(w, 0, tau, eps_ratio);
 }
 
 // The pivot swap P_d on a bf16 tile's LDS row.
@@ -1326,7 +1319,7 @@ __device__ __forceinline__ void quant_pack_batch(const void *__restrict__ in, ui
     if constexpr (!PIVOTS) {
         store_batch<B, FULL>(v, nvalid, lds, tid);
         __syncthreads();
-        if (valid) pv = pivot_of<G, true, 1>(lds + slot * B::STRIDE, 0, tau, eps_ratio);
+        if (valid) pv = pivot_of_row<G>(lds + slot * B::STRIDE, tau, eps_ratio);
     }
     // stage one: my tile's class
     uint32_t cls = 4;                            // tiles past the end sort nowhere
