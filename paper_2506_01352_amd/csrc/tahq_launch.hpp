@@ -45,9 +45,11 @@ private:
 
 // Fewer wavefronts than the chip has vector units (256 compute units of four), at the usual number of lanes per tile: the launch
 // takes as long as one lane does, and tiles are spread over more lanes, as long as those make no more wavefronts per vector
-// unit than `deep`: 4, all that run at once, or 2 in the quantizer, which has more to do once per lane.  Above that the usual
-// lanes have less to issue.  bf16, G = 64, usual -> few: 25600 tiles: entropies 4.2 -> 3.1 us, quantizer 5.6 -> 4.4, decoder
-// 4.5 -> 3.6; 51200: 4.3 -> 3.9, 5.7 -> 5.8, 4.7 -> 4.2; 64512: 4.4 -> 4.0, 5.8 -> 6.0, 4.8 -> 4.4.
+// unit than `deep`: 4, all that run at once, or 2 in the quantizer.  Above that the usual lanes have less to issue.  bf16, G = 64,
+// usual -> few: 25600 tiles: entropies 4.2 -> 3.1 us, decoder 4.5 -> 3.6; 51200: 4.3 -> 3.9, 4.7 -> 4.2; 64512: 4.4 -> 4.0, 4.8 -> 4.4.
+// Encode at one width, the quantizer alone: 25600 tiles 6.2 -> 4.5, G = 128 5.8 -> 5.5.  (Its 2 is from when several lanes per tile
+// worked by workgroups, where 51200 tiles took 5.7 and 5.8.  By wavefronts they take less above it, too: 51200 tiles 6.3 -> 5.5, G = 32
+// 5.1 -> 4.6, G = 128 alike.)
 template <class N>
 inline bool few_tiles(uint64_t T, uint32_t deep) { return T * N::usual < 65536u && T * N::few < deep * 65536u; }
 

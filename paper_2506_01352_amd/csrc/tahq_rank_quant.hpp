@@ -378,7 +378,7 @@ __device__ __forceinline__ void swap_across(float *x, uint32_t part, uint32_t d)
 // entropies are counted.  bf16 [1,1024,1600] G = 64 (25600 tiles, 200 workgroups), by the 100 MHz clock: entropies in LDS after 1.3 us,
 // counted, and rows transformed, after 4.2, threshold bin 4.9, its tiles listed 6.5 and placed 6.8, payload written 7.7.  Bound by
 // what one compute unit issues for 25600 entropies (LDS additions 1.8 us, comparisons 1.0), the same in every one.
-// Encode, two launches -> one: that tensor 14.1 -> 11.7 us; fp32 [4,512,2048] with its decode 22.8 -> 20.8; 256 to 8192 tiles of
+// Encode, two launches -> one: that tensor 14.1 -> 11.7 us; fp32 [4,512,2048] with its decode 22.7 -> 21.1; 256 to 8192 tiles of
 // 8 to 64 channels 12.4 -> 9.0; [1,1600,2048] G = 128 16.5 -> 14.7; [10,1638,128] G = 8, 256 workgroups, 16.7 -> 16.3.
 // (With the entropies in registers and loops unrolled over them: [1,1024,1600] 13.1.  Rows requested before the entropies have
 // arrived: the fp32 tensor 22.5, as those wait behind all workgroups' rows.  Two histograms, by the lanes' parity: no faster.)

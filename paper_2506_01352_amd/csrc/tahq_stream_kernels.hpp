@@ -1174,8 +1174,8 @@ __device__ __forceinline__ TileRange tile_range(const float *x)
     mx = __builtin_fmaxf(mx, x[G - 1]);
     if constexpr (LPT >= 2) { mn = __builtin_fminf(mn, lane_xor<1>(mn)); mx = __builtin_fmaxf(mx, lane_xor<1>(mx)); }
     if constexpr (LPT >= 4) { mn = __builtin_fminf(mn, lane_xor<2>(mn)); mx = __builtin_fmaxf(mx, lane_xor<2>(mx)); }
-    mn = mn + 0.0f;
-    mx = mx + 0.0f;
+    mn = mn + 0.0f;                              // (as statements: inside the return the compiler orders k_quant_pack<64> otherwise, which
+    mx = mx + 0.0f;                              // took 18.2 us instead of 17.7 on bf16 [4,2048,4096] A = 4096)
     return {mn, mx};
 }
 
